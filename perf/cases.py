@@ -94,7 +94,7 @@ def draw(rng):
         dtype = "bf16" if packed or rng.random() < 0.8 else "fp32"
         if packed:  # what packed weights are for: enough tiles of 128 x 256 in either direction
             rows = rng.randint(1700, 2048)
-            inner, outer = 256 * rng.randint(14, 40), 256 * rng.randint(14, 40)
+            inner, outer = 256 * rng.randint(15, 40), 256 * rng.randint(15, 40)
         else:
             rows = _log(rng, 32, 2048)
             inner, outer = 8 * _log(rng, 8, 512), 8 * _log(rng, 8, 512)
