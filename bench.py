@@ -161,7 +161,7 @@ def kernel_bench(reps, n_weights=1, vendor=False, ksweep=False):
         alg_bytes = 2 * (M * K + N * K) + (4 if of else 2) * M * N
         out[name] = {"M": M, "N": N, "K": K, "us": 1e3 * ms, "tflops": 2.0 * M * N * K / ms / 1e9,
                      "algorithmic_bytes": alg_bytes, "weights_in_rotation": n_weights,
-                     "kernel": "gemm_pk_k" if packed else ("gemm_tt_k" if not ak and not bk else "gemm_mfma_k")}
+                     "kernel": "gemm_pk_k" if packed else ("gemm_tt_k" if not ak and not bk else "gemm_lds_k")}
         if vendor:
             Am = A.view(M, K) if ak else A.view(K, M).t()
             Bms = [B.view(N, K).t() if bk else B.view(K, N) for B in Bs]

@@ -58,3 +58,15 @@ __device__ __forceinline__ float block_max(float v, float* red) {
   for (int i = 1; i < NW; ++i) t = fmaxf(t, red[i]);
   return t;
 }
+
+typedef __attribute__((ext_vector_type(4))) uint32_t hift_u32x4;
+// Direct-to-LDS load of 16 bytes per lane: M0 carries the LDS address of lane 0's piece and lane l
+// lands 16 l bytes further.  Inline assembly, with hand-placed s_waitcnt where the data is read:
+// the compiler cannot see which LDS reads depend on which load and would otherwise wait for all
+// of them before every read.
+__device__ __forceinline__ void load_to_lds_b128(hift_u32x4 rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+               : "memory");
+}

@@ -65,8 +65,11 @@ struct Gemm {
 constexpr size_t PACKED_WS_BYTES = 1024 + size_t(256) * 128 * 256 * 4;
 enum { EPI_NONE = 0, EPI_SWIGLU = 1, EPI_ROPE = 2, EPI_SWIGLU_BWD = 3, EPI_GELU = 4, EPI_GELU_BWD = 5 };
 enum { BAND_NONE = 0, BAND_SKIP_UPPER = 1, BAND_K_UPTO_ROW = 2, BAND_K_FROM_ROW = 3 };
-// variant (optional) receives which kernel ran: 0 plain FMA, 1 MFMA 128x128 tiles, 2 MFMA 256x256 tiles
-hipError_t gemm(const Gemm& g, hipStream_t st, int* variant = nullptr);
+hipError_t gemm(const Gemm& g, hipStream_t st);
+
+// The kernel for problems whose tiles do not fill the chip (gemm_lds.hip); gemm() chooses it.
+bool lds_gemm_applies(const Gemm& g);
+hipError_t gemm_lds(const Gemm& g, hipStream_t st);
 
 // Weight operand pre-packed in MFMA fragment order (see gemm.hip).  packed_b_bytes: size of the packed
 // copy of a [N, K] operand, 0 if the shape cannot be packed.  pack_b: builds it from B given as in Gemm

@@ -95,6 +95,41 @@ def test_weight_gradient_contraction(M, N, K):
         assert not bad.any(), (out_f32, extras, int(bad.sum()), float(np.max(np.abs(got - ref))))
 
 
+LDS_CASES = [  # M, N, K: the edges of the seven tiles of gemm_lds_k (32 to 128 rows and columns), stages of 64 k and their remainders
+    (32, 32, 64), (24, 40, 8), (40, 24, 72), (8, 200, 136), (200, 8, 184), (64, 64, 320), (72, 56, 56),
+    (128, 4096, 64), (1000, 1208, 72), (136, 12296, 24), (2056, 520, 104), (1024, 768, 768), (520, 520, 2056), (232, 4104, 240),
+]
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,K", LDS_CASES)
+def test_contraction_inside_wider_buffers(ak, bk, M, N, K):
+    """Operands are parts of buffers that hold NaN everywhere else (after every row, after the last one): nothing beyond an
+    operand's own rows and k may reach the result, and nothing beyond C's M x N part may be written."""
+    import torch
+    import paper_2401_15207_amd as H
+    rng = np.random.default_rng(M * 3 + N * 5 + K + 2 * ak + bk)
+    A, B = _bf16_round(rng.standard_normal((M, K))), _bf16_round(rng.standard_normal((N, K)))
+    ref = A.astype(np.float64) @ B.astype(np.float64).T
+
+    def inside(x):  # [rows + 8, cols + 8] of NaN with x at its start
+        t = torch.full((x.shape[0] + 8, x.shape[1] + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+        t[:x.shape[0], :x.shape[1]] = torch.from_numpy(x).cuda().to(torch.bfloat16)
+        return t
+    dA, dB = inside(A if ak else np.ascontiguousarray(A.T)), inside(B if bk else np.ascontiguousarray(B.T))
+    scale = np.sqrt(K) + 1.0
+    for out_f32 in (0, 1):
+        dC = torch.full((M + 1, N + 8), 7.0, dtype=torch.float32 if out_f32 else torch.bfloat16, device="cuda")
+        H.kernel_gemm(BF16, ak, bk, out_f32, M, N, K, dA, dA.shape[1], dB, dB.shape[1], dC, N + 8)
+        torch.cuda.synchronize()
+        full = dC.float().cpu().numpy().astype(np.float64)
+        assert np.all(full[M:] == 7.0) and np.all(full[:, N:] == 7.0)
+        # exact products, fp32 sums; bf16 output: one rounding
+        tol = (1e-5 * (np.abs(ref) + scale)) if out_f32 else 2 ** -8 * (np.abs(ref) + 0.02 * scale)
+        bad = ~(np.abs(full[:M, :N] - ref) <= tol)
+        assert not bad.any(), (out_f32, int(bad.sum()))
+
+
 def test_gemm_batched_strided_bf16():
     import torch
     import paper_2401_15207_amd as H
