@@ -301,7 +301,7 @@ struct hift_model {
   int64_t n_fac = 0;
   size_t af_work_floats = 0;
   float* grad = nullptr;
-  float* state_full = nullptr;  // [n_state][n_params] when state stays in HBM
+  float* state_full = nullptr;  // [n_state] arrays of n_params values, state_stride apart, when state stays in HBM
   // State of the active group when the rest lives on the host: [n_state][grad_cap] each.  Three slots:
   // while one is updated, the next group's state arrives in the second and the previous group's
   // drains from the third, so the two directions of the host link run at the same time.
@@ -351,6 +351,8 @@ struct hift_model {
   Prof prof;
 
   int64_t wc_count = 0;  // elements of the bf16 copy
+  // n_params rounded up: the second state array starts 16-byte aligned whatever the number of parameters
+  int64_t state_stride() const { return (lay.n_params + 63) & ~(int64_t)63; }
   const Tensor& T_(const std::string& n) const { return lay.t[lay.find(n)]; }
   // the tensor as the forward pass reads it (null for a matrix that lives only in its fragment-order copies)
   void* W(const Tensor& t) const {
@@ -392,7 +394,7 @@ void carve(hift_model* mm, void* dev, size_t* dev_bytes, size_t* pinned_bytes, s
     }
   } else if (M.n_state > 0) {
     b.cat = MEM_STATE;
-    M.state_full = (float*)b.take((size_t)M.n_state * np * 4);
+    M.state_full = (float*)b.take((size_t)M.n_state * M.state_stride() * 4);
   }
   if (M.n_fac > 0) {
     b.cat = MEM_STATE;
@@ -1547,7 +1549,7 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
   CR_TRY(hipEventCreate(&M->ev_w1));
   for (const PinnedSpace::Chunk& ch : M->pin.chunks) memset(ch.base, 0, ch.bytes);
   // state and gradient buffers start at zero
-  if (M->state_full) CR_TRY(fill_zero(M->state_full, (size_t)M->n_state * M->lay.n_params * 4, M->cs));
+  if (M->state_full) CR_TRY(fill_zero(M->state_full, (size_t)M->n_state * M->state_stride() * 4, M->cs));
   for (int q = 0; q < NSLOT; ++q)
     if (M->slot[q]) CR_TRY(fill_zero(M->slot[q], (size_t)M->n_move * M->grad_cap * 4, M->cs));
   CR_TRY(fill_zero(M->grad, (size_t)M->grad_cap * 4, M->cs));
@@ -1733,7 +1735,7 @@ hift_status hift_checkpoint_save(hift_model* M, void* host_buffer, size_t bytes)
   p += np4;
   for (int j = 0; j < M->n_state; ++j, p += np4) {
     if (M->on_host) ST_TRY(M->pin.read(p, M->host_state_off + (size_t)j * np4, np4));
-    else HIP_TRY(hipMemcpy(p, M->state_full + (size_t)j * M->lay.n_params, np4, hipMemcpyDeviceToHost));
+    else HIP_TRY(hipMemcpy(p, M->state_full + (size_t)j * M->state_stride(), np4, hipMemcpyDeviceToHost));
   }
   if (M->n_fac) HIP_TRY(hipMemcpy(p, M->fac, (size_t)M->n_fac * 4, hipMemcpyDeviceToHost));
   return HIFT_OK;
@@ -1777,7 +1779,7 @@ hift_status hift_checkpoint_load(hift_model* M, const void* host_buffer, size_t 
   p += np4;
   for (int j = 0; j < M->n_state; ++j, p += np4) {
     if (M->on_host) ST_TRY(M->pin.write(M->host_state_off + (size_t)j * np4, p, np4));
-    else HIP_TRY(hipMemcpy(M->state_full + (size_t)j * M->lay.n_params, p, np4, hipMemcpyHostToDevice));
+    else HIP_TRY(hipMemcpy(M->state_full + (size_t)j * M->state_stride(), p, np4, hipMemcpyHostToDevice));
   }
   if (M->n_fac) HIP_TRY(hipMemcpy(M->fac, p, (size_t)M->n_fac * 4, hipMemcpyHostToDevice));
   for (int& g : M->slot_group) g = -1;  // whatever the slots hold is stale
@@ -1848,7 +1850,7 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
       s2b = s1b + M->grad_cap;
     } else {
       s1b = M->state_full;
-      s2b = M->state_full + M->lay.n_params;
+      s2b = M->state_full + M->state_stride();
       sbase = 0;
     }
   }
@@ -1857,6 +1859,7 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
     if (M->opt.kind == HIFT_ADAFACTOR) bytes_per = 24.0;  // the gradient is read four times (row, column, clipping, update)
     if (M->dt == DT_BF16) bytes_per += 2.0;
     Scope sc(M, CAT_OPT, bytes_per * cnt);
+    std::vector<OptItem> items;
     for (int i = M->lay.unit_first[ulo]; i < M->lay.unit_first[uhi]; ++i) {
       const Tensor& t = M->lay.t[i];
       const int64_t tg = M->unit_steps[t.unit];
@@ -1866,10 +1869,11 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
                                mbase + t.off, M->grad + (t.off - plo), M->fac + t.fac_off, M->af_work, cc, M->cs));
         continue;
       }
-      K_TRY(optimizer_update(oa, t.count(), t.kind == HIFT_KIND_MATRIX, tg, mbase + t.off,
-                             M->grad + (t.off - plo), s1b ? s1b + (t.off - sbase) : nullptr,
-                             (s2b && M->n_state == 2) ? s2b + (t.off - sbase) : nullptr, cc, M->cs));
+      items.push_back(OptItem{t.off - plo, t.count(), t.kind == HIFT_KIND_MATRIX, tg, cc});
     }
+    if (!items.empty())
+      K_TRY(optimizer_update(oa, items.data(), (int)items.size(), mbase + plo, M->grad, s1b ? s1b + (plo - sbase) : nullptr,
+                             (s2b && M->n_state == 2) ? s2b + (plo - sbase) : nullptr, M->cs));
   }
   if (moving) HIP_TRY(hipEventRecord(M->ev_opt[s], M->cs));
   if (M->wpk) {  // the updated matrices in fragment order, for the next forward and dX
@@ -1964,8 +1968,8 @@ hift_status hift_lora_step(hift_model* M, const hift_batch* bt, float* loss_out)
     const double bytes_per = 28.0 + (M->dt == DT_BF16 ? 2.0 : 0.0);
     Scope sc(M, CAT_OPT, bytes_per * M->n_lora);
     OptArgs oa{M->opt.kind, M->opt.lr, M->opt.beta1, M->opt.beta2, M->opt.eps, M->opt.weight_decay, M->opt.momentum};
-    K_TRY(optimizer_update(oa, M->n_lora, true, M->lora_t, M->lora_master, M->lora_grad, M->lora_m, M->lora_v,
-                           M->dt == DT_BF16 ? M->lora_wc : nullptr, M->cs));
+    const OptItem all{0, M->n_lora, true, M->lora_t, M->dt == DT_BF16 ? M->lora_wc : nullptr};
+    K_TRY(optimizer_update(oa, &all, 1, M->lora_master, M->lora_grad, M->lora_m, M->lora_v, M->cs));
   }
   HIP_TRY(hipEventRecord(M->ev_w0, M->cs));
   HIP_TRY(hipEventRecord(M->ev_w1, M->cs));
@@ -2070,7 +2074,7 @@ hift_status hift_read_state(hift_model* M, int32_t ulo, int32_t uhi, int32_t slo
   if (M->on_host) {
     ST_TRY(M->pin.read(dst, M->host_state_off + ((size_t)slot * M->lay.n_params + off) * 4, (size_t)cnt * 4));  // write-back has landed
   } else {
-    HIP_TRY(hipMemcpy(dst, M->state_full + (size_t)slot * M->lay.n_params + off, (size_t)cnt * 4, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(dst, M->state_full + (size_t)slot * M->state_stride() + off, (size_t)cnt * 4, hipMemcpyDeviceToHost));
   }
   return HIFT_OK;
 }
@@ -2377,7 +2381,8 @@ hift_status hift_kernel_optimizer(const hift_opt* opt, int64_t count, int32_t de
   if (count < 0 || t < 1) return fail(HIFT_EINVAL, "count must be >= 0 and t >= 1");
   if (opt->kind == HIFT_ADAFACTOR) return fail(HIFT_EINVAL, "Adafactor works on whole tensors; it has no element-wise kernel entry");
   OptArgs oa{opt->kind, opt->lr, opt->beta1, opt->beta2, opt->eps, opt->weight_decay, opt->momentum};
-  HIP_TRY(optimizer_update(oa, count, decay != 0, t, master, grad, state1, state2, compute_copy, (hipStream_t)stream));
+  const OptItem all{0, count, decay != 0, t, compute_copy};
+  HIP_TRY(optimizer_update(oa, &all, 1, master, grad, state1, state2, (hipStream_t)stream));
   return HIFT_OK;
 }
 

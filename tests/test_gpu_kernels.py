@@ -271,6 +271,33 @@ def test_optimizer_kernel_against_oracle_formulas(kind, n):
         assert np.allclose(d_s2.cpu().numpy(), o_s2, rtol=1e-5, atol=1e-12)
 
 
+@pytest.mark.parametrize("off", [1, 4])
+@pytest.mark.parametrize("n", [1, 3, 5, 1023, 1025, 4100])
+def test_optimizer_on_part_of_a_buffer(n, off):
+    """Pieces of four parameters, the last ones of a tensor, and tensors that do not start at a multiple of 16 bytes; nothing
+    outside the n parameters is written."""
+    import torch
+    import paper_2401_15207_amd as H
+    rng = np.random.default_rng(n + off)
+    opt = dict(kind="adamw", lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01, momentum=0.0)
+    full = {k: rng.standard_normal(n + 8).astype(np.float32) * s for k, s in (("th", 1.0), ("g", 0.1), ("s1", 0.01), ("s2", 0.0))}
+    full["s2"] = np.abs(full["th"] * 1e-3).astype(np.float32)
+    dev = {k: torch.from_numpy(v.copy()).cuda() for k, v in full.items()}
+    cc = torch.full((n + 8,), 3.0, dtype=torch.bfloat16, device="cuda")
+    part = {k: v[off:off + n] for k, v in dev.items()}
+    H.kernel_optimizer(opt, n, 1, 2, part["th"], part["g"], part["s1"], part["s2"], cc[off:off + n])
+    torch.cuda.synchronize()
+    ref = {k: v[off:off + n].astype(np.float64) for k, v in full.items()}
+    O.adamw_update(ref["th"], ref["g"], ref["s1"], ref["s2"], 2, opt["lr"], opt["beta1"], opt["beta2"], opt["eps"], opt["weight_decay"], np.ones(n))
+    for k in ("th", "s1", "s2"):
+        got = dev[k].cpu().numpy()
+        assert np.all(np.abs(got[off:off + n] - ref[k]) <= 1e-6 * np.abs(ref[k]) + 1e-8), k   # a few fp32 roundings
+        assert np.array_equal(got[:off], full[k][:off]) and np.array_equal(got[off + n:], full[k][off + n:]), k
+    c = cc.float().cpu().numpy()
+    assert np.array_equal(c[off:off + n], _bf16_round(dev["th"].cpu().numpy()[off:off + n]))
+    assert np.all(c[:off] == 3.0) and np.all(c[off + n:] == 3.0)
+
+
 @pytest.mark.parametrize("dtype", [F32, BF16], ids=["f32", "bf16"])
 @pytest.mark.parametrize("rows,d", [(5, 64), (1, 8), (130, 4096), (3, 100), (0, 64)])
 @pytest.mark.parametrize("rms", [0, 1])

@@ -81,6 +81,15 @@ def test_single_group_is_full_finetuning_step():
     assert rel_l2(gpu.read_params(), orc.theta) <= TOL
 
 
+def test_group_of_more_tensors_than_one_update_launch_takes():
+    wl = dict(WORKLOADS["C1"], n_layers=4)   # 53 tensors in one group
+    orc, gpu, _ = make_pair(wl, seed=2, m=6, jitter=0.02)
+    assert orc.k == 1 and gpu.k == 1
+    for t, gid, lo_, lg, chk, tb_g in run_steps(orc, gpu, wl, 2, 2):
+        assert abs(lg - lo_) <= TOL * abs(lo_)
+    assert rel_l2(gpu.read_params(), orc.theta) <= TOL
+
+
 @pytest.mark.parametrize("engine", [0, 1], ids=["memcpy_async", "copy_kernel"])
 def test_state_offload_matches_resident_state_bitwise(engine):
     wl = WORKLOADS["C1"]
