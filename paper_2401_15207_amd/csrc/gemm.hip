@@ -924,53 +924,79 @@ __global__ void __launch_bounds__(256) gemm_tt_k(GemmP p) {
 // ------------------------------------------------------------------------------------------
 // plain FMA kernel: any strides, any element type, fp32 accumulation
 // ------------------------------------------------------------------------------------------
-template <typename T, typename OutT>
+// A workgroup of 256 threads computes BT x BT outputs, each thread a (BT / 16)^2 square of them, every output one chain of fused
+// multiply-adds over ascending k.  KC k-values of both operands per pass through LDS; the next pass's elements are on their
+// way in registers meanwhile.  Small problems are a chain of passes, each a trip to memory: 16 k per pass with nothing in
+// flight took 3 us a pass (64 x 64, k 256: 50 us; now 8).  32 x 32 tiles where 64 x 64 would leave compute units without one.
+template <int BT, int KC, typename T, typename OutT>
 __global__ void __launch_bounds__(256) gemm_fma_k(GemmP p, int64_t sam, int64_t sak, int64_t sbn, int64_t sbk) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
+  constexpr int TM = BT / 16, NLD = BT * KC / 256, PITCH = BT + 4;
+  __shared__ __attribute__((aligned(16))) float As[2][KC][PITCH];
+  __shared__ __attribute__((aligned(16))) float Bs[2][KC][PITCH];
   const int tid = threadIdx.x;
   const int tile = blockIdx.x;
   const int tm = tile % p.tiles_m, tn = tile / p.tiles_m;
   const int z = blockIdx.y, zb = z / p.nh, zh = z % p.nh;
   const T* A = reinterpret_cast<const T*>(p.A) + zb * p.sa1 + zh * p.sa2;
   const T* B = reinterpret_cast<const T*>(p.B) + zb * p.sb1 + zh * p.sb2;
-  const int64_t m0 = (int64_t)tm * 64, n0 = (int64_t)tn * 64;
-  const int tx = tid & 15, ty = tid >> 4;  // thread computes rows ty*4..+3, cols tx*4..+3
-  float acc[4][4] = {};
-  for (int64_t k0 = 0; k0 < p.K; k0 += 16) {
+  const int64_t m0 = (int64_t)tm * BT, n0 = (int64_t)tn * BT;
+  const int tx = tid & 15, ty = tid >> 4;  // thread computes rows ty*TM..+TM-1, cols tx*TM..+TM-1
+  // element e = tid + 256 i of a pass: neighbouring threads take neighbours along the operand's contiguous direction
+  auto place = [&](int i, bool along_k, int* r, int* k) __attribute__((always_inline)) {
+    const int e = tid + 256 * i;
+    *r = along_k ? e / KC : e % BT;
+    *k = along_k ? e % KC : e / BT;
+  };
+  T ra[NLD], rb[NLD];
+  auto load = [&](int64_t k0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;
+    for (int i = 0; i < NLD; ++i) {
       int r, k;
-      if (sak == 1) { k = e & 15; r = e >> 4; } else { r = e & 63; k = e >> 6; }
-      const int64_t gm = m0 + r, gk = k0 + k;
-      As[k][r] = (gm < p.M && gk < p.K) ? to_f32(A[gm * sam + gk * sak]) : 0.f;
-      if (sbk == 1) { k = e & 15; r = e >> 4; } else { r = e & 63; k = e >> 6; }
-      const int64_t gn = n0 + r, gk2 = k0 + k;
-      Bs[k][r] = (gn < p.N && gk2 < p.K) ? to_f32(B[gn * sbn + gk2 * sbk]) : 0.f;
+      place(i, sak == 1, &r, &k);
+      ra[i] = (m0 + r < p.M && k0 + k < p.K) ? A[(m0 + r) * sam + (k0 + k) * sak] : from_f32<T>(0.f);
+      place(i, sbk == 1, &r, &k);
+      rb[i] = (n0 + r < p.N && k0 + k < p.K) ? B[(n0 + r) * sbn + (k0 + k) * sbk] : from_f32<T>(0.f);
     }
-    __syncthreads();
+  };
+  auto store = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = As[k][ty * 4 + i]; b[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    for (int i = 0; i < NLD; ++i) {
+      int r, k;
+      place(i, sak == 1, &r, &k);
+      As[buf][k][r] = to_f32(ra[i]);
+      place(i, sbk == 1, &r, &k);
+      Bs[buf][k][r] = to_f32(rb[i]);
     }
-    __syncthreads();
+  };
+  float acc[TM][TM] = {};
+  load(0);
+  store(0);
+  __syncthreads();
+  int buf = 0;
+  for (int64_t k0 = 0; k0 < p.K; k0 += KC, buf ^= 1) {
+    const bool more = k0 + KC < p.K;
+    if (more) load(k0 + KC);
+#pragma unroll 16
+    for (int k = 0; k < KC; ++k) {
+      const Vec<float, TM> a = *reinterpret_cast<const Vec<float, TM>*>(&As[buf][k][ty * TM]);
+      const Vec<float, TM> b = *reinterpret_cast<const Vec<float, TM>*>(&Bs[buf][k][tx * TM]);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] = fmaf(a.v[i], b.v[j], acc[i][j]);
+    }
+    if (more) store(buf ^ 1);
+    __syncthreads();  // the other buffer is complete, this one is no longer read
   }
   OutT* C = reinterpret_cast<OutT*>(p.C) + zb * p.sc1 + zh * p.sc2;
   const OutT* R = p.R ? reinterpret_cast<const OutT*>(p.R) + zb * p.sc1 + zh * p.sc2 : nullptr;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = m0 + ty * 4 + i;
+  for (int i = 0; i < TM; ++i) {
+    const int64_t row = m0 + ty * TM + i;
     if (row >= p.M) continue;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t col = n0 + tx * 4 + j;
+    for (int j = 0; j < TM; ++j) {
+      const int64_t col = n0 + tx * TM + j;
       if (col >= p.N) continue;
       float v = acc[i][j] + (p.bias ? to_f32(reinterpret_cast<const T*>(p.bias)[col]) : 0.f);
       if (R) v += to_f32(R[row * p.ldr + col]);
@@ -1179,17 +1205,21 @@ hipError_t gemm(const Gemm& g, hipStream_t st) {
     }
     if (lds_gemm_applies(g)) return gemm_lds(g, st);
   }
-  p.tiles_m = (int)((g.M + 63) / 64);
-  p.tiles_n = (int)((g.N + 63) / 64);
-  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)nz);
   const int64_t sam = g.a_kmajor ? g.lda : 1, sak = g.a_kmajor ? 1 : g.lda;
   const int64_t sbn = g.b_kmajor ? g.ldb : 1, sbk = g.b_kmajor ? 1 : g.ldb;
-  if (g.dtype == DT_F32)
-    gemm_fma_k<float, float><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk);
-  else if (g.out_f32)
-    gemm_fma_k<bf16, float><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk);
-  else
-    gemm_fma_k<bf16, bf16><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk);
+  const int bt = ((g.M + 63) / 64) * ((g.N + 63) / 64) * nz >= 256 ? 64 : 32;
+  p.tiles_m = (int)((g.M + bt - 1) / bt);
+  p.tiles_n = (int)((g.N + bt - 1) / bt);
+  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)nz);
+#define FMA(T, OutT)                                                                  \
+  do {                                                                                \
+    if (bt == 64) gemm_fma_k<64, 32, T, OutT><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk); \
+    else gemm_fma_k<32, 64, T, OutT><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk);          \
+  } while (0)
+  if (g.dtype == DT_F32) FMA(float, float);
+  else if (g.out_f32) FMA(bf16, float);
+  else FMA(bf16, bf16);
+#undef FMA
   return hipGetLastError();
 }
 
