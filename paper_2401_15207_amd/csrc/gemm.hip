@@ -927,65 +927,86 @@ __global__ void __launch_bounds__(256) gemm_tt_k(GemmP p) {
 // A workgroup of 256 threads computes BT x BT outputs, each thread a (BT / 16)^2 square of them, every output one chain of fused
 // multiply-adds over ascending k.  KC k-values of both operands per pass through LDS; the next pass's elements are on their
 // way in registers meanwhile.  Small problems are a chain of passes, each a trip to memory: 16 k per pass with nothing in
-// flight took 3 us a pass (64 x 64, k 256: 50 us; now 8).  32 x 32 tiles where 64 x 64 would leave compute units without one.
-template <int BT, int KC, typename T, typename OutT>
-__global__ void __launch_bounds__(256) gemm_fma_k(GemmP p, int64_t sam, int64_t sak, int64_t sbn, int64_t sbk) {
-  constexpr int TM = BT / 16, NLD = BT * KC / 256, PITCH = BT + 4;
-  __shared__ __attribute__((aligned(16))) float As[2][KC][PITCH];
-  __shared__ __attribute__((aligned(16))) float Bs[2][KC][PITCH];
+// flight took 3 us a pass (64 x 64, k 256: 36 us, now 9, a launch being 4 of them; 2048 x 1024, k 1024: 171 us, now 100).
+// 32 x 32 tiles where 64 x 64 would leave compute units without one.
+// One operand's share of a pass for a thread: NLD elements a fixed distance apart, found by one pointer and one stride
+// (KMAJOR: element i is row tid / KC + i 256 / KC at k = tid % KC; else row tid % BT at k = tid / BT + i 256 / BT), so that
+// neighbouring threads take neighbours along the operand's contiguous direction.  Elements outside are read from the operand's
+// start and dropped.
+template <int BT, int KC, bool KMAJOR, typename T>
+struct FmaOperand {
+  static constexpr int NLD = BT * KC / 256, STEP = KMAJOR ? 256 / KC : 256 / BT;
+  const T* base;
+  const T* at;
+  int64_t stride, advance;
+  int r0, k0, rows;  // first row and k of this thread within the tile and pass; rows of the tile inside the matrix
+  T v[NLD];
+  __device__ __forceinline__ void init(const T* src, int64_t ld, int64_t row0, int64_t nrows, int tid) {
+    base = src;
+    r0 = KMAJOR ? tid / KC : tid % BT;
+    k0 = KMAJOR ? tid % KC : tid / BT;
+    rows = (int)(nrows - row0 < BT ? nrows - row0 : BT);
+    at = src + (KMAJOR ? (row0 + r0) * ld + k0 : k0 * ld + row0 + r0);
+    stride = STEP * ld;
+    advance = KMAJOR ? KC : KC * ld;
+  }
+  __device__ __forceinline__ bool inside(int i, int64_t left) const {  // left: k-values that remain from this pass on
+    return KMAJOR ? r0 + i * STEP < rows && k0 < left : r0 < rows && k0 + i * STEP < left;
+  }
+  __device__ __forceinline__ void load(int64_t left) {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) v[i] = *(inside(i, left) ? at + i * stride : base);
+    at += advance;
+  }
+  __device__ __forceinline__ void store(float (*dst)[BT + 4], int64_t left) const {
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) dst[KMAJOR ? k0 : k0 + i * STEP][KMAJOR ? r0 + i * STEP : r0] = inside(i, left) ? to_f32(v[i]) : 0.f;
+  }
+};
+
+template <int BT, int KC, bool AK, bool BKM, typename T, typename OutT>
+__global__ void __launch_bounds__(256) gemm_fma_k(GemmP p) {
+  constexpr int TM = BT / 16;
+  __shared__ __attribute__((aligned(16))) float As[2][KC][BT + 4];
+  __shared__ __attribute__((aligned(16))) float Bs[2][KC][BT + 4];
   const int tid = threadIdx.x;
   const int tile = blockIdx.x;
   const int tm = tile % p.tiles_m, tn = tile / p.tiles_m;
   const int z = blockIdx.y, zb = z / p.nh, zh = z % p.nh;
-  const T* A = reinterpret_cast<const T*>(p.A) + zb * p.sa1 + zh * p.sa2;
-  const T* B = reinterpret_cast<const T*>(p.B) + zb * p.sb1 + zh * p.sb2;
   const int64_t m0 = (int64_t)tm * BT, n0 = (int64_t)tn * BT;
   const int tx = tid & 15, ty = tid >> 4;  // thread computes rows ty*TM..+TM-1, cols tx*TM..+TM-1
-  // element e = tid + 256 i of a pass: neighbouring threads take neighbours along the operand's contiguous direction
-  auto place = [&](int i, bool along_k, int* r, int* k) __attribute__((always_inline)) {
-    const int e = tid + 256 * i;
-    *r = along_k ? e / KC : e % BT;
-    *k = along_k ? e % KC : e / BT;
-  };
-  T ra[NLD], rb[NLD];
-  auto load = [&](int64_t k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      int r, k;
-      place(i, sak == 1, &r, &k);
-      ra[i] = (m0 + r < p.M && k0 + k < p.K) ? A[(m0 + r) * sam + (k0 + k) * sak] : from_f32<T>(0.f);
-      place(i, sbk == 1, &r, &k);
-      rb[i] = (n0 + r < p.N && k0 + k < p.K) ? B[(n0 + r) * sbn + (k0 + k) * sbk] : from_f32<T>(0.f);
-    }
-  };
-  auto store = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      int r, k;
-      place(i, sak == 1, &r, &k);
-      As[buf][k][r] = to_f32(ra[i]);
-      place(i, sbk == 1, &r, &k);
-      Bs[buf][k][r] = to_f32(rb[i]);
-    }
-  };
+  FmaOperand<BT, KC, AK, T> a;
+  FmaOperand<BT, KC, BKM, T> b;
+  a.init(reinterpret_cast<const T*>(p.A) + zb * p.sa1 + zh * p.sa2, p.lda, m0, p.M, tid);
+  b.init(reinterpret_cast<const T*>(p.B) + zb * p.sb1 + zh * p.sb2, p.ldb, n0, p.N, tid);
   float acc[TM][TM] = {};
-  load(0);
-  store(0);
+  if (p.K > 0) {
+    a.load(p.K);
+    b.load(p.K);
+    a.store(As[0], p.K);
+    b.store(Bs[0], p.K);
+  }
   __syncthreads();
   int buf = 0;
-  for (int64_t k0 = 0; k0 < p.K; k0 += KC, buf ^= 1) {
-    const bool more = k0 + KC < p.K;
-    if (more) load(k0 + KC);
+  for (int64_t left = p.K; left > 0; left -= KC, buf ^= 1) {
+    const bool more = left > KC;
+    if (more) {
+      a.load(left - KC);
+      b.load(left - KC);
+    }
 #pragma unroll 16
     for (int k = 0; k < KC; ++k) {
-      const Vec<float, TM> a = *reinterpret_cast<const Vec<float, TM>*>(&As[buf][k][ty * TM]);
-      const Vec<float, TM> b = *reinterpret_cast<const Vec<float, TM>*>(&Bs[buf][k][tx * TM]);
+      const Vec<float, TM> x = *reinterpret_cast<const Vec<float, TM>*>(&As[buf][k][ty * TM]);
+      const Vec<float, TM> y = *reinterpret_cast<const Vec<float, TM>*>(&Bs[buf][k][tx * TM]);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j) acc[i][j] = fmaf(a.v[i], b.v[j], acc[i][j]);
+        for (int j = 0; j < TM; ++j) acc[i][j] = fmaf(x.v[i], y.v[j], acc[i][j]);
     }
-    if (more) store(buf ^ 1);
+    if (more) {
+      a.store(As[buf ^ 1], left - KC);
+      b.store(Bs[buf ^ 1], left - KC);
+    }
     __syncthreads();  // the other buffer is complete, this one is no longer read
   }
   OutT* C = reinterpret_cast<OutT*>(p.C) + zb * p.sc1 + zh * p.sc2;
@@ -1205,21 +1226,25 @@ hipError_t gemm(const Gemm& g, hipStream_t st) {
     }
     if (lds_gemm_applies(g)) return gemm_lds(g, st);
   }
-  const int64_t sam = g.a_kmajor ? g.lda : 1, sak = g.a_kmajor ? 1 : g.lda;
-  const int64_t sbn = g.b_kmajor ? g.ldb : 1, sbk = g.b_kmajor ? 1 : g.ldb;
   const int bt = ((g.M + 63) / 64) * ((g.N + 63) / 64) * nz >= 256 ? 64 : 32;
   p.tiles_m = (int)((g.M + bt - 1) / bt);
   p.tiles_n = (int)((g.N + bt - 1) / bt);
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)nz);
-#define FMA(T, OutT)                                                                  \
-  do {                                                                                \
-    if (bt == 64) gemm_fma_k<64, 32, T, OutT><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk); \
-    else gemm_fma_k<32, 64, T, OutT><<<grid, 256, 0, st>>>(p, sam, sak, sbn, sbk);          \
+#define FMA_TILE(AK, BKM, T, OutT)                                                       \
+  do {                                                                                   \
+    if (bt == 64) gemm_fma_k<64, 32, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);         \
+    else gemm_fma_k<32, 64, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);                  \
+  } while (0)
+#define FMA(T, OutT)                                                                     \
+  do {                                                                                   \
+    if (g.a_kmajor) { if (g.b_kmajor) FMA_TILE(true, true, T, OutT); else FMA_TILE(true, false, T, OutT); }   \
+    else { if (g.b_kmajor) FMA_TILE(false, true, T, OutT); else FMA_TILE(false, false, T, OutT); }            \
   } while (0)
   if (g.dtype == DT_F32) FMA(float, float);
   else if (g.out_f32) FMA(bf16, float);
   else FMA(bf16, bf16);
 #undef FMA
+#undef FMA_TILE
   return hipGetLastError();
 }
 
