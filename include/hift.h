@@ -228,10 +228,7 @@ hift_status hift_group_units(const hift_model* mdl, int32_t group_id, int32_t* u
  * scheduled one, fetched synchronously otherwise); optimizer update; state sent back.
  * Parameters outside the group are not written.  The work is queued on the three streams;
  * if loss_out (host) is not NULL the call waits for the compute stream and stores the mean
- * loss.  With NULL it does not wait for the step, but it may wait (when state moves and the default copy
- * engine is in use) until the host-to-device copy queued by the previous call has finished -- at most one
- * state transfer's time, normally over long before: a copy submitted while the copy engine still has a
- * backlog is run by the runtime as a full-grid kernel, which starves the step's own kernels.
+ * loss.  With NULL it does not wait for the GPU.
  * The batch's buffers must be complete on the compute stream's timeline: the caller orders the compute
  * stream after whatever wrote them (the Python binding does this against torch's current stream).
  * Errors: HIFT_ESTATE without a schedule; HIFT_EINVAL for group_id outside [0,k), batch or seq
@@ -318,9 +315,8 @@ hift_status hift_transfer_stats(hift_model* mdl, uint64_t* h2d_bytes, uint64_t* 
 hift_status hift_last_step_ms(hift_model* mdl, float* step_ms, float* exposed_copy_ms);
 
 /* How optimizer state moves between the pinned arena and HBM (Algorithm 1 steps i and k).
- * engine 0 (default): hipMemcpyAsync on the two copy streams; the library lets at most one
- * host-to-device transfer be outstanding when it submits the next, which keeps the runtime on
- * its DMA engines.  engine 1: a copy kernel with a fixed grid of `blocks` workgroups on the copy
+ * engine 0 (default): asynchronous copies on the two copy streams, in the form that the runtime
+ * runs on its DMA engines.  engine 1: a copy kernel with a fixed grid of `blocks` workgroups on the copy
  * streams (for comparison; kernels that touch host memory slow concurrent kernels).  Results are
  * identical.  Waits for the streams. */
 hift_status hift_set_state_copy_engine(hift_model* mdl, int32_t engine, int32_t blocks);

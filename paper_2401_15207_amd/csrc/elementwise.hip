@@ -885,7 +885,10 @@ __device__ __forceinline__ void stnt(float* p, const float (&f)[V]) {
 // Memory bound: 5.8 TB/s on a layer of 202 M parameters.  Launched tensor by tensor, the 16 tensors of an encoder layer took
 // 16 launches of which 12 were gains and biases: 2.8 us each for work of less than one.
 struct OptTensor {
-  int64_t off, n;  // first parameter within the group, number of parameters
+  int64_t n;       // parameters
+  float* master;
+  const float* grad;
+  float *s1, *s2;
   bf16* cc;        // where the rounded new values go, or null
   float wd, inv_bc1, inv_bc2;
   int first;       // the tensor's first update
@@ -901,14 +904,12 @@ struct OptHyper {
 };
 
 template <int KIND, int V>
-__device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t, int64_t i, float* __restrict__ master,
-                                           const float* __restrict__ grad, float* __restrict__ s1, float* __restrict__ s2) {
+__device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t, int64_t i) {
   float th[V], g[V], a[V], b[V];
-  const int64_t at = t.off + i;
-  ldnt<V>(master + at, th);
-  ldnt<V>(grad + at, g);
-  if (KIND != 3) ldnt<V>(s1 + at, a);
-  if (KIND == 0) ldnt<V>(s2 + at, b);
+  ldnt<V>(t.master + i, th);
+  ldnt<V>(t.grad + i, g);
+  if (KIND != 3) ldnt<V>(t.s1 + i, a);
+  if (KIND == 0) ldnt<V>(t.s2 + i, b);
 #pragma unroll
   for (int e = 0; e < V; ++e) {
     if (KIND == 0) {
@@ -929,26 +930,25 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
       th[e] -= h.lr * gg;
     }
   }
-  stnt<V>(master + at, th);
-  if (KIND != 3) stnt<V>(s1 + at, a);
-  if (KIND == 0) stnt<V>(s2 + at, b);
+  stnt<V>(t.master + i, th);
+  if (KIND != 3) stnt<V>(t.s1 + i, a);
+  if (KIND == 0) stnt<V>(t.s2 + i, b);
   if (t.cc) stv<bf16, V>(t.cc + i, th);
 }
 
 template <int KIND>
-__global__ void __launch_bounds__(BLK) opt_k(OptHyper h, OptTable table, float* __restrict__ master,
-                                              const float* __restrict__ grad, float* __restrict__ s1, float* __restrict__ s2) {
+__global__ void __launch_bounds__(BLK) opt_k(OptHyper h, OptTable table) {
   int q = 0;
   while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].block0) ++q;  // uniform over the block
   const OptTensor& t = table.t[q];
   const int64_t i0 = (int64_t)(blockIdx.x - t.block0) * (BLK * 4);
   const int64_t i = i0 + threadIdx.x * 4;
   if (t.vec && i + 4 <= t.n) {
-    opt_update<KIND, 4>(h, t, i, master, grad, s1, s2);
+    opt_update<KIND, 4>(h, t, i);
   } else if (t.vec) {
-    for (int64_t k = i; k < t.n; ++k) opt_update<KIND, 1>(h, t, k, master, grad, s1, s2);
+    for (int64_t k = i; k < t.n; ++k) opt_update<KIND, 1>(h, t, k);
   } else {
-    for (int64_t k = i0 + threadIdx.x; k < t.n && k < i0 + BLK * 4; k += BLK) opt_update<KIND, 1>(h, t, k, master, grad, s1, s2);
+    for (int64_t k = i0 + threadIdx.x; k < t.n && k < i0 + BLK * 4; k += BLK) opt_update<KIND, 1>(h, t, k);
   }
 }
 
@@ -1365,8 +1365,7 @@ hipError_t copy_stream(void* dst, const void* src, size_t bytes, int blocks, hip
   LAUNCH_CHECK();
 }
 
-hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, float* master, const float* grad, float* s1,
-                            float* s2, hipStream_t st) {
+hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, hipStream_t st) {
   int kind = o.kind;
   if (kind == 2 && o.momentum == 0.0) kind = 3;
   if (kind < 0 || kind > 3) return hipErrorInvalidValue;
@@ -1381,23 +1380,22 @@ hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items,
       const int64_t more = cdiv(it.n, 4 * BLK);
       if (table.n > 0 && blocks + more > 0x7FFFFFFF) break;
       OptTensor& t = table.t[table.n++];
-      t.off = it.off; t.n = it.n; t.cc = (bf16*)it.compute_copy;
+      t.n = it.n; t.master = it.master; t.grad = it.grad; t.s1 = it.s1; t.s2 = it.s2; t.cc = (bf16*)it.compute_copy;
       t.wd = it.decay ? (float)o.wd : 0.f;
       t.inv_bc1 = (float)(1.0 / (1.0 - pow(o.beta1, (double)it.t)));
       t.inv_bc2 = (float)(1.0 / (1.0 - pow(o.beta2, (double)it.t)));
       t.first = it.t == 1 ? 1 : 0;
       t.block0 = (uint32_t)blocks;
-      t.vec = aligned16(master + it.off) && aligned16(grad + it.off) && (!s1 || aligned16(s1 + it.off)) &&
-              (!s2 || aligned16(s2 + it.off)) && aligned16(it.compute_copy);
+      t.vec = aligned16(it.master) && aligned16(it.grad) && aligned16(it.s1) && aligned16(it.s2) && aligned16(it.compute_copy);
       blocks += more;
     }
     if (table.n == 0) continue;
     const dim3 grid((unsigned)blocks);
     switch (kind) {
-      case 0: opt_k<0><<<grid, BLK, 0, st>>>(h, table, master, grad, s1, s2); break;
-      case 1: opt_k<1><<<grid, BLK, 0, st>>>(h, table, master, grad, s1, s2); break;
-      case 2: opt_k<2><<<grid, BLK, 0, st>>>(h, table, master, grad, s1, s2); break;
-      default: opt_k<3><<<grid, BLK, 0, st>>>(h, table, master, grad, s1, s2); break;
+      case 0: opt_k<0><<<grid, BLK, 0, st>>>(h, table); break;
+      case 1: opt_k<1><<<grid, BLK, 0, st>>>(h, table); break;
+      case 2: opt_k<2><<<grid, BLK, 0, st>>>(h, table); break;
+      default: opt_k<3><<<grid, BLK, 0, st>>>(h, table); break;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -167,14 +167,15 @@ hipError_t copy_stream(void* dst, const void* src, size_t bytes, int blocks, hip
 struct OptArgs {
   int kind; double lr, beta1, beta2, eps, wd, momentum;
 };
-// The tensors of one update: off = first parameter, as an index into master, grad, s1 and s2 alike; n parameters; t the
-// tensor's update number from 1; compute_copy (bf16, or null) receives the rounded new values.  One launch per OPT_TABLE tensors.
+// The tensors of one update: n parameters; t the tensor's update number from 1; the fp32 arrays (s1, s2 null where the optimizer
+// keeps none); compute_copy (bf16, or null) receives the rounded new values.  One launch per OPT_TABLE tensors.
 struct OptItem {
-  int64_t off, n; bool decay; int64_t t; void* compute_copy;
+  int64_t n; bool decay; int64_t t;
+  float* master; const float* grad; float *s1, *s2;
+  void* compute_copy;
 };
 constexpr int OPT_TABLE = 32;
-hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, float* master, const float* grad, float* s1,
-                            float* s2, hipStream_t st);
+hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, hipStream_t st);
 
 // Adafactor on one tensor (Shazeer and Stern 2018, Algorithm 4 without momentum, external step
 // size; constants: epsilon_1 1e-30, clipping threshold 1, decay exponent 0.8).

@@ -234,8 +234,9 @@ struct Prof {
 };
 
 // The pinned host arena as the caller hands it in: one block, or several chunks (a host may grant page-locked memory
-// only in pieces smaller than the whole).  The library addresses it as one range of bytes -- [master (if it lives on
-// the host)][state 0][state 1], each n_params floats -- and splits every access where a chunk ends.
+// only in pieces smaller than the whole).  The library addresses it as one range of bytes -- unit after unit, each unit as
+// [master (if it lives on the host)][state 0][state 1] of its parameters -- and splits every access where a chunk ends.
+// What a group moves is then one piece in either direction (see fetch_state).
 struct PinnedSpace {
   struct Chunk { unsigned char* base; size_t bytes, start; };
   std::vector<Chunk> chunks;  // in address order of the logical range
@@ -258,18 +259,6 @@ struct PinnedSpace {
       done += n;
     }
     return done == bytes ? HIFT_OK : fail(HIFT_ESTATE, "access outside the pinned arena");
-  }
-  hift_status read(void* dst, size_t off, size_t bytes) const {
-    return pieces(off, bytes, [&](unsigned char* p, size_t n, size_t at) {
-      memcpy(reinterpret_cast<unsigned char*>(dst) + at, p, n);
-      return HIFT_OK;
-    });
-  }
-  hift_status write(size_t off, const void* src, size_t bytes) const {
-    return pieces(off, bytes, [&](unsigned char* p, size_t n, size_t at) {
-      memcpy(p, reinterpret_cast<const unsigned char*>(src) + at, n);
-      return HIFT_OK;
-    });
   }
 };
 
@@ -302,12 +291,11 @@ struct hift_model {
   size_t af_work_floats = 0;
   float* grad = nullptr;
   float* state_full = nullptr;  // [n_state] arrays of n_params values, state_stride apart, when state stays in HBM
-  // State of the active group when the rest lives on the host: [n_state][grad_cap] each.  Three slots:
+  // State of the active group when the rest lives on the host, laid out as in the pinned arena.  Three slots:
   // while one is updated, the next group's state arrives in the second and the previous group's
   // drains from the third, so the two directions of the host link run at the same time.
   float* slot[NSLOT] = {nullptr, nullptr, nullptr};
-  PinnedSpace pin;                      // [master (when it lives on the host)][n_state][n_params] floats
-  size_t host_state_off = 0;            // byte offset of the state arrays in `pin` (the master, if there, comes first)
+  PinnedSpace pin;
   float* cos_sin = nullptr;
   // low-rank adapters on the query and value projections (cfg.lora_rank > 0).  Per layer, r = rank: A_q | A_v stacked
   // [2r, d], then B_q [d, r], B_v [d, r]; all layers one after the other.  fp32 master, copy in the compute type,
@@ -329,7 +317,6 @@ struct hift_model {
   hipStream_t cs, hs, ds;
   hipEvent_t ev_h2d[NSLOT], ev_opt[NSLOT], ev_d2h[NSLOT], ev_t0, ev_t1, ev_w0, ev_w1;
   bool d2h_pending[NSLOT] = {false, false, false};
-  int h2d_last = -1;            // slot of the most recent host-to-device transfer
   int d2h_group[NSLOT] = {-1, -1, -1};  // group whose state the pending write-back of a slot carries
   int slot_group[NSLOT] = {-1, -1, -1};  // group whose state a slot holds (arrived or in flight)
   int cur_slot = 0;
@@ -384,7 +371,7 @@ void carve(hift_model* mm, void* dev, size_t* dev_bytes, size_t* pinned_bytes, s
   b.cat = MEM_GRAD;
   M.grad = (float*)b.take(M.grad_cap * 4);
   if (M.n_move > 0 && M.on_host) {
-    // a slot holds [master (if it travels)][state 0][state 1] of one group
+    // a slot holds what travels with one group: n_move arrays
     for (auto& sl : M.slot) {
       b.cat = MEM_MASTER;
       sl = M.master_host ? (float*)b.take((size_t)M.grad_cap * 4) : nullptr;
@@ -1314,20 +1301,53 @@ void group_range(const hift_model* M, int gid, int* ulo, int* uhi, int64_t* plo,
   *pcnt = c;
 }
 
-// One leg of the optimizer-state movement, on the host-to-device or device-to-host stream:
-// hipMemcpyAsync (DMA engines) by default, or a copy kernel with a small fixed grid.  Any
-// kernel that reads or writes host memory while the step runs slows the step's own kernels
-// severely (measured: 4x on the contractions even with 16 workgroups), so the DMA path is the
-// one to use; fetch_state keeps it on the DMA engines.
+// One leg of the optimizer-state movement, on the host-to-device or device-to-host stream, on the DMA engines: any kernel that
+// reads or writes host memory while the step runs slows the step's own kernels severely (4x on the contractions even with 16
+// workgroups), and the runtime runs a plain hipMemcpyAsync as such a kernel whenever it goes to the host, or finds its engine
+// busy with the copy before.  It does not for rectangles: the piece is handed over as one of two rows that follow each other,
+// which is the same bytes (56 GB/s).  The remainder of less than 32 bytes, and copies too small to matter, go the plain way.
+// Measured, 12-layer 768-wide encoder with its state on the host: 32.5 ms a sweep with plain copies, 29.6 with rectangles, 21.9
+// with the state resident.  copy_engine 1: a copy kernel with a small fixed grid, for comparison.
 hift_status state_copy(hift_model* M, void* dst, const void* src, size_t bytes, bool to_device) {
   hipStream_t st = to_device ? M->hs : M->ds;
   if (M->copy_engine == 1 && bytes % 16 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0 &&
       (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
     HIP_TRY(copy_stream(dst, src, bytes, M->copy_blocks, st));
   } else {
-    HIP_TRY(hipMemcpyAsync(dst, src, bytes, to_device ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost, st));
+    const hipMemcpyKind kind = to_device ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost;
+    const size_t row = bytes >= (64 << 10) ? bytes / 32 * 16 : 0, rest = bytes - 2 * row;
+    if (row) HIP_TRY(hipMemcpy2DAsync(dst, row, src, row, row, 2, kind, st));
+    if (rest)
+      HIP_TRY(hipMemcpyAsync(reinterpret_cast<unsigned char*>(dst) + 2 * row, reinterpret_cast<const unsigned char*>(src) + 2 * row, rest, kind, st));
   }
   return HIFT_OK;
+}
+
+// fn(host pointer, bytes, offset within the request) for every piece of values [off, off + cnt) of array j of the pinned
+// arena (the master first when it lives there, then the state arrays), in order
+template <class F>
+hift_status host_pieces(const hift_model* M, int j, int64_t off, int64_t cnt, F fn) {
+  for (int u = 0; u < M->lay.n_units; ++u) {
+    const int64_t lo = std::max(off, M->lay.unit_off[u]), hi = std::min(off + cnt, M->lay.unit_off[u] + M->lay.unit_cnt[u]);
+    if (lo >= hi) continue;
+    const int64_t first = M->lay.unit_off[u] * M->n_move + j * M->lay.unit_cnt[u] + (lo - M->lay.unit_off[u]);
+    ST_TRY(M->pin.pieces((size_t)first * 4, (size_t)(hi - lo) * 4, [&](unsigned char* h, size_t n, size_t at) {
+      return fn(h, n, (size_t)(lo - off) * 4 + at);
+    }));
+  }
+  return HIFT_OK;
+}
+hift_status host_read(const hift_model* M, int j, int64_t off, int64_t cnt, void* dst) {
+  return host_pieces(M, j, off, cnt, [&](unsigned char* h, size_t n, size_t at) {
+    memcpy(reinterpret_cast<unsigned char*>(dst) + at, h, n);
+    return HIFT_OK;
+  });
+}
+hift_status host_write(const hift_model* M, int j, int64_t off, int64_t cnt, const void* src) {
+  return host_pieces(M, j, off, cnt, [&](unsigned char* h, size_t n, size_t at) {
+    memcpy(h, reinterpret_cast<const unsigned char*>(src) + at, n);
+    return HIFT_OK;
+  });
 }
 
 // Queue the host-to-device copy of a group's state into a slot (Algorithm 1 step i).
@@ -1339,19 +1359,11 @@ hift_status fetch_state(hift_model* M, int gid, int s) {
   // drained this slot, and one that carries this group's own state to the host
   for (int q = 0; q < NSLOT; ++q)
     if (M->d2h_pending[q] && (q == s || M->d2h_group[q] == gid)) HIP_TRY(hipStreamWaitEvent(M->hs, M->ev_d2h[q], 0));
-  // keep one host-to-device transfer outstanding at the moment the next is submitted: the host
-  // runs up to a step ahead of the GPU, and a copy submitted while the copy engine still has
-  // a backlog is executed by a full-grid copy kernel instead, which starves the step's kernels
-  if (M->copy_engine == 0 && M->h2d_last >= 0) HIP_TRY(hipEventSynchronize(M->ev_h2d[M->h2d_last]));
-  for (int j = 0; j < M->n_move; ++j) {  // array j of the pinned range: the master first when it travels, then the state
-    unsigned char* dst = reinterpret_cast<unsigned char*>(M->slot[s] + (size_t)j * M->grad_cap);
-    ST_TRY(M->pin.pieces(((size_t)j * M->lay.n_params + plo) * 4, (size_t)cnt * 4, [&](unsigned char* h, size_t n, size_t at) {
-      return state_copy(M, dst + at, h, n, true);
-    }));
-    M->h2d_bytes += (uint64_t)cnt * 4;
-  }
+  ST_TRY(M->pin.pieces((size_t)plo * M->n_move * 4, (size_t)cnt * M->n_move * 4, [&](unsigned char* h, size_t n, size_t at) {
+    return state_copy(M, reinterpret_cast<unsigned char*>(M->slot[s]) + at, h, n, true);
+  }));
+  M->h2d_bytes += (uint64_t)cnt * M->n_move * 4;
   HIP_TRY(hipEventRecord(M->ev_h2d[s], M->hs));
-  M->h2d_last = s;
   M->slot_group[s] = gid;
   return HIFT_OK;
 }
@@ -1363,7 +1375,7 @@ hift_status sync_all(hift_model* M);
 hift_status load_forward_copy(hift_model* M, int64_t off, int64_t cnt) {
   for (int64_t done = 0; done < cnt; done += M->grad_cap) {
     const int64_t n = std::min<int64_t>(M->grad_cap, cnt - done);
-    ST_TRY(M->pin.pieces((size_t)(off + done) * 4, (size_t)n * 4, [&](unsigned char* h, size_t nb, size_t at) {
+    ST_TRY(host_pieces(M, 0, off + done, n, [&](unsigned char* h, size_t nb, size_t at) {
       HIP_TRY(hipMemcpyAsync(reinterpret_cast<unsigned char*>(M->slot[0]) + at, h, nb, hipMemcpyHostToDevice, M->cs));
       return HIFT_OK;
     }));
@@ -1525,7 +1537,6 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
     return fail(HIFT_ENOMEM, "arenas too small: need %zu device and %zu pinned bytes", need_dev, need_pin);
   }
   carve(M, device_arena, nullptr, nullptr);
-  M->host_state_off = M->master_host ? (size_t)M->lay.n_params * 4 : 0;
   M->cs = (hipStream_t)compute_stream;
   M->hs = (hipStream_t)h2d_stream;
   M->ds = (hipStream_t)d2h_stream;
@@ -1575,7 +1586,7 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
     CR_TRY(hipStreamSynchronize(M->cs));
   }
   if (M->master_host) {
-    if (init_params_host && M->pin.write(0, init_params_host, (size_t)M->lay.n_params * 4) != HIFT_OK) return bail(HIFT_ESTATE);
+    if (init_params_host && host_write(M, 0, 0, M->lay.n_params, init_params_host) != HIFT_OK) return bail(HIFT_ESTATE);
     if (load_forward_copy(M, 0, M->lay.n_params) != HIFT_OK) return bail(HIFT_EDEVICE);
   } else {
     if (init_params_host) {
@@ -1730,11 +1741,11 @@ hift_status hift_checkpoint_save(hift_model* M, void* host_buffer, size_t bytes)
   memcpy(p, M->order.data(), (size_t)M->k * 4); p += (size_t)M->k * 4;
   memcpy(p, M->unit_steps.data(), (size_t)M->lay.n_units * 8); p += (size_t)M->lay.n_units * 8;
   const size_t np4 = (size_t)M->lay.n_params * 4;
-  if (M->master_host) ST_TRY(M->pin.read(p, 0, np4));
+  if (M->master_host) ST_TRY(host_read(M, 0, 0, M->lay.n_params, p));
   else HIP_TRY(hipMemcpy(p, M->master, np4, hipMemcpyDeviceToHost));
   p += np4;
   for (int j = 0; j < M->n_state; ++j, p += np4) {
-    if (M->on_host) ST_TRY(M->pin.read(p, M->host_state_off + (size_t)j * np4, np4));
+    if (M->on_host) ST_TRY(host_read(M, M->n_move - M->n_state + j, 0, M->lay.n_params, p));
     else HIP_TRY(hipMemcpy(p, M->state_full + (size_t)j * M->state_stride(), np4, hipMemcpyDeviceToHost));
   }
   if (M->n_fac) HIP_TRY(hipMemcpy(p, M->fac, (size_t)M->n_fac * 4, hipMemcpyDeviceToHost));
@@ -1778,7 +1789,7 @@ hift_status hift_checkpoint_load(hift_model* M, const void* host_buffer, size_t 
   ST_TRY(hift_write_params(M, 0, M->lay.n_units, reinterpret_cast<const float*>(p), (size_t)M->lay.n_params));
   p += np4;
   for (int j = 0; j < M->n_state; ++j, p += np4) {
-    if (M->on_host) ST_TRY(M->pin.write(M->host_state_off + (size_t)j * np4, p, np4));
+    if (M->on_host) ST_TRY(host_write(M, M->n_move - M->n_state + j, 0, M->lay.n_params, p));
     else HIP_TRY(hipMemcpy(M->state_full + (size_t)j * M->state_stride(), p, np4, hipMemcpyHostToDevice));
   }
   if (M->n_fac) HIP_TRY(hipMemcpy(M->fac, p, (size_t)M->n_fac * 4, hipMemcpyHostToDevice));
@@ -1819,8 +1830,6 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
       s = M->cur_slot;
       ST_TRY(fetch_state(M, gid, s));
     }
-    // a slot reused without a new fetch may still be draining to the host from its last update
-    if (M->d2h_pending[s]) HIP_TRY(hipStreamWaitEvent(M->cs, M->ev_d2h[s], 0));
     M->cur_slot = s;
     // prefetch the state of the group the schedule visits next into the slot after this one (the
     // one after that is still draining the previous group's state); the write-back that last used
@@ -1837,23 +1846,27 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
 
   // ---- optimizer on the group (its update number drives AdamW's bias correction) ----
   HIP_TRY(hipEventRecord(M->ev_w0, M->cs));
-  if (moving) HIP_TRY(hipStreamWaitEvent(M->cs, M->ev_h2d[s], 0));
+  if (moving) {
+    HIP_TRY(hipStreamWaitEvent(M->cs, M->ev_h2d[s], 0));
+    // a slot reused without a new fetch may still be draining to the host from its last update (a fetch was
+    // ordered behind that)
+    if (M->d2h_pending[s] && M->d2h_group[s] == gid) HIP_TRY(hipStreamWaitEvent(M->cs, M->ev_d2h[s], 0));
+  }
   HIP_TRY(hipEventRecord(M->ev_w1, M->cs));
   for (int u = ulo; u < uhi; ++u) M->unit_steps[u] += 1;
   OptArgs oa{M->opt.kind, M->opt.lr, M->opt.beta1, M->opt.beta2, M->opt.eps, M->opt.weight_decay, M->opt.momentum};
-  float *s1b = nullptr, *s2b = nullptr;
-  int64_t sbase = plo;  // state index = parameter offset - sbase
-  float* mbase = M->master_host ? M->slot[s] - plo : M->master;  // master of parameter i at mbase[i]
-  if (M->n_state > 0) {
-    if (moving) {
-      s1b = M->slot[s] + (size_t)(M->master_host ? 1 : 0) * M->grad_cap;
-      s2b = s1b + M->grad_cap;
-    } else {
-      s1b = M->state_full;
-      s2b = M->state_full + M->state_stride();
-      sbase = 0;
-    }
-  }
+  // array j of what travels with unit u, in the slot (laid out as in the pinned arena)
+  auto in_slot = [&](int u, int j) {
+    return M->slot[s] + (M->lay.unit_off[u] - plo) * M->n_move + j * M->lay.unit_cnt[u];
+  };
+  auto master_of = [&](const Tensor& t) {
+    return M->master_host ? in_slot(t.unit, 0) + (t.off - M->lay.unit_off[t.unit]) : M->master + t.off;
+  };
+  auto state_of = [&](const Tensor& t, int j) -> float* {
+    if (j >= M->n_state) return nullptr;
+    return moving ? in_slot(t.unit, M->n_move - M->n_state + j) + (t.off - M->lay.unit_off[t.unit])
+                  : M->state_full + j * M->state_stride() + t.off;
+  };
   {
     double bytes_per = M->n_state == 2 ? 28.0 : (M->n_state == 1 ? 20.0 : 12.0);
     if (M->opt.kind == HIFT_ADAFACTOR) bytes_per = 24.0;  // the gradient is read four times (row, column, clipping, update)
@@ -1866,14 +1879,12 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
       void* cc = M->dt == DT_BF16 ? M->W(t) : nullptr;  // null also for a matrix kept only in fragment order
       if (M->opt.kind == HIFT_ADAFACTOR) {
         K_TRY(adafactor_update(M->opt.lr, M->opt.weight_decay, t.kind == HIFT_KIND_MATRIX, tg, t.rows, t.cols,
-                               mbase + t.off, M->grad + (t.off - plo), M->fac + t.fac_off, M->af_work, cc, M->cs));
+                               master_of(t), M->grad + (t.off - plo), M->fac + t.fac_off, M->af_work, cc, M->cs));
         continue;
       }
-      items.push_back(OptItem{t.off - plo, t.count(), t.kind == HIFT_KIND_MATRIX, tg, cc});
+      items.push_back(OptItem{t.count(), t.kind == HIFT_KIND_MATRIX, tg, master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc});
     }
-    if (!items.empty())
-      K_TRY(optimizer_update(oa, items.data(), (int)items.size(), mbase + plo, M->grad, s1b ? s1b + (plo - sbase) : nullptr,
-                             (s2b && M->n_state == 2) ? s2b + (plo - sbase) : nullptr, M->cs));
+    if (!items.empty()) K_TRY(optimizer_update(oa, items.data(), (int)items.size(), M->cs));
   }
   if (moving) HIP_TRY(hipEventRecord(M->ev_opt[s], M->cs));
   if (M->wpk) {  // the updated matrices in fragment order, for the next forward and dX
@@ -1891,13 +1902,10 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
   // ---- state back to the host (Algorithm 1 step k) ----
   if (moving) {
     HIP_TRY(hipStreamWaitEvent(M->ds, M->ev_opt[s], 0));
-    for (int j = 0; j < M->n_move; ++j) {
-      const unsigned char* src = reinterpret_cast<const unsigned char*>(M->slot[s] + (size_t)j * M->grad_cap);
-      ST_TRY(M->pin.pieces(((size_t)j * M->lay.n_params + plo) * 4, (size_t)cnt * 4, [&](unsigned char* h, size_t n, size_t at) {
-        return state_copy(M, h, src + at, n, false);
-      }));
-      M->d2h_bytes += (uint64_t)cnt * 4;
-    }
+    ST_TRY(M->pin.pieces((size_t)plo * M->n_move * 4, (size_t)cnt * M->n_move * 4, [&](unsigned char* h, size_t n, size_t at) {
+      return state_copy(M, h, reinterpret_cast<const unsigned char*>(M->slot[s]) + at, n, false);
+    }));
+    M->d2h_bytes += (uint64_t)cnt * M->n_move * 4;
     HIP_TRY(hipEventRecord(M->ev_d2h[s], M->ds));
     M->d2h_pending[s] = true;
     M->d2h_group[s] = gid;
@@ -1968,8 +1976,8 @@ hift_status hift_lora_step(hift_model* M, const hift_batch* bt, float* loss_out)
     const double bytes_per = 28.0 + (M->dt == DT_BF16 ? 2.0 : 0.0);
     Scope sc(M, CAT_OPT, bytes_per * M->n_lora);
     OptArgs oa{M->opt.kind, M->opt.lr, M->opt.beta1, M->opt.beta2, M->opt.eps, M->opt.weight_decay, M->opt.momentum};
-    const OptItem all{0, M->n_lora, true, M->lora_t, M->dt == DT_BF16 ? M->lora_wc : nullptr};
-    K_TRY(optimizer_update(oa, &all, 1, M->lora_master, M->lora_grad, M->lora_m, M->lora_v, M->cs));
+    const OptItem all{M->n_lora, true, M->lora_t, M->lora_master, M->lora_grad, M->lora_m, M->lora_v, M->dt == DT_BF16 ? M->lora_wc : nullptr};
+    K_TRY(optimizer_update(oa, &all, 1, M->cs));
   }
   HIP_TRY(hipEventRecord(M->ev_w0, M->cs));
   HIP_TRY(hipEventRecord(M->ev_w1, M->cs));
@@ -1990,7 +1998,7 @@ hift_status hift_read_params(hift_model* M, int32_t ulo, int32_t uhi, int32_t wh
   if (which != 0 && which != 1) return fail(HIFT_EINVAL, "which must be 0 or 1");
   ST_TRY(sync_all(M));
   if (which == 0 && M->master_host) {
-    ST_TRY(M->pin.read(dst, (size_t)off * 4, (size_t)cnt * 4));  // every write-back has landed
+    ST_TRY(host_read(M, 0, off, cnt, dst));  // every write-back has landed
   } else if (which == 0 || M->dt == DT_F32) {
     HIP_TRY(hipMemcpy(dst, M->master + off, (size_t)cnt * 4, hipMemcpyDeviceToHost));
   } else {
@@ -2031,12 +2039,12 @@ hift_status write_params_from(hift_model* M, int32_t ulo, int32_t uhi, const flo
   ST_TRY(sync_all(M));
   if (M->master_host) {
     if (src_on_device) {
-      ST_TRY(M->pin.pieces((size_t)off * 4, (size_t)cnt * 4, [&](unsigned char* h, size_t n, size_t at) {
+      ST_TRY(host_pieces(M, 0, off, cnt, [&](unsigned char* h, size_t n, size_t at) {
         HIP_TRY(hipMemcpy(h, reinterpret_cast<const unsigned char*>(src) + at, n, hipMemcpyDeviceToHost));
         return HIFT_OK;
       }));
     } else {
-      ST_TRY(M->pin.write((size_t)off * 4, src, (size_t)cnt * 4));
+      ST_TRY(host_write(M, 0, off, cnt, src));
     }
     ST_TRY(load_forward_copy(M, off, cnt));
     HIP_TRY(repack_units(M, ulo, uhi));
@@ -2072,7 +2080,7 @@ hift_status hift_read_state(hift_model* M, int32_t ulo, int32_t uhi, int32_t slo
   if (slot < 0 || slot >= M->n_state) return fail(HIFT_EINVAL, "state slot %d outside [0,%d)", slot, M->n_state);
   ST_TRY(sync_all(M));
   if (M->on_host) {
-    ST_TRY(M->pin.read(dst, M->host_state_off + ((size_t)slot * M->lay.n_params + off) * 4, (size_t)cnt * 4));  // write-back has landed
+    ST_TRY(host_read(M, M->n_move - M->n_state + slot, off, cnt, dst));  // write-back has landed
   } else {
     HIP_TRY(hipMemcpy(dst, M->state_full + (size_t)slot * M->state_stride() + off, (size_t)cnt * 4, hipMemcpyDeviceToHost));
   }
@@ -2381,8 +2389,8 @@ hift_status hift_kernel_optimizer(const hift_opt* opt, int64_t count, int32_t de
   if (count < 0 || t < 1) return fail(HIFT_EINVAL, "count must be >= 0 and t >= 1");
   if (opt->kind == HIFT_ADAFACTOR) return fail(HIFT_EINVAL, "Adafactor works on whole tensors; it has no element-wise kernel entry");
   OptArgs oa{opt->kind, opt->lr, opt->beta1, opt->beta2, opt->eps, opt->weight_decay, opt->momentum};
-  const OptItem all{0, count, decay != 0, t, compute_copy};
-  HIP_TRY(optimizer_update(oa, &all, 1, master, grad, state1, state2, (hipStream_t)stream));
+  const OptItem all{count, decay != 0, t, master, grad, state1, state2, compute_copy};
+  HIP_TRY(optimizer_update(oa, &all, 1, (hipStream_t)stream));
   return HIFT_OK;
 }
 
