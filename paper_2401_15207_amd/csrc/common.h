@@ -70,3 +70,11 @@ __device__ __forceinline__ void load_to_lds_b128(hift_u32x4 rsrc, uint32_t lds_a
                : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                : "memory");
 }
+
+// x Phi(x) and its derivative Phi(x) + x phi(x)
+__device__ __forceinline__ float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
+__device__ __forceinline__ float gelu_df(float x) {
+  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
+  const float pdf = 0.3989422804014327f * expf(-0.5f * x * x);
+  return cdf + x * pdf;
+}

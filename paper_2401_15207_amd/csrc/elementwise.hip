@@ -486,12 +486,6 @@ __global__ void __launch_bounds__(BLK) rope_k(T* __restrict__ qkv, int64_t T_, i
 }
 
 // ---------------------------------------------------------------------------- activations
-__device__ __forceinline__ float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_df(float x) {
-  const float cdf = 0.5f * (1.0f + erff(x * 0.70710678118654752f));
-  const float pdf = 0.3989422804014327f * expf(-0.5f * x * x);
-  return cdf + x * pdf;
-}
 
 template <typename T, int V, bool BWD>
 __global__ void __launch_bounds__(BLK) gelu_k(int64_t n, const T* __restrict__ dact, const T* __restrict__ pre,

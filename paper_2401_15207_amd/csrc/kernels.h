@@ -30,8 +30,8 @@ struct Gemm {
   //   BAND_K_UPTO_ROW   A(m,k) = 0 for k > m: the contraction of a tile stops at its last row
   //   BAND_K_FROM_ROW   A(m,k) = 0 for k < m: the contraction of a tile starts at its first row
   int band = 0;
-  // Fused epilogue of the packed-operand kernel (gemm_packed only; the packed copy must have been built
-  // with the matching column order, see pack_b):
+  // Fused epilogue of the packed-operand kernel (the packed copy must have been built with the matching column order,
+  // see pack_b); EPI_GELU and EPI_GELU_BWD also of gemm(), where lds_gelu_applies():
   //   EPI_SWIGLU  B = gate | up, N = 2 f.  C [M, N] (may be null: not kept) receives the pre-activations as
   //               usual; C2 [M, f] (ldc2) receives silu(gate) * up computed from the rounded pre-activations.
   //   EPI_ROPE    B = q | k | v of heads of width 128.  Columns below rot_cols are rotated pairwise
@@ -69,6 +69,7 @@ hipError_t gemm(const Gemm& g, hipStream_t st);
 
 // The kernel for problems whose tiles do not fill the chip (gemm_lds.hip); gemm() chooses it.
 bool lds_gemm_applies(const Gemm& g);
+bool lds_gelu_applies(const Gemm& g);  // with g.epi = EPI_GELU or EPI_GELU_BWD
 hipError_t gemm_lds(const Gemm& g, hipStream_t st);
 
 // Weight operand pre-packed in MFMA fragment order (see gemm.hip).  packed_b_bytes: size of the packed

@@ -716,6 +716,16 @@ hift_status linear(hift_model* M, const void* x, int64_t rows, const Tensor& w, 
   if (rowsq) *rowsq = false;
   if (only_packed) return fail(HIFT_ESTATE, "%s has no row-major copy and the packed-operand kernel refused the problem", w.name.c_str());
   if (sc.r) sc.r->cat = CAT_GEMM_REST;
+  if (epi && epi->gelu && epi->act && !(M->cfg.unfused & HIFT_UNFUSED_EPILOGUES)) {
+    Gemm f = g;
+    f.epi = EPI_GELU;
+    f.C2 = epi->act; f.ldc2 = w.rows;
+    if (!epi->keep_pre) f.C = nullptr;
+    if (lds_gelu_applies(f)) {
+      g = f;
+      epi->fused = true;
+    }
+  }
   K_TRY(gemm(g, M->cs));
   return HIFT_OK;
 }
@@ -752,6 +762,16 @@ hift_status linear_dx(hift_model* M, const void* dy, int64_t rows, const Tensor&
   }
   if (only_packed) return fail(HIFT_ESTATE, "%s has no row-major copy and the packed-operand kernel refused the problem", w.name.c_str());
   if (sc.r) sc.r->cat = CAT_GEMM_REST;
+  if (gelu && gate_pre && dgu && fused && !(M->cfg.unfused & HIFT_UNFUSED_EPILOGUES)) {
+    Gemm f = g;
+    f.epi = EPI_GELU_BWD;
+    f.C2 = const_cast<void*>(gate_pre); f.ldc2 = w.cols;
+    f.C = dgu;
+    if (lds_gelu_applies(f)) {
+      g = f;
+      *fused = true;
+    }
+  }
   K_TRY(gemm(g, M->cs));
   return HIFT_OK;
 }

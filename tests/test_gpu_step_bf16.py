@@ -314,3 +314,26 @@ def test_master_on_host_gives_the_same_trajectory(optk):
     assert m["device_master"] < hbm.memory()["device_master"]
 
 
+@pytest.mark.parametrize("arch,batch,seq", [(0, 3, 21), (1, 2, 40), (1, 5, 64)])
+def test_gelu_in_the_contraction_is_the_separate_kernel_bit_for_bit(arch, batch, seq):
+    """Layers too small for packed weights: GELU and its derivative on the way out of the contraction (rows in no multiple of
+    any tile, pre-activations kept and not kept) against the contraction followed by the elementwise kernels."""
+    import torch
+    import paper_2401_15207_amd as H
+    cfg = dict(arch=arch, n_layers=2, d_model=128, n_heads=2, d_ffn=328, vocab=304, max_seq=64, n_classes=3, norm_eps=1e-5,
+               rope_base=10000.0, dtype=1)
+    wl = dict(cfg, batch=batch, seq=seq)
+    opt = dict(kind="adamw", lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01, momentum=0.0)
+    got = []
+    for unfused in (0, H.UNFUSED_EPILOGUES):
+        tensors, _n = H.tensor_list(cfg)
+        theta = init_params(1, [(n, s, k) for n, s, k, _u, _o in tensors], bf16_exact=True, jitter=0.02)
+        gpu = H.HiftModel(cfg, opt, 1, batch, seq, init_params=theta, unfused=unfused)
+        gpu.set_group_schedule("bottom2up", 1)
+        losses = []
+        for t in range(1, 2 * gpu.k + 1):
+            tok, lab = make_batch(wl, 3, t)
+            losses.append(gpu.step(torch.from_numpy(tok).cuda(), torch.from_numpy(lab).cuda(), gpu.schedule_group_at(t)))
+        got.append((losses, gpu.read_params(), gpu.read_state(0, gpu.n_units, 0)))
+    assert got[0][0] == got[1][0]
+    assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])
