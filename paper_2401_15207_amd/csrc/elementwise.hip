@@ -889,8 +889,9 @@ struct OptTensor {
   uint32_t block0; // first block of the launch that works on it
   int vec;         // pieces of four are 16-byte aligned in every array
 };
+template <int NT>  // 1 for a single tensor (the small table saves 0.2 us of a 3.6 us launch), OPT_TABLE for a group
 struct OptTable {
-  OptTensor t[OPT_TABLE];
+  OptTensor t[NT];
   int n;
 };
 struct OptHyper {
@@ -930,10 +931,11 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
   if (t.cc) stv<bf16, V>(t.cc + i, th);
 }
 
-template <int KIND>
-__global__ void __launch_bounds__(BLK) opt_k(OptHyper h, OptTable table) {
+template <int KIND, int NT>
+__global__ void __launch_bounds__(BLK) opt_k(OptHyper h, OptTable<NT> table) {
   int q = 0;
-  while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].block0) ++q;  // uniform over the block
+  if (NT > 1)
+    while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].block0) ++q;  // uniform over the block
   const OptTensor& t = table.t[q];
   const int64_t i0 = (int64_t)(blockIdx.x - t.block0) * (BLK * 4);
   const int64_t i = i0 + threadIdx.x * 4;
@@ -1359,42 +1361,45 @@ hipError_t copy_stream(void* dst, const void* src, size_t bytes, int blocks, hip
   LAUNCH_CHECK();
 }
 
-hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, hipStream_t st) {
-  int kind = o.kind;
-  if (kind == 2 && o.momentum == 0.0) kind = 3;
-  if (kind < 0 || kind > 3) return hipErrorInvalidValue;
+template <int NT>
+static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_items, int* done, hipStream_t st) {
+  const int kind = o.kind == 2 && o.momentum == 0.0 ? 3 : o.kind;
   const OptHyper h{(float)o.lr, (float)o.beta1, (float)(1.0 - o.beta1), (float)o.beta2, (float)(1.0 - o.beta2), (float)o.eps, (float)o.momentum};
-  for (int at = 0; at < n_items;) {
-    OptTable table;
-    table.n = 0;
-    int64_t blocks = 0;
-    for (; at < n_items && table.n < OPT_TABLE; ++at) {
-      const OptItem& it = items[at];
-      if (it.n == 0) continue;
-      const int64_t more = cdiv(it.n, 4 * BLK);
-      if (table.n > 0 && blocks + more > 0x7FFFFFFF) break;
-      OptTensor& t = table.t[table.n++];
-      t.n = it.n; t.master = it.master; t.grad = it.grad; t.s1 = it.s1; t.s2 = it.s2; t.cc = (bf16*)it.compute_copy;
-      t.wd = it.decay ? (float)o.wd : 0.f;
-      t.inv_bc1 = (float)(1.0 / (1.0 - pow(o.beta1, (double)it.t)));
-      t.inv_bc2 = (float)(1.0 / (1.0 - pow(o.beta2, (double)it.t)));
-      t.first = it.t == 1 ? 1 : 0;
-      t.block0 = (uint32_t)blocks;
-      t.vec = aligned16(it.master) && aligned16(it.grad) && aligned16(it.s1) && aligned16(it.s2) && aligned16(it.compute_copy);
-      blocks += more;
-    }
-    if (table.n == 0) continue;
-    const dim3 grid((unsigned)blocks);
-    switch (kind) {
-      case 0: opt_k<0><<<grid, BLK, 0, st>>>(h, table); break;
-      case 1: opt_k<1><<<grid, BLK, 0, st>>>(h, table); break;
-      case 2: opt_k<2><<<grid, BLK, 0, st>>>(h, table); break;
-      default: opt_k<3><<<grid, BLK, 0, st>>>(h, table); break;
-    }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  OptTable<NT> table;
+  table.n = 0;
+  int64_t blocks = 0;
+  for (; *done < n_items && table.n < NT; ++*done) {
+    const OptItem& it = items[*done];
+    if (it.n == 0) continue;
+    const int64_t more = cdiv(it.n, 4 * BLK);
+    if (table.n > 0 && blocks + more > 0x7FFFFFFF) break;
+    OptTensor& t = table.t[table.n++];
+    t.n = it.n; t.master = it.master; t.grad = it.grad; t.s1 = it.s1; t.s2 = it.s2; t.cc = (bf16*)it.compute_copy;
+    t.wd = it.decay ? (float)o.wd : 0.f;
+    t.inv_bc1 = (float)(1.0 / (1.0 - pow(o.beta1, (double)it.t)));
+    t.inv_bc2 = (float)(1.0 / (1.0 - pow(o.beta2, (double)it.t)));
+    t.first = it.t == 1 ? 1 : 0;
+    t.block0 = (uint32_t)blocks;
+    t.vec = aligned16(it.master) && aligned16(it.grad) && aligned16(it.s1) && aligned16(it.s2) && aligned16(it.compute_copy);
+    blocks += more;
   }
-  return hipSuccess;
+  if (table.n == 0) return hipSuccess;
+  const dim3 grid((unsigned)blocks);
+  switch (kind) {
+    case 0: opt_k<0, NT><<<grid, BLK, 0, st>>>(h, table); break;
+    case 1: opt_k<1, NT><<<grid, BLK, 0, st>>>(h, table); break;
+    case 2: opt_k<2, NT><<<grid, BLK, 0, st>>>(h, table); break;
+    default: opt_k<3, NT><<<grid, BLK, 0, st>>>(h, table); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, hipStream_t st) {
+  if (o.kind < 0 || o.kind > 3) return hipErrorInvalidValue;
+  hipError_t e = hipSuccess;
+  for (int done = 0; done < n_items && e == hipSuccess;)
+    e = n_items == 1 ? launch_update<1>(o, items, n_items, &done, st) : launch_update<OPT_TABLE>(o, items, n_items, &done, st);
+  return e;
 }
 
 size_t adafactor_work_floats(int64_t rows, int64_t cols) {
