@@ -369,6 +369,28 @@ def test_cross_entropy_without_any_target(dtype):
     assert float(loss) == 0.0 and float(dz.float().abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("dtype", [F32, BF16])
+@pytest.mark.parametrize("rows,V", [(255, 40), (2047, 40), (2048, 33), (2049, 40), (2100, 33)])
+def test_cross_entropy_counts_its_targets(dtype, rows, V):
+    """Up to 2048 rows the row kernel counts the rows with a target itself, beyond that a kernel of its own does; rows without
+    one at both ends, among them the row that leaves the count for the mean.  The count is exact, tolerances as above."""
+    import torch
+    import paper_2401_15207_amd as H
+    rng = np.random.default_rng(rows + V)
+    z = rng.standard_normal((rows, V)).astype(np.float32)
+    z = _bf16_round(z) if dtype == BF16 else z
+    lab = rng.integers(0, V, size=rows).astype(np.int32)
+    lab[rng.random(rows) < 0.3] = -1
+    lab[[0, rows - 1]] = -1
+    dz, scratch, loss = _dev(z, dtype == BF16), torch.full((rows + 1,), -5.0, device="cuda"), torch.full((1,), -7.0, device="cuda")
+    H.kernel_cross_entropy(dtype, rows, V, dz, torch.from_numpy(lab).cuda(), scratch, loss)
+    torch.cuda.synchronize()
+    ref_loss, ref_d = O.cross_entropy_fwd(z.astype(np.float64), lab.astype(np.int64))
+    assert float(scratch[rows]) == int((lab >= 0).sum())
+    assert abs(float(loss) - ref_loss) <= 2e-6 * abs(ref_loss) + 1e-6
+    assert np.all(np.abs(dz.float().cpu().numpy() - ref_d) <= (2 ** -8 if dtype == BF16 else 1e-5) * np.abs(ref_d) + 1e-8)
+
+
 def test_fused_attention_refuses_what_it_cannot_take():
     import torch
     import paper_2401_15207_amd as H_
