@@ -114,10 +114,10 @@ __device__ __forceinline__ void store_rows_staged(const f32x16 (&acc)[NB], float
 // dQ goes to the q columns of dqkv (row stride ld, like qkv), un-rotated if cos_sin is given.  Neither P nor dS
 // is stored: the key-major kernel below forms its own.
 template <int HD, bool CAUSAL, int NW, bool BWD>
-__global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
-                                                   bf16* __restrict__ prob, bf16* __restrict__ ctx, int64_t ldc,
-                                                   const bf16* __restrict__ dctx, float* __restrict__ lse, float* __restrict__ dsum,
-                                                   bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
+__device__ __forceinline__ void attn_rows(unsigned char* lds /* [buffer][K | V] tiles */, const int block, const bf16* __restrict__ qkv, int64_t ld,
+                                          int S, int H, int BH, float scale, bf16* __restrict__ prob, bf16* __restrict__ ctx, int64_t ldc,
+                                          const bf16* __restrict__ dctx, float* __restrict__ lse, float* __restrict__ dsum,
+                                          bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
   const float scale_log2e = BWD ? scale * 1.4426950408889634f : scale;
   constexpr int QB = 32 * NW;       // query rows per workgroup
   constexpr int ROWB = HD * 2;      // bytes per LDS row
@@ -126,7 +126,6 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* _
   constexpr int KS = HD / 16;       // k-steps of a score block
   constexpr int NB = HD / 32;       // 32-column blocks of the output
   constexpr int IPW = KTILE * PPR / 64 / NW;  // load instructions per wavefront and tile
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * TILEB];  // [buffer][K | V]
   auto swz = [](int r) { return PPR == 16 ? (r & 15) : ((r >> 1) & 7); };
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -139,7 +138,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* _
   int bh, qb;
   if (CAUSAL) {
     const int n_long = (nqb + 1) / 2, n_short = nqb - n_long;
-    const int L = (int)blockIdx.x, first = n_long * BH;
+    const int L = block, first = n_long * BH;
     if (L < first) {
       bh = L / n_long;
       qb = nqb - 1 - L % n_long;
@@ -148,8 +147,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* _
       qb = (L - first) % n_short;
     }
   } else {
-    bh = (int)blockIdx.x / nqb;
-    qb = (int)blockIdx.x % nqb;
+    bh = block / nqb;
+    qb = block % nqb;
   }
   const int b = bh / H, h = bh % H;
   const int64_t d = (int64_t)H * HD;
@@ -553,6 +552,15 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* _
   }
 }
 
+template <int HD, bool CAUSAL, int NW, bool BWD>
+__global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
+                                                   bf16* __restrict__ prob, bf16* __restrict__ ctx, int64_t ldc,
+                                                   const bf16* __restrict__ dctx, float* __restrict__ lse, float* __restrict__ dsum,
+                                                   bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * KTILE * HD * 2];
+  attn_rows<HD, CAUSAL, NW, BWD>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, prob, ctx, ldc, dctx, lse, dsum, dqkv, cos_sin);
+}
+
 // Key-major half of the attention backward: dV = P^T dO and dK = dS^T Q, both sums over the queries.  A workgroup
 // owns 128 keys of one (batch, head), a wavefront 32 of them from start to end with their K and V rows in
 // registers; queries pass through LDS in tiles of 64 (Q and dO rows, double-buffered direct-to-LDS loads).  Per
@@ -561,21 +569,25 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* _
 // that order of rows the 16 values a lane holds per 32 queries are, as they lie in registers, the operand
 // fragments of the two sums, whose other operands (dO^T, Q^T) come from the same tiles by transposing LDS
 // reads.  Nothing of size S x S is read or written.  One workgroup per compute unit (the accumulators of four
-// products and 64 K / V registers); workgroups are issued longest first under the causal mask.
+// products and 64 K / V registers) for heads 128 wide; two for heads 64 wide, whose 302 registers fit 256 without a spill: a
+// wavefront alone waits for its own chain of reads, products and exponentials, and the backward of 16 x 16 heads at 512 tokens
+// takes 90 us instead of 123 (1024 tokens: 303 instead of 423).  Workgroups are issued longest first under the causal mask.
 // lse: log2 of each query's sum of exponentials (forward kernel); dsum: D = dO . O per query (query-major kernel).
 // cos_sin, if given, un-rotates dK (k was rotated after its projection).
+constexpr int KV_QT = 64;  // queries per tile
+template <int HD>
+constexpr int KV_LDS = 2 * (2 * KV_QT * HD * 2 + 2048);  // two buffers of Q | dO | lse (1 KB, 256 bytes used) | D (same)
+
 template <int HD, bool CAUSAL>
-__global__ void __launch_bounds__(256, 1) attn_bwd_kv_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
-                                                         const float* __restrict__ lse, const float* __restrict__ dsum,
-                                                         const bf16* __restrict__ dctx, int64_t ldc, bf16* __restrict__ dqkv,
-                                                         const float2* __restrict__ cos_sin) {
+__device__ __forceinline__ void attn_bwd_keys(unsigned char* lds, const int block, const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH,
+                                              float scale, const float* lse, const float* dsum, const bf16* __restrict__ dctx, int64_t ldc,
+                                              bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
   constexpr int KB = 128;           // keys per workgroup
-  constexpr int QT = 64;            // queries per tile
+  constexpr int QT = KV_QT;
   constexpr int ROWB = HD * 2, PPR = HD / 8, NB = HD / 32, KS = HD / 16;
   constexpr int TQ = QT * ROWB;     // bytes of the Q (or dO) tile
   constexpr int IQ = QT * PPR / 64 / 4;  // load instructions per wavefront, tile and operand
-  constexpr int BUF = 2 * TQ + 2048;  // Q | dO | lse (1 KB, 256 bytes used) | D (same)
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * BUF];
+  constexpr int BUF = KV_LDS<HD> / 2;
   auto swq = [](int r) { return PPR == 16 ? (r & 15) : ((r >> 1) & 7); };
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -583,7 +595,7 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_kv_k(const bf16* __restrict__
   const int fr = lane & 31, fh = lane >> 5;
   // key blocks early in the sequence see the most queries under the causal mask and go first
   const int nkb = (S + KB - 1) / KB;
-  const int kb = (int)blockIdx.x / BH, bh = (int)blockIdx.x % BH;
+  const int kb = block / BH, bh = block % BH;
   const int b = bh / H, h = bh % H;
   const int64_t d = (int64_t)H * HD;
   const bf16* q = qkv + (int64_t)b * S * ld + (int64_t)h * HD;
@@ -782,6 +794,33 @@ __global__ void __launch_bounds__(256, 1) attn_bwd_kv_k(const bf16* __restrict__
   store_rows_staged<NB>(vacc, 1.0f, lds + (2 * wave + 1) * OSTG, dk0 + d, ld, S - j0, lane);
 }
 
+template <int HD, bool CAUSAL>
+__global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) attn_bwd_kv_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
+                                                         const float* lse, const float* dsum, const bf16* __restrict__ dctx, int64_t ldc,
+                                                         bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[KV_LDS<HD>];
+  attn_bwd_keys<HD, CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
+}
+
+// Both halves of the backward in one launch where a sequence of 64-wide heads is one block of rows and one of keys (up to
+// 128): the workgroup of a (batch, head) takes its 128 query rows, then its 128 keys; what it left in dsum it reads itself.
+// A call of this size is a few microseconds per launch and the next launch waits for the last workgroup of the one before:
+// 128 tokens, 256 heads in all 19.7 us in two launches, 13.5 in one; 16 heads 13.1 and 11.0; 2048 heads 100 and 78 (two
+// workgroups a compute unit, at the price of ten registers spilled between the halves; with one: 111).  Heads 128 wide need
+// 416 registers for the key half, so one workgroup a compute unit, and lose by it from 512 heads on (19.2 against 21.8 us at
+// 16 tokens), while up to 256 they win a tenth at most: they keep two launches.
+template <bool CAUSAL>
+__global__ void __launch_bounds__(256, 2) attn_bwd_one_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
+                                                         bf16* __restrict__ ctx, int64_t ldc, const bf16* __restrict__ dctx, float* lse,
+                                                         float* dsum, bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[KV_LDS<64>];
+  static_assert(4 * KTILE * 64 * 2 <= KV_LDS<64>, "the key and value tiles fit");
+  attn_rows<64, CAUSAL, 4, true>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, nullptr, ctx, ldc, dctx, lse, dsum, dqkv, cos_sin);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();  // dsum is written, and every wavefront is done with LDS
+  attn_bwd_keys<64, CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
+}
+
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
@@ -842,18 +881,27 @@ hipError_t attention_bwd_fused(int B, int H, int S, int hd, bool causal, const v
                                const float* lse, const void* dctx, int64_t ldc, float* dsum, void* dqkv, const float* cos_sin,
                                hipStream_t st) {
   if (!lse || !dsum) return hipErrorInvalidValue;
-  hipError_t e = attn_launch<true>(B, H, S, hd, causal, qkv, ld, nullptr, const_cast<void*>(ctx), ldc, dctx, const_cast<float*>(lse),
-                                   dsum, dqkv, cos_sin, st);
-  if (e != hipSuccess || B == 0 || H == 0 || S == 0) return e;
+  if (B == 0 || H == 0 || S == 0) return hipSuccess;
   const int64_t nblk = (int64_t)((S + 127) / 128) * B * H;
   if (nblk > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const bool one = hd == 64 && S <= 128;
+  if (!one) {
+    const hipError_t e = attn_launch<true>(B, H, S, hd, causal, qkv, ld, nullptr, const_cast<void*>(ctx), ldc, dctx, const_cast<float*>(lse),
+                                           dsum, dqkv, cos_sin, st);
+    if (e != hipSuccess) return e;
+  }
   const dim3 grid((unsigned)nblk);
   const bf16* x = reinterpret_cast<const bf16*>(qkv);
   const bf16* dO = reinterpret_cast<const bf16*>(dctx);
   bf16* dq = reinterpret_cast<bf16*>(dqkv);
   const float2* cs = reinterpret_cast<const float2*>(cos_sin);
   const float sc = 1.0f / sqrtf((float)hd);
-  if (hd == 128) {
+  if (one) {
+    bf16* o = reinterpret_cast<bf16*>(const_cast<void*>(ctx));
+    float* l = const_cast<float*>(lse);
+    if (causal) attn_bwd_one_k<true><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, o, ldc, dO, l, dsum, dq, cs);
+    else attn_bwd_one_k<false><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, o, ldc, dO, l, dsum, dq, cs);
+  } else if (hd == 128) {
     if (causal) attn_bwd_kv_k<128, true><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
     else attn_bwd_kv_k<128, false><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
   } else if (hd == 64) {

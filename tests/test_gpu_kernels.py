@@ -821,3 +821,10 @@ def test_fused_attention_backward(B, H, S, hd, causal, rope):
             bad = err > 2 ** -7 * np.abs(ref) + 2e-2 * rms + slack + 1e-6
             assert not bad.any(), (name, b, h, int(bad.sum()), float(err.max()), float(rms))
             assert np.sqrt(np.mean(err ** 2)) <= 5e-3 * rms + np.sqrt(np.mean(np.square(slack))) + 1e-6, (name, b, h)
+
+
+@pytest.mark.parametrize("S", [8, 64, 120, 128, 136, 256, 264])
+@pytest.mark.parametrize("causal,rope", [(0, 0), (1, 1)])
+def test_fused_attention_backward_of_narrow_heads(S, causal, rope):
+    """Heads 64 wide: both halves in one launch up to 128 tokens, two launches beyond, at the edges of the row and key blocks."""
+    test_fused_attention_backward(2, 3, S, 64, causal, rope)
