@@ -918,6 +918,7 @@ struct OptTensor {
   int first;       // the tensor's first update
   uint32_t block0; // first block of the launch that works on it
   int vec;         // pieces of four are 16-byte aligned in every array
+  int grad_fused;  // AdamW: which product of a moment's sum is fused
 };
 template <int NT>  // 1 for a single tensor (the small table saves 0.2 us of a 3.6 us launch), OPT_TABLE for a group
 struct OptTable {
@@ -928,6 +929,10 @@ struct OptHyper {
   float lr, b1, omb1, b2, omb2, eps, mu;
 };
 
+// Each of AdamW's moments is a sum of two products, one of them rounded and one fused.  Which one is fixed here and not left to
+// the compiler, and is the one it has always been for the tensor, so that a resumed run goes on bit for bit: the old moment's
+// where 16-byte pieces covered master, gradient, copy and both state arrays lying back to back, else (n no multiple of 8, or
+// the second array off by an odd count: states_odd) the gradient's.
 template <int KIND, int V>
 __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t, int64_t i) {
   float th[V], g[V], a[V], b[V];
@@ -939,8 +944,9 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
   for (int e = 0; e < V; ++e) {
     if (KIND == 0) {
       th[e] -= h.lr * t.wd * th[e];
-      a[e] = fmaf(h.b1, a[e], h.omb1 * g[e]);  // which product of the sum is fused is fixed here, not left to the compiler
-      b[e] = fmaf(h.b2, b[e], h.omb2 * g[e] * g[e]);
+      const float g2 = h.omb2 * g[e];
+      a[e] = t.grad_fused ? fmaf(h.omb1, g[e], h.b1 * a[e]) : fmaf(h.b1, a[e], h.omb1 * g[e]);
+      b[e] = t.grad_fused ? fmaf(g2, g[e], h.b2 * b[e]) : fmaf(h.b2, b[e], g2 * g[e]);
       th[e] -= h.lr * (a[e] * t.inv_bc1) / (sqrtf(b[e] * t.inv_bc2) + h.eps);
     } else if (KIND == 1) {
       const float gg = g[e] + t.wd * th[e];
@@ -1411,6 +1417,7 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
     t.first = it.t == 1 ? 1 : 0;
     t.block0 = (uint32_t)blocks;
     t.vec = aligned16(it.master) && aligned16(it.grad) && aligned16(it.s1) && aligned16(it.s2) && aligned16(it.compute_copy);
+    t.grad_fused = it.states_odd || it.n % 8 != 0 || !aligned16(it.master) || !aligned16(it.grad) || !aligned16(it.compute_copy);
     blocks += more;
   }
   if (table.n == 0) return hipSuccess;
