@@ -166,7 +166,7 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem);
   auto slot = [](int st) __attribute__((always_inline)) { return RING & (RING - 1) ? st % RING : st & (RING - 1); };
   auto request = [&](int st) __attribute__((always_inline)) {
-const int left = st < ke ? K - st * LK : 0;
+    const int left = st < ke ? K - st * LK : 0;
     const uint32_t at = lds0 + (uint32_t)slot(st) * STG;
     sa.request(st, left, at, wave);
     sb.request(st, left, at + OpA::BYTES, wave);
