@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/hift.h"
+#include "copy_parts.h"
 #include "kernels.h"
 
 using namespace hift;
@@ -1324,22 +1325,26 @@ void group_range(const hift_model* M, int gid, int* ulo, int* uhi, int64_t* plo,
 // One leg of the optimizer-state movement, on the host-to-device or device-to-host stream, on the DMA engines: any kernel that
 // reads or writes host memory while the step runs slows the step's own kernels severely (4x on the contractions even with 16
 // workgroups), and the runtime runs a plain hipMemcpyAsync as such a kernel whenever it goes to the host, or finds its engine
-// busy with the copy before.  It does not for rectangles: the piece is handed over as one of two rows that follow each other,
-// which is the same bytes (56 GB/s).  The remainder of less than 32 bytes, and copies too small to matter, go the plain way.
+// busy with the copy before.  It does not for rectangles: a piece is handed over in parts of two rows that follow each other,
+// which is the same bytes (56 GB/s); see copy_parts.h for their sizes.  The remainder of less than 32 bytes, and copies too small
+// to matter, go the plain way.
 // Measured, 12-layer 768-wide encoder with its state on the host: 32.5 ms a sweep with plain copies, 29.6 with rectangles, 21.9
-// with the state resident.  copy_engine 1: a copy kernel with a small fixed grid, for comparison.
+// with the state resident.  That rectangles go to the engines is this runtime's choice and nowhere promised: a runtime that runs
+// them as kernels too moves the same bytes and gives that difference back.  copy_engine 1: a copy kernel with a small fixed grid,
+// for comparison.
 hift_status state_copy(hift_model* M, void* dst, const void* src, size_t bytes, bool to_device) {
   hipStream_t st = to_device ? M->hs : M->ds;
   if (M->copy_engine == 1 && bytes % 16 == 0 && (reinterpret_cast<uintptr_t>(dst) & 15) == 0 &&
       (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
     HIP_TRY(copy_stream(dst, src, bytes, M->copy_blocks, st));
-  } else {
-    const hipMemcpyKind kind = to_device ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost;
-    const size_t row = bytes >= (64 << 10) ? bytes / 32 * 16 : 0, rest = bytes - 2 * row;
-    if (row) HIP_TRY(hipMemcpy2DAsync(dst, row, src, row, row, 2, kind, st));
-    if (rest)
-      HIP_TRY(hipMemcpyAsync(reinterpret_cast<unsigned char*>(dst) + 2 * row, reinterpret_cast<const unsigned char*>(src) + 2 * row, rest, kind, st));
+    return HIFT_OK;
   }
+  const hipMemcpyKind kind = to_device ? hipMemcpyHostToDevice : hipMemcpyDeviceToHost;
+  HIP_TRY((hipError_t)copy_parts(bytes, [&](size_t at, size_t row, size_t n) -> int {
+    unsigned char* d = reinterpret_cast<unsigned char*>(dst) + at;
+    const unsigned char* s = reinterpret_cast<const unsigned char*>(src) + at;
+    return row ? hipMemcpy2DAsync(d, row, s, row, row, 2, kind, st) : hipMemcpyAsync(d, s, n, kind, st);
+  }));
   return HIFT_OK;
 }
 

@@ -4,9 +4,9 @@ the update of the active group; frozen parameters bit-identical; schedules bit-e
 import numpy as np
 import pytest
 
-from hift_inputs import WORKLOADS, make_batch
+from hift_inputs import WORKLOADS, make_batch, model_config
 from oracle import hift_oracle as O
-from tests.hift_pair import make_pair, rel_l2, run_steps, to_dev
+from tests.hift_pair import initial_weights, make_pair, rel_l2, run_steps, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -255,6 +255,37 @@ def test_pinned_arena_in_chunks_changes_nothing(master_on_host):
     batch = to_dev(*make_batch(wl, 9, 9))
     assert a.step(*batch, 2) == b.step(*batch, 2)
     assert np.array_equal(a.read_params(), b.read_params())
+
+
+@pytest.mark.parametrize("shape,chunk", [
+    (dict(arch=0, d_model=128, n_heads=2, d_ffn=512, vocab=5000), 300_016),      # blocks of no whole number of 32-byte pairs
+    (dict(arch=0, d_model=128, n_heads=2, d_ffn=512, vocab=5000), 1 << 40),
+    (dict(arch=1, d_model=768, n_heads=12, d_ffn=3072, vocab=50265, n_classes=4), 1 << 40),   # 310 MB for the embeddings
+], ids=["blocks_of_300KB", "one_block", "parts_of_64MB"])
+@pytest.mark.parametrize("master_on_host", [0, 1])
+def test_parked_state_in_rectangles_is_the_resident_state(shape, chunk, master_on_host):
+    """State that moves in pieces of more than 64 KB (rectangles that end at a block of the pinned arena, rectangles with a
+    remainder, several parts to a piece) against resident state: two sweeps, so that what was written back is fetched again;
+    losses, parameters and both moments bit for bit."""
+    import paper_2401_15207_amd as H
+    wl = dict(WORKLOADS["C1"], n_layers=2, dtype=1, batch=2, seq=32, max_seq=32, **shape)
+    theta0 = initial_weights(model_config(wl), 21, 0.02)
+    models = [H.HiftModel(model_config(wl), wl["opt"], 1, 2, 32, init_params=theta0, **kw) for kw in
+              (dict(state_on_host=0), dict(state_on_host=1, master_on_host=master_on_host, pinned_chunk_bytes=chunk))]
+    a, b = models
+    if chunk < 1 << 20:
+        assert len(b.pinned_chunks) > 20
+    k = [mdl.set_group_schedule("bottom2up", 1) for mdl in models][0]
+    for t in range(1, 2 * k + 1):
+        batch = to_dev(*make_batch(wl, 21, t))
+        gid = a.schedule_group_at(t)
+        assert a.step(*batch, gid) == b.step(*batch, gid), t
+    assert np.array_equal(a.read_params(), b.read_params())
+    assert np.array_equal(a.read_params(which=1), b.read_params(which=1))
+    for j in (0, 1):
+        moment = a.read_state(0, a.n_units, j)
+        assert moment.any() and np.array_equal(moment, b.read_state(0, b.n_units, j))
+    assert b.transfer_stats()[1] == 2 * 4 * b.n_params * (2 + master_on_host)
 
 
 @pytest.mark.parametrize("bf16,master_on_host", [(0, 0), (1, 0), (1, 1)])
