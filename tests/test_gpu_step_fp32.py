@@ -261,7 +261,7 @@ def test_pinned_arena_in_chunks_changes_nothing(master_on_host):
     (dict(arch=0, d_model=128, n_heads=2, d_ffn=512, vocab=5000), 300_016),      # blocks of no whole number of 32-byte pairs
     (dict(arch=0, d_model=128, n_heads=2, d_ffn=512, vocab=5000), 1 << 40),
     (dict(arch=1, d_model=768, n_heads=12, d_ffn=3072, vocab=50265, n_classes=4), 1 << 40),   # 310 MB for the embeddings
-], ids=["blocks_of_300KB", "one_block", "parts_of_64MB"])
+], ids=["blocks_of_300KB", "one_block", "several_parts"])
 @pytest.mark.parametrize("master_on_host", [0, 1])
 def test_parked_state_in_rectangles_is_the_resident_state(shape, chunk, master_on_host):
     """State that moves in pieces of more than 64 KB (rectangles that end at a block of the pinned arena, rectangles with a
