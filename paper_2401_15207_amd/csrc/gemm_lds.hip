@@ -16,8 +16,11 @@
 // Measured against the kernel before it (operands through registers, turned around on the way, 128 x 128 tiles): 1024 tokens,
 // 768 -> 3072 with input and weight gradients 13 + 51 + 27 us, now 11 + 14 + 13; 231 tokens, 4096 -> 12288: 49 + 185 + 348 us,
 // now 37 + 50 + 63.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
+#include "lds_tiles.h"
 
 namespace hift {
 namespace {
@@ -82,9 +85,9 @@ struct Operand {
     }
   }
 
-  // stage `st` (k from st * 64 on; `left` = K - st * 64 values remain, perhaps none) into LDS at `lds`
+  // stage `st` (k from st * 64 on; `left` = K - st * 64 > 0 values remain) into LDS at `lds`
   __device__ __forceinline__ void request(int st, int left, uint32_t lds, int wave) const {
-    const uint64_t a = base + (left > 0 ? (uint64_t)st * step : 0);
+    const uint64_t a = base + (uint64_t)st * step;
     const u32x4 rsrc = {(uint32_t)a, (uint32_t)(a >> 32) & 0xFFFFu, BUF_BYTES, 0x00020000u};
 #pragma unroll
     for (int i = 0; i < NL; ++i)
@@ -166,7 +169,7 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
   const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem);
   auto slot = [](int st) __attribute__((always_inline)) { return RING & (RING - 1) ? st % RING : st & (RING - 1); };
   auto request = [&](int st) __attribute__((always_inline)) {
-    const int left = st < ke ? K - st * LK : 0;
+    const int left = K - st * LK;
     const uint32_t at = lds0 + (uint32_t)slot(st) * STG;
     sa.request(st, left, at, wave);
     sb.request(st, left, at + OpA::BYTES, wave);
@@ -202,34 +205,47 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
         for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ks][j], a[ks][i], acc[i][j], 0, 0, 0);
   };
 
+  // Nothing is asked for past the end, so what is in flight shrinks over the last RING stages and the waits there are for all of
+  // it (TAIL; a loop of its own, as a branch in the main one costs a tenth).  Stages of zeros past the end, which keep one count
+  // throughout, cost a tile of one or two stages a quarter of its time (see the store below).
 #pragma unroll
-  for (int s = 0; s < RING; ++s) request(kb + s);
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 1) * NL) : "memory");
+  for (int s = 0; s < RING; ++s)
+    if (kb + s < ke) request(kb + s);
+  if (kb + RING <= ke) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 1) * NL) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   read(fa[0], fb[0], kb);
 
   // One stage: its fragments are in registers (or on their way there).  The next stage must have landed (all but the younger
   // stages' requests); past the barrier its fragments are read under this stage's products, and this stage's buffer, read by
-  // every wavefront, is free for the stage a whole ring further on.
-  auto stage = [&](int st, int cur) __attribute__((always_inline)) {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * NL) : "memory");
+  // every wavefront, is free for the stage a whole ring further on.  (Fragments read past the end are never multiplied.)
+  auto stage = [&](int st, int cur, auto tail) __attribute__((always_inline)) {
+    constexpr bool TAIL = decltype(tail)::value;
+    if (!TAIL || st + RING <= ke) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * NL) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     read(fa[cur ^ 1], fb[cur ^ 1], st + 1);
-    request(st + RING);
+    if (!TAIL || st + RING < ke) request(st + RING);
     multiply(fa[cur], fb[cur]);
   };
   int st = kb;
-  for (; st + 1 < ke; st += 2) {
-    stage(st, 0);
-    stage(st + 1, 1);
+  for (; st + 1 + RING < ke; st += 2) {
+    stage(st, 0, std::false_type());
+    stage(st + 1, 1, std::false_type());
   }
-  if (st < ke) stage(st, 0);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // stray requests must land before LDS is reused
-  __syncthreads();
+  for (; st + 1 < ke; st += 2) {
+    stage(st, 0, std::true_type());
+    stage(st + 1, 1, std::true_type());
+  }
+  if (st < ke) stage(st, 0, std::true_type());
+  __syncthreads();  // every wavefront has its last fragments, and every request has landed (waited for in the last stages)
 
-  // ---- out: the tile into LDS as fp32 rows (16-byte pieces XOR-ed by the row), then row by row: bias and residual in fp32,
-  // one rounding, 16-byte stores.
+  // ---- out: the tile into LDS as fp32 rows, then row by row: bias and residual in fp32, one rounding, 16-byte stores.
+  // 16-byte piece `ch` of a row sits at `place`: XOR-ed by the row, so that the 16 rows that a store takes at a time fall into
+  // different banks, and the second 256 bytes with their lowest bit turned, so that the every other piece that a read takes does
+  // (it read the same banks twice before).  512 x 512, k 128, 128 of them: 37.9 us with both, 32.6 with neither.
   constexpr int CH = BN / 4 < 16 ? BN / 4 : 16;  // pieces that the XOR permutes
+  auto place = [](int row, int ch) __attribute__((always_inline)) { return ch ^ (row & (CH - 1)) ^ ((ch >> 4) & 1); };
   {
     const int frow = lane & 31, fh = lane >> 5;
 #pragma unroll
@@ -238,7 +254,7 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
       for (int j = 0; j < NT; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const int row = wm * WM + i * 32 + frow, ch = (wn * (WN / 4) + j * 8 + 2 * g + fh) ^ (row & (CH - 1));
+          const int row = wm * WM + i * 32 + frow, ch = place(row, wn * (WN / 4) + j * 8 + 2 * g + fh);
           const f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
           *reinterpret_cast<f32x4*>(smem + row * (BN * 4) + ch * 16) = v;
         }
@@ -253,8 +269,8 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
     const int64_t row = m0 + r, col = n0 + c;
     if (row >= p.M || col >= p.N) continue;
     const unsigned char* src = smem + r * (BN * 4);
-    f32x4 lo = *reinterpret_cast<const f32x4*>(src + ((c / 4) ^ (r & (CH - 1))) * 16);
-    f32x4 hi = *reinterpret_cast<const f32x4*>(src + ((c / 4 + 1) ^ (r & (CH - 1))) * 16);
+    f32x4 lo = *reinterpret_cast<const f32x4*>(src + place(r, c / 4) * 16);
+    f32x4 hi = *reinterpret_cast<const f32x4*>(src + place(r, c / 4 + 1) * 16);
     if constexpr (EPI != EPI_NONE) {  // bf16 in 16-byte pieces, no residual
       float x[8];
 #pragma unroll
@@ -317,8 +333,9 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
 
 inline bool al16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
 
-template <int BM, int BN, int RING, bool AK, bool BKM, typename OutT, int EPI>
+template <int I, bool AK, bool BKM, typename OutT, int EPI>
 hipError_t launch(LdsP& p, int nz, hipStream_t st) {
+  constexpr int BM = LDS_TILES[I].bm, BN = LDS_TILES[I].bn, RING = LDS_TILES[I].ring;
   constexpr int LDS = Tile<BM, BN, RING>::LDS;
   static_assert(LDS <= 160 * 1024, "LDS of a gfx950 compute unit");
   static bool attr_done = false;  // one flag per instantiation
@@ -334,35 +351,18 @@ hipError_t launch(LdsP& p, int nz, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tile by estimated time, in 10 ns: a round of tiles over the 256 compute units takes (stages x time of a stage + what a tile
-// costs besides); a stage takes longer when the round is the only one and the workgroup has its compute unit to itself.  The
-// constants are a fit to measured times of all the tiles in the three layouts of a linear layer (75 sizes: 32 to 2048 rows, 64
-// to 12288 columns and k): the tile chosen is on average 4 % slower than the best and at most 1.25 times.  A ring of four
-// 64 x 64 stages is the better one when it runs alone (231 x 4096, k 11008: 40 us, 47 with three), three otherwise (three
-// workgroups per compute unit: 1024 x 2304, k 768: 11.3 us, 12.6 with four).
 template <bool AK, bool BKM, typename OutT, int EPI = EPI_NONE>
 hipError_t pick_tile(LdsP& p, int nz, hipStream_t st) {
-  struct Cost { int bm, bn, alone, stage, fixed; };
-  constexpr Cost tiles[] = {{128, 128, 87, 33, 300}, {128, 64, 32, 24, 300}, {64, 128, 32, 24, 300}, {64, 64, 18, 18, 111},
-                            {64, 64, 15, 22, 162},   {64, 32, 23, 19, 70},   {32, 64, 23, 19, 70},   {32, 32, 20, 10, 90}};
-  const int64_t nk = (p.K + LK - 1) / LK;
-  int best = 0;
-  int64_t least = INT64_MAX;
-  for (int i = 0; i < 8; ++i) {
-    const Cost& t = tiles[i];
-    const int64_t rounds = ((p.M + t.bm - 1) / t.bm * ((p.N + t.bn - 1) / t.bn) * nz + 255) / 256;
-    const int64_t cost = rounds * (nk * (rounds == 1 ? t.alone : t.stage) + t.fixed);
-    if (cost < least) { least = cost; best = i; }
-  }
-  switch (best) {
-    case 0: return launch<128, 128, 2, AK, BKM, OutT, EPI>(p, nz, st);
-    case 1: return launch<128, 64, 3, AK, BKM, OutT, EPI>(p, nz, st);
-    case 2: return launch<64, 128, 3, AK, BKM, OutT, EPI>(p, nz, st);
-    case 3: return launch<64, 64, 3, AK, BKM, OutT, EPI>(p, nz, st);
-    case 4: return launch<64, 64, 4, AK, BKM, OutT, EPI>(p, nz, st);
-    case 5: return launch<64, 32, 4, AK, BKM, OutT, EPI>(p, nz, st);
-    case 6: return launch<32, 64, 4, AK, BKM, OutT, EPI>(p, nz, st);
-    default: return launch<32, 32, 4, AK, BKM, OutT, EPI>(p, nz, st);
+  static_assert(N_LDS_TILES == 8, "one case per tile");
+  switch (lds_tile(p.M, p.N, p.K, nz)) {
+    case 0: return launch<0, AK, BKM, OutT, EPI>(p, nz, st);
+    case 1: return launch<1, AK, BKM, OutT, EPI>(p, nz, st);
+    case 2: return launch<2, AK, BKM, OutT, EPI>(p, nz, st);
+    case 3: return launch<3, AK, BKM, OutT, EPI>(p, nz, st);
+    case 4: return launch<4, AK, BKM, OutT, EPI>(p, nz, st);
+    case 5: return launch<5, AK, BKM, OutT, EPI>(p, nz, st);
+    case 6: return launch<6, AK, BKM, OutT, EPI>(p, nz, st);
+    default: return launch<7, AK, BKM, OutT, EPI>(p, nz, st);
   }
 }
 
