@@ -67,7 +67,7 @@ struct Operand {
 
   static __device__ __forceinline__ int swizzle(int row) {
     if (KMAJOR) return (row >> 1) & 7;
-    if (ROWS == 128) return (row & 3) << 2;
+    if (ROWS >= 128) return (row & 3) << 2;
     if (ROWS == 64) return ((row >> 1) & 1) << 2;
     return 0;  // 64-byte rows: four of them are four bank groups
   }
@@ -120,12 +120,16 @@ struct Fragments {
   }
 };
 
-// Wavefronts of a tile: 2 x 2, fewer where a tile has fewer than four 32 x 32 blocks.
+// Wavefronts of a tile: 2 x 2, fewer where a tile has fewer than four 32 x 32 blocks; 2 x 4 for the large tile, whose
+// accumulators leave room for the fragments of one k-step ahead instead of a whole stage (two wavefronts a SIMD: 2048 x 32000,
+// k 4096 takes 442 us, with 2 x 2 of them, one a SIMD, 461) and whose outputs pass through LDS in two halves.
 template <int BM, int BN, int RING>
 struct Tile {
-  static constexpr int SWM = BM >= 64 ? 2 : 1, SWN = BN >= 64 ? 2 : 1, NW = SWM * SWN;
+  static constexpr bool LARGE = BM * BN > 128 * 128;
+  static constexpr int SWM = BM >= 64 ? 2 : 1, SWN = LARGE ? 4 : (BN >= 64 ? 2 : 1), NW = SWM * SWN;
   static constexpr int WM = BM / SWM, WN = BN / SWN;
-  static constexpr int RING_BYTES = RING * (BM + BN) * 128, OUT_BYTES = BM * BN * 4;
+  static constexpr int OUT_PASSES = LARGE ? 2 : 1;
+  static constexpr int RING_BYTES = RING * (BM + BN) * 128, OUT_BYTES = BM / OUT_PASSES * BN * 4;
   static constexpr int LDS = RING_BYTES > OUT_BYTES ? RING_BYTES : OUT_BYTES;
 };
 
@@ -134,7 +138,7 @@ struct Tile {
 // library's erff, as the separate kernels do that it replaces (6 us each at 1024 x 3072 and two trips of the matrix to memory):
 // the same bits, and a 12-layer encoder of width 768 passes through its layers' sweep in 28.6 ms instead of 29.2.
 template <int BM, int BN, int RING, bool AK, bool BKM, typename OutT, int EPI>
-__global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(LdsP p) {
+__global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), (Tile<BM, BN, RING>::LARGE ? 1 : 2)) gemm_lds_k(LdsP p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   typedef Tile<BM, BN, RING> T;
   constexpr int NW = T::NW, WM = T::WM, WN = T::WN, MT = WM / 32, NT = WN / 32, KSP = LK / 16;
@@ -185,24 +189,18 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
 
   Fragments<BM, AK> ra;
   Fragments<BN, BKM> rb;
-  bf16x8 fa[2][KSP][MT], fb[2][KSP][NT];
-  auto read = [&](bf16x8(&a)[KSP][MT], bf16x8(&b)[KSP][NT], int st) __attribute__((always_inline)) {
+  auto read = [&](bf16x8(&a)[MT], bf16x8(&b)[NT], int st, int ks) __attribute__((always_inline)) {
     const unsigned char* at = smem + slot(st) * STG;
 #pragma unroll
-    for (int ks = 0; ks < KSP; ++ks) {
+    for (int i = 0; i < MT; ++i) a[i] = ra.read(at, wm * WM + i * 32, ks, lane);
 #pragma unroll
-      for (int i = 0; i < MT; ++i) a[ks][i] = ra.read(at, wm * WM + i * 32, ks, lane);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) b[ks][j] = rb.read(at + OpA::BYTES, wn * WN + j * 32, ks, lane);
-    }
+    for (int j = 0; j < NT; ++j) b[j] = rb.read(at + OpA::BYTES, wn * WN + j * 32, ks, lane);
   };
-  auto multiply = [&](const bf16x8(&a)[KSP][MT], const bf16x8(&b)[KSP][NT]) __attribute__((always_inline)) {
+  auto multiply = [&](const bf16x8(&a)[MT], const bf16x8(&b)[NT]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KSP; ++ks)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ks][j], a[ks][i], acc[i][j], 0, 0, 0);
+      for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
   };
 
   // Nothing is asked for past the end, so what is in flight shrinks over the last RING stages and the waits there are for all of
@@ -214,118 +212,153 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), 2) gemm_lds_k(L
   if (kb + RING <= ke) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 1) * NL) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  read(fa[0], fb[0], kb);
-
-  // One stage: its fragments are in registers (or on their way there).  The next stage must have landed (all but the younger
-  // stages' requests); past the barrier its fragments are read under this stage's products, and this stage's buffer, read by
-  // every wavefront, is free for the stage a whole ring further on.  (Fragments read past the end are never multiplied.)
-  auto stage = [&](int st, int cur, auto tail) __attribute__((always_inline)) {
-    constexpr bool TAIL = decltype(tail)::value;
-    if (!TAIL || st + RING <= ke) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * NL) : "memory");
+  // Past this the stage after `st` has landed (all but the younger stages' requests), and this stage's buffer, whose last
+  // fragments every wavefront has, is free for the stage a whole ring further on.
+  auto next_stage = [&](int st, auto tail) __attribute__((always_inline)) {
+    if (!decltype(tail)::value || st + RING <= ke) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((RING - 2) * NL) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    read(fa[cur ^ 1], fb[cur ^ 1], st + 1);
-    if (!TAIL || st + RING < ke) request(st + RING);
-    multiply(fa[cur], fb[cur]);
   };
-  int st = kb;
-  for (; st + 1 + RING < ke; st += 2) {
-    stage(st, 0, std::false_type());
-    stage(st + 1, 1, std::false_type());
+  // (Fragments read past the end are never multiplied.)
+  if constexpr (T::LARGE) {
+    // One stage: the next k-step's fragments are read under the products of the one before.
+    bf16x8 fa[2][MT], fb[2][NT];
+    auto stage = [&](int st, auto tail) __attribute__((always_inline)) {
+#pragma unroll
+      for (int ks = 0; ks < KSP - 1; ++ks) {
+        read(fa[(ks + 1) & 1], fb[(ks + 1) & 1], st, ks + 1);
+        multiply(fa[ks & 1], fb[ks & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      next_stage(st, tail);
+      read(fa[0], fb[0], st + 1, 0);
+      if (!decltype(tail)::value || st + RING < ke) request(st + RING);
+      multiply(fa[1], fb[1]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    read(fa[0], fb[0], kb, 0);
+    int st = kb;
+    for (; st + RING < ke; ++st) stage(st, std::false_type());
+    for (; st < ke; ++st) stage(st, std::true_type());
+  } else {
+    // One stage: its fragments are in registers (or on their way there), the next one's are read under its products.
+    bf16x8 fa[2][KSP][MT], fb[2][KSP][NT];
+    auto read_stage = [&](bf16x8(&a)[KSP][MT], bf16x8(&b)[KSP][NT], int st) __attribute__((always_inline)) {
+#pragma unroll
+      for (int ks = 0; ks < KSP; ++ks) read(a[ks], b[ks], st, ks);
+    };
+    auto stage = [&](int st, int cur, auto tail) __attribute__((always_inline)) {
+      next_stage(st, tail);
+      read_stage(fa[cur ^ 1], fb[cur ^ 1], st + 1);
+      if (!decltype(tail)::value || st + RING < ke) request(st + RING);
+#pragma unroll
+      for (int ks = 0; ks < KSP; ++ks) multiply(fa[cur][ks], fb[cur][ks]);
+    };
+    read_stage(fa[0], fb[0], kb);
+    int st = kb;
+    for (; st + 1 + RING < ke; st += 2) {
+      stage(st, 0, std::false_type());
+      stage(st + 1, 1, std::false_type());
+    }
+    for (; st + 1 < ke; st += 2) {
+      stage(st, 0, std::true_type());
+      stage(st + 1, 1, std::true_type());
+    }
+    if (st < ke) stage(st, 0, std::true_type());
   }
-  for (; st + 1 < ke; st += 2) {
-    stage(st, 0, std::true_type());
-    stage(st + 1, 1, std::true_type());
-  }
-  if (st < ke) stage(st, 0, std::true_type());
   __syncthreads();  // every wavefront has its last fragments, and every request has landed (waited for in the last stages)
 
   // ---- out: the tile into LDS as fp32 rows, then row by row: bias and residual in fp32, one rounding, 16-byte stores.
   // 16-byte piece `ch` of a row sits at `place`: XOR-ed by the row, so that the 16 rows that a store takes at a time fall into
   // different banks, and the second 256 bytes with their lowest bit turned, so that the every other piece that a read takes does
-  // (it read the same banks twice before).  512 x 512, k 128, 128 of them: 37.9 us with both, 32.6 with neither.
+  // (it read the same banks twice before).  512 x 512, k 128, 128 of them: 37.1 us with that and the stages of zeros, 31.4 now.
   constexpr int CH = BN / 4 < 16 ? BN / 4 : 16;  // pieces that the XOR permutes
   auto place = [](int row, int ch) __attribute__((always_inline)) { return ch ^ (row & (CH - 1)) ^ ((ch >> 4) & 1); };
-  {
-    const int frow = lane & 31, fh = lane >> 5;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int row = wm * WM + i * 32 + frow, ch = place(row, wn * (WN / 4) + j * 8 + 2 * g + fh);
-          const f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(smem + row * (BN * 4) + ch * 16) = v;
-        }
-  }
-  __syncthreads();
+  constexpr int PMT = MT / T::OUT_PASSES, PWM = PMT * 32;  // blocks and rows of a wavefront that leave per pass
   OutT* C = reinterpret_cast<OutT*>(p.C) + zb * p.sc1 + zh * p.sc2;
   const OutT* R = p.R ? reinterpret_cast<const OutT*>(p.R) + zb * p.sc1 + zh * p.sc2 : nullptr;
-  constexpr int CPR = BN / 8, UNITS = BM * CPR;
+#pragma unroll
+  for (int pass = 0; pass < T::OUT_PASSES; ++pass) {
+    if (pass) __syncthreads();
+    {
+      const int frow = lane & 31, fh = lane >> 5;
+#pragma unroll
+      for (int ii = 0; ii < PMT; ++ii)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const int i = pass * PMT + ii, row = wm * PWM + ii * 32 + frow, ch = place(row, wn * (WN / 4) + j * 8 + 2 * g + fh);
+            const f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+            *reinterpret_cast<f32x4*>(smem + row * (BN * 4) + ch * 16) = v;
+          }
+    }
+    __syncthreads();
+    constexpr int CPR = BN / 8, UNITS = BM / T::OUT_PASSES * CPR;
 #pragma unroll 2
-  for (int u = tid; u < UNITS; u += 64 * NW) {
-    const int r = u / CPR, c = (u % CPR) * 8;
-    const int64_t row = m0 + r, col = n0 + c;
-    if (row >= p.M || col >= p.N) continue;
-    const unsigned char* src = smem + r * (BN * 4);
-    f32x4 lo = *reinterpret_cast<const f32x4*>(src + place(r, c / 4) * 16);
-    f32x4 hi = *reinterpret_cast<const f32x4*>(src + place(r, c / 4 + 1) * 16);
-    if constexpr (EPI != EPI_NONE) {  // bf16 in 16-byte pieces, no residual
-      float x[8];
+    for (int u = tid; u < UNITS; u += 64 * NW) {
+      const int r = u / CPR, c = (u % CPR) * 8;
+      const int64_t row = m0 + r / PWM * WM + pass * PWM + r % PWM, col = n0 + c;
+      if (row >= p.M || col >= p.N) continue;
+      const unsigned char* src = smem + r * (BN * 4);
+      f32x4 lo = *reinterpret_cast<const f32x4*>(src + place(r, c / 4) * 16);
+      f32x4 hi = *reinterpret_cast<const f32x4*>(src + place(r, c / 4 + 1) * 16);
+      if constexpr (EPI != EPI_NONE) {  // bf16 in 16-byte pieces, no residual
+        float x[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[e] = e < 4 ? lo[e & 3] : hi[e & 3];
-      if (p.bias) {
-        const bf16x8 t = *reinterpret_cast<const bf16x8*>(p.bias + col);
+        for (int e = 0; e < 8; ++e) x[e] = e < 4 ? lo[e & 3] : hi[e & 3];
+        if (p.bias) {
+          const bf16x8 t = *reinterpret_cast<const bf16x8*>(p.bias + col);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += static_cast<float>(t[e]);
-      }
-      bf16x8 t, o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) t[e] = static_cast<__bf16>(x[e]);
-      if constexpr (EPI == EPI_GELU) {
-        if (p.C) *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = t;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(gelu_f(static_cast<float>(t[e])));
-        *reinterpret_cast<bf16x8*>(p.C2 + row * p.ldc2 + col) = o;
-      } else {
-        const bf16x8 pre = *reinterpret_cast<const bf16x8*>(p.C2 + row * p.ldc2 + col);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(static_cast<float>(t[e]) * gelu_df(static_cast<float>(pre[e])));
-        *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = o;
-      }
-    } else if (p.vec) {
-      if (p.bias) {
-        const bf16x8 t = *reinterpret_cast<const bf16x8*>(p.bias + col);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { lo[e] += static_cast<float>(t[e]); hi[e] += static_cast<float>(t[4 + e]); }
-      }
-      if constexpr (sizeof(OutT) == 2) {
-        if (R) {
-          const bf16x8 rv = *reinterpret_cast<const bf16x8*>(R + row * p.ldr + col);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { lo[e] += static_cast<float>(rv[e]); hi[e] += static_cast<float>(rv[4 + e]); }
+          for (int e = 0; e < 8; ++e) x[e] += static_cast<float>(t[e]);
         }
-        bf16x8 t;
+        bf16x8 t, o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { t[e] = static_cast<__bf16>(lo[e]); t[4 + e] = static_cast<__bf16>(hi[e]); }
-        *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = t;
-      } else {
-        if (R) {
-          lo += *reinterpret_cast<const f32x4*>(R + row * p.ldr + col);
-          hi += *reinterpret_cast<const f32x4*>(R + row * p.ldr + col + 4);
+        for (int e = 0; e < 8; ++e) t[e] = static_cast<__bf16>(x[e]);
+        if constexpr (EPI == EPI_GELU) {
+          if (p.C) *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = t;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(gelu_f(static_cast<float>(t[e])));
+          *reinterpret_cast<bf16x8*>(p.C2 + row * p.ldc2 + col) = o;
+        } else {
+          const bf16x8 pre = *reinterpret_cast<const bf16x8*>(p.C2 + row * p.ldc2 + col);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(static_cast<float>(t[e]) * gelu_df(static_cast<float>(pre[e])));
+          *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = o;
         }
-        *reinterpret_cast<f32x4*>(C + row * p.ldc + col) = lo;
-        *reinterpret_cast<f32x4*>(C + row * p.ldc + col + 4) = hi;
-      }
-    } else {
+      } else if (p.vec) {
+        if (p.bias) {
+          const bf16x8 t = *reinterpret_cast<const bf16x8*>(p.bias + col);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        if (col + e >= p.N) break;
-        float v = e < 4 ? lo[e & 3] : hi[e & 3];
-        if (p.bias) v += static_cast<float>(p.bias[col + e]);
-        if (R) v += to_f32(R[row * p.ldr + col + e]);
-        C[row * p.ldc + col + e] = from_f32<OutT>(v);
+          for (int e = 0; e < 4; ++e) { lo[e] += static_cast<float>(t[e]); hi[e] += static_cast<float>(t[4 + e]); }
+        }
+        if constexpr (sizeof(OutT) == 2) {
+          if (R) {
+            const bf16x8 rv = *reinterpret_cast<const bf16x8*>(R + row * p.ldr + col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { lo[e] += static_cast<float>(rv[e]); hi[e] += static_cast<float>(rv[4 + e]); }
+          }
+          bf16x8 t;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { t[e] = static_cast<__bf16>(lo[e]); t[4 + e] = static_cast<__bf16>(hi[e]); }
+          *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = t;
+        } else {
+          if (R) {
+            lo += *reinterpret_cast<const f32x4*>(R + row * p.ldr + col);
+            hi += *reinterpret_cast<const f32x4*>(R + row * p.ldr + col + 4);
+          }
+          *reinterpret_cast<f32x4*>(C + row * p.ldc + col) = lo;
+          *reinterpret_cast<f32x4*>(C + row * p.ldc + col + 4) = hi;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if (col + e >= p.N) break;
+          float v = e < 4 ? lo[e & 3] : hi[e & 3];
+          if (p.bias) v += static_cast<float>(p.bias[col + e]);
+          if (R) v += to_f32(R[row * p.ldr + col + e]);
+          C[row * p.ldc + col + e] = from_f32<OutT>(v);
+        }
       }
     }
   }
@@ -353,7 +386,7 @@ hipError_t launch(LdsP& p, int nz, hipStream_t st) {
 
 template <bool AK, bool BKM, typename OutT, int EPI = EPI_NONE>
 hipError_t pick_tile(LdsP& p, int nz, hipStream_t st) {
-  static_assert(N_LDS_TILES == 8, "one case per tile");
+  static_assert(N_LDS_TILES == 9, "one case per tile");
   switch (lds_tile(p.M, p.N, p.K, nz)) {
     case 0: return launch<0, AK, BKM, OutT, EPI>(p, nz, st);
     case 1: return launch<1, AK, BKM, OutT, EPI>(p, nz, st);
@@ -362,7 +395,8 @@ hipError_t pick_tile(LdsP& p, int nz, hipStream_t st) {
     case 4: return launch<4, AK, BKM, OutT, EPI>(p, nz, st);
     case 5: return launch<5, AK, BKM, OutT, EPI>(p, nz, st);
     case 6: return launch<6, AK, BKM, OutT, EPI>(p, nz, st);
-    default: return launch<7, AK, BKM, OutT, EPI>(p, nz, st);
+    case 7: return launch<7, AK, BKM, OutT, EPI>(p, nz, st);
+    default: return launch<8, AK, BKM, OutT, EPI>(p, nz, st);
   }
 }
 

@@ -99,6 +99,7 @@ LDS_CASES = [  # M, N, K: the edges of the tiles of gemm_lds_k (every tile is ta
     (32, 32, 64), (24, 40, 8), (40, 24, 72), (8, 200, 136), (200, 8, 184), (64, 64, 320), (72, 56, 56),
     (128, 4096, 64), (1000, 1208, 72), (136, 12296, 24), (2056, 520, 104), (1024, 768, 768), (520, 520, 2056), (232, 4104, 240),
     (8, 40, 520), (72, 8200, 2056), (8200, 72, 520), (232, 4104, 2056), (136, 8200, 2056), (264, 12296, 520), (520, 4104, 24), (2056, 2056, 136),
+    (3848, 4040, 328),
 ]
 
 

@@ -314,26 +314,42 @@ def test_master_on_host_gives_the_same_trajectory(optk):
     assert m["device_master"] < hbm.memory()["device_master"]
 
 
-@pytest.mark.parametrize("arch,batch,seq", [(0, 3, 21), (1, 2, 40), (1, 5, 64)])
-def test_gelu_in_the_contraction_is_the_separate_kernel_bit_for_bit(arch, batch, seq):
-    """Layers too small for packed weights: GELU and its derivative on the way out of the contraction (rows in no multiple of
+# arch, batch, seq, width, inner width: every tile of gemm_lds_k is taken by one of them (test_lds_tiles.py)
+GELU_CASES = [(0, 3, 21, 128, 328), (1, 2, 40, 128, 328), (1, 5, 64, 128, 328), (0, 3, 8, 512, 40), (1, 3, 24, 128, 8200), (0, 4, 34, 512, 8200),
+              (1, 8, 29, 64, 8200), (0, 8, 29, 2056, 4104), (1, 4, 34, 2056, 8200), (0, 8, 128, 768, 768), (1, 8, 481, 328, 4040)]
+
+
+@pytest.mark.parametrize("arch,batch,seq,d,f", GELU_CASES)
+def test_gelu_in_the_contraction_is_the_separate_kernel_bit_for_bit(arch, batch, seq, d, f):
+    """Layers without packed weights: GELU and its derivative on the way out of the contraction (rows in no multiple of
     any tile, pre-activations kept and not kept) against the contraction followed by the elementwise kernels."""
     import torch
     import paper_2401_15207_amd as H
-    cfg = dict(arch=arch, n_layers=2, d_model=128, n_heads=2, d_ffn=328, vocab=304, max_seq=64, n_classes=3, norm_eps=1e-5,
-               rope_base=10000.0, dtype=1)
+    cfg = dict(arch=arch, n_layers=2 if d < 512 else 1, d_model=d, n_heads=2 if d == 128 else 1, d_ffn=f, vocab=304, max_seq=max(64, seq),
+               n_classes=3, norm_eps=1e-5, rope_base=10000.0, dtype=1)
     wl = dict(cfg, batch=batch, seq=seq)
     opt = dict(kind="adamw", lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.01, momentum=0.0)
     got = []
+    tensors, _n = H.tensor_list(cfg)
+    theta = init_params(1, [(n, s, k) for n, s, k, _u, _o in tensors], bf16_exact=True, jitter=0.02)
     for unfused in (0, H.UNFUSED_EPILOGUES):
-        tensors, _n = H.tensor_list(cfg)
-        theta = init_params(1, [(n, s, k) for n, s, k, _u, _o in tensors], bf16_exact=True, jitter=0.02)
-        gpu = H.HiftModel(cfg, opt, 1, batch, seq, init_params=theta, unfused=unfused)
+        gpu = H.HiftModel(cfg, opt, 1, batch, seq, init_params=theta, unfused=unfused, no_packed_copies=int(d > 128 or f > 328))
         gpu.set_group_schedule("bottom2up", 1)
         losses = []
         for t in range(1, 2 * gpu.k + 1):
             tok, lab = make_batch(wl, 3, t)
             losses.append(gpu.step(torch.from_numpy(tok).cuda(), torch.from_numpy(lab).cuda(), gpu.schedule_group_at(t)))
         got.append((losses, gpu.read_params(), gpu.read_state(0, gpu.n_units, 0)))
+        gpu.close()
     assert got[0][0] == got[1][0]
     assert np.array_equal(got[0][1], got[1][1]) and np.array_equal(got[0][2], got[1][2])
+
+
+@pytest.mark.parametrize("batch,seq", [(2, 40), (1, 264), (8, 264), (1, 520)])
+def test_causal_bands_on_tiles_of_several_sizes(batch, seq):
+    """Attention as separate contractions that skip the masked half: 64 x 32, 64 x 64 and 128 x 128 tiles, sequences that end
+    inside a tile; gradients of the layer and of the embeddings below it against the oracle, with the bounds of this file."""
+    import paper_2401_15207_amd as H
+    wl = dict(arch=0, n_layers=1, d_model=512, n_heads=8, d_ffn=512, vocab=304, max_seq=seq, n_classes=0, norm_eps=1e-5, rope_base=10000.0,
+              dtype=1, batch=batch, seq=seq, m=1, strategy="bottom2up", opt=SGD1)
+    _gradient_check(wl, lambda k: [0, 1], test=f"causal bands, {batch} x {seq}", unfused=H.UNFUSED_ATTENTION)

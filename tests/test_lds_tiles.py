@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from tests.test_gpu_kernels import LDS_CASES
+from tests.test_gpu_step_bf16 import GELU_CASES
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2401_15207_amd", "csrc")
 SRC = r"""
@@ -46,7 +47,8 @@ def test_the_gpu_cases_reach_every_tile(lib):
     t = tiles(lib)
     reached = {lib.pick(M, N, K, 1) for M, N, K in LDS_CASES if M % 64 and N % 64 and K % 64}
     assert reached >= set(range(len(t))) - {i for i, x in enumerate(t) if x == (64, 64)}
-    assert {t[lib.pick(*c, 1)] for c in LDS_CASES} == set(t)
+    assert {lib.pick(*c, 1) for c in LDS_CASES} == set(range(len(t)))
+    assert {lib.pick(batch * seq, f, d, 1) for _arch, batch, seq, d, f in GELU_CASES} == set(range(len(t)))
 
 
 # problem, tile; beside it the time that was measured on this tile and on another, microseconds
@@ -56,7 +58,12 @@ MEASURED = [
     ((64, 64, 128, 2048), (64, 64)),        # 15.5, 128 x 64: 19.1
     ((1024, 1024, 64, 32), (128, 128)),     # 23.3, 64 x 64: 27.2
     ((231, 4096, 11008, 1), (64, 64)),      # 39.5, 128 x 64: 57.4
-    ((2048, 4096, 1024, 1), (128, 128)),    # 24.1, 128 x 64: 26.0
+    ((2048, 4096, 1024, 1), (128, 128)),    # 24.1, 256 x 256: 28.0
+    ((2048, 32000, 4096, 1), (256, 256)),   # 442, 128 x 128: 594
+    ((8192, 4096, 11008, 1), (256, 256)),   # 556, 128 x 128: 753
+    ((256, 51200, 1024, 1), (256, 256)),    # 32.0, 128 x 128: 40.0
+    ((2048, 4096, 4096, 1), (128, 128)),    # 68.8, 256 x 256: 83.2
+    ((16384, 16384, 256, 1), (128, 128)),   # 246, 256 x 256: 275
 ]
 
 
