@@ -46,7 +46,7 @@ struct LdsP {
 
 constexpr int LK = 64;       // k extent of a stage
 constexpr uint32_t OUT_OF_RANGE = 0xFFFFFFF0u;  // beyond every buffer below: such a lane's 16 bytes arrive as zeros
-constexpr uint32_t BUF_BYTES = 0x80000000u;     // lds_gemm_applies keeps every valid offset below this
+constexpr uint32_t BUF_BYTES = OUT_OF_RANGE;    // lds_gemm_applies keeps every valid offset below this
 
 // One operand's tile, ROWS rows (of C: rows for A, columns for B) x 64 k per stage.
 // k-major: LDS row = tile row, 128 bytes, 16-byte piece c at position c ^ ((row / 2) % 8): sixteen consecutive rows of a
@@ -402,14 +402,18 @@ hipError_t pick_tile(LdsP& p, int nz, hipStream_t st) {
 
 }  // namespace
 
-// Operands in 16-byte pieces along their contiguous direction, and offsets within a stage's rows of at most 2 GiB.
+// Operands in 16-byte pieces along their contiguous direction, and offsets within a stage's rows (up to 256 of a k-major operand,
+// 64 of a transposed one) below BUF_BYTES.
 bool lds_gemm_applies(const Gemm& g) {
   if (g.dtype != DT_BF16 || g.K < 8) return false;
+  const auto fits = [&](bool kmajor, int64_t rows, int64_t ld) {
+    const int64_t in_stage = kmajor ? (rows < 256 ? rows : 256) : (g.K < LK ? g.K : LK);
+    return ld < (int64_t(1) << 31) && in_stage * ld * 2 <= BUF_BYTES;
+  };
   const bool a_ok = al16(g.A) && g.lda % 8 == 0 && g.sa1 % 8 == 0 && g.sa2 % 8 == 0 && (g.a_kmajor ? g.K % 8 == 0 : g.M % 8 == 0);
   const bool b_ok = al16(g.B) && g.ldb % 8 == 0 && g.sb1 % 8 == 0 && g.sb2 % 8 == 0 && (g.b_kmajor ? g.K % 8 == 0 : g.N % 8 == 0);
-  const int64_t most = int64_t(1) << 22;  // leading dimension: 128 rows of 2 x 4 M bytes stay below BUF_BYTES
-  return a_ok && b_ok && g.lda < most && g.ldb < most && g.K < (int64_t(1) << 30) && g.M < (int64_t(1) << 30) && g.N < (int64_t(1) << 30) &&
-         ((g.M + 31) / 32) * ((g.N + 31) / 32) < (int64_t(1) << 31);
+  return a_ok && b_ok && fits(g.a_kmajor, g.M, g.lda) && fits(g.b_kmajor, g.N, g.ldb) && g.K < (int64_t(1) << 30) && g.M < (int64_t(1) << 30) &&
+         g.N < (int64_t(1) << 30) && ((g.M + 31) / 32) * ((g.N + 31) / 32) < (int64_t(1) << 31);
 }
 
 // GELU or its derivative on the way out: one bf16 problem whose rows move in 16-byte pieces, in the layout of the pass it belongs to.

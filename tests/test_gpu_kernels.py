@@ -132,6 +132,34 @@ def test_contraction_inside_wider_buffers(ak, bk, M, N, K):
         assert not bad.any(), (out_f32, int(bad.sum()))
 
 
+@pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 1), (0, 0)])
+def test_contraction_of_a_slice_of_very_wide_rows(ak, bk):
+    """Rows more than 4 M values apart (offsets beyond 2 GiB within a tile): the matrix instructions still take them, so that the
+    fp32 sums are those of the same operands lying close together, bit for bit."""
+    import torch
+    import paper_2401_15207_amd as H
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    M, N, K, wide = 120, 56, 72, 17_500_008   # row 63 of a 64-row tile 2.2 GB from row 0; a second tile of rows, a second stage
+    A = torch.randn(*((M, K) if ak else (K, M)), generator=g, device="cuda").to(torch.bfloat16)
+    B = torch.randn(*((N, K) if bk else (K, N)), generator=g, device="cuda").to(torch.bfloat16)
+    rows = max(M if ak else K, N if bk else K)
+    space = torch.empty(rows * wide, dtype=torch.bfloat16, device="cuda")
+    out = []
+    for lda, ldb in ((A.shape[1], B.shape[1]), (wide, B.shape[1]), (A.shape[1], wide)):
+        ops = []
+        for x, ld in ((A, lda), (B, ldb)):
+            if ld == wide:
+                x = space.as_strided(x.shape, (wide, 1)).copy_(x)
+            ops.append(x)
+        C = torch.full((M, N), 7.0, device="cuda")
+        H.kernel_gemm(BF16, ak, bk, 1, M, N, K, ops[0], lda, ops[1], ldb, C, N)
+        out.append(C)
+    ref = (A.double() if ak else A.double().t()) @ (B.double().t() if bk else B.double())
+    assert float((out[0] - ref).abs().max()) <= 1e-5 * (float(ref.abs().max()) + K ** 0.5)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
 def test_gemm_batched_strided_bf16():
     import torch
     import paper_2401_15207_amd as H
