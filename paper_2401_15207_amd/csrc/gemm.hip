@@ -9,7 +9,7 @@
 //     forward and backward, folded RMS normalisation) straight from the accumulators.  See further down.
 //   * bf16 weight gradients that fill the chip with whole 256x256 tiles: gemm_tt_k.
 //   * every other bf16 problem whose operands move in 16-byte pieces: gemm_lds_k (gemm_lds.hip).
-//   * fp32 and odd shapes: a plain 64x64x16 LDS-tiled FMA kernel with arbitrary strides.
+//   * fp32 and odd shapes: gemm_fma_k, a plain LDS-tiled FMA kernel (64 x 64 or 32 x 32 outputs) for any leading dimensions.
 #include <type_traits>
 
 #include "common.h"
@@ -928,7 +928,8 @@ __global__ void __launch_bounds__(256) gemm_tt_k(GemmP p) {
 // multiply-adds over ascending k.  KC k-values of both operands per pass through LDS; the next pass's elements are on their
 // way in registers meanwhile.  Small problems are a chain of passes, each a trip to memory: 16 k per pass with nothing in
 // flight took 3 us a pass (64 x 64, k 256: 36 us, now 9, a launch being 4 of them; 2048 x 1024, k 1024: 171 us, now 100).
-// 32 x 32 tiles where 64 x 64 would leave compute units without one.
+// 32 x 32 tiles where 64 x 64 would leave compute units without one.  A pass that k does not fill is loaded and multiplied only as
+// far as k goes, in fours, and up to 16 k have passes of 16: 4096 x 4096, k 4 in bf16 takes 15 us, 28 with 32 k whatever k is.
 // One operand's share of a pass for a thread: NLD elements a fixed distance apart, found by one pointer and one stride
 // (KMAJOR: element i is row tid / KC + i 256 / KC at k = tid % KC; else row tid % BT at k = tid / BT + i 256 / BT), so that
 // neighbouring threads take neighbours along the operand's contiguous direction.  Elements outside are read from the operand's
@@ -936,6 +937,7 @@ __global__ void __launch_bounds__(256) gemm_tt_k(GemmP p) {
 template <int BT, int KC, bool KMAJOR, typename T>
 struct FmaOperand {
   static constexpr int NLD = BT * KC / 256, STEP = KMAJOR ? 256 / KC : 256 / BT;
+  static_assert(KMAJOR || STEP % 4 == 0, "the products walk k in fours: all of a four are stored, or none");
   const T* base;
   const T* at;
   int64_t stride, advance;
@@ -955,12 +957,14 @@ struct FmaOperand {
   }
   __device__ __forceinline__ void load(int64_t left) {
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) v[i] = *(inside(i, left) ? at + i * stride : base);
+    for (int i = 0; i < NLD; ++i)
+      if (KMAJOR || i * STEP < left) v[i] = *(inside(i, left) ? at + i * stride : base);
     at += advance;
   }
   __device__ __forceinline__ void store(float (*dst)[BT + 4], int64_t left) const {
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) dst[KMAJOR ? k0 : k0 + i * STEP][KMAJOR ? r0 + i * STEP : r0] = inside(i, left) ? to_f32(v[i]) : 0.f;
+    for (int i = 0; i < NLD; ++i)
+      if (KMAJOR || i * STEP < left) dst[KMAJOR ? k0 : k0 + i * STEP][KMAJOR ? r0 + i * STEP : r0] = inside(i, left) ? to_f32(v[i]) : 0.f;
   }
 };
 
@@ -994,14 +998,22 @@ __global__ void __launch_bounds__(256) gemm_fma_k(GemmP p) {
       a.load(left - KC);
       b.load(left - KC);
     }
-#pragma unroll 16
-    for (int k = 0; k < KC; ++k) {
+    auto step = [&](int k) __attribute__((always_inline)) {
       const Vec<float, TM> x = *reinterpret_cast<const Vec<float, TM>*>(&As[buf][k][ty * TM]);
       const Vec<float, TM> y = *reinterpret_cast<const Vec<float, TM>*>(&Bs[buf][k][tx * TM]);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j) acc[i][j] = fmaf(x.v[i], y.v[j], acc[i][j]);
+    };
+    if (left >= KC) {
+#pragma unroll 16
+      for (int k = 0; k < KC; ++k) step(k);
+    } else {
+      for (int k = 0; k < (int)left; k += 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) step(k + e);
+      }
     }
     if (more) {
       a.store(As[buf ^ 1], left - KC);
@@ -1233,7 +1245,8 @@ hipError_t gemm(const Gemm& g, hipStream_t st) {
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)nz);
 #define FMA_TILE(AK, BKM, T, OutT)                                                       \
   do {                                                                                   \
-    if (bt == 64) gemm_fma_k<64, 32, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);         \
+    if (bt == 64 && g.K <= 16) gemm_fma_k<64, 16, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p); \
+    else if (bt == 64) gemm_fma_k<64, 32, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);         \
     else gemm_fma_k<32, 64, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);                  \
   } while (0)
 #define FMA(T, OutT)                                                                     \

@@ -133,6 +133,33 @@ def test_contraction_inside_wider_buffers(ak, bk, M, N, K):
 
 
 @pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 1), (0, 0)])
+@pytest.mark.parametrize("M,N,K", [(1030, 1031, k) for k in (1, 3, 4, 5, 15, 16, 17, 31, 32, 33, 67)] + [(70, 33, k) for k in (1, 7, 63, 65)])
+def test_plain_contraction_of_few_k(ak, bk, M, N, K):
+    """The plain FMA kernel where k ends inside a pass (16 or 32 k on 64 x 64 tiles, 64 on 32 x 32), operands inside buffers of NaN:
+    what lies past the end of k must not be multiplied, and all before it must."""
+    import torch
+    import paper_2401_15207_amd as H
+    rng = np.random.default_rng(K * 7 + M + 2 * ak + bk)
+    A, B = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((N, K)).astype(np.float32)
+    for dtype in (F32, BF16):
+        a, b = (A, B) if dtype == F32 else (_bf16_round(A), _bf16_round(B))
+        ref = a.astype(np.float64) @ b.astype(np.float64).T
+        ops = []
+        for x, kmajor in ((a, ak), (b, bk)):
+            x = x if kmajor else np.ascontiguousarray(x.T)
+            t = torch.full((x.shape[0] + 3, x.shape[1] + 3), float("nan"), device="cuda")
+            t[:x.shape[0], :x.shape[1]] = torch.from_numpy(x).cuda()
+            ops.append(t if dtype == F32 else t.to(torch.bfloat16))
+        C = torch.full((M + 1, N + 3), 7.0, device="cuda")
+        H.kernel_gemm(dtype, ak, bk, 1, M, N, K, ops[0], ops[0].shape[1], ops[1], ops[1].shape[1], C, N + 3)
+        got = C.cpu().numpy().astype(np.float64)
+        assert np.all(got[M:] == 7.0) and np.all(got[:, N:] == 7.0)
+        # one chain of K fused multiply-adds: K roundings of at most half a unit of the largest partial sum
+        bound = K * 2.0 ** -24 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64).T) + 1e-30
+        assert np.all(np.abs(got[:M, :N] - ref) <= bound), (dtype, float(np.max(np.abs(got[:M, :N] - ref) / bound)))
+
+
+@pytest.mark.parametrize("ak,bk", [(1, 1), (1, 0), (0, 1), (0, 0)])
 def test_contraction_of_a_slice_of_very_wide_rows(ak, bk):
     """Rows more than 4 M values apart (offsets beyond 2 GiB within a tile): the matrix instructions still take them, so that the
     fp32 sums are those of the same operands lying close together, bit for bit."""
