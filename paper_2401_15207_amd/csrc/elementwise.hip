@@ -905,7 +905,8 @@ __device__ __forceinline__ void stnt(float* p, const float (&f)[V]) {
 
 // Group-local update over contiguous fp32 master weights, all tensors of a group in one launch.  KIND 0 AdamW (decoupled
 // decay), 1 AdaGrad, 2 SGD with momentum, 3 plain SGD.  Four parameters per thread (16-byte accesses) where a tensor's
-// pieces are aligned for it.  A block finds its tensor in the table that came with the launch.
+// pieces are aligned for it, else one (20 M parameters of AdamW: 114 us; four to a thread 126, one after the other 134).  A
+// block finds its tensor in the table that came with the launch.
 // Memory bound: 5.8 TB/s on a layer of 202 M parameters.  Launched tensor by tensor, the 16 tensors of an encoder layer took
 // 16 launches of which 12 were gains and biases: 2.8 us each for work of less than one.
 struct OptTensor {
@@ -973,14 +974,13 @@ __global__ void __launch_bounds__(BLK) opt_k(OptHyper h, OptTable<NT> table) {
   if (NT > 1)
     while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].block0) ++q;  // uniform over the block
   const OptTensor& t = table.t[q];
-  const int64_t i0 = (int64_t)(blockIdx.x - t.block0) * (BLK * 4);
-  const int64_t i = i0 + threadIdx.x * 4;
-  if (t.vec && i + 4 <= t.n) {
+  const int64_t at = (int64_t)(blockIdx.x - t.block0) * BLK + threadIdx.x, i = at * 4;
+  if (!t.vec) {
+    if (at < t.n) opt_update<KIND, 1>(h, t, at);
+  } else if (i + 4 <= t.n) {
     opt_update<KIND, 4>(h, t, i);
-  } else if (t.vec) {
-    for (int64_t k = i; k < t.n; ++k) opt_update<KIND, 1>(h, t, k);
   } else {
-    for (int64_t k = i0 + threadIdx.x; k < t.n && k < i0 + BLK * 4; k += BLK) opt_update<KIND, 1>(h, t, k);
+    for (int64_t k = i; k < t.n; ++k) opt_update<KIND, 1>(h, t, k);
   }
 }
 
@@ -1407,7 +1407,8 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
   for (; *done < n_items && table.n < NT; ++*done) {
     const OptItem& it = items[*done];
     if (it.n == 0) continue;
-    const int64_t more = cdiv(it.n, 4 * BLK);
+    const bool vec = aligned16(it.master) && aligned16(it.grad) && aligned16(it.s1) && aligned16(it.s2) && aligned16(it.compute_copy);
+    const int64_t more = cdiv(it.n, vec ? 4 * BLK : BLK);
     if (table.n > 0 && blocks + more > 0x7FFFFFFF) break;
     OptTensor& t = table.t[table.n++];
     t.n = it.n; t.master = it.master; t.grad = it.grad; t.s1 = it.s1; t.s2 = it.s2; t.cc = (bf16*)it.compute_copy;
@@ -1416,7 +1417,7 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
     t.inv_bc2 = (float)(1.0 / (1.0 - pow(o.beta2, (double)it.t)));
     t.first = it.t == 1 ? 1 : 0;
     t.block0 = (uint32_t)blocks;
-    t.vec = aligned16(it.master) && aligned16(it.grad) && aligned16(it.s1) && aligned16(it.s2) && aligned16(it.compute_copy);
+    t.vec = vec;
     t.grad_fused = it.states_odd || it.n % 8 != 0 || !aligned16(it.master) || !aligned16(it.grad) || !aligned16(it.compute_copy);
     blocks += more;
   }
