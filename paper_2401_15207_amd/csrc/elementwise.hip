@@ -685,38 +685,48 @@ __global__ void __launch_bounds__(BLK) ce_count_k(int64_t rows, const int32_t* _
 // Up to CE_COUNT_ROWS rows every row's workgroup counts the targets itself (eight labels a thread, requested before the
 // row's logits and added up while those are on their way; whole numbers, so the same count) and the first one leaves the
 // count for ce_final_k: one launch less in front of the row kernel, 65.1 -> 60.3 us
-// for the whole loss at 2048 x 32000.  Beyond that the labels that all workgroups read together grow with the square of rows
-// (16 MB of L2 reads at 2048, under 2 us), and ce_count_k counts once.
+// for the whole loss at 2048 x 32000 in bf16.  Beyond that ce_count_k counts once: with 32 labels a thread the row kernel takes
+// longer than the launch that it saves, but for the widest rows (4096 x 2000 in bf16 33 us, 23 counted once; 4096 x 8000 41 and 33;
+// 4096 x 32000 90 and 94).  The kernels come in both forms, as one that asks how many rows there are is slower on both sides of the
+// line (2049 x 4000 in fp32 19.6 us, 18.5 in two forms; 2048 x 2000 in bf16 13.7 and 13.2).
 constexpr int CE_COUNT_ROWS = 8 * BLK;
+template <bool COUNT>
 struct CeTargets {
-  int32_t lb[8];
-  __device__ __forceinline__ void request(int64_t rows, const int32_t* __restrict__ labels) {
-    if (rows > CE_COUNT_ROWS) return;
+  int32_t lb[COUNT ? 8 : 1];
+  float inv_n;  // 1 / targets, if counted before
+  __device__ __forceinline__ void request(int64_t rows, const int32_t* __restrict__ labels, const float* __restrict__ row_loss) {
+    if (!COUNT) {
+      inv_n = 1.0f / row_loss[rows];
+      return;
+    }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) lb[i] = i * BLK + (int)threadIdx.x < rows ? labels[i * BLK + threadIdx.x] : -1;
+    for (int i = 0; i < (COUNT ? 8 : 0); ++i) {  // past the end the last label again (a load under a condition is waited for there and then)
+      const int at = i * BLK + (int)threadIdx.x;
+      lb[i] = labels[at < rows ? at : (int)rows - 1];
+    }
   }
-  __device__ __forceinline__ float count(int64_t rows, float* __restrict__ row_loss, float* red) const {
-    if (rows > CE_COUNT_ROWS) return row_loss[rows];
+  __device__ __forceinline__ float inverse(int64_t rows, float* __restrict__ row_loss, float* red) const {
+    if (!COUNT) return inv_n;
     float c = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) c += lb[i] >= 0 ? 1.f : 0.f;
+    for (int i = 0; i < (COUNT ? 8 : 0); ++i) c += lb[i] >= 0 && i * BLK + (int)threadIdx.x < rows ? 1.f : 0.f;
     c = block_sum<BLK / 64>(c, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) row_loss[rows] = c;
-    return c;
+    return 1.0f / c;
   }
 };
 
-template <typename T, int V>
+template <typename T, int V, bool COUNT>
 __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __restrict__ logits,
                                                  const int32_t* __restrict__ labels, float* __restrict__ row_loss) {
   __shared__ float red[BLK / 64];
   const int64_t row = blockIdx.x;
   T* lr = logits + row * vocab;
   int lab = labels[row];
-  CeTargets targets;
-  targets.request(rows, labels);
+  CeTargets<COUNT> targets;
+  targets.request(rows, labels, row_loss);
   if (lab < 0) {  // no target: zero gradient, zero loss
-    if (blockIdx.x == 0) targets.count(rows, row_loss, red);
+    if (COUNT && blockIdx.x == 0) targets.inverse(rows, row_loss, red);
     float z[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) z[e] = 0.f;
@@ -725,7 +735,7 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
     return;
   }
   if (lab >= vocab) lab = vocab - 1;
-  const float inv_n = 1.0f / targets.count(rows, row_loss, red);
+  const float inv_n = targets.inverse(rows, row_loss, red);
   float mx = -INFINITY;
   for (int j = threadIdx.x * V; j < vocab; j += BLK * V) {
     float a[V];
@@ -757,17 +767,17 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
 // Same, with the row held in registers (vocab <= BLK * V * NV): every logit is read once and its gradient written
 // once, all loads of a row in flight together; the maximum, the sum of exponentials and the gradient are three
 // passes over registers.  The values stay in their storage type (16 bytes per piece) until they are used.
-template <typename T, int V, int NV>
+template <typename T, int V, int NV, bool COUNT>
 __global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* __restrict__ logits,
                                                      const int32_t* __restrict__ labels, float* __restrict__ row_loss) {
   __shared__ float red[BLK / 64];
   const int64_t row = blockIdx.x;
   T* lr = logits + row * vocab;
   int lab = labels[row];
-  CeTargets targets;
-  targets.request(rows, labels);
+  CeTargets<COUNT> targets;
+  targets.request(rows, labels, row_loss);
   if (lab < 0) {  // no target: zero gradient, zero loss
-    if (blockIdx.x == 0) targets.count(rows, row_loss, red);
+    if (COUNT && blockIdx.x == 0) targets.inverse(rows, row_loss, red);
     float z[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) z[e] = 0.f;
@@ -782,7 +792,7 @@ __global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* 
     const int j = (i * BLK + threadIdx.x) * V;
     if (j < vocab) raw[i] = *reinterpret_cast<const Vec<T, V>*>(lr + j);
   }
-  const float inv_n = 1.0f / targets.count(rows, row_loss, red);
+  const float inv_n = targets.inverse(rows, row_loss, red);
   constexpr float LOG2E = 1.4426950408889634f;
   float mx = -INFINITY;
 #pragma unroll
@@ -1325,23 +1335,30 @@ hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_l
   LAUNCH_CHECK();
 }
 
-hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
-                              hipStream_t st) {
-  if (rows == 0) return hipSuccess;
+template <bool COUNT>
+static void launch_ce_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss, hipStream_t st) {
+  const dim3 grid((unsigned)rows);
 #define OK(v) (V_ % (v) == 0 && aligned16(logits))
   // 16-byte pieces of a row a thread keeps: 16 (rows of up to 32768 bf16 or 16384 fp32 values) or 32
   if (dt == DT_BF16 && OK(8) && V_ <= BLK * 8 * 16) {
-    ce_row_reg_k<bf16, 8, 16><<<dim3((unsigned)rows), BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
+    ce_row_reg_k<bf16, 8, 16, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
   } else if (dt == DT_BF16 && OK(8) && V_ <= BLK * 8 * 32) {
-    ce_row_reg_k<bf16, 8, 32><<<dim3((unsigned)rows), BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
+    ce_row_reg_k<bf16, 8, 32, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
   } else if (dt == DT_F32 && OK(4) && V_ <= BLK * 4 * 16) {
-    ce_row_reg_k<float, 4, 16><<<dim3((unsigned)rows), BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
+    ce_row_reg_k<float, 4, 16, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
   } else if (dt == DT_F32 && OK(4) && V_ <= BLK * 4 * 32) {
-    ce_row_reg_k<float, 4, 32><<<dim3((unsigned)rows), BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
+    ce_row_reg_k<float, 4, 32, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
   } else {
-    DISPATCH_TV(dt, OK, (ce_row_k<T, V><<<dim3((unsigned)rows), BLK, 0, st>>>(rows, V_, (T*)logits, labels, row_loss)));
+    DISPATCH_TV(dt, OK, (ce_row_k<T, V, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (T*)logits, labels, row_loss)));
   }
 #undef OK
+}
+
+hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
+                              hipStream_t st) {
+  if (rows == 0) return hipSuccess;
+  if (rows > CE_COUNT_ROWS) launch_ce_rows<false>(dt, rows, V_, logits, labels, row_loss, st);
+  else launch_ce_rows<true>(dt, rows, V_, logits, labels, row_loss, st);
   LAUNCH_CHECK();
 }
 
