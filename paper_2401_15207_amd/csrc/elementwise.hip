@@ -1329,9 +1329,11 @@ hipError_t softmax_bwd(int dt, int64_t nbh, int S, float scale, bool causal, con
   LAUNCH_CHECK();
 }
 
+bool cross_entropy_counts_apart(int64_t rows) { return rows > CE_COUNT_ROWS; }
+
 hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_loss, hipStream_t st) {
   if (rows == 0) return hipSuccess;
-  if (rows > CE_COUNT_ROWS) ce_count_k<<<1, BLK, 0, st>>>(rows, labels, row_loss);
+  if (cross_entropy_counts_apart(rows)) ce_count_k<<<1, BLK, 0, st>>>(rows, labels, row_loss);
   LAUNCH_CHECK();
 }
 
@@ -1357,7 +1359,7 @@ static void launch_ce_rows(int dt, int64_t rows, int V_, void* logits, const int
 hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st) {
   if (rows == 0) return hipSuccess;
-  if (rows > CE_COUNT_ROWS) launch_ce_rows<false>(dt, rows, V_, logits, labels, row_loss, st);
+  if (cross_entropy_counts_apart(rows)) launch_ce_rows<false>(dt, rows, V_, logits, labels, row_loss, st);
   else launch_ce_rows<true>(dt, rows, V_, logits, labels, row_loss, st);
   LAUNCH_CHECK();
 }

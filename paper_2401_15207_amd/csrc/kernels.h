@@ -143,8 +143,10 @@ hipError_t softmax_bwd(int dt, int64_t nbh, int S, float scale, bool causal, con
 // logits [rows, V] -> d loss / d logits in place; loss = mean over labels >= 0
 hipError_t cross_entropy(int dt, int64_t rows, int V, void* logits, const int32_t* labels,
                          float* row_loss, float* loss_out, hipStream_t st);
-// its three launches one by one (row_loss: rows + 1 floats): the number of rows with a target into row_loss[rows];
-// the rows (per-row loss into row_loss[r], gradient over the logits); the mean of the per-row losses
+// its launches one by one (row_loss: rows + 1 floats): the number of rows with a target into row_loss[rows], unless the row
+// kernels count them (up to 2048 rows: cross_entropy_count then launches nothing); the rows (per-row loss into row_loss[r],
+// gradient over the logits); the mean of the per-row losses
+bool cross_entropy_counts_apart(int64_t rows);
 hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_loss, hipStream_t st);
 hipError_t cross_entropy_rows(int dt, int64_t rows, int V, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st);

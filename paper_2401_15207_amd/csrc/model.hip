@@ -601,7 +601,7 @@ const char* const RW_NAMES[RW_N] = {
     "embedding lookup", "normalisation forward", "row sums of squares", "rotary embedding", "activation forward",
     "activation backward", "softmax forward", "softmax backward", "cross-entropy with gradient", "normalisation backward dX",
     "normalisation backward gain/shift", "column sums (bias gradient)", "embedding gradient (clear + scatter)",
-    "first-token gather / scatter", "loss bookkeeping (count of targets, mean of row losses; one workgroup each)"};
+    "first-token gather / scatter", "loss bookkeeping (mean of row losses; beyond 2048 rows also count of targets; one workgroup each)"};
 
 struct Scope {
   hift_model* M;
@@ -1129,7 +1129,7 @@ hift_status forward(hift_model* M, const hift_batch* bt, int keep_from) {
       RW(RW_FIRST_ROWS, 2.0 * B * d * es, gather_first(dt, B, S, d, xl, M->xcls, st));
     }
     ST_TRY(linear(M, M->xcls, B, M->T_("wc"), &M->T_("bc"), nullptr, M->logits));
-    RW(RW_LOSS_MEAN, 4.0 * (B), cross_entropy_count(B, bt->labels, M->row_loss, st));
+    if (cross_entropy_counts_apart(B)) RW(RW_LOSS_MEAN, 4.0 * (B), cross_entropy_count(B, bt->labels, M->row_loss, st));
     RW(RW_CROSS_ENTROPY, 2.0 * (B) * (c.n_classes) * es, cross_entropy_rows(dt, B, c.n_classes, M->logits, bt->labels, M->row_loss, st));
     RW(RW_LOSS_MEAN, 4.0 * (B), cross_entropy_mean(B, M->row_loss, M->loss_dev, st));
   } else {
@@ -1138,7 +1138,7 @@ hift_status forward(hift_model* M, const hift_batch* bt, int keep_from) {
       else RW(RW_NORM_FWD, 2.0 * T * d * es, norm_fwd(dt, false, T, d, c.norm_eps, xl, M->W("lnf_g"), M->W("lnf_b"), M->xf, M->st_f, st));
     }
     ST_TRY(linear(M, M->xf, T, M->T_(c.tie_embeddings ? "tok_emb" : "whead"), nullptr, nullptr, M->logits));
-    RW(RW_LOSS_MEAN, 4.0 * (T), cross_entropy_count(T, bt->labels, M->row_loss, st));
+    if (cross_entropy_counts_apart(T)) RW(RW_LOSS_MEAN, 4.0 * (T), cross_entropy_count(T, bt->labels, M->row_loss, st));
     RW(RW_CROSS_ENTROPY, 2.0 * (T) * (c.vocab) * es, cross_entropy_rows(dt, T, c.vocab, M->logits, bt->labels, M->row_loss, st));
     RW(RW_LOSS_MEAN, 4.0 * (T), cross_entropy_mean(T, M->row_loss, M->loss_dev, st));
   }

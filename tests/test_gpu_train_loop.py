@@ -3,7 +3,7 @@ schedule (delayed update, section 3) against the oracle run step by step, and ch
 import numpy as np
 import pytest
 
-from hift_inputs import make_batch
+from hift_inputs import WORKLOADS, make_batch, model_config
 from oracle import hift_oracle as O
 from tests.hift_pair import make_pair, rel_l2, to_dev
 from tests.test_gpu_step_fp32 import SMALL2
@@ -140,3 +140,20 @@ def test_checkpoint_resume_at_the_7b_widths_in_bf16(master_on_host):
     for j in (0, 1):
         assert np.array_equal(a.read_state(0, a.n_units, j), b.read_state(0, b.n_units, j))
 
+
+
+@pytest.mark.parametrize("batch,seq,launches", [(2, 32, 1), (64, 32, 1), (65, 32, 2)])
+def test_profile_counts_the_kernels_around_the_loss(batch, seq, launches):
+    """Up to 2048 rows the mean of the row losses is the only kernel beside the row kernels, beyond them the targets are counted
+    by one of their own: no entry of the profile may stand for a launch that does not happen."""
+    import paper_2401_15207_amd as H
+    wl = dict(WORKLOADS["C1"], batch=batch, seq=seq)
+    gpu = H.HiftModel(model_config(wl), wl["opt"], 1, batch, seq)
+    gpu.set_group_schedule("bottom2up", 1)
+    gpu.profile_enable(True)
+    steps = 3
+    for t in range(1, steps + 1):
+        gpu.step(*to_dev(*make_batch(wl, 1, t)), gpu.schedule_group_at(t))
+    rows = {name: v for name, v in gpu.profile_read_rowwise().items() if name.startswith("loss bookkeeping")}
+    (n, _ms, bytes_), = rows.values()
+    assert n == launches * steps and bytes_ == 4.0 * batch * seq * launches * steps
