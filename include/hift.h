@@ -79,7 +79,8 @@ typedef struct {
                             HIFT_BF16: bf16 weights/activations with fp32 accumulation and fp32
                             master weights (appendix "Mixing Precision", adapted mixed precision) */
   int32_t state_on_host; /* 1: optimizer state of inactive groups lives in the pinned arena and is
-                            moved per step (Algorithm 1 steps i and k); 0: all state stays in HBM */
+                            moved per step (Algorithm 1 steps i and k); 0: all state stays in HBM.  Results are
+                            identical */
   int32_t master_on_host; /* 1 (bf16 mode with state_on_host only): the fp32 master weights of inactive
                             groups live in the pinned arena too and travel with the state, so that HBM
                             holds the bf16 model plus one group's fp32 master (appendix "Mixing

@@ -940,10 +940,9 @@ struct OptHyper {
   float lr, b1, omb1, b2, omb2, eps, mu;
 };
 
-// Each of AdamW's moments is a sum of two products, one of them rounded and one fused.  Which one is fixed here and not left to
-// the compiler, and is the one it has always been for the tensor, so that a resumed run goes on bit for bit: the old moment's
-// where 16-byte pieces covered master, gradient, copy and both state arrays lying back to back, else (n no multiple of 8, or
-// the second array off by an odd count: states_odd) the gradient's.
+// Each of AdamW's moments is a sum of two products, one of them rounded and one fused.  Which one is not left to the compiler
+// but is the caller's to say (grad_fused: the gradient's, else the old moment's), and must not depend on where the arrays happen to
+// lie: state resident or parked on the host, the same update gives the same bits.
 template <int KIND, int V>
 __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t, int64_t i) {
   float th[V], g[V], a[V], b[V];
@@ -1437,7 +1436,7 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
     t.first = it.t == 1 ? 1 : 0;
     t.block0 = (uint32_t)blocks;
     t.vec = vec;
-    t.grad_fused = it.states_odd || it.n % 8 != 0 || !aligned16(it.master) || !aligned16(it.grad) || !aligned16(it.compute_copy);
+    t.grad_fused = it.grad_fused;
     blocks += more;
   }
   if (table.n == 0) return hipSuccess;

@@ -1897,7 +1897,13 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
     if (M->opt.kind == HIFT_ADAFACTOR) bytes_per = 24.0;  // the gradient is read four times (row, column, clipping, update)
     if (M->dt == DT_BF16) bytes_per += 2.0;
     Scope sc(M, CAT_OPT, bytes_per * cnt);
-    const bool states_odd = !moving && M->n_state == 2 && M->lay.n_params % 4 != 0;
+    // Which product of AdamW's moments is fused (see opt_update) follows from the layout alone, so that it is the same wherever state
+    // and master live: the old moment's for tensors that lie in whole 16-byte pieces in the model and in the group, in a model whose
+    // parameters are a multiple of four, else the gradient's (what resident state has always had, so that its runs go on
+    // bit for bit).
+    auto grad_fused = [&](const Tensor& t) {
+      return t.count() % 8 != 0 || t.off % 4 != 0 || (t.off - plo) % 4 != 0 || (M->n_state == 2 && M->lay.n_params % 4 != 0);
+    };
     std::vector<OptItem> items;
     for (int i = M->lay.unit_first[ulo]; i < M->lay.unit_first[uhi]; ++i) {
       const Tensor& t = M->lay.t[i];
@@ -1908,7 +1914,7 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
                                master_of(t), M->grad + (t.off - plo), M->fac + t.fac_off, M->af_work, cc, M->cs));
         continue;
       }
-      items.push_back(OptItem{t.count(), t.kind == HIFT_KIND_MATRIX, tg, master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, states_odd});
+      items.push_back(OptItem{t.count(), t.kind == HIFT_KIND_MATRIX, tg, master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, grad_fused(t)});
     }
     if (!items.empty()) K_TRY(optimizer_update(oa, items.data(), (int)items.size(), M->cs));
   }
@@ -2002,7 +2008,8 @@ hift_status hift_lora_step(hift_model* M, const hift_batch* bt, float* loss_out)
     const double bytes_per = 28.0 + (M->dt == DT_BF16 ? 2.0 : 0.0);
     Scope sc(M, CAT_OPT, bytes_per * M->n_lora);
     OptArgs oa{M->opt.kind, M->opt.lr, M->opt.beta1, M->opt.beta2, M->opt.eps, M->opt.weight_decay, M->opt.momentum};
-    const OptItem all{M->n_lora, true, M->lora_t, M->lora_master, M->lora_grad, M->lora_m, M->lora_v, M->dt == DT_BF16 ? M->lora_wc : nullptr, false};
+    const OptItem all{M->n_lora, true, M->lora_t, M->lora_master, M->lora_grad, M->lora_m, M->lora_v, M->dt == DT_BF16 ? M->lora_wc : nullptr,
+                      M->n_lora % 8 != 0};
     K_TRY(optimizer_update(oa, &all, 1, M->cs));
   }
   HIP_TRY(hipEventRecord(M->ev_w0, M->cs));
@@ -2415,8 +2422,9 @@ hift_status hift_kernel_optimizer(const hift_opt* opt, int64_t count, int32_t de
   if (count < 0 || t < 1) return fail(HIFT_EINVAL, "count must be >= 0 and t >= 1");
   if (opt->kind == HIFT_ADAFACTOR) return fail(HIFT_EINVAL, "Adafactor works on whole tensors; it has no element-wise kernel entry");
   OptArgs oa{opt->kind, opt->lr, opt->beta1, opt->beta2, opt->eps, opt->weight_decay, opt->momentum};
-  const OptItem all{count, decay != 0, t, master, grad, state1, state2, compute_copy,
-                    ((reinterpret_cast<uintptr_t>(state1) | reinterpret_cast<uintptr_t>(state2)) & 15) != 0};
+  const uintptr_t low = reinterpret_cast<uintptr_t>(master) | reinterpret_cast<uintptr_t>(grad) | reinterpret_cast<uintptr_t>(state1) |
+                        reinterpret_cast<uintptr_t>(state2) | reinterpret_cast<uintptr_t>(compute_copy);
+  const OptItem all{count, decay != 0, t, master, grad, state1, state2, compute_copy, count % 8 != 0 || (low & 15) != 0};
   HIP_TRY(optimizer_update(oa, &all, 1, (hipStream_t)stream));
   return HIFT_OK;
 }
