@@ -232,7 +232,7 @@ def main():
     ap.add_argument("--workload", default="C4")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--seed", type=int, default=0)
-    ap.add_argument("--copy-engine", type=int, default=0, help="0 hipMemcpyAsync, 1 small-grid copy kernel")
+    ap.add_argument("--copy-engine", type=int, default=0, help="0 asynchronous copies on the DMA engines, 1 small-grid copy kernel")
     ap.add_argument("--copy-blocks", type=int, default=16)
     ap.add_argument("--m", type=int, default=0,
                     help="units per group (default: the workload's); the number of units gives one group, "
@@ -435,7 +435,7 @@ def main():
         "weight_repack_gbps": by_pack / (ms_pack * 1e-3) / 1e9 if ms_pack > 0 else 0.0,
         "state_copy_gb_per_step": {"h2d": (h2d1 - h2d0) / 1e9 / max(a.steps, 1), "d2h": (d2h1 - d2h0) / 1e9 / max(a.steps, 1)},
         "exposed_state_copy_ms_last_step": exposed,
-        "state_copy_engine": "copy kernel, %d workgroups" % a.copy_blocks if a.copy_engine == 1 else "hipMemcpyAsync",
+        "state_copy_engine": "copy kernel, %d workgroups" % a.copy_blocks if a.copy_engine == 1 else "DMA engines (hipMemcpy2DAsync)",
         "ms_per_step_with_event_brackets": 1e3 * t_prof / max(a.steps, 1),
         "compute_stream_ms_by_group": [by_group[g] for g in sorted(by_group)],
         "last_loss": loss,

@@ -334,7 +334,7 @@ struct hift_model {
   int64_t lr_warmup = 0, lr_total = 0;
   uint64_t h2d_bytes = 0, d2h_bytes = 0;
   bool timed = false;
-  int copy_engine = 0;   // 0: hipMemcpyAsync, 1: small-grid copy kernel
+  int copy_engine = 0;   // 0: asynchronous copies (see state_copy), 1: small-grid copy kernel
   int copy_blocks = 16;
   Prof prof;
 

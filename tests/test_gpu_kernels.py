@@ -885,3 +885,30 @@ def test_fused_attention_backward(B, H, S, hd, causal, rope):
 def test_fused_attention_backward_of_narrow_heads(S, causal, rope):
     """Heads 64 wide: both halves in one launch up to 128 tokens, two launches beyond, at the edges of the row and key blocks."""
     test_fused_attention_backward(2, 3, S, 64, causal, rope)
+
+
+@pytest.mark.parametrize("S", [8, 104, 128])
+@pytest.mark.parametrize("causal", [0, 1])
+def test_fused_attention_backward_of_narrow_heads_on_a_full_chip(S, causal):
+    """1280 workgroups, two to a compute unit and several rounds of them, each handing its row sums from one half of the backward to
+    the other: every sequence must get the bits that it gets in a call of its own (those are compared with the oracle above)."""
+    import torch
+    import paper_2401_15207_amd as H_
+    g = torch.Generator(device="cuda")
+    g.manual_seed(S + causal)
+    B, copies, H, hd = 2, 40, 16, 64
+    d = H * hd
+
+    def backward(qkv, dctx, b):
+        new = lambda *s, dt=torch.bfloat16: torch.full(s, float("nan"), dtype=dt, device="cuda")
+        ctx, lse, dsum, dqkv = new(b * S, d), new(b * H * S, dt=torch.float32), new(b * H * S, dt=torch.float32), new(b * S, 3 * d)
+        H_.kernel_attention_fwd(b, H, S, hd, causal, qkv, None, ctx, lse)
+        H_.kernel_attention_bwd(b, H, S, hd, causal, qkv, ctx, lse, dctx, dsum, dqkv)
+        return dsum, dqkv
+    qkv = torch.randn(B * S, 3 * d, generator=g, device="cuda").to(torch.bfloat16)
+    dctx = torch.randn(B * S, d, generator=g, device="cuda").to(torch.bfloat16)
+    dsum, dqkv = backward(qkv, dctx, B)
+    assert torch.isfinite(dqkv.float()).all()
+    many_sum, many = backward(qkv.repeat(copies, 1), dctx.repeat(copies, 1), B * copies)
+    assert torch.equal(many_sum.view(copies, -1), dsum.expand(copies, -1))
+    assert torch.equal(many.view(copies, B * S, 3 * d), dqkv.expand(copies, -1, -1))
