@@ -8,14 +8,14 @@
 // (ds_read_b64_tr_b16, see gemm_tt_k for their lane layout).
 //
 // What bounds it is the rate at which a compute unit draws operands out of L2 (about 50 bytes per clock) and, for the
-// smallest problems, latency: a stage is a barrier, LDS reads and few products.  So every tile's ring leaves room for two or
-// more workgroups in a compute unit's LDS (they hide each other's waits: 2048 x 4096, k 4096 takes 71 us with a ring of two
+// smallest problems, latency: a stage is a barrier, LDS reads and few products.  So up to 128 x 128 every tile's ring leaves room
+// for two or more workgroups in a compute unit's LDS (they hide each other's waits: 2048 x 4096, k 4096 takes 71 us with a ring of two
 // stages of 128 x 128 tiles, 88 us with four stages and one workgroup), and a stage's fragments are all read into registers
 // one stage ahead, under the products of the stage before (231 x 4096, k 11008: 40 us, 50 with fragments read one k-step
-// ahead).  An output's sum runs over k in one chain, in ascending order, whatever the tile.
+// ahead).  256 x 256 tiles, for products of several full rounds, work differently (see Tile).  An output's sum runs over k in one chain, in ascending order, whatever the tile.
 // Measured against the kernel before it (operands through registers, turned around on the way, 128 x 128 tiles): 1024 tokens,
-// 768 -> 3072 with input and weight gradients 13 + 51 + 27 us, now 11 + 14 + 13; 231 tokens, 4096 -> 12288: 49 + 185 + 348 us,
-// now 37 + 50 + 63.
+// 768 -> 3072 with input and weight gradients 12 + 50 + 26 us, now 11 + 13 + 13; 231 tokens, 4096 -> 12288: 49 + 185 + 348 us,
+// now 37 + 45 + 63.
 #include <type_traits>
 
 #include "common.h"
