@@ -293,14 +293,16 @@ def test_parked_state_in_rectangles_is_the_resident_state(shape, chunk, master_o
     dict(arch=0, d_model=60, n_heads=3, d_ffn=250, vocab=301), dict(arch=2, d_model=60, n_heads=3, d_ffn=251, vocab=303),
 ], ids=["2_classes", "3_classes", "odd_decoder", "odd_rope_decoder"])
 @pytest.mark.parametrize("bf16", [0, 1])
-@pytest.mark.parametrize("m", [1, 2])
-def test_where_state_lives_changes_no_bit(shape, bf16, m):
+@pytest.mark.parametrize("m,optk", [(1, "adamw"), (2, "adamw"), (1, "adagrad"), (2, "sgdm")])
+def test_where_state_lives_changes_no_bit(shape, bf16, m, optk):
     """Parameter counts and units that are no multiple of four: state resident, parked, and parked with the master beside it."""
     import paper_2401_15207_amd as H
     wl = dict(WORKLOADS["C1"], dtype=bf16, batch=2, seq=24, max_seq=32, **shape)
     theta0 = initial_weights(model_config(wl), 23, 0.02)
+    opt = {"adamw": wl["opt"], "adagrad": dict(kind="adagrad", lr=1e-2, eps=1e-10, weight_decay=0.01),
+           "sgdm": dict(kind="sgd", lr=1e-2, momentum=0.9, weight_decay=0.01)}[optk]
     places = [dict(state_on_host=0), dict(state_on_host=1)] + [dict(state_on_host=1, master_on_host=1)] * bf16
-    models = [H.HiftModel(model_config(wl), wl["opt"], m, 2, 24, init_params=theta0, **kw) for kw in places]
+    models = [H.HiftModel(model_config(wl), opt, m, 2, 24, init_params=theta0, **kw) for kw in places]
     k = [mdl.set_group_schedule("random", m, 5) for mdl in models][0]
     for t in range(1, 3 * k + 1):
         batch = to_dev(*make_batch(wl, 23, t))
@@ -309,7 +311,7 @@ def test_where_state_lives_changes_no_bit(shape, bf16, m):
     a = models[0]
     for b in models[1:]:
         assert np.array_equal(a.read_params(), b.read_params())
-        for j in (0, 1):
+        for j in range(2 if optk == "adamw" else 1):
             assert np.array_equal(a.read_state(0, a.n_units, j), b.read_state(0, b.n_units, j)), j
 
 
