@@ -8,6 +8,7 @@
 // wavefront shuffles.  Arithmetic is fp32 whatever the storage type is.
 #include "common.h"
 #include "kernels.h"
+#include "optimizer.h"
 
 namespace hift {
 
@@ -887,62 +888,17 @@ __global__ void __launch_bounds__(BLK) copy_stream_k(u32x4_t* __restrict__ dst, 
 }
 
 // ---------------------------------------------------------------------------- optimizer
-// fp32 loads and stores of data that is touched once per step (master weights, gradients, moments): non-temporal,
-// so that 6 GB of them do not push everything else out of the caches
-template <int V>
-__device__ __forceinline__ void ldnt(const float* p, float (&f)[V]) {
-  typedef float vt __attribute__((ext_vector_type(V)));
-  if constexpr (V == 1) {
-    f[0] = __builtin_nontemporal_load(p);
-  } else {
-    const vt t = __builtin_nontemporal_load(reinterpret_cast<const vt*>(p));
-#pragma unroll
-    for (int e = 0; e < V; ++e) f[e] = t[e];
-  }
-}
-template <int V>
-__device__ __forceinline__ void stnt(float* p, const float (&f)[V]) {
-  typedef float vt __attribute__((ext_vector_type(V)));
-  if constexpr (V == 1) {
-    __builtin_nontemporal_store(f[0], p);
-  } else {
-    vt t;
-#pragma unroll
-    for (int e = 0; e < V; ++e) t[e] = f[e];
-    __builtin_nontemporal_store(t, reinterpret_cast<vt*>(p));
-  }
-}
-
 // Group-local update over contiguous fp32 master weights, all tensors of a group in one launch.  KIND 0 AdamW (decoupled
 // decay), 1 AdaGrad, 2 SGD with momentum, 3 plain SGD.  Four parameters per thread (16-byte accesses) where a tensor's
 // pieces are aligned for it, else one (20 M parameters of AdamW: 114 us; four to a thread 126, one after the other 134).  A
 // block finds its tensor in the table that came with the launch.
 // Memory bound: 5.8 TB/s on a layer of 202 M parameters.  Launched tensor by tensor, the 16 tensors of an encoder layer took
 // 16 launches of which 12 were gains and biases: 2.8 us each for work of less than one.
-struct OptTensor {
-  int64_t n;       // parameters
-  float* master;
-  const float* grad;
-  float *s1, *s2;
-  bf16* cc;        // where the rounded new values go, or null
-  float wd, inv_bc1, inv_bc2;
-  int first;       // the tensor's first update
-  uint32_t block0; // first block of the launch that works on it
-  int vec;         // pieces of four are 16-byte aligned in every array
-  int grad_fused;  // AdamW: which product of a moment's sum is fused
-};
 template <int NT>  // 1 for a single tensor (the small table saves 0.2 us of a 3.6 us launch), OPT_TABLE for a group
 struct OptTable {
   OptTensor t[NT];
   int n;
 };
-struct OptHyper {
-  float lr, b1, omb1, b2, omb2, eps, mu;
-};
-
-// Each of AdamW's moments is a sum of two products, one of them rounded and one fused.  Which one is not left to the compiler
-// but is the caller's to say (grad_fused: the gradient's, else the old moment's), and must not depend on where the arrays happen to
-// lie: state resident or parked on the host, the same update gives the same bits.
 template <int KIND, int V>
 __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t, int64_t i) {
   float th[V], g[V], a[V], b[V];
@@ -950,27 +906,7 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
   ldnt<V>(t.grad + i, g);
   if (KIND != 3) ldnt<V>(t.s1 + i, a);
   if (KIND == 0) ldnt<V>(t.s2 + i, b);
-#pragma unroll
-  for (int e = 0; e < V; ++e) {
-    if (KIND == 0) {
-      th[e] -= h.lr * t.wd * th[e];
-      const float g2 = h.omb2 * g[e];
-      a[e] = t.grad_fused ? fmaf(h.omb1, g[e], h.b1 * a[e]) : fmaf(h.b1, a[e], h.omb1 * g[e]);
-      b[e] = t.grad_fused ? fmaf(g2, g[e], h.b2 * b[e]) : fmaf(h.b2, b[e], g2 * g[e]);
-      th[e] -= h.lr * (a[e] * t.inv_bc1) / (sqrtf(b[e] * t.inv_bc2) + h.eps);
-    } else if (KIND == 1) {
-      const float gg = g[e] + t.wd * th[e];
-      a[e] += gg * gg;
-      th[e] -= h.lr * gg / (sqrtf(a[e]) + h.eps);
-    } else {
-      float gg = g[e] + t.wd * th[e];
-      if (KIND == 2) {
-        a[e] = t.first ? gg : h.mu * a[e] + gg;
-        gg = a[e];
-      }
-      th[e] -= h.lr * gg;
-    }
-  }
+  opt_math<KIND, V>(h, t, th, g, a, b);
   stnt<V>(t.master + i, th);
   if (KIND != 3) stnt<V>(t.s1 + i, a);
   if (KIND == 0) stnt<V>(t.s2 + i, b);
@@ -1417,8 +1353,8 @@ hipError_t copy_stream(void* dst, const void* src, size_t bytes, int blocks, hip
 
 template <int NT>
 static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_items, int* done, hipStream_t st) {
-  const int kind = o.kind == 2 && o.momentum == 0.0 ? 3 : o.kind;
-  const OptHyper h{(float)o.lr, (float)o.beta1, (float)(1.0 - o.beta1), (float)o.beta2, (float)(1.0 - o.beta2), (float)o.eps, (float)o.momentum};
+  const int kind = opt_kind(o);
+  const OptHyper h = opt_hyper(o);
   OptTable<NT> table;
   table.n = 0;
   int64_t blocks = 0;
@@ -1429,14 +1365,9 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
     const int64_t more = cdiv(it.n, vec ? 4 * BLK : BLK);
     if (table.n > 0 && blocks + more > 0x7FFFFFFF) break;
     OptTensor& t = table.t[table.n++];
-    t.n = it.n; t.master = it.master; t.grad = it.grad; t.s1 = it.s1; t.s2 = it.s2; t.cc = (bf16*)it.compute_copy;
-    t.wd = it.decay ? (float)o.wd : 0.f;
-    t.inv_bc1 = (float)(1.0 / (1.0 - pow(o.beta1, (double)it.t)));
-    t.inv_bc2 = (float)(1.0 / (1.0 - pow(o.beta2, (double)it.t)));
-    t.first = it.t == 1 ? 1 : 0;
+    t = opt_tensor(o, it);
     t.block0 = (uint32_t)blocks;
     t.vec = vec;
-    t.grad_fused = it.grad_fused;
     blocks += more;
   }
   if (table.n == 0) return hipSuccess;

@@ -14,6 +14,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "packed_layout.h"
 
 namespace hift {
 namespace {
@@ -127,41 +128,11 @@ __device__ __forceinline__ void store_tile(const GemmP& p, f32x16 (&acc)[WM / 32
 // ------------------------------------------------------------------------------------------
 // Weights do not change inside a step, so the library keeps a second copy of every large weight
 // matrix in the order the MFMA wants it: block (nb, kk) of 1 KB holds, for lane l, the 8 values
-// B[nb*32 + pi(l%32)][kk*16 + (l/32)*8 ..+7] (pi_row below: why the rows of a block are permuted).  A wavefront loads its B fragments straight from
+// B[nb*32 + pi(l%32)][kk*16 + (l/32)*8 ..+7] (packed_layout.h: why the rows of a block are permuted, and in which order blocks lie).  A wavefront loads its B fragments straight from
 // HBM/L2 into registers with fully coalesced 1 KB loads, eight k-steps ahead; only the activation
 // operand goes through LDS.  Rows of the packed copy are padded to a multiple of 256, so no load
 // leaves the buffer.
 constexpr int PKF = 8;  // k-steps of B fragments in flight per wavefront
-
-// Position in the packed copy of the 32-row block s of B (half = blocks in half of B).
-__device__ __forceinline__ int64_t pk_block_pos(int64_t s, int order, int64_t half) {
-  if (order == PK_ORDER_HALVES) {
-    if (s >= 2 * half) return s;  // no such block: N is a multiple of 256 in this order
-    const int64_t h = s >= half ? 1 : 0, i = s - h * half;
-    return (i >> 2) * 8 + (i & 3) * 2 + h;
-  }
-  if (order == PK_ORDER_PAIR64) {
-    const int64_t q = s & 3;
-    return (s & ~int64_t(3)) | (q == 1 ? 2 : q == 2 ? 1 : q);
-  }
-  return s;
-}
-
-// Row r of a 32-row block of B sits where row pi(r) would (bits 2 and 3 of the index exchanged).  acc = mfma(B
-// fragment, A fragment, acc) leaves in lane l, element e the entry (A row l % 32, B row 8 (e / 4) + 4 (l / 32) + e % 4);
-// with the rows fed in this order, element e belongs to column 16 (e / 8) + 8 (l / 32) + e % 8 of the block: elements
-// 0..7 and 8..15 are eight consecutive columns each, 16 bytes of a bf16 output row, and the epilogues of the
-// packed-operand kernel write rows straight from the registers.
-__device__ __forceinline__ int pi_row(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
-
-// Product of eight bf16 pairs, each rounded once.
-__device__ __forceinline__ u32x4 scale8(u32x4 a, u32x4 b) {
-  bf16x8 x = __builtin_bit_cast(bf16x8, a);
-  const bf16x8 y = __builtin_bit_cast(bf16x8, b);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) x[e] = static_cast<__bf16>(static_cast<float>(x[e]) * static_cast<float>(y[e]));
-  return __builtin_bit_cast(u32x4, x);
-}
 
 // Eight consecutive values of the source as bf16: a 16-byte load, or, for an fp32 source (the master weights), two
 // loads and eight roundings to nearest even -- the bf16 model is by definition that rounding of the master.

@@ -181,6 +181,17 @@ struct OptItem {
 };
 constexpr int OPT_TABLE = 32;
 hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, hipStream_t st);
+// The same for matrices [rows, cols] that have fragment-order copies, which it rebuilds on the way (update_pack.hip): fwd as pack_b makes
+// it of the matrix with `order` and `gain`, bwd of its transpose in plain order; either may be null.  Only where update_packs() accepts
+// each.  A gain has to have its new values before.
+struct PackItem {
+  int64_t rows, cols;
+  void *fwd, *bwd;
+  const void* gain;
+  int order;
+};
+bool update_packs(const OptItem& it, const PackItem& pk);
+hipError_t optimizer_update_packed(const OptArgs& o, const OptItem* items, const PackItem* packs, int n_items, hipStream_t st);
 
 // Adafactor on one tensor (Shazeer and Stern 2018, Algorithm 4 without momentum, external step
 // size; constants: epsilon_1 1e-30, clipping threshold 1, decay exponent 0.8).

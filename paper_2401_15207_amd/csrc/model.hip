@@ -568,23 +568,24 @@ hipError_t cast_units(hift_model* M, int ulo, int uhi) {
   return hipSuccess;
 }
 
-// Rebuilds the fragment-order copies of the matrices of units [ulo, uhi) from the bf16 weights.
+// Rebuilds the fragment-order copies of a matrix from the bf16 weights.
+hipError_t repack(hift_model* M, const Tensor& t) {
+  // source: the row-major bf16 copy, or, where none is kept, the fp32 master (rounded on the way: the same values)
+  const bool f32src = M->dt == DT_BF16 && t.wc_off < 0;
+  const void* src = f32src ? (const void*)(M->master + t.off) : (const void*)M->W(t);
+  if (t.pk_fwd >= 0) {
+    hipError_t e = pack_b(src, t.cols, t.rows, t.cols, true, M->wpk + t.pk_fwd, M->cs, t.pk_order,
+                          t.pk_gain >= 0 ? M->W(M->lay.t[t.pk_gain]) : nullptr, f32src);
+    if (e != hipSuccess) return e;
+  }
+  if (t.pk_bwd >= 0) return pack_b(src, t.cols, t.cols, t.rows, false, M->wpk + t.pk_bwd, M->cs, PK_ORDER_PLAIN, nullptr, f32src);
+  return hipSuccess;
+}
 hipError_t repack_units(hift_model* M, int ulo, int uhi) {
   if (!M->wpk) return hipSuccess;
   for (int i = M->lay.unit_first[ulo]; i < M->lay.unit_first[uhi]; ++i) {
-    const Tensor& t = M->lay.t[i];
-    // source: the row-major bf16 copy, or, where none is kept, the fp32 master (rounded on the way: the same values)
-    const bool f32src = M->dt == DT_BF16 && t.wc_off < 0;
-    const void* src = f32src ? (const void*)(M->master + t.off) : (const void*)M->W(t);
-    if (t.pk_fwd >= 0) {
-      hipError_t e = pack_b(src, t.cols, t.rows, t.cols, true, M->wpk + t.pk_fwd, M->cs, t.pk_order,
-                            t.pk_gain >= 0 ? M->W(M->lay.t[t.pk_gain]) : nullptr, f32src);
-      if (e != hipSuccess) return e;
-    }
-    if (t.pk_bwd >= 0) {
-      hipError_t e = pack_b(src, t.cols, t.cols, t.rows, false, M->wpk + t.pk_bwd, M->cs, PK_ORDER_PLAIN, nullptr, f32src);
-      if (e != hipSuccess) return e;
-    }
+    hipError_t e = repack(M, M->lay.t[i]);
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -1892,41 +1893,58 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
     return moving ? in_slot(t.unit, M->n_move - M->n_state + j) + (t.off - M->lay.unit_off[t.unit])
                   : M->state_full + j * M->state_stride() + t.off;
   };
+  std::vector<const Tensor*> repack_after;  // matrices whose fragment-order copies the update does not write itself
   {
     double bytes_per = M->n_state == 2 ? 28.0 : (M->n_state == 1 ? 20.0 : 12.0);
     if (M->opt.kind == HIFT_ADAFACTOR) bytes_per = 24.0;  // the gradient is read four times (row, column, clipping, update)
-    if (M->dt == DT_BF16) bytes_per += 2.0;
-    Scope sc(M, CAT_OPT, bytes_per * cnt);
-    // Which product of AdamW's moments is fused (see opt_update) follows from the layout alone, so that it is the same wherever state
+    // Which product of AdamW's moments is fused (see opt_math) follows from the layout alone, so that it is the same wherever state
     // and master live: the old moment's for tensors that lie in whole 16-byte pieces in the model and in the group, in a model whose
     // parameters are a multiple of four, else the gradient's (what resident state has always had, so that its runs go on
     // bit for bit).
     auto grad_fused = [&](const Tensor& t) {
       return t.count() % 8 != 0 || t.off % 4 != 0 || (t.off - plo) % 4 != 0 || (M->n_state == 2 && M->lay.n_params % 4 != 0);
     };
-    std::vector<OptItem> items;
+    std::vector<OptItem> items, packed_items;
+    std::vector<PackItem> packs;
+    double bytes = bytes_per * cnt;
     for (int i = M->lay.unit_first[ulo]; i < M->lay.unit_first[uhi]; ++i) {
       const Tensor& t = M->lay.t[i];
-      const int64_t tg = M->unit_steps[t.unit];
+      const bool has_copies = M->wpk && (t.pk_fwd >= 0 || t.pk_bwd >= 0);
       void* cc = M->dt == DT_BF16 ? M->W(t) : nullptr;  // null also for a matrix kept only in fragment order
-      if (M->opt.kind == HIFT_ADAFACTOR) {
-        K_TRY(adafactor_update(M->opt.lr, M->opt.weight_decay, t.kind == HIFT_KIND_MATRIX, tg, t.rows, t.cols,
-                               master_of(t), M->grad + (t.off - plo), M->fac + t.fac_off, M->af_work, cc, M->cs));
+      if (cc) bytes += 2.0 * t.count();
+      const OptItem item{t.count(), t.kind == HIFT_KIND_MATRIX, M->unit_steps[t.unit], master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, grad_fused(t)};
+      const PackItem pack{t.rows, t.cols, t.pk_fwd >= 0 ? M->wpk + t.pk_fwd : nullptr, t.pk_bwd >= 0 ? M->wpk + t.pk_bwd : nullptr,
+                          t.pk_gain >= 0 ? M->W(M->lay.t[t.pk_gain]) : nullptr, t.pk_order};
+      if (has_copies && M->opt.kind != HIFT_ADAFACTOR && update_packs(item, pack)) {
+        bytes += 2.0 * t.count() * ((t.pk_fwd >= 0) + (t.pk_bwd >= 0));
+        packed_items.push_back(item);
+        packs.push_back(pack);
         continue;
       }
-      items.push_back(OptItem{t.count(), t.kind == HIFT_KIND_MATRIX, tg, master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, grad_fused(t)});
+      if (has_copies) repack_after.push_back(&t);
+      items.push_back(item);
     }
+    Scope sc(M, CAT_OPT, bytes);
+    if (M->opt.kind == HIFT_ADAFACTOR) {
+      for (int i = M->lay.unit_first[ulo]; i < M->lay.unit_first[uhi]; ++i) {
+        const Tensor& t = M->lay.t[i];
+        K_TRY(adafactor_update(M->opt.lr, M->opt.weight_decay, t.kind == HIFT_KIND_MATRIX, M->unit_steps[t.unit], t.rows, t.cols,
+                               master_of(t), M->grad + (t.off - plo), M->fac + t.fac_off, M->af_work, M->dt == DT_BF16 ? M->W(t) : nullptr, M->cs));
+      }
+      items.clear();
+    }
+    // gains first: those of a normalisation that is folded into a weight go into its copy with their new values
     if (!items.empty()) K_TRY(optimizer_update(oa, items.data(), (int)items.size(), M->cs));
+    if (!packs.empty()) K_TRY(optimizer_update_packed(oa, packed_items.data(), packs.data(), (int)packs.size(), M->cs));
   }
   if (moving) HIP_TRY(hipEventRecord(M->ev_opt[s], M->cs));
-  if (M->wpk) {  // the updated matrices in fragment order, for the next forward and dX
+  if (!repack_after.empty()) {  // in fragment order, for the next forward and dX
     double bytes = 0;
-    for (int i = M->lay.unit_first[ulo]; i < M->lay.unit_first[uhi]; ++i)
+    for (const Tensor* t : repack_after)
       // per copy: the source read once (fp32 master, or the bf16 copy where one is kept) and the copy written once
-      bytes += ((M->lay.t[i].wc_off < 0 ? 4.0 : 2.0) + 2.0) * M->lay.t[i].count() *
-               ((M->lay.t[i].pk_fwd >= 0) + (M->lay.t[i].pk_bwd >= 0));
+      bytes += ((t->wc_off < 0 ? 4.0 : 2.0) + 2.0) * t->count() * ((t->pk_fwd >= 0) + (t->pk_bwd >= 0));
     Scope sc(M, CAT_PACK, bytes);
-    K_TRY(repack_units(M, ulo, uhi));
+    for (const Tensor* t : repack_after) K_TRY(repack(M, *t));
   }
   HIP_TRY(hipEventRecord(M->ev_t1, M->cs));
   M->timed = true;
