@@ -43,6 +43,16 @@ constexpr int KTILE = 64;  // keys per LDS tile
 
 __device__ __forceinline__ int pi_row(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
+// Tiles in LDS: the 16-byte piece c of row r sits at piece position c ^ swizzle(r).  A fragment read takes one piece of sixteen rows: the
+// sixteen (PPR = 16: rows of 256 bytes) or eight (128 bytes, two rows side by side) values differ, so the pieces fall into different
+// banks.  A transposing read takes 64 bytes (four pieces) of rows r0 ..+3 and r0 + 8 ..+11: the upper bits of the value are the 64-byte group
+// of banks, and the four groups get two rows each.  (With r & 15 instead, rows r0 ..+3 fell into one group and every transposing read
+// took twice its time: half of all LDS cycles of the kernels for heads 128 wide were conflicts.)
+template <int PPR>
+__device__ __forceinline__ int swizzle(int r) {
+  return PPR == 16 ? (r & 3) << 2 | ((r >> 2) & 3) : (r >> 1) & 7;
+}
+
 // 16 bytes per lane straight from memory into LDS: M0 carries the LDS address of lane 0's piece, lane l
 // lands 16 l bytes further; reads past the buffer's end deliver zeros.
 __device__ __forceinline__ void dma_b128(u32x4 rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
@@ -99,10 +109,8 @@ __device__ __forceinline__ void store_rows_staged(const f32x16 (&acc)[NB], float
   }
 }
 
-// LDS tiles are [64 keys][HD] bf16 without padding; the 16-byte piece c of row r sits at piece position
-// c ^ swz(r), which spreads both the fragment reads (sixteen rows, one piece) and the transposing
-// reads over the banks.  A tile is filled by loads that write 1 KB of consecutive LDS bytes each, so
-// the swizzle is applied by choosing which piece of its row a lane fetches.
+// LDS tiles are [64 keys][HD] bf16 without padding, swizzled (see swizzle).  A tile is filled by loads that write 1 KB of consecutive
+// LDS bytes each, so the swizzle is applied by choosing which piece of its row a lane fetches.
 //
 // BWD = false: the forward kernel.  `scale` is log2(e) / sqrt(HD); writes ctx, the probabilities if prob is
 // given, and lse (if given): log2 of each row's sum of exponentials, m + log2(l) in the notation below.
@@ -126,7 +134,7 @@ __device__ __forceinline__ void attn_rows(unsigned char* lds /* [buffer][K | V] 
   constexpr int KS = HD / 16;       // k-steps of a score block
   constexpr int NB = HD / 32;       // 32-column blocks of the output
   constexpr int IPW = KTILE * PPR / 64 / NW;  // load instructions per wavefront and tile
-  auto swz = [](int r) { return PPR == 16 ? (r & 15) : ((r >> 1) & 7); };
+  auto swz = [](int r) { return swizzle<PPR>(r); };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -568,10 +576,10 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) attn_k(const bf16* _
 // the forward kernel), from them P^T = exp2(S^T c - lse[query]) and dS^T = scale P^T (dP^T - D[query]); in
 // that order of rows the 16 values a lane holds per 32 queries are, as they lie in registers, the operand
 // fragments of the two sums, whose other operands (dO^T, Q^T) come from the same tiles by transposing LDS
-// reads.  Nothing of size S x S is read or written.  One workgroup per compute unit (the accumulators of four
-// products and 64 K / V registers) for heads 128 wide; two for heads 64 wide, whose 302 registers fit 256 without a spill: a
-// wavefront alone waits for its own chain of reads, products and exponentials, and the backward of 16 x 16 heads at 512 tokens
-// takes 90 us instead of 123 (1024 tokens: 303 instead of 423).  Workgroups are issued longest first under the causal mask.
+// reads.  Nothing of size S x S is read or written.  Heads 64 wide: two workgroups per compute unit (302 registers fit 256 without a
+// spill): a wavefront alone waits for its own chain of reads, products and exponentials, and the backward of 16 x 16 heads at 512 tokens
+// takes 90 us instead of 123 (1024 tokens: 303 instead of 423).  (Heads 128 wide: attn_bwd_kv8_k.)  Workgroups are issued longest first
+// under the causal mask.
 // lse: log2 of each query's sum of exponentials (forward kernel); dsum: D = dO . O per query (query-major kernel).
 // cos_sin, if given, un-rotates dK (k was rotated after its projection).
 constexpr int KV_QT = 64;  // queries per tile
@@ -588,7 +596,7 @@ __device__ __forceinline__ void attn_bwd_keys(unsigned char* lds, const int bloc
   constexpr int TQ = QT * ROWB;     // bytes of the Q (or dO) tile
   constexpr int IQ = QT * PPR / 64 / 4;  // load instructions per wavefront, tile and operand
   constexpr int BUF = KV_LDS<HD> / 2;
-  auto swq = [](int r) { return PPR == 16 ? (r & 15) : ((r >> 1) & 7); };
+  auto swq = [](int r) { return swizzle<PPR>(r); };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -794,21 +802,235 @@ __device__ __forceinline__ void attn_bwd_keys(unsigned char* lds, const int bloc
   store_rows_staged<NB>(vacc, 1.0f, lds + (2 * wave + 1) * OSTG, dk0 + d, ld, S - j0, lane);
 }
 
-template <int HD, bool CAUSAL>
-__global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) attn_bwd_kv_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
+template <bool CAUSAL>
+__global__ void __launch_bounds__(256, 2) attn_bwd_kv_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
                                                          const float* lse, const float* dsum, const bf16* __restrict__ dctx, int64_t ldc,
                                                          bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[KV_LDS<HD>];
-  attn_bwd_keys<HD, CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[KV_LDS<64>];
+  attn_bwd_keys<64, CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
+}
+
+// The key-major half for heads 128 wide, on eight wavefronts.  One wavefront per 32 keys would need 410 registers, so one a SIMD, which
+// then does nothing while it waits for its own reads, products and exponentials in turn (3.2 us a tile, of which the products are 1).
+// Here two wavefronts share 32 keys: each forms S^T and dP^T, P and dS for one of the tile's two blocks of 32 queries, they exchange the
+// fragments through LDS (4 KB each), and each adds both blocks into half of dV's and dK's columns.  No product is made twice, and every
+// sum runs over the queries in the same order as on one wavefront.  A wavefront's columns are the 32-column blocks `half` and half + 2, so that
+// the pairs that the rotary embedding turns stay in one wavefront.
+// The workgroup's K and V rows come through LDS (whole rows, into the second tile buffer and the exchange region, which are free then):
+// fetched lane by lane they took 2.8 us, each instruction touching 32 lines.
+// Both halves of the backward, 4 x 32 heads, 512 tokens: causal 82 us on four wavefronts and with conflicts in LDS (see swizzle), 69 now;
+// all keys 103 and 88; 40 heads, 1016 tokens, all keys 164 and 135.
+constexpr int KV8_XCH = 8 * 4096;
+template <bool CAUSAL>
+__global__ void __launch_bounds__(512) attn_bwd_kv8_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
+                                                      const float* lse, const float* dsum, const bf16* __restrict__ dctx, int64_t ldc,
+                                                      bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
+  constexpr int HD = 128, KB = 128, QT = KV_QT, ROWB = HD * 2, PPR = HD / 8, KS = HD / 16;
+  constexpr int TQ = QT * ROWB, BUF = KV_LDS<HD> / 2;
+  constexpr int IQ = QT * PPR / 64 / 8, IK = KB * PPR / 64 / 8;  // load instructions per wavefront: tile and operand, K or V
+  static_assert(KB * ROWB <= BUF && KB * ROWB <= KV8_XCH, "K and V rows on their way into registers");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * BUF + KV8_XCH];
+  auto swq = [](int r) { return swizzle<PPR>(r); };
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = wave & 1;  // the query block this wavefront takes, and which columns of dK and dV
+  const int fr = lane & 31, fh = lane >> 5;
+  const int kb = (int)blockIdx.x / BH, bh = (int)blockIdx.x % BH;  // longest first under the causal mask
+  const int b = bh / H, h = bh % H;
+  const int64_t d = (int64_t)H * HD;
+  const bf16* q = qkv + (int64_t)b * S * ld + (int64_t)h * HD;
+  const bf16* dO = dctx + (int64_t)b * S * ldc + (int64_t)h * HD;
+  const int j0 = kb * KB + (wave >> 1) * 32;  // the pair's first key
+  const int row = j0 + fr;
+  const bool row_ok = row < S;
+  const float scale_log2e = scale * 1.4426950408889634f;
+
+  const uint64_t qa = reinterpret_cast<uint64_t>(q), oa = reinterpret_cast<uint64_t>(dO);
+  const uint32_t recq = (uint32_t)((((int64_t)S - 1) * ld + HD) * 2), reco = (uint32_t)((((int64_t)S - 1) * ldc + HD) * 2);
+  const u32x4 rsQ = {(uint32_t)qa, (uint32_t)(qa >> 32) & 0xFFFFu, recq, 0x00020000u};
+  const u32x4 rsO = {(uint32_t)oa, (uint32_t)(oa >> 32) & 0xFFFFu, reco, 0x00020000u};
+  const uint64_t la = reinterpret_cast<uint64_t>(lse + (int64_t)bh * S), da = reinterpret_cast<uint64_t>(dsum + (int64_t)bh * S);
+  const u32x4 rsL = {(uint32_t)la, (uint32_t)(la >> 32) & 0xFFFFu, (uint32_t)S * 4u, 0x00020000u};
+  const u32x4 rsD = {(uint32_t)da, (uint32_t)(da >> 32) & 0xFFFFu, (uint32_t)S * 4u, 0x00020000u};
+  const uint32_t vos = lane < 16 ? (uint32_t)lane * 16u : 0x80000000u;
+  uint32_t voq[IQ], voo[IQ];
+#pragma unroll
+  for (int jj = 0; jj < IQ; ++jj) {
+    const int pc = (wave * IQ + jj) * 64 + lane, r = pc / PPR, c = (pc % PPR) ^ swq(r);
+    voq[jj] = (uint32_t)((r * ld + c * 8) * 2);
+    voo[jj] = (uint32_t)((r * ldc + c * 8) * 2);
+  }
+  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(lds);
+  auto request = [&](int it) __attribute__((always_inline)) {
+    const uint32_t sq = (uint32_t)((int64_t)it * QT * ld * 2), so = (uint32_t)((int64_t)it * QT * ldc * 2);
+    const uint32_t buf = lds0 + (uint32_t)(it & 1) * BUF, dst = buf + (uint32_t)wave * (IQ * 1024);
+#pragma unroll
+    for (int jj = 0; jj < IQ; ++jj) dma_b128(rsQ, dst + jj * 1024, voq[jj], sq);
+#pragma unroll
+    for (int jj = 0; jj < IQ; ++jj) dma_b128(rsO, dst + TQ + jj * 1024, voo[jj], so);
+    if (wave == 0) dma_b128(rsL, buf + 2 * TQ, vos, (uint32_t)(it * QT * 4));
+    if (wave == 1) dma_b128(rsD, buf + 2 * TQ + 1024, vos, (uint32_t)(it * QT * 4));
+  };
+
+  const int all_tiles = (S + QT - 1) / QT;
+  const int it0 = CAUSAL ? kb * KB / QT : 0;  // even: the first tile's buffer is the first one
+  bf16x8 kf[KS], vf[KS];                      // this lane's key row: fragments of K and V
+  {
+    const uint64_t ka = reinterpret_cast<uint64_t>(q + d), va = reinterpret_cast<uint64_t>(q + 2 * d);
+    const u32x4 rsK = {(uint32_t)ka, (uint32_t)(ka >> 32) & 0xFFFFu, recq, 0x00020000u};
+    const u32x4 rsV = {(uint32_t)va, (uint32_t)(va >> 32) & 0xFFFFu, recq, 0x00020000u};
+#pragma unroll
+    for (int jj = 0; jj < IK; ++jj) {
+      const int pc = (wave * IK + jj) * 64 + lane, r = pc / PPR, c = (pc % PPR) ^ swq(r);
+      const uint32_t vo = kb * KB + r < S ? (uint32_t)(((int64_t)(kb * KB + r) * ld + c * 8) * 2) : recq;  // rows past the end: zeros
+      dma_b128(rsK, lds0 + BUF + (uint32_t)(wave * IK + jj) * 1024, vo, 0);
+      dma_b128(rsV, lds0 + 2 * BUF + (uint32_t)(wave * IK + jj) * 1024, vo, 0);
+    }
+    request(it0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const int r = (wave >> 1) * 32 + fr;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int at = r * ROWB + (((2 * ks + fh) ^ swq(r)) * 16);
+      kf[ks] = *reinterpret_cast<const bf16x8*>(lds + BUF + at);
+      vf[ks] = *reinterpret_cast<const bf16x8*>(lds + 2 * BUF + at);
+    }
+  }
+
+  // fragments of the block's rows in pi order, and transposing reads, as on four wavefronts
+  int faddr[KS];
+  {
+    const int r = half * 32 + pi_row(fr);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) faddr[ks] = r * ROWB + (((2 * ks + fh) ^ swq(r)) * 16);
+  }
+  const int sl = lane & 15;
+  int xaddr[2][2];
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh) {
+    const int krow = 8 * fh + (sl >> 2) + 4 * hh;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = (half + 2 * j) * 32 + 16 * ((lane >> 4) & 1) + 4 * (sl & 3);
+      xaddr[j][hh] = krow * ROWB + (((col >> 3) ^ swq(krow)) * 16) + (col & 7) * 2;
+    }
+  }
+  auto tr_frag = [&](const unsigned char* base, int a0, int a1) __attribute__((always_inline)) {
+    const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16 __attribute__((address_space(3)))*)(base + a0));
+    const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((v4i16 __attribute__((address_space(3)))*)(base + a1));
+    typedef short v8i16 __attribute__((ext_vector_type(8)));
+    const v8i16 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, both);
+  };
+  unsigned char* const mine = lds + 2 * BUF + wave * 4096 + lane * 16;
+  const unsigned char* const theirs = lds + 2 * BUF + (wave ^ 1) * 4096 + lane * 16;
+
+  f32x16 vacc[2], kacc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) vacc[j][e] = kacc[j][e] = 0.f;
+
+  for (int it = it0; it < all_tiles; ++it) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();  // tile `it` has landed for everyone; nobody reads the other buffer or the exchange region any more
+    if (it + 1 < all_tiles) request(it + 1);
+    const bool before = CAUSAL && it * QT + QT - 1 < j0;  // every query of the tile precedes the pair's keys
+    const unsigned char* Qb = lds + (it & 1) * BUF;
+    const unsigned char* Ob = Qb + TQ;
+    bf16x8 pf[2], sf[2];
+    if (!before) {
+      f32x16 st, dpt;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) st[e] = dpt[e] = 0.f;
+      bf16x8 xq[2], xo[2];
+      xq[0] = *reinterpret_cast<const bf16x8*>(Qb + faddr[0]);
+      xo[0] = *reinterpret_cast<const bf16x8*>(Ob + faddr[0]);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + 1 < KS) {
+          xq[(ks + 1) & 1] = *reinterpret_cast<const bf16x8*>(Qb + faddr[ks + 1]);
+          xo[(ks + 1) & 1] = *reinterpret_cast<const bf16x8*>(Ob + faddr[ks + 1]);
+        }
+        st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xq[ks & 1], kf[ks], st, 0, 0, 0);
+        dpt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xo[ks & 1], vf[ks], dpt, 0, 0, 0);
+      }
+      const int qb0 = it * QT + half * 32;
+      auto probabilities = [&](auto MASKED_) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int off = (half * 32 + 16 * (c >> 1) + 8 * fh + 4 * (c & 1)) * 4;
+          const f32x4 lq = *reinterpret_cast<const f32x4*>(Qb + 2 * TQ + off), dq4 = *reinterpret_cast<const f32x4*>(Qb + 2 * TQ + 1024 + off);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int e = 4 * c + k, qi = qb0 + 16 * (e / 8) + 8 * fh + e % 8;
+            float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], scale_log2e, -lq[k]));
+            if (decltype(MASKED_)::value) pr = (qi < S) & (!CAUSAL | (qi >= row)) ? pr : 0.f;
+            pf[e / 8][e % 8] = static_cast<__bf16>(pr);
+            sf[e / 8][e % 8] = static_cast<__bf16>(scale * pr * (dpt[e] - dq4[k]));
+          }
+        }
+      };
+      // no query of the block is masked for any key of the pair: all inside the sequence and, under the causal mask, at or after its last key
+      if (qb0 + 32 <= S && (!CAUSAL || qb0 >= j0 + 31)) probabilities(std::false_type{});
+      else probabilities(std::true_type{});
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        *reinterpret_cast<bf16x8*>(mine + t * 1024) = pf[t];
+        *reinterpret_cast<bf16x8*>(mine + (2 + t) * 1024) = sf[t];
+      }
+    }
+    __syncthreads();  // the fragments are exchanged
+    if (before) continue;
+    // four k-steps of 16 queries, both blocks; the next one's operands are read under the products
+    bf16x8 xo[2][2], xq[2][2];
+    auto read = [&](int k) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        xo[k & 1][j] = tr_frag(Ob + k * 16 * ROWB, xaddr[j][0], xaddr[j][1]);
+        xq[k & 1][j] = tr_frag(Qb + k * 16 * ROWB, xaddr[j][0], xaddr[j][1]);
+      }
+    };
+    bf16x8 pk[2], sk[2];
+    auto read_p = [&](int k) __attribute__((always_inline)) {
+      const unsigned char* from = lds + 2 * BUF + ((wave & ~1) + (k >> 1)) * 4096 + lane * 16 + (k & 1) * 1024;
+      pk[k & 1] = *reinterpret_cast<const bf16x8*>(from);
+      sk[k & 1] = *reinterpret_cast<const bf16x8*>(from + 2048);
+    };
+    read(0);
+    read_p(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k < 3) { read(k + 1); read_p(k + 1); }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        vacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xo[k & 1][j], pk[k & 1], vacc[j], 0, 0, 0);
+        kacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xq[k & 1][j], sk[k & 1], kacc[j], 0, 0, 0);
+      }
+    }
+  }
+  if (row_ok && cos_sin) unrotate<2>(kacc, cos_sin + (int64_t)row * (HD / 2) + half * 32, fh);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();  // every wavefront is done with the tiles: dK and dV leave through their buffers
+  constexpr int OSTG = 32 * (64 + 16);
+  static_assert(8 * 4 * OSTG <= 2 * BUF + KV8_XCH, "staging fits");
+  bf16* dk0 = dqkv + (int64_t)b * S * ld + d + (int64_t)h * HD + (int64_t)j0 * ld;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const f32x16 ko[1] = {kacc[j]}, vo[1] = {vacc[j]};
+    store_rows_staged<1>(ko, 1.0f, lds + (wave * 4 + 2 * j) * OSTG, dk0 + (half + 2 * j) * 32, ld, S - j0, lane);
+    store_rows_staged<1>(vo, 1.0f, lds + (wave * 4 + 2 * j + 1) * OSTG, dk0 + d + (half + 2 * j) * 32, ld, S - j0, lane);
+  }
 }
 
 // Both halves of the backward in one launch where a sequence of 64-wide heads is one block of rows and one of keys (up to
 // 128): the workgroup of a (batch, head) takes its 128 query rows, then its 128 keys; what it left in dsum it reads itself.
 // A call of this size is a few microseconds per launch and the next launch waits for the last workgroup of the one before:
 // 128 tokens, 256 heads in all 19.7 us in two launches, 13.5 in one; 16 heads 13.1 and 11.0; 2048 heads 100 and 78 (two
-// workgroups a compute unit, at the price of ten registers spilled between the halves; with one: 111).  Heads 128 wide need
-// 416 registers for the key half, so one workgroup a compute unit, and lose by it from 512 heads on (19.2 against 21.8 us at
-// 16 tokens), while up to 256 they win a tenth at most: they keep two launches.
+// workgroups a compute unit, at the price of ten registers spilled between the halves; with one: 111).  Heads 128 wide have a
+// key half of eight wavefronts and a query half of four, and keep two launches.
 template <bool CAUSAL>
 __global__ void __launch_bounds__(256, 2) attn_bwd_one_k(const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH, float scale,
                                                          bf16* __restrict__ ctx, int64_t ldc, const bf16* __restrict__ dctx, float* lse,
@@ -902,11 +1124,11 @@ hipError_t attention_bwd_fused(int B, int H, int S, int hd, bool causal, const v
     if (causal) attn_bwd_one_k<true><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, o, ldc, dO, l, dsum, dq, cs);
     else attn_bwd_one_k<false><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, o, ldc, dO, l, dsum, dq, cs);
   } else if (hd == 128) {
-    if (causal) attn_bwd_kv_k<128, true><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
-    else attn_bwd_kv_k<128, false><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
+    if (causal) attn_bwd_kv8_k<true><<<grid, 512, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
+    else attn_bwd_kv8_k<false><<<grid, 512, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
   } else if (hd == 64) {
-    if (causal) attn_bwd_kv_k<64, true><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
-    else attn_bwd_kv_k<64, false><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
+    if (causal) attn_bwd_kv_k<true><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
+    else attn_bwd_kv_k<false><<<grid, 256, 0, st>>>(x, ld, S, H, B * H, sc, lse, dsum, dO, ldc, dq, cs);
   } else {
     return hipErrorInvalidValue;
   }

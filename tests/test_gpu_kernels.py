@@ -887,6 +887,13 @@ def test_fused_attention_backward_of_narrow_heads(S, causal, rope):
     test_fused_attention_backward(2, 3, S, 64, causal, rope)
 
 
+@pytest.mark.parametrize("S", [8, 32, 40, 64, 72, 104, 128, 136, 192, 264])
+@pytest.mark.parametrize("causal,rope", [(0, 0), (1, 0), (1, 1)])
+def test_fused_attention_backward_of_wide_heads(S, causal, rope):
+    """Heads 128 wide, two wavefronts to 32 keys: at the edges of a block of 32 queries, a tile of 64 and 128 keys."""
+    test_fused_attention_backward(2, 3, S, 128, causal, rope)
+
+
 @pytest.mark.parametrize("S", [8, 104, 128])
 @pytest.mark.parametrize("causal", [0, 1])
 def test_fused_attention_backward_of_narrow_heads_on_a_full_chip(S, causal):
