@@ -16,6 +16,7 @@
 #include "../../include/hift.h"
 #include "copy_parts.h"
 #include "kernels.h"
+#include "state_slots.h"
 
 using namespace hift;
 
@@ -265,7 +266,13 @@ struct PinnedSpace {
 
 }  // namespace
 
-constexpr int NSLOT = 3;
+constexpr int NSLOT = StateSlots::N;
+
+// What orders the copies of one group's state: its arrival, its update, its write-back.
+struct GroupEvents {
+  hipEvent_t h2d = nullptr, opt = nullptr, d2h = nullptr;
+  bool d2h_pending = false;  // a write-back that no later fetch has been ordered behind
+};
 
 struct hift_model {
   hift_config cfg;
@@ -292,10 +299,11 @@ struct hift_model {
   size_t af_work_floats = 0;
   float* grad = nullptr;
   float* state_full = nullptr;  // [n_state] arrays of n_params values, state_stride apart, when state stays in HBM
-  // State of the active group when the rest lives on the host, laid out as in the pinned arena.  Three slots:
-  // while one is updated, the next group's state arrives in the second and the previous group's
-  // drains from the third, so the two directions of the host link run at the same time.
+  // State of the active group and its neighbours in the schedule when the rest lives on the host, laid out as in the pinned
+  // arena.  Three slots: while the groups of one are updated, those of the next arrive and those of the one before drain, so
+  // the two directions of the host link run at the same time.
   float* slot[NSLOT] = {nullptr, nullptr, nullptr};
+  StateSlots held;
   PinnedSpace pin;
   float* cos_sin = nullptr;
   // low-rank adapters on the query and value projections (cfg.lora_rank > 0).  Per layer, r = rank: A_q | A_v stacked
@@ -316,11 +324,8 @@ struct hift_model {
        *dcls = nullptr;
   // streams and events
   hipStream_t cs, hs, ds;
-  hipEvent_t ev_h2d[NSLOT], ev_opt[NSLOT], ev_d2h[NSLOT], ev_t0, ev_t1, ev_w0, ev_w1;
-  bool d2h_pending[NSLOT] = {false, false, false};
-  int d2h_group[NSLOT] = {-1, -1, -1};  // group whose state the pending write-back of a slot carries
-  int slot_group[NSLOT] = {-1, -1, -1};  // group whose state a slot holds (arrived or in flight)
-  int cur_slot = 0;
+  hipEvent_t ev_t0, ev_t1, ev_w0, ev_w1;
+  std::vector<GroupEvents> gev;  // by group (there are at most as many as units)
   // schedule
   int m = 0, k = 0;
   std::vector<int32_t> order;
@@ -341,6 +346,8 @@ struct hift_model {
   int64_t wc_count = 0;  // elements of the bf16 copy
   // n_params rounded up: the second state array starts 16-byte aligned whatever the number of parameters
   int64_t state_stride() const { return (lay.n_params + 63) & ~(int64_t)63; }
+  // state held in a slot is mirrored on the host (every step writes it back), so it can be forgotten once the streams are idle
+  void forget_slots() { held.reset((int)gev.size(), (int64_t)n_move * grad_cap); }
   const Tensor& T_(const std::string& n) const { return lay.t[lay.find(n)]; }
   // the tensor as the forward pass reads it (null for a matrix that lives only in its fragment-order copies)
   void* W(const Tensor& t) const {
@@ -1376,21 +1383,29 @@ hift_status host_write(const hift_model* M, int j, int64_t off, int64_t cnt, con
   });
 }
 
-// Queue the host-to-device copy of a group's state into a slot (Algorithm 1 step i).
-hift_status fetch_state(hift_model* M, int gid, int s) {
+// Where the state of a group that a slot holds starts.
+float* held_state(const hift_model* M, int gid) { return M->slot[M->held.slot(gid)] + M->held.at(gid); }
+
+// Queue the host-to-device copy of a group's state into a slot (Algorithm 1 step i).  `spare`: a group whose state is not to be
+// given up for it (-1: none).  *done is false, and nothing happened, if no slot can take it now.
+hift_status fetch_state(hift_model* M, int gid, int spare, bool* done) {
   int ulo, uhi;
   int64_t plo, cnt;
   group_range(M, gid, &ulo, &uhi, &plo, &cnt);
-  // order the copy after the write-backs it depends on, and only those: the one that last
-  // drained this slot, and one that carries this group's own state to the host
-  for (int q = 0; q < NSLOT; ++q)
-    if (M->d2h_pending[q] && (q == s || M->d2h_group[q] == gid)) HIP_TRY(hipStreamWaitEvent(M->hs, M->ev_d2h[q], 0));
+  std::vector<int> emptied;
+  *done = M->held.put(gid, cnt * M->n_move, spare, emptied);
+  if (!*done) return HIFT_OK;
+  // order the copy after the write-backs it depends on, and only those: of what the slot held, and of this group's own state
+  emptied.push_back(gid);
+  for (int g : emptied) {
+    if (M->gev[g].d2h_pending) HIP_TRY(hipStreamWaitEvent(M->hs, M->gev[g].d2h, 0));
+    M->gev[g].d2h_pending = false;
+  }
   ST_TRY(M->pin.pieces((size_t)plo * M->n_move * 4, (size_t)cnt * M->n_move * 4, [&](unsigned char* h, size_t n, size_t at) {
-    return state_copy(M, reinterpret_cast<unsigned char*>(M->slot[s]) + at, h, n, true);
+    return state_copy(M, reinterpret_cast<unsigned char*>(held_state(M, gid)) + at, h, n, true);
   }));
   M->h2d_bytes += (uint64_t)cnt * M->n_move * 4;
-  HIP_TRY(hipEventRecord(M->ev_h2d[s], M->hs));
-  M->slot_group[s] = gid;
+  HIP_TRY(hipEventRecord(M->gev[gid].h2d, M->hs));
   return HIFT_OK;
 }
 
@@ -1408,7 +1423,7 @@ hift_status load_forward_copy(hift_model* M, int64_t off, int64_t cnt) {
     HIP_TRY(cast_f32_to(DT_BF16, n, M->slot[0], (unsigned char*)M->wc + (off + done) * 2, M->cs));
     HIP_TRY(hipStreamSynchronize(M->cs));
   }
-  for (int& g : M->slot_group) g = -1;  // slot 0 no longer holds a group's state
+  M->forget_slots();  // slot 0 no longer holds a group's state
   return HIFT_OK;
 }
 
@@ -1416,7 +1431,7 @@ hift_status sync_all(hift_model* M) {
   HIP_TRY(hipStreamSynchronize(M->cs));
   HIP_TRY(hipStreamSynchronize(M->hs));
   HIP_TRY(hipStreamSynchronize(M->ds));
-  for (bool& b : M->d2h_pending) b = false;
+  for (GroupEvents& g : M->gev) g.d2h_pending = false;
   return HIFT_OK;
 }
 
@@ -1576,8 +1591,10 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
     }                                                                                                 \
   } while (0)
   std::vector<hipEvent_t*> evs;
-  for (int q = 0; q < NSLOT; ++q) { evs.push_back(&M->ev_h2d[q]); evs.push_back(&M->ev_opt[q]); evs.push_back(&M->ev_d2h[q]); }
-  for (auto e : evs) *e = nullptr;
+  M->gev.resize(M->lay.n_units);
+  M->forget_slots();
+  if (M->on_host && M->n_move > 0)
+    for (GroupEvents& g : M->gev) { evs.push_back(&g.h2d); evs.push_back(&g.opt); evs.push_back(&g.d2h); }
   M->ev_t0 = M->ev_t1 = M->ev_w0 = M->ev_w1 = nullptr;
   for (auto e : evs) CR_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
   CR_TRY(hipEventCreate(&M->ev_t0));
@@ -1634,8 +1651,8 @@ void hift_model_destroy(hift_model* M) {
   if (M->cs) (void)hipStreamSynchronize(M->cs);
   if (M->hs) (void)hipStreamSynchronize(M->hs);
   if (M->ds) (void)hipStreamSynchronize(M->ds);
-  hipEvent_t evs[] = {M->ev_h2d[0], M->ev_h2d[1], M->ev_h2d[2], M->ev_opt[0], M->ev_opt[1], M->ev_opt[2], M->ev_d2h[0], M->ev_d2h[1], M->ev_d2h[2],
-                      M->ev_t0, M->ev_t1, M->ev_w0, M->ev_w1};
+  std::vector<hipEvent_t> evs = {M->ev_t0, M->ev_t1, M->ev_w0, M->ev_w1};
+  for (const GroupEvents& g : M->gev) evs.insert(evs.end(), {g.h2d, g.opt, g.d2h});
   for (auto e : evs)
     if (e) (void)hipEventDestroy(e);
   for (auto& r : M->prof.pool) {
@@ -1653,8 +1670,7 @@ hift_status hift_set_group_schedule(hift_model* M, hift_strategy s, int32_t m, u
                                       (long long)need, (long long)M->grad_cap);
   hift_status st = sync_all(M);
   if (st != HIFT_OK) return st;
-  // state held in a slot is already mirrored on the host (every step writes it back)
-  for (int& g : M->slot_group) g = -1;
+  M->forget_slots();
   M->m = m;
   M->k = group_count(M->lay.n_units, m);
   M->order.resize(M->k);
@@ -1819,7 +1835,7 @@ hift_status hift_checkpoint_load(hift_model* M, const void* host_buffer, size_t 
     else HIP_TRY(hipMemcpy(M->state_full + (size_t)j * M->state_stride(), p, np4, hipMemcpyHostToDevice));
   }
   if (M->n_fac) HIP_TRY(hipMemcpy(M->fac, p, (size_t)M->n_fac * 4, hipMemcpyHostToDevice));
-  for (int& g : M->slot_group) g = -1;  // whatever the slots hold is stale
+  M->forget_slots();  // whatever the slots hold is stale
   return HIFT_OK;
 }
 
@@ -1847,24 +1863,32 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
   HIP_TRY(hipEventRecord(M->ev_t0, M->cs));
 
   // ---- state movement, queued ahead of the compute (Algorithm 1 step i, issued early) ----
-  int s = 0;
   if (moving) {
-    s = -1;
-    for (int q = 0; q < NSLOT; ++q)
-      if (M->slot_group[q] == gid) s = q;
-    if (s < 0) {
-      s = M->cur_slot;
-      ST_TRY(fetch_state(M, gid, s));
+    bool done = true;
+    if (!M->held.holds(gid)) {
+      M->held.let_go();  // what was fetched ahead for another order gives way
+      ST_TRY(fetch_state(M, gid, -1, &done));
     }
-    M->cur_slot = s;
-    // prefetch the state of the group the schedule visits next into the slot after this one (the
-    // one after that is still draining the previous group's state); the write-back that last used
-    // the slot is ordered before the copy inside fetch_state
-    const int next = M->order[(M->t + 1) % M->k];
+    M->held.keep(gid);
+    // Fetch the state of the groups that the schedule visits next, as far ahead as the slots have room.  The next one always gets
+    // its place; further ones leave the state of the group updated last where it is (a caller may step it again), and never are
+    // groups whose own update is so recent that their write-back would hold up the copies behind it.
     const bool on_schedule = M->order[M->t % M->k] == gid;
-    bool resident = false;
-    for (int q = 0; q < NSLOT; ++q) resident = resident || M->slot_group[q] == next;
-    if (on_schedule && !resident) ST_TRY(fetch_state(M, next, (s + 1) % NSLOT));
+    const int ahead = M->k > NSLOT + 1 ? M->k - NSLOT : 1;
+    for (int j = 1; on_schedule && done && j <= ahead; ++j) {
+      const int next = M->order[(M->t + j) % M->k];
+      if (M->held.kept(next)) continue;
+      if (j == 1 && M->held.holds(next) && (M->k <= NSLOT || M->held.recent(next))) {
+        M->held.keep(next);
+        continue;
+      }
+      ST_TRY(fetch_state(M, next, j == 1 ? -1 : M->held.last(), &done));
+      if (!done && j == 1) {
+        M->held.let_go();
+        M->held.keep(gid);
+        ST_TRY(fetch_state(M, next, -1, &done));
+      }
+    }
   }
 
   ST_TRY(forward(M, bt, ulo));
@@ -1873,17 +1897,17 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
   // ---- optimizer on the group (its update number drives AdamW's bias correction) ----
   HIP_TRY(hipEventRecord(M->ev_w0, M->cs));
   if (moving) {
-    HIP_TRY(hipStreamWaitEvent(M->cs, M->ev_h2d[s], 0));
-    // a slot reused without a new fetch may still be draining to the host from its last update (a fetch was
+    HIP_TRY(hipStreamWaitEvent(M->cs, M->gev[gid].h2d, 0));
+    // state that a slot held without a new fetch may still be draining to the host from its last update (a fetch was
     // ordered behind that)
-    if (M->d2h_pending[s] && M->d2h_group[s] == gid) HIP_TRY(hipStreamWaitEvent(M->cs, M->ev_d2h[s], 0));
+    if (M->gev[gid].d2h_pending) HIP_TRY(hipStreamWaitEvent(M->cs, M->gev[gid].d2h, 0));
   }
   HIP_TRY(hipEventRecord(M->ev_w1, M->cs));
   for (int u = ulo; u < uhi; ++u) M->unit_steps[u] += 1;
   OptArgs oa{M->opt.kind, M->opt.lr, M->opt.beta1, M->opt.beta2, M->opt.eps, M->opt.weight_decay, M->opt.momentum};
   // array j of what travels with unit u, in the slot (laid out as in the pinned arena)
   auto in_slot = [&](int u, int j) {
-    return M->slot[s] + (M->lay.unit_off[u] - plo) * M->n_move + j * M->lay.unit_cnt[u];
+    return held_state(M, gid) + (M->lay.unit_off[u] - plo) * M->n_move + j * M->lay.unit_cnt[u];
   };
   auto master_of = [&](const Tensor& t) {
     return M->master_host ? in_slot(t.unit, 0) + (t.off - M->lay.unit_off[t.unit]) : M->master + t.off;
@@ -1937,7 +1961,7 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
     if (!items.empty()) K_TRY(optimizer_update(oa, items.data(), (int)items.size(), M->cs));
     if (!packs.empty()) K_TRY(optimizer_update_packed(oa, packed_items.data(), packs.data(), (int)packs.size(), M->cs));
   }
-  if (moving) HIP_TRY(hipEventRecord(M->ev_opt[s], M->cs));
+  if (moving) HIP_TRY(hipEventRecord(M->gev[gid].opt, M->cs));
   if (!repack_after.empty()) {  // in fragment order, for the next forward and dX
     double bytes = 0;
     for (const Tensor* t : repack_after)
@@ -1951,15 +1975,14 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
 
   // ---- state back to the host (Algorithm 1 step k) ----
   if (moving) {
-    HIP_TRY(hipStreamWaitEvent(M->ds, M->ev_opt[s], 0));
+    HIP_TRY(hipStreamWaitEvent(M->ds, M->gev[gid].opt, 0));
     ST_TRY(M->pin.pieces((size_t)plo * M->n_move * 4, (size_t)cnt * M->n_move * 4, [&](unsigned char* h, size_t n, size_t at) {
-      return state_copy(M, h, reinterpret_cast<const unsigned char*>(M->slot[s]) + at, n, false);
+      return state_copy(M, h, reinterpret_cast<const unsigned char*>(held_state(M, gid)) + at, n, false);
     }));
     M->d2h_bytes += (uint64_t)cnt * M->n_move * 4;
-    HIP_TRY(hipEventRecord(M->ev_d2h[s], M->ds));
-    M->d2h_pending[s] = true;
-    M->d2h_group[s] = gid;
-    M->cur_slot = (s + 1) % NSLOT;
+    HIP_TRY(hipEventRecord(M->gev[gid].d2h, M->ds));
+    M->gev[gid].d2h_pending = true;
+    M->held.updated(gid);
   }
   M->t += 1;
   if (loss_out) {

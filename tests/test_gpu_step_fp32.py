@@ -315,6 +315,30 @@ def test_where_state_lives_changes_no_bit(shape, bf16, m, optk):
             assert np.array_equal(a.read_state(0, a.n_units, j), b.read_state(0, b.n_units, j)), j
 
 
+@pytest.mark.parametrize("bf16,master_on_host", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("m,strategy", [(1, "top2down"), (1, "bottom2up"), (1, "random"), (2, "random"), (4, "top2down"), (10, "random")])
+def test_groups_that_share_a_slot_keep_their_state(m, strategy, bf16, master_on_host):
+    """An embeddings unit as large as six layers, so that a slot holds several groups and they are fetched steps ahead: sweeps that
+    the host queues without waiting, steps off the schedule and twice the same group between them, against resident state."""
+    import paper_2401_15207_amd as H
+    wl = dict(WORKLOADS["C1"], n_layers=8, vocab=4700, dtype=bf16, batch=2, seq=24, max_seq=32)
+    theta0 = initial_weights(model_config(wl), 31, 0.02)
+    models = [H.HiftModel(model_config(wl), wl["opt"], m, 2, 24, init_params=theta0, **kw)
+              for kw in (dict(state_on_host=0), dict(state_on_host=1, master_on_host=master_on_host))]
+    a, b = models
+    k = [mdl.set_group_schedule(strategy, m, 5) for mdl in models][0]
+    batches = [to_dev(*make_batch(wl, 31, t)) for t in range(4)]
+    for off in ([], [k - 1, 0, 0, k // 2, k - 1, 0], [b.schedule_group_at(2)] * 2, [1 % k, 2 % k, 3 % k] * 2):
+        for gid in off:
+            assert a.step(*batches[0], gid) == b.step(*batches[0], gid)
+        for mdl in models:
+            mdl.train(batches, 2 * k + 1, want_losses=False)
+    assert np.array_equal(a.read_params(), b.read_params())
+    for j in (0, 1):
+        assert np.array_equal(a.read_state(0, a.n_units, j), b.read_state(0, b.n_units, j))
+    assert b.transfer_stats()[1] > 7 * (2 + master_on_host) * 4 * b.n_params
+
+
 @pytest.mark.parametrize("bf16,master_on_host", [(0, 0), (1, 0), (1, 1)])
 def test_parameters_written_from_device_memory(bf16, master_on_host):
     # hift_write_params_device: the same parameters, forward copy and (through a step) packed copies as the host writer
