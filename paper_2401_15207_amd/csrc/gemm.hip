@@ -9,7 +9,7 @@
 //     forward and backward, folded RMS normalisation) straight from the accumulators.  See further down.
 //   * bf16 weight gradients that fill the chip with whole 256x256 tiles: gemm_tt_k.
 //   * every other bf16 problem whose operands move in 16-byte pieces: gemm_lds_k (gemm_lds.hip).
-//   * fp32 and odd shapes: gemm_fma_k, a plain LDS-tiled FMA kernel (64 x 64 or 32 x 32 outputs) for any leading dimensions.
+//   * fp32 and odd shapes: gemm_f32_k (gemm_f32.hip).
 #include <type_traits>
 
 #include "common.h"
@@ -892,123 +892,6 @@ __global__ void __launch_bounds__(256) gemm_tt_k(GemmP p) {
   store_tile<WM, WN, OutT>(p, acc, smem, m0, n0, wm, wn, wave, lane);
 }
 
-// ------------------------------------------------------------------------------------------
-// plain FMA kernel: any strides, any element type, fp32 accumulation
-// ------------------------------------------------------------------------------------------
-// A workgroup of 256 threads computes BT x BT outputs, each thread a (BT / 16)^2 square of them, every output one chain of fused
-// multiply-adds over ascending k.  KC k-values of both operands per pass through LDS; the next pass's elements are on their
-// way in registers meanwhile.  Small problems are a chain of passes, each a trip to memory: 16 k per pass with nothing in
-// flight took 3 us a pass (64 x 64, k 256: 36 us, now 9, a launch being 4 of them; 2048 x 1024, k 1024: 171 us, now 100).
-// 32 x 32 tiles where 64 x 64 would leave compute units without one.  A pass that k does not fill is loaded and multiplied only as
-// far as k goes, in fours, and up to 16 k have passes of 16: 4096 x 4096, k 4 in bf16 takes 15 us, 28 with 32 k whatever k is.
-// One operand's share of a pass for a thread: NLD elements a fixed distance apart, found by one pointer and one stride
-// (KMAJOR: element i is row tid / KC + i 256 / KC at k = tid % KC; else row tid % BT at k = tid / BT + i 256 / BT), so that
-// neighbouring threads take neighbours along the operand's contiguous direction.  Elements outside are read from the operand's
-// start and dropped.
-template <int BT, int KC, bool KMAJOR, typename T>
-struct FmaOperand {
-  static constexpr int NLD = BT * KC / 256, STEP = KMAJOR ? 256 / KC : 256 / BT;
-  static_assert(KMAJOR || STEP % 4 == 0, "the products walk k in fours: all of a four are stored, or none");
-  const T* base;
-  const T* at;
-  int64_t stride, advance;
-  int r0, k0, rows;  // first row and k of this thread within the tile and pass; rows of the tile inside the matrix
-  T v[NLD];
-  __device__ __forceinline__ void init(const T* src, int64_t ld, int64_t row0, int64_t nrows, int tid) {
-    base = src;
-    r0 = KMAJOR ? tid / KC : tid % BT;
-    k0 = KMAJOR ? tid % KC : tid / BT;
-    rows = (int)(nrows - row0 < BT ? nrows - row0 : BT);
-    at = src + (KMAJOR ? (row0 + r0) * ld + k0 : k0 * ld + row0 + r0);
-    stride = STEP * ld;
-    advance = KMAJOR ? KC : KC * ld;
-  }
-  __device__ __forceinline__ bool inside(int i, int64_t left) const {  // left: k-values that remain from this pass on
-    return KMAJOR ? r0 + i * STEP < rows && k0 < left : r0 < rows && k0 + i * STEP < left;
-  }
-  __device__ __forceinline__ void load(int64_t left) {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i)
-      if (KMAJOR || i * STEP < left) v[i] = *(inside(i, left) ? at + i * stride : base);
-    at += advance;
-  }
-  __device__ __forceinline__ void store(float (*dst)[BT + 4], int64_t left) const {
-#pragma unroll
-    for (int i = 0; i < NLD; ++i)
-      if (KMAJOR || i * STEP < left) dst[KMAJOR ? k0 : k0 + i * STEP][KMAJOR ? r0 + i * STEP : r0] = inside(i, left) ? to_f32(v[i]) : 0.f;
-  }
-};
-
-template <int BT, int KC, bool AK, bool BKM, typename T, typename OutT>
-__global__ void __launch_bounds__(256) gemm_fma_k(GemmP p) {
-  constexpr int TM = BT / 16;
-  __shared__ __attribute__((aligned(16))) float As[2][KC][BT + 4];
-  __shared__ __attribute__((aligned(16))) float Bs[2][KC][BT + 4];
-  const int tid = threadIdx.x;
-  const int tile = blockIdx.x;
-  const int tm = tile % p.tiles_m, tn = tile / p.tiles_m;
-  const int z = blockIdx.y, zb = z / p.nh, zh = z % p.nh;
-  const int64_t m0 = (int64_t)tm * BT, n0 = (int64_t)tn * BT;
-  const int tx = tid & 15, ty = tid >> 4;  // thread computes rows ty*TM..+TM-1, cols tx*TM..+TM-1
-  FmaOperand<BT, KC, AK, T> a;
-  FmaOperand<BT, KC, BKM, T> b;
-  a.init(reinterpret_cast<const T*>(p.A) + zb * p.sa1 + zh * p.sa2, p.lda, m0, p.M, tid);
-  b.init(reinterpret_cast<const T*>(p.B) + zb * p.sb1 + zh * p.sb2, p.ldb, n0, p.N, tid);
-  float acc[TM][TM] = {};
-  if (p.K > 0) {
-    a.load(p.K);
-    b.load(p.K);
-    a.store(As[0], p.K);
-    b.store(Bs[0], p.K);
-  }
-  __syncthreads();
-  int buf = 0;
-  for (int64_t left = p.K; left > 0; left -= KC, buf ^= 1) {
-    const bool more = left > KC;
-    if (more) {
-      a.load(left - KC);
-      b.load(left - KC);
-    }
-    auto step = [&](int k) __attribute__((always_inline)) {
-      const Vec<float, TM> x = *reinterpret_cast<const Vec<float, TM>*>(&As[buf][k][ty * TM]);
-      const Vec<float, TM> y = *reinterpret_cast<const Vec<float, TM>*>(&Bs[buf][k][tx * TM]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j) acc[i][j] = fmaf(x.v[i], y.v[j], acc[i][j]);
-    };
-    if (left >= KC) {
-#pragma unroll 16
-      for (int k = 0; k < KC; ++k) step(k);
-    } else {
-      for (int k = 0; k < (int)left; k += 4) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) step(k + e);
-      }
-    }
-    if (more) {
-      a.store(As[buf ^ 1], left - KC);
-      b.store(Bs[buf ^ 1], left - KC);
-    }
-    __syncthreads();  // the other buffer is complete, this one is no longer read
-  }
-  OutT* C = reinterpret_cast<OutT*>(p.C) + zb * p.sc1 + zh * p.sc2;
-  const OutT* R = p.R ? reinterpret_cast<const OutT*>(p.R) + zb * p.sc1 + zh * p.sc2 : nullptr;
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int64_t row = m0 + ty * TM + i;
-    if (row >= p.M) continue;
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int64_t col = n0 + tx * TM + j;
-      if (col >= p.N) continue;
-      float v = acc[i][j] + (p.bias ? to_f32(reinterpret_cast<const T*>(p.bias)[col]) : 0.f);
-      if (R) v += to_f32(R[row * p.ldr + col]);
-      C[row * p.ldc + col] = from_f32<OutT>(v);
-    }
-  }
-}
-
 inline bool al16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
 
 }  // namespace
@@ -1210,27 +1093,7 @@ hipError_t gemm(const Gemm& g, hipStream_t st) {
     }
     if (lds_gemm_applies(g)) return gemm_lds(g, st);
   }
-  const int bt = ((g.M + 63) / 64) * ((g.N + 63) / 64) * nz >= 256 ? 64 : 32;
-  p.tiles_m = (int)((g.M + bt - 1) / bt);
-  p.tiles_n = (int)((g.N + bt - 1) / bt);
-  const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)nz);
-#define FMA_TILE(AK, BKM, T, OutT)                                                       \
-  do {                                                                                   \
-    if (bt == 64 && g.K <= 16) gemm_fma_k<64, 16, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p); \
-    else if (bt == 64) gemm_fma_k<64, 32, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);         \
-    else gemm_fma_k<32, 64, AK, BKM, T, OutT><<<grid, 256, 0, st>>>(p);                  \
-  } while (0)
-#define FMA(T, OutT)                                                                     \
-  do {                                                                                   \
-    if (g.a_kmajor) { if (g.b_kmajor) FMA_TILE(true, true, T, OutT); else FMA_TILE(true, false, T, OutT); }   \
-    else { if (g.b_kmajor) FMA_TILE(false, true, T, OutT); else FMA_TILE(false, false, T, OutT); }            \
-  } while (0)
-  if (g.dtype == DT_F32) FMA(float, float);
-  else if (g.out_f32) FMA(bf16, float);
-  else FMA(bf16, bf16);
-#undef FMA
-#undef FMA_TILE
-  return hipGetLastError();
+  return gemm_f32(g, st);
 }
 
 }  // namespace hift

@@ -71,6 +71,8 @@ hipError_t gemm(const Gemm& g, hipStream_t st);
 bool lds_gemm_applies(const Gemm& g);
 bool lds_gelu_applies(const Gemm& g);  // with g.epi = EPI_GELU or EPI_GELU_BWD
 hipError_t gemm_lds(const Gemm& g, hipStream_t st);
+// fp32, and bf16 operands that do not lie in 16-byte pieces (gemm_f32.hip)
+hipError_t gemm_f32(const Gemm& g, hipStream_t st);
 
 // Weight operand pre-packed in MFMA fragment order (see gemm.hip).  packed_b_bytes: size of the packed
 // copy of a [N, K] operand, 0 if the shape cannot be packed.  pack_b: builds it from B given as in Gemm
