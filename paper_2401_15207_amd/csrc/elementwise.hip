@@ -8,6 +8,8 @@
 // wavefront shuffles.  Arithmetic is fp32 whatever the storage type is.
 #include <type_traits>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 #include "optimizer.h"
@@ -422,19 +424,16 @@ __global__ void __launch_bounds__(64) norm_bwd_dx_reg_k(int64_t rows, int d, con
   }
 }
 
-// Column sums in two deterministic stages.  Stage 1: block (256 columns) x chunk (64 rows), one column per thread, rows added
-// in order; a chunk's rows are requested 32 at a time before the first is added (the loop was bound by the latency of a few
-// loads in flight: 64 rows took 16 to 26 us, the norm gains of 2048 x 1024 now 5).
+// Column sums over chunks of 64 rows: the rows of a chunk added in order, then the chunks in order, so the bits do not depend on
+// which kernels run.  A chunk's rows are requested 32 at a time before the first is added (the loop was bound by the latency of
+// a few loads in flight: 64 rows took 16 to 26 us, the norm gains of 2048 x 1024 then 5).
 // MODE 0: sum y.  MODE 1: sum dy * xhat and sum dy (norm gain / shift gradients).
 template <typename T, int MODE>
-__global__ void __launch_bounds__(BLK) col_part_k(int64_t rows, int64_t n, const T* __restrict__ y, int64_t ld,
-                                                   const T* __restrict__ x, const float* __restrict__ stats,
-                                                   float* __restrict__ part) {
+__device__ __forceinline__ void col_chunk(int64_t chunk, int64_t rows, const T* __restrict__ y, int64_t ld, const T* __restrict__ x,
+                                          const float* __restrict__ stats, int64_t j, float& a, float& b) {
   constexpr int AT_ONCE = 32;
-  const int64_t j = (int64_t)blockIdx.x * BLK + threadIdx.x;
-  if (j >= n) return;
-  const int64_t r0 = (int64_t)blockIdx.y * 64, r1 = r0 + 64 < rows ? r0 + 64 : rows;
-  float a = 0.f, b = 0.f;
+  const int64_t r0 = chunk * 64, r1 = r0 + 64 < rows ? r0 + 64 : rows;
+  a = b = 0.f;
   auto add = [&](int64_t r, T yv, T xv) __attribute__((always_inline)) {
     const float v = to_f32(yv);
     if (MODE == 0) {
@@ -456,6 +455,46 @@ __global__ void __launch_bounds__(BLK) col_part_k(int64_t rows, int64_t n, const
     for (int e = 0; e < AT_ONCE; ++e) add(r + e, yv[e], xv[MODE == 1 ? e : 0]);
   }
   for (; r < r1; ++r) add(r, y[r * ld + j], MODE == 1 ? x[r * ld + j] : T());
+}
+// Up to 4096 rows, one launch: a workgroup takes 64 columns, a wavefront of it a chunk at a time (whose number is uniform, so that the
+// rows' statistics come by scalar loads), and the chunks are added up in LDS.  A sum (MODE 0) of 2048 x 1024 or x 4096 in bf16 takes 6.7
+// to 7.2 us, two launches 8 to 10; 64 x 64 in fp32 2.9, two launches 4.4.  The two sums of MODE 1 up to 1024 rows (1024 x 768: 9.1 us, two
+// launches 9.6; 64 x 64: 3.0 and 5.4), as few workgroups then have twice the loads to wait for: 2048 x 1024 14 us, two launches 9.4.
+constexpr int COL_ONE_CHUNKS = 64, COL_ONE_WAVES = 16;
+template <typename T, int MODE>
+__global__ void __launch_bounds__(64 * COL_ONE_WAVES) col_one_k(int64_t rows, int64_t n, const T* __restrict__ y, int64_t ld,
+                                                               const T* __restrict__ x, const float* __restrict__ stats,
+                                                               float* __restrict__ out0, float* __restrict__ out1) {
+  __shared__ float sums[MODE + 1][COL_ONE_CHUNKS][64];
+  const int lane = threadIdx.x & 63, nchunk = (int)((rows + 63) / 64);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = (int)blockDim.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+  if (j < n)
+    for (int c = wave; c < nchunk; c += waves) {
+      float a, b;
+      col_chunk<T, MODE>(c, rows, y, ld, x, stats, j, a, b);
+      sums[0][c][lane] = a;
+      if (MODE == 1) sums[MODE][c][lane] = b;
+    }
+  __syncthreads();
+  for (int o = wave; o <= MODE; o += waves) {
+    float* out = o ? out1 : out0;
+    if (!out || j >= n) continue;
+    float t = 0.f;
+#pragma unroll 8
+    for (int c = 0; c < nchunk; ++c) t += sums[o][c][lane];
+    out[j] = t;
+  }
+}
+// More rows, two: stage 1, block (256 columns) x chunk, one column per thread.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(BLK) col_part_k(int64_t rows, int64_t n, const T* __restrict__ y, int64_t ld,
+                                                   const T* __restrict__ x, const float* __restrict__ stats,
+                                                   float* __restrict__ part) {
+  const int64_t j = (int64_t)blockIdx.x * BLK + threadIdx.x;
+  if (j >= n) return;
+  float a, b;
+  col_chunk<T, MODE>(blockIdx.y, rows, y, ld, x, stats, j, a, b);
   part[(int64_t)blockIdx.y * n + j] = a;
   if (MODE == 1) part[((int64_t)gridDim.y + blockIdx.y) * n + j] = b;
 }
@@ -1181,6 +1220,12 @@ hipError_t norm_bwd_params(int dt, bool rms, int64_t rows, int d, const void* dy
     if (e == hipSuccess && db) e = fill_zero(db, (size_t)d * 4, st);
     return e;
   }
+  if (nchunk <= COL_ONE_WAVES) {
+    const unsigned blocks = (unsigned)cdiv(d, 64), threads = 64 * (unsigned)std::min<int64_t>(nchunk, COL_ONE_WAVES);
+    if (dt == DT_F32) col_one_k<float, 1><<<blocks, threads, 0, st>>>(rows, d, (const float*)dy, d, (const float*)x, stats, dg, db);
+    else col_one_k<bf16, 1><<<blocks, threads, 0, st>>>(rows, d, (const bf16*)dy, d, (const bf16*)x, stats, dg, db);
+    LAUNCH_CHECK();
+  }
   const dim3 grid((unsigned)cdiv(d, BLK), (unsigned)nchunk);
   if (dt == DT_F32)
     col_part_k<float, 1><<<grid, BLK, 0, st>>>(rows, d, (const float*)dy, d, (const float*)x, stats, part);
@@ -1195,6 +1240,12 @@ hipError_t col_sum(int dt, int64_t rows, int64_t n, const void* y, int64_t ld, f
   if (n == 0) return hipSuccess;
   if (rows == 0) return fill_zero(out, (size_t)n * 4, st);
   const int64_t nchunk = cdiv(rows, 64);
+  if (nchunk <= COL_ONE_CHUNKS) {
+    const unsigned blocks = (unsigned)cdiv(n, 64), threads = 64 * (unsigned)std::min<int64_t>(nchunk, COL_ONE_WAVES);
+    if (dt == DT_F32) col_one_k<float, 0><<<blocks, threads, 0, st>>>(rows, n, (const float*)y, ld, nullptr, nullptr, out, nullptr);
+    else col_one_k<bf16, 0><<<blocks, threads, 0, st>>>(rows, n, (const bf16*)y, ld, nullptr, nullptr, out, nullptr);
+    LAUNCH_CHECK();
+  }
   const dim3 grid((unsigned)cdiv(n, BLK), (unsigned)nchunk);
   if (dt == DT_F32)
     col_part_k<float, 0><<<grid, BLK, 0, st>>>(rows, n, (const float*)y, ld, nullptr, nullptr, part);
