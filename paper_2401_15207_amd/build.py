@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhift.so")
-SOURCES = ["elementwise.hip", "gemm.hip", "gemm_lds.hip", "gemm_f32.hip", "attention.hip", "update_pack.hip", "model.hip"]
+SOURCES = ["elementwise.hip", "gemm.hip", "gemm_lds.hip", "gemm_f32.hip", "attention.hip", "attention_f32.hip", "update_pack.hip", "model.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -1059,7 +1059,7 @@ hipError_t gemm(const Gemm& g, hipStream_t st) {
   p.nh = g.nh; p.sa1 = g.sa1; p.sa2 = g.sa2; p.sb1 = g.sb1; p.sb2 = g.sb2; p.sc1 = g.sc1; p.sc2 = g.sc2;
   const int nz = g.nb * g.nh;
   if (nz > 65535) return hipErrorInvalidValue;
-  if (g.epi != EPI_NONE) return gemm_lds(g, st);
+  if (g.epi != EPI_NONE) return g.dtype == DT_F32 ? gemm_f32(g, st) : gemm_lds(g, st);
 
   if (g.dtype == DT_BF16) {
     // gemm_tt_k: both operands contraction-index first in 16-byte pieces, whole tiles, enough of them to fill the chip

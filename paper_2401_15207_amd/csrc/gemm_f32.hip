@@ -30,6 +30,7 @@ struct F32P {
   int nh;
   int64_t sa1, sa2, sb1, sb2, sc1, sc2;
   int tiles_m;
+  void* C2; int64_t ldc2;  // EPI_GELU, EPI_GELU_BWD (see Gemm in kernels.h)
   int vec;  // rows of C, R and bias can be moved four values at a time
 };
 
@@ -98,7 +99,7 @@ struct F32Operand {
 };
 
 // BUFS: LDS buffers; with one the next pass waits in registers until every wavefront has multiplied this one.
-template <int BT, int KC, int BUFS, bool AK, bool BKM, typename T, typename OutT>
+template <int BT, int KC, int BUFS, bool AK, bool BKM, typename T, typename OutT, int EPI>
 __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   constexpr int WT = BT / 2, MT = WT / 16, LD = KC + 4, OP = BT * LD;
   extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -171,6 +172,29 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   const OutT* R = p.R ? reinterpret_cast<const OutT*>(p.R) + zb * p.sc1 + zh * p.sc2 : nullptr;
   const T* bias = reinterpret_cast<const T*>(p.bias);
   const int64_t row0 = m0 + wm * WT + (lane & 15), col0 = n0 + wn * WT + (lane >> 4) * 4;
+  if constexpr (EPI != EPI_NONE) {  // no residual, no batch; the library's erff, as the separate kernels take it: the same bits
+    float* C2 = reinterpret_cast<float*>(p.C2);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int64_t row = row0 + i * 16;
+      if (row >= p.M) continue;
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int64_t col = col0 + j * 16 + e;
+          if (col >= p.N) continue;
+          const float v = acc[i][j][e] + (bias ? to_f32(bias[col]) : 0.f);
+          if constexpr (EPI == EPI_GELU) {
+            if (p.C) C[row * p.ldc + col] = v;
+            C2[row * p.ldc2 + col] = gelu_f(v);
+          } else {
+            C[row * p.ldc + col] = v * gelu_df(C2[row * p.ldc2 + col]);
+          }
+        }
+    }
+    return;
+  }
   if (p.vec && m0 + BT <= p.M && n0 + BT <= p.N) {
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
@@ -215,11 +239,11 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   }
 }
 
-template <int BT, int KC, int BUFS, bool AK, bool BKM, typename T, typename OutT>
+template <int BT, int KC, int BUFS, bool AK, bool BKM, typename T, typename OutT, int EPI>
 hipError_t launch(F32P& p, int nz, hipStream_t st) {
   constexpr int LDS = BUFS * 2 * BT * (KC + 4) * (int)sizeof(float);
   static_assert(LDS <= 160 * 1024, "LDS of a gfx950 compute unit");
-  auto kern = gemm_f32_k<BT, KC, BUFS, AK, BKM, T, OutT>;
+  auto kern = gemm_f32_k<BT, KC, BUFS, AK, BKM, T, OutT, EPI>;
   if (LDS > 64 * 1024) {
     static bool attr_done = false;  // one flag per instantiation
     if (!attr_done) {
@@ -236,15 +260,15 @@ hipError_t launch(F32P& p, int nz, hipStream_t st) {
 
 // 64 x 64 tiles where they give every compute unit one (1024 x 1024, k 256: 12.2 us), else 32 x 32 (512 x 1024: 9.7), whose passes are no
 // longer than k needs: elements past its end cost their loads.
-template <bool AK, bool BKM, typename T, typename OutT>
+template <bool AK, bool BKM, typename T, typename OutT, int EPI = EPI_NONE>
 hipError_t pick(F32P& p, int nz, hipStream_t st) {
   if (((p.M + 63) / 64) * ((p.N + 63) / 64) * nz >= 256) {
-    if (p.K <= 16) return launch<64, 16, 2, AK, BKM, T, OutT>(p, nz, st);
-    return launch<64, 32, 2, AK, BKM, T, OutT>(p, nz, st);
+    if (p.K <= 16) return launch<64, 16, 2, AK, BKM, T, OutT, EPI>(p, nz, st);
+    return launch<64, 32, 2, AK, BKM, T, OutT, EPI>(p, nz, st);
   }
-  if (p.K <= 64) return launch<32, 64, 1, AK, BKM, T, OutT>(p, nz, st);
-  if (p.K <= 128) return launch<32, 128, 1, AK, BKM, T, OutT>(p, nz, st);
-  return launch<32, 256, 1, AK, BKM, T, OutT>(p, nz, st);
+  if (p.K <= 64) return launch<32, 64, 1, AK, BKM, T, OutT, EPI>(p, nz, st);
+  if (p.K <= 128) return launch<32, 128, 1, AK, BKM, T, OutT, EPI>(p, nz, st);
+  return launch<32, 256, 1, AK, BKM, T, OutT, EPI>(p, nz, st);
 }
 
 template <typename T, typename OutT>
@@ -258,6 +282,13 @@ hipError_t pick_layout(const Gemm& g, F32P& p, int nz, hipStream_t st) {
 
 }  // namespace
 
+// GELU or its derivative on the way out: one fp32 problem in the layout of the pass it belongs to.
+bool f32_gelu_applies(const Gemm& g) {
+  const bool fwd = g.epi == EPI_GELU;
+  return g.dtype == DT_F32 && (fwd || g.epi == EPI_GELU_BWD) && !g.R && g.nb * g.nh == 1 && g.a_kmajor && g.b_kmajor == fwd && g.C2 &&
+         (fwd || (g.C && !g.bias));
+}
+
 hipError_t gemm_f32(const Gemm& g, hipStream_t st) {
   F32P p{};
   p.M = g.M; p.N = g.N; p.K = g.K;
@@ -265,6 +296,11 @@ hipError_t gemm_f32(const Gemm& g, hipStream_t st) {
   p.bias = g.bias; p.R = g.R; p.ldr = g.ldr;
   p.nh = g.nh; p.sa1 = g.sa1; p.sa2 = g.sa2; p.sb1 = g.sb1; p.sb2 = g.sb2; p.sc1 = g.sc1; p.sc2 = g.sc2;
   const int nz = g.nb * g.nh;
+  if (g.epi != EPI_NONE) {
+    if (!f32_gelu_applies(g)) return hipErrorInvalidValue;
+    p.C2 = g.C2; p.ldc2 = g.ldc2;
+    return g.epi == EPI_GELU ? pick<true, true, float, float, EPI_GELU>(p, nz, st) : pick<true, false, float, float, EPI_GELU_BWD>(p, nz, st);
+  }
   if (g.dtype == DT_F32) return pick_layout<float, float>(g, p, nz, st);
   return g.out_f32 ? pick_layout<bf16, float>(g, p, nz, st) : pick_layout<bf16, bf16>(g, p, nz, st);
 }

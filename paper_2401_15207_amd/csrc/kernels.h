@@ -31,7 +31,8 @@ struct Gemm {
   //   BAND_K_FROM_ROW   A(m,k) = 0 for k < m: the contraction of a tile starts at its first row
   int band = 0;
   // Fused epilogue of the packed-operand kernel (the packed copy must have been built with the matching column order,
-  // see pack_b); EPI_GELU and EPI_GELU_BWD also of gemm(), where lds_gelu_applies():
+  // see pack_b); EPI_GELU and EPI_GELU_BWD also of gemm(), where lds_gelu_applies() or
+  // f32_gelu_applies():
   //   EPI_SWIGLU  B = gate | up, N = 2 f.  C [M, N] (may be null: not kept) receives the pre-activations as
   //               usual; C2 [M, f] (ldc2) receives silu(gate) * up computed from the rounded pre-activations.
   //   EPI_ROPE    B = q | k | v of heads of width 128.  Columns below rot_cols are rotated pairwise
@@ -73,6 +74,7 @@ bool lds_gelu_applies(const Gemm& g);  // with g.epi = EPI_GELU or EPI_GELU_BWD
 hipError_t gemm_lds(const Gemm& g, hipStream_t st);
 // fp32, and bf16 operands that do not lie in 16-byte pieces (gemm_f32.hip)
 hipError_t gemm_f32(const Gemm& g, hipStream_t st);
+bool f32_gelu_applies(const Gemm& g);
 
 // Weight operand pre-packed in MFMA fragment order (see gemm.hip).  packed_b_bytes: size of the packed
 // copy of a [N, K] operand, 0 if the shape cannot be packed.  pack_b: builds it from B given as in Gemm
@@ -129,6 +131,12 @@ hipError_t swiglu_bwd(int dt, int64_t T, int f, const void* dact, const void* gu
 bool attention_fwd_fused_applies(int dt, int S, int hd, int64_t ld, int64_t ldc, const void* qkv, const void* prob, const void* ctx);
 hipError_t attention_fwd_fused(int B, int H, int S, int hd, bool causal, const void* qkv, int64_t ld, void* prob, void* ctx,
                                int64_t ldc, float* lse, hipStream_t st);
+// The same for fp32 models (attention_f32.hip): the forward writes the context; of the backward dq, and the probabilities and the
+// gradient of the scores [B, H, S, S] for the contractions that give dv and dk.
+bool attention_f32_applies(int dt, int B, int H, int S, int hd, int64_t ld, int64_t ldc, const void* qkv, const void* ctx);
+hipError_t attention_fwd_f32(int B, int H, int S, int hd, bool causal, const void* qkv, int64_t ld, void* ctx, int64_t ldc, hipStream_t st);
+hipError_t attention_bwd_f32(int B, int H, int S, int hd, bool causal, const void* qkv, int64_t ld, const void* dctx, int64_t ldc, void* prob,
+                             void* dprob, void* dqkv, hipStream_t st);
 // Backward in two kernels, query-major (dq; leaves D = dO . O per query in dsum [B*H*S] fp32) and key-major
 // (dk, dv); both form the probabilities again from q, k and lse, so nothing of size S x S is read or written.
 // All of dqkv [B*S, ld] is written.  cos_sin: fp32 [>= S, hd/2] pairs (cos, sin) or null; if given, dq and dk

@@ -730,7 +730,7 @@ hift_status linear(hift_model* M, const void* x, int64_t rows, const Tensor& w, 
     f.epi = EPI_GELU;
     f.C2 = epi->act; f.ldc2 = w.rows;
     if (!epi->keep_pre) f.C = nullptr;
-    if (lds_gelu_applies(f)) {
+    if (lds_gelu_applies(f) || f32_gelu_applies(f)) {
       g = f;
       epi->fused = true;
     }
@@ -776,7 +776,7 @@ hift_status linear_dx(hift_model* M, const void* dy, int64_t rows, const Tensor&
     f.epi = EPI_GELU_BWD;
     f.C2 = const_cast<void*>(gate_pre); f.ldc2 = w.cols;
     f.C = dgu;
-    if (lds_gelu_applies(f)) {
+    if (lds_gelu_applies(f) || f32_gelu_applies(f)) {
       g = f;
       *fused = true;
     }
@@ -811,6 +811,12 @@ bool attention_is_fused(const hift_model* M, const LayerAct& a, int S) {
   const int64_t d = M->cfg.d_model, hd = d / M->cfg.n_heads;
   return fused_on && attention_fwd_fused_applies(M->dt, S, (int)hd, 3 * d, d, a.qkv, nullptr, a.ctx) &&
          attention_bwd_fused_applies(M->dt, S, (int)hd, 3 * d, d, a.qkv, a.ctx, M->D[2], M->dqkv);
+}
+
+// Whether attn_f32_k does a layer's attention (of an fp32 model; its backward forms the probabilities again, so either pass may ask).
+bool attention_is_f32(const hift_model* M, const void* qkv, const void* ctx, int B, int S) {
+  const int64_t d = M->cfg.d_model, H = M->cfg.n_heads;
+  return !(M->cfg.unfused & HIFT_UNFUSED_ATTENTION) && attention_f32_applies(M->dt, B, (int)H, S, (int)(d / H), 3 * d, d, qkv, ctx);
 }
 
 // Probabilities of one layer into M->prob, for the unfused attention: scores q . k^T, then the softmax in place.
@@ -849,6 +855,11 @@ hift_status attention_fwd(hift_model* M, LayerAct& a, int B, int S, bool keep) {
     // scores, softmax and P.V in one kernel; of the softmax only each row's log-sum is kept for the backward pass
     Scope sc(M, CAT_ATTN, 4.0 * B * H * S * S * hd);
     K_TRY(attention_fwd_fused(B, (int)H, S, (int)hd, causal, a.qkv, 3 * d, nullptr, a.ctx, d, keep ? a.lse : nullptr, M->cs));
+    return HIFT_OK;
+  }
+  if (attention_is_f32(M, a.qkv, a.ctx, B, S)) {
+    Scope sc(M, CAT_ATTN, 4.0 * B * H * S * S * hd);
+    K_TRY(attention_fwd_f32(B, (int)H, S, (int)hd, causal, a.qkv, 3 * d, a.ctx, d, M->cs));
     return HIFT_OK;
   }
   ST_TRY(attention_probs(M, a, B, S));
@@ -894,7 +905,13 @@ hift_status attention_bwd(hift_model* M, LayerAct& a, const void* dctx, int B, i
                               M->cs));
     return HIFT_OK;
   }
-  ST_TRY(attention_probs(M, a, B, S));  // the forward pass kept q and k, not the probabilities
+  const bool f32 = attention_is_f32(M, a.qkv, dctx, B, S) && (reinterpret_cast<uintptr_t>(dqkv) & 15) == 0;
+  if (f32) {  // probabilities, gradient of the scores and dq
+    Scope sc(M, CAT_ATTN, 3 * fl);
+    K_TRY(attention_bwd_f32(B, (int)H, S, (int)hd, causal, a.qkv, 3 * d, dctx, d, M->prob, M->dprob, dqkv, M->cs));
+  } else {
+    ST_TRY(attention_probs(M, a, B, S));  // the forward pass kept q and k, not the probabilities
+  }
   {
     Gemm g;  // dv[j,e] = sum_i p[i,j] dctx[i,e]
     batch(g);
@@ -906,7 +923,7 @@ hift_status attention_bwd(hift_model* M, LayerAct& a, const void* dctx, int B, i
     Scope sc(M, CAT_ATTN, fl);
     K_TRY(gemm(g, M->cs));
   }
-  {
+  if (!f32) {
     Gemm g;  // dp[i,j] = sum_e dctx[i,e] v[j,e]
     batch(g);
     g.M = S; g.N = S; g.K = hd;
@@ -917,8 +934,8 @@ hift_status attention_bwd(hift_model* M, LayerAct& a, const void* dctx, int B, i
     Scope sc(M, CAT_ATTN, fl);
     K_TRY(gemm(g, M->cs));
   }
-  RW(RW_SOFTMAX_BWD, 3.0 * B * H * S * S * es, softmax_bwd(M->dt, (int64_t)B * H, S, 1.0f / sqrtf((float)hd), causal, M->prob, M->dprob, M->cs));
-  {
+  if (!f32) RW(RW_SOFTMAX_BWD, 3.0 * B * H * S * S * es, softmax_bwd(M->dt, (int64_t)B * H, S, 1.0f / sqrtf((float)hd), causal, M->prob, M->dprob, M->cs));
+  if (!f32) {
     Gemm g;  // dq[i,e] = sum_j ds[i,j] k[j,e]
     batch(g);
     g.M = S; g.N = hd; g.K = S;
