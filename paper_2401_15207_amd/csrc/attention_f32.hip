@@ -7,8 +7,8 @@
 // What bounds it: launches.  In fp32 models of a few tokens a launch costs the host 3 to 4 us and the GPU 3; scores, softmax and context
 // were three of them a layer, and seven in the backward pass, three now (this query-major kernel leaves P and dS to two contractions
 // for dV and dK).  With GELU in the contractions' epilogues and the column sums in one launch each, a sweep of two layers, 2 x 32 tokens
-// of width 64, takes 145 launches instead of 217: 1.14 -> 0.93 ms.  Four layers, 8 x 256 tokens, heads of 64: 9.3 -> 6.4 ms, of which
-// gemm_f32_k has its part.
+// of width 64, takes 155 launches instead of 217: 1.14 -> 0.83 ms.  Four layers, 8 x 256 tokens, heads of 64: 9.3 -> 5.4 ms, both with
+// gemm_f32_k's part.
 // Every sum has the order that the separate contractions and softmax kernels give it, so the bits are theirs: chains over ascending
 // k, and a row's sums in the tree of a wavefront whose lanes hold four consecutive keys each (QUADS: S a multiple of four) or every 64th
 // key.  AdamW makes a full step of a gradient that is nothing but rounding (a key's bias), so other bits would show.

@@ -8,8 +8,8 @@
 // A workgroup of four wavefronts computes BT x BT outputs, a wavefront a quarter of them.  Elements travel one by one through
 // registers (converted to fp32 there) into LDS rows of KC k-values, the next pass's on their way while one is multiplied.
 // What bounds it: small problems, a trip to memory per pass, so that 32 x 32 tiles take up to 256 k in one pass (256 x 1024, k 1024
-// in the three layouts of a linear layer 17 us; a kernel of fused multiply-adds on the vector unit with passes of 64 took
-// 31 to 43); large ones, element-wise loads and LDS writes: 2048 x 2048, k 2048 193 us, 89 TFLOP/s, before 287 to 297.
+// in the three layouts of a linear layer 11 us; a kernel of fused multiply-adds on the vector unit with passes of 64 took
+// 31 to 43); large ones, element-wise loads and LDS writes: 2048 x 2048, k 2048 145 to 151 us, 114 TFLOP/s, before 287 to 297.
 #include <algorithm>
 
 #include "common.h"
@@ -38,19 +38,29 @@ struct F32P {
 // j takes k = 4 j + g of lane group g).
 __device__ __forceinline__ int f32_place(int k) { return (k & ~15) | ((k & 3) << 2) | ((k >> 2) & 3); }
 
-// One operand's share of a pass for a thread: NLD elements at fixed distances, found by one pointer and one stride, so that
-// neighbouring threads take neighbours along the operand's contiguous direction.  KMAJOR: element i is row tid / KC + i 256 / KC
-// at k = tid % KC.  Else row tid % BT; four elements after one another are k = c, c + 4, c + 8, c + 12 of one sixteen, which
-// lie side by side in LDS and leave as one 16-byte write (one by one, the 64 rows of a write would share 16 banks: 512 x 1024,
-// k 256 with transposed operands 21 us, 9 so).  Elements outside are read from the operand's start and dropped; `whole`
-// passes have none.  LDS rows are KC + 4 floats: the 16 rows of a 16-byte access fall into different banks.
-template <int BT, int KC, bool KMAJOR, typename T>
+__device__ __forceinline__ float f32_load(__amdgpu_buffer_rsrc_t r, uint32_t at, const float*) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
+}
+__device__ __forceinline__ bf16 f32_load(__amdgpu_buffer_rsrc_t r, uint32_t at, const bf16*) {
+  return __builtin_bit_cast(bf16, __builtin_amdgcn_raw_buffer_load_b16(r, at, 0, 0));
+}
+
+// One operand's share of a pass for a thread: NLD elements at fixed distances, so that neighbouring threads take neighbours along
+// the operand's contiguous direction.  KMAJOR: element i is row tid / KC + i 256 / KC at k = tid % KC.  Else row tid % BT; four
+// elements after one another are k = c, c + 4, c + 8, c + 12 of one sixteen, which lie side by side in LDS and leave as one 16-byte
+// write (one by one, the 64 rows of a write would share 16 banks: 512 x 1024, k 256 with transposed operands 21 us, 9 so).
+// LDS rows are KC + 4 floats: the 16 rows of a 16-byte access fall into different banks.
+// Elements outside arrive as zeros, for which the loads are bounded: the direction that the elements of a thread advance in by the length
+// of the buffer, the other one by an offset beyond it (with pointers and a branch per element at the edges, 26 KB of code for a pass of
+// 256 k and 6 now, 256 x 1024, k 1024 took 17 us and 2048 x 2048, k 2048 193).  Lengths and offsets stay below 2^31 (f32_fits); WIDE, for rows too far apart for that, goes by pointers.
+constexpr uint32_t F32_OUTSIDE = 0x80000000u;
+template <int BT, int KC, bool KMAJOR, bool WIDE, typename T>
 struct F32Operand {
   static constexpr int NLD = BT * KC / 256, STEP = KMAJOR ? 256 / KC : 256 / BT, LD = KC + 4;
   static_assert(KMAJOR || (STEP % 4 == 0 && NLD % 4 == 0), "a thread's elements come in fours");
   const T* base;
-  const T* at;
-  int64_t ld, advance;
+  const T* tile;  // the tile's first element in this pass
+  int64_t ld;
   int r0, k0, rows;  // first row and k of this thread within the tile and pass; rows of the tile inside the matrix
   T v[NLD];
   static __device__ __forceinline__ constexpr int row(int i) { return KMAJOR ? i * STEP : 0; }
@@ -61,45 +71,46 @@ struct F32Operand {
     r0 = KMAJOR ? tid / KC : tid % BT;
     k0 = KMAJOR ? tid % KC : tid / BT / 4 * 16 + tid / BT % 4;
     rows = (int)(nrows - row0 < BT ? nrows - row0 : BT);
-    at = src + (KMAJOR ? (row0 + r0) * ld + k0 : k0 * ld + row0 + r0);
-    advance = KMAJOR ? KC : KC * ld;
+    tile = src + (KMAJOR ? row0 * ld : row0);
   }
-  __device__ __forceinline__ bool whole(int64_t left) const { return rows == BT && left >= KC; }
-  __device__ __forceinline__ bool inside(int i, int64_t left) const {  // left: k-values that remain from this pass on
-    return r0 + row(i) < rows && k0 + kk(i) < left;
-  }
-  __device__ __forceinline__ void load(int64_t left) {
-    if (whole(left)) {
+  __device__ __forceinline__ void load(int64_t left) {  // left: k-values that remain from this pass on
+    const int ks = (int)(left < KC ? left : KC);
+    if constexpr (WIDE) {
 #pragma unroll
-      for (int i = 0; i < NLD; ++i) v[i] = at[(KMAJOR ? row(i) : kk(i)) * ld];
+      for (int i = 0; i < NLD; ++i) {
+        const int r = r0 + row(i), k = k0 + kk(i);
+        const bool in = r < rows && k < ks;
+        const T t = *(in ? tile + (KMAJOR ? r * ld + k : k * ld + r) : base);
+        v[i] = in ? t : T();
+      }
     } else {
+      const uint32_t ld32 = (uint32_t)ld * (uint32_t)sizeof(T);
+      const __amdgpu_buffer_rsrc_t buf =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(tile), 0, (int)((KMAJOR ? rows : ks) * ld32), 0x00020000);
+      const bool in = KMAJOR ? k0 < ks : r0 < rows;
+      const uint32_t at = in ? (KMAJOR ? r0 * ld32 + k0 * (uint32_t)sizeof(T) : k0 * ld32 + r0 * (uint32_t)sizeof(T)) : F32_OUTSIDE;
 #pragma unroll
-      for (int i = 0; i < NLD; ++i)
-        if (KMAJOR ? row(i) < rows : kk(i) < left) v[i] = *(inside(i, left) ? at + (KMAJOR ? row(i) : kk(i)) * ld : base);
+      for (int i = 0; i < NLD; ++i) v[i] = f32_load(buf, at + (uint32_t)(KMAJOR ? row(i) : kk(i)) * ld32, static_cast<const T*>(nullptr));
     }
-    at += advance;
+    tile += KMAJOR ? KC : KC * ld;
   }
-  __device__ __forceinline__ void store(float* dst, int64_t left) const {
+  __device__ __forceinline__ void store(float* dst) const {
     float* to = dst + r0 * LD + f32_place(k0);
-    const bool all = whole(left);
     if constexpr (KMAJOR) {
 #pragma unroll
-      for (int i = 0; i < NLD; ++i) to[row(i) * LD] = all || inside(i, left) ? to_f32(v[i]) : 0.f;
+      for (int i = 0; i < NLD; ++i) to[row(i) * LD] = to_f32(v[i]);
     } else {
 #pragma unroll
       for (int i = 0; i < NLD; i += 4)
-        if (kk(i) < left) {
-          f32x4 x;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = all || inside(i + e, left) ? to_f32(v[i + e]) : 0.f;
-          *reinterpret_cast<f32x4*>(to + kk(i)) = x;
-        }
+        *reinterpret_cast<f32x4*>(to + kk(i)) = f32x4{to_f32(v[i]), to_f32(v[i + 1]), to_f32(v[i + 2]), to_f32(v[i + 3])};
     }
   }
 };
+// What the buffers of the largest tile and pass (64 rows of k-major operands, 256 k of others) need.
+bool f32_fits(bool kmajor, int64_t ld, int64_t size) { return ld < (int64_t(1) << 31) && (kmajor ? 64 : 256) * ld * size <= 0x7FF00000; }
 
 // BUFS: LDS buffers; with one the next pass waits in registers until every wavefront has multiplied this one.
-template <int BT, int KC, int BUFS, bool AK, bool BKM, typename T, typename OutT, int EPI>
+template <int BT, int KC, int BUFS, bool AK, bool BKM, bool WIDE, typename T, typename OutT, int EPI>
 __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   constexpr int WT = BT / 2, MT = WT / 16, LD = KC + 4, OP = BT * LD;
   extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -108,16 +119,16 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   const int tm = tile % p.tiles_m, tn = tile / p.tiles_m;
   const int z = blockIdx.y, zb = z / p.nh, zh = z % p.nh;
   const int64_t m0 = (int64_t)tm * BT, n0 = (int64_t)tn * BT;
-  F32Operand<BT, KC, AK, T> a;
-  F32Operand<BT, KC, BKM, T> b;
+  F32Operand<BT, KC, AK, WIDE, T> a;
+  F32Operand<BT, KC, BKM, WIDE, T> b;
   a.init(reinterpret_cast<const T*>(p.A) + zb * p.sa1 + zh * p.sa2, p.lda, m0, p.M, tid);
   b.init(reinterpret_cast<const T*>(p.B) + zb * p.sb1 + zh * p.sb2, p.ldb, n0, p.N, tid);
   f32x4 acc[MT][MT] = {};
   if (p.K > 0) {
     a.load(p.K);
     b.load(p.K);
-    a.store(lds, p.K);
-    b.store(lds + OP, p.K);
+    a.store(lds);
+    b.store(lds + OP);
   }
   __syncthreads();
   const int frag = (lane & 15) * LD + (lane >> 4) * 4;  // lane l: row l % 16, the k-values that its group takes of four products
@@ -162,8 +173,8 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
     if (BUFS == 1) __syncthreads();
     else buf ^= 1;
     if (more) {
-      a.store(lds + buf * 2 * OP, left - KC);
-      b.store(lds + buf * 2 * OP + OP, left - KC);
+      a.store(lds + buf * 2 * OP);
+      b.store(lds + buf * 2 * OP + OP);
     }
     __syncthreads();  // the next pass is complete, this one is no longer read
   }
@@ -239,11 +250,11 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   }
 }
 
-template <int BT, int KC, int BUFS, bool AK, bool BKM, typename T, typename OutT, int EPI>
+template <int BT, int KC, int BUFS, bool AK, bool BKM, bool WIDE, typename T, typename OutT, int EPI>
 hipError_t launch(F32P& p, int nz, hipStream_t st) {
   constexpr int LDS = BUFS * 2 * BT * (KC + 4) * (int)sizeof(float);
   static_assert(LDS <= 160 * 1024, "LDS of a gfx950 compute unit");
-  auto kern = gemm_f32_k<BT, KC, BUFS, AK, BKM, T, OutT, EPI>;
+  auto kern = gemm_f32_k<BT, KC, BUFS, AK, BKM, WIDE, T, OutT, EPI>;
   if (LDS > 64 * 1024) {
     static bool attr_done = false;  // one flag per instantiation
     if (!attr_done) {
@@ -258,17 +269,21 @@ hipError_t launch(F32P& p, int nz, hipStream_t st) {
   return hipGetLastError();
 }
 
-// 64 x 64 tiles where they give every compute unit one (1024 x 1024, k 256: 12.2 us), else 32 x 32 (512 x 1024: 9.7), whose passes are no
+// 64 x 64 tiles where they give every compute unit one (1024 x 1024, k 256: 10.4 us), else 32 x 32 (512 x 1024: 7.9), whose passes are no
 // longer than k needs: elements past its end cost their loads.
 template <bool AK, bool BKM, typename T, typename OutT, int EPI = EPI_NONE>
 hipError_t pick(F32P& p, int nz, hipStream_t st) {
-  if (((p.M + 63) / 64) * ((p.N + 63) / 64) * nz >= 256) {
-    if (p.K <= 16) return launch<64, 16, 2, AK, BKM, T, OutT, EPI>(p, nz, st);
-    return launch<64, 32, 2, AK, BKM, T, OutT, EPI>(p, nz, st);
+  if (!f32_fits(AK, p.lda, sizeof(T)) || !f32_fits(BKM, p.ldb, sizeof(T))) {
+    if constexpr (EPI == EPI_NONE) return launch<32, 64, 1, AK, BKM, true, T, OutT, EPI>(p, nz, st);
+    return hipErrorInvalidValue;
   }
-  if (p.K <= 64) return launch<32, 64, 1, AK, BKM, T, OutT, EPI>(p, nz, st);
-  if (p.K <= 128) return launch<32, 128, 1, AK, BKM, T, OutT, EPI>(p, nz, st);
-  return launch<32, 256, 1, AK, BKM, T, OutT, EPI>(p, nz, st);
+  if (((p.M + 63) / 64) * ((p.N + 63) / 64) * nz >= 256) {
+    if (p.K <= 16) return launch<64, 16, 2, AK, BKM, false, T, OutT, EPI>(p, nz, st);
+    return launch<64, 32, 2, AK, BKM, false, T, OutT, EPI>(p, nz, st);
+  }
+  if (p.K <= 64) return launch<32, 64, 1, AK, BKM, false, T, OutT, EPI>(p, nz, st);
+  if (p.K <= 128) return launch<32, 128, 1, AK, BKM, false, T, OutT, EPI>(p, nz, st);
+  return launch<32, 256, 1, AK, BKM, false, T, OutT, EPI>(p, nz, st);
 }
 
 template <typename T, typename OutT>
@@ -286,7 +301,7 @@ hipError_t pick_layout(const Gemm& g, F32P& p, int nz, hipStream_t st) {
 bool f32_gelu_applies(const Gemm& g) {
   const bool fwd = g.epi == EPI_GELU;
   return g.dtype == DT_F32 && (fwd || g.epi == EPI_GELU_BWD) && !g.R && g.nb * g.nh == 1 && g.a_kmajor && g.b_kmajor == fwd && g.C2 &&
-         (fwd || (g.C && !g.bias));
+         (fwd || (g.C && !g.bias)) && f32_fits(true, g.lda, sizeof(float)) && f32_fits(fwd, g.ldb, sizeof(float));
 }
 
 hipError_t gemm_f32(const Gemm& g, hipStream_t st) {

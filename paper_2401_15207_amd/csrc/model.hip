@@ -1414,16 +1414,21 @@ hift_status fetch_state(hift_model* M, int gid, int spare, bool* done) {
   if (!*done) return HIFT_OK;
   // order the copy after the write-backs it depends on, and only those: of what the slot held, and of this group's own state
   emptied.push_back(gid);
-  for (int g : emptied) {
-    if (M->gev[g].d2h_pending) HIP_TRY(hipStreamWaitEvent(M->hs, M->gev[g].d2h, 0));
-    M->gev[g].d2h_pending = false;
-  }
-  ST_TRY(M->pin.pieces((size_t)plo * M->n_move * 4, (size_t)cnt * M->n_move * 4, [&](unsigned char* h, size_t n, size_t at) {
-    return state_copy(M, reinterpret_cast<unsigned char*>(held_state(M, gid)) + at, h, n, true);
-  }));
-  M->h2d_bytes += (uint64_t)cnt * M->n_move * 4;
-  HIP_TRY(hipEventRecord(M->gev[gid].h2d, M->hs));
-  return HIFT_OK;
+  auto queue = [&]() -> hift_status {
+    for (int g : emptied) {
+      if (M->gev[g].d2h_pending) HIP_TRY(hipStreamWaitEvent(M->hs, M->gev[g].d2h, 0));
+      M->gev[g].d2h_pending = false;
+    }
+    ST_TRY(M->pin.pieces((size_t)plo * M->n_move * 4, (size_t)cnt * M->n_move * 4, [&](unsigned char* h, size_t n, size_t at) {
+      return state_copy(M, reinterpret_cast<unsigned char*>(held_state(M, gid)) + at, h, n, true);
+    }));
+    M->h2d_bytes += (uint64_t)cnt * M->n_move * 4;
+    HIP_TRY(hipEventRecord(M->gev[gid].h2d, M->hs));
+    return HIFT_OK;
+  };
+  const hift_status st = queue();
+  if (st != HIFT_OK) M->held.drop(gid);
+  return st;
 }
 
 hift_status sync_all(hift_model* M);

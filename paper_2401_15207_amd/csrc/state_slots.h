@@ -47,6 +47,14 @@ class StateSlots {
     if (g != last_[0]) { last_[1] = last_[0]; last_[0] = g; }
   }
 
+  // Group g has no place any more (its copy could not be queued).
+  void drop(int g) {
+    if (!holds(g)) return;
+    std::vector<int>& v = in_[place_[g].slot];
+    v.erase(std::find(v.begin(), v.end(), g));
+    place_[g] = Place();
+  }
+
   // A place for `floats` values of group g, kept from now on; false if that takes a slot with a kept group, or the one of group
   // `spare` (-1: none).  `emptied` receives the groups whose place is given up for it.
   bool put(int g, int64_t floats, int spare, std::vector<int>& emptied) {
@@ -58,10 +66,7 @@ class StateSlots {
       for (int o : in_[q])
         if (o != g) { emptied.push_back(o); place_[o].slot = -1; }
     }
-    if (holds(g)) {  // what it had is given up too; the caller orders the copy behind its write-back
-      std::vector<int>& v = in_[place_[g].slot];
-      v.erase(std::find(v.begin(), v.end(), g));
-    }
+    drop(g);  // what it had is given up too; the caller orders the copy behind its write-back
     if (q != open_ || fill_[q] + floats > cap_) {
       in_[q].clear();
       fill_[q] = 0;

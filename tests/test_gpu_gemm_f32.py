@@ -59,3 +59,21 @@ def test_bias_residual_and_batches():
         H.kernel_gemm(0, 1, 1, 0, M, N, K, A, K, B, K, C, N, BI, R, batch=batch, sa=M * K, sb=N * K, sc=M * N)
         want = np.stack([(chain(a[z], b[z]) + bias) + r[z] for z in range(batch)])
         assert np.array_equal(C.cpu().numpy(), want)
+
+
+def test_rows_too_far_apart_for_32_bit_offsets():
+    import torch
+
+    import paper_2401_15207_amd as H
+    rng = np.random.default_rng(5)
+    M, N, K = 35, 3, 71
+    a, b = (rng.standard_normal((r, K)).astype(np.float32) for r in (M, N))
+    want = chain(a, b)
+    for ak, bk, lda, ldb in [(1, 1, K, 8_400_000), (1, 0, K, 2_100_000), (0, 1, 2_100_000, K), (0, 0, M, 2_100_000)]:
+        A = torch.zeros(M if ak else K, lda, device="cuda")
+        B = torch.zeros(N if bk else K, ldb, device="cuda")
+        A[:, :K if ak else M] = torch.from_numpy(a if ak else a.T.copy()).cuda()
+        B[:, :K if bk else N] = torch.from_numpy(b if bk else b.T.copy()).cuda()
+        C = torch.empty(M, N, device="cuda")
+        H.kernel_gemm(0, ak, bk, 0, M, N, K, A, lda, B, ldb, C, N)
+        assert np.array_equal(C.cpu().numpy(), want), (ak, bk)
