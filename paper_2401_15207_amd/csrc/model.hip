@@ -1886,31 +1886,7 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
 
   // ---- state movement, queued ahead of the compute (Algorithm 1 step i, issued early) ----
   if (moving) {
-    bool done = true;
-    if (!M->held.holds(gid)) {
-      M->held.let_go();  // what was fetched ahead for another order gives way
-      ST_TRY(fetch_state(M, gid, -1, &done));
-    }
-    M->held.keep(gid);
-    // Fetch the state of the groups that the schedule visits next, as far ahead as the slots have room.  The next one always gets
-    // its place; further ones leave the state of the group updated last where it is (a caller may step it again), and never are
-    // groups whose own update is so recent that their write-back would hold up the copies behind it.
-    const bool on_schedule = M->order[M->t % M->k] == gid;
-    const int ahead = M->k > NSLOT + 1 ? M->k - NSLOT : 1;
-    for (int j = 1; on_schedule && done && j <= ahead; ++j) {
-      const int next = M->order[(M->t + j) % M->k];
-      if (M->held.kept(next)) continue;
-      if (j == 1 && M->held.holds(next) && (M->k <= NSLOT || M->held.recent(next))) {
-        M->held.keep(next);
-        continue;
-      }
-      ST_TRY(fetch_state(M, next, j == 1 ? -1 : M->held.last(), &done));
-      if (!done && j == 1) {
-        M->held.let_go();
-        M->held.keep(gid);
-        ST_TRY(fetch_state(M, next, -1, &done));
-      }
-    }
+    ST_TRY(M->held.advance(gid, M->order, M->t, [&](int g, int spare, bool* done) { return fetch_state(M, g, spare, done); }));
   }
 
   ST_TRY(forward(M, bt, ulo));

@@ -29,6 +29,17 @@ extern "C" int last() { return s.last(); }
 extern "C" void keep(int g) { s.keep(g); }
 extern "C" void let_go() { s.let_go(); }
 extern "C" void updated(int g) { s.updated(g); }
+extern "C" int advance(int gid, const int* order, int k, int64_t t, const int64_t* floats, int* fetched, int* lost) {
+  int n = 0;  // lost[g]: g's place was given up
+  std::vector<int> v;
+  s.advance(gid, std::vector<int32_t>(order, order + k), t, [&](int g, int spare, bool* done) {
+    if ((*done = s.put(g, floats[g], spare, v))) fetched[n++] = g;
+    for (int o : v) lost[o] = 1;
+    return 0;
+  });
+  s.updated(gid);
+  return n;
+}
 """
 
 
@@ -43,6 +54,7 @@ def slots(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "t.so"))
     lib.at.restype = ctypes.c_int64
     lib.put.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]
+    lib.advance.argtypes = [ctypes.c_int, ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
     lib.reset.argtypes = [ctypes.c_int, ctypes.c_int64]
     return lib
 
@@ -105,3 +117,53 @@ def test_a_kept_group_leaves_room_for_another_whatever_the_sizes(slots):
                 assert slots.put(cur, size[cur], -1, buf) >= 0
             assert slots.put((cur + 1) % 9, size[(cur + 1) % 9], -1, buf) >= 0 and slots.slot(cur) >= 0
             slots.updated(cur)
+
+
+SIZES = {"embeddings": [1000] + [160] * 12 + [100], "deep": [1000] + [160] * 33, "alike": [160] * 34, "few": [160] * 5, "four": [160] * 4}
+ORDERS = {"on": lambda i, rng: "next", "one in ten": lambda i, rng: "any" if rng.random() < 0.1 else "next",
+          "every other": lambda i, rng: "any" if i % 2 else "next", "twice": lambda i, rng: "same" if i % 2 else "next", "any": lambda i, rng: "any"}
+
+
+def one_group_to_a_slot(size, groups):
+    """Values copied in where every slot holds one group and only the next of the schedule is fetched ahead."""
+    held, at, k, copied = [-1] * 3, 0, len(size), 0
+    for t, g in enumerate(groups):
+        if g in held:
+            at = held.index(g)
+        else:
+            held[at] = g
+            copied += size[g]
+        following = (t + 1) % k
+        if g == t % k and following not in held:
+            held[(at + 1) % 3] = following
+            copied += size[following]
+        at = (at + 1) % 3
+    return copied
+
+
+@pytest.mark.parametrize("sizes", SIZES)
+@pytest.mark.parametrize("visits", ORDERS)
+def test_steps_off_the_schedule_do_not_copy_the_same_state_again(slots, sizes, visits):
+    """Groups in the schedule's order, in another one, and mixed: a step queues its own group, if need be, and at most two more;
+    nothing is copied again that a slot still holds unused; and in all hardly more than with one group to a slot (where there are
+    hardly more groups than slots, which one is given up is luck: up to half more)."""
+    size, rng = SIZES[sizes], random.Random(7)
+    k = len(size)
+    order, floats, buf = (ctypes.c_int * k)(*range(k)), (ctypes.c_int64 * k)(*size), (ctypes.c_int * (2 * k))()
+    slots.reset(k, (max(size) + 63) // 64 * 64)
+    groups, fresh, copied = [], set(), 0  # fresh: copied in and not updated since
+    for t in range(40 * k):
+        kind = ORDERS[visits](t, rng)
+        g = t % k if kind == "next" else groups[-1] if kind == "same" else rng.randrange(k)
+        lost = (ctypes.c_int * k)()
+        fetched = buf[:slots.advance(g, order, k, t, floats, buf, lost)]
+        assert slots.slot(g) >= 0 and (g == t % k or set(fetched) <= {g}) and len([o for o in fetched if o != g]) <= 2
+        fresh -= {o for o in range(k) if lost[o]}
+        assert not set(fetched) & fresh, (t, g, fetched)
+        copied += sum(size[o] for o in fetched)
+        fresh = (fresh | {o for o in fetched if slots.slot(o) >= 0}) - {g}
+        groups.append(g)
+    plain, updated = one_group_to_a_slot(size, groups), sum(size[g] for g in groups)
+    if visits == "on":
+        assert copied - updated <= 3 * max(size)  # what is fetched ahead at the end
+    assert copied <= (1.5 if k <= 5 else 1.1) * plain + 3 * max(size)
