@@ -1,4 +1,4 @@
-// Attention of fp32 models (and of nothing else: bf16 has attention.hip): heads up to 64 wide, sequences up to 256.
+// Attention of fp32 models (and of nothing else: bf16 has attention.hip): heads up to 64 wide, sequences up to 64.
 //
 // A wavefront owns 16 query rows of one (batch, head).  Their scores against all keys stay in its registers: in the layout of
 // v_mfma_f32_16x16x4_f32 lane l holds, of row l % 16, four consecutive keys of every sixteen; an exchange among the four lanes of a row
@@ -7,11 +7,10 @@
 // What bounds it: launches.  In fp32 models of a few tokens a launch costs the host 3 to 4 us and the GPU 3; scores, softmax and context
 // were three of them a layer, and seven in the backward pass, three now (this query-major kernel leaves P and dS to two contractions
 // for dV and dK).  With GELU in the contractions' epilogues and the column sums in one launch each, a sweep of two layers, 2 x 32 tokens
-// of width 64, takes 155 launches instead of 217: 1.14 -> 0.83 ms.  Four layers, 8 x 256 tokens, heads of 64: 9.3 -> 5.4 ms, both with
-// gemm_f32_k's part.
+// of width 64, takes 155 launches instead of 217: 1.14 -> 0.83 ms, gemm_f32_k's part included.
 // Every sum has the order that the separate contractions and softmax kernels give it, so the bits are theirs: chains over ascending
-// k, and a row's sums in the tree of a wavefront whose lanes hold four consecutive keys each (QUADS: S a multiple of four) or every 64th
-// key.  AdamW makes a full step of a gradient that is nothing but rounding (a key's bias), so other bits would show.
+// k, and a row's sums in the tree of a wavefront whose lanes hold four consecutive keys each (QUADS: S a multiple of four) or one.  AdamW
+// makes a full step of a gradient that is nothing but rounding (a key's bias), so other bits would show.
 #include "common.h"
 #include "kernels.h"
 
@@ -73,7 +72,7 @@ __device__ __forceinline__ f32x4 exchange(f32x4 v, int lane) {
 }
 
 // Sum over a row of a (DOT: of a b), in the order of softmax_fwd_reg_k and softmax_bwd_reg_k (QUADS) or softmax_fwd_k and
-// softmax_bwd_k: there the lane of key j is j / 4 or j % 64, here those lanes are (block, lane group) or (block % 4, lane group, element).
+// softmax_bwd_k: there the lane of key j is j / 4 or j, here those lanes are (block, lane group) or (block, lane group, element).
 template <int NB, bool QUADS, bool DOT>
 __device__ __forceinline__ float row_sum(const f32x4 (&a)[NB], const f32x4 (&b)[NB]) {
   auto add = [&](float t, int c, int e) __attribute__((always_inline)) { return DOT ? fmaf(a[c][e], b[c][e], t) : t + a[c][e]; };
@@ -94,18 +93,13 @@ __device__ __forceinline__ float row_sum(const f32x4 (&a)[NB], const f32x4 (&b)[
     v += __shfl_xor(v, 16, 64);
     return v;
   } else {
-    constexpr int NC = NB < 4 ? NB : 4;
-    float t[NC][4];
+    float t[NB][4];
 #pragma unroll
-    for (int c0 = 0; c0 < NC; ++c0)
+    for (int c = 0; c < NB; ++c)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        t[c0][e] = 0.f;
+      for (int e = 0; e < 4; ++e) t[c][e] = add(0.f, c, e);
 #pragma unroll
-        for (int c = c0; c < NB; c += 4) t[c0][e] = add(t[c0][e], c, e);
-      }
-#pragma unroll
-    for (int w = NC / 2; w > 0; w /= 2)
+    for (int w = NB / 2; w > 0; w /= 2)
 #pragma unroll
       for (int c = 0; c < w; ++c)
 #pragma unroll
@@ -246,9 +240,7 @@ template <int NK, bool BWD>
 void launch(const AttF& p, int B, hipStream_t st) {
   const dim3 grid((unsigned)((p.S + 15) / 16), (unsigned)(B * p.H));
   if (p.S <= 32) launch_nb<NK, 2, BWD>(p, grid, st);
-  else if (p.S <= 64) launch_nb<NK, 4, BWD>(p, grid, st);
-  else if (p.S <= 128) launch_nb<NK, 8, BWD>(p, grid, st);
-  else launch_nb<NK, 16, BWD>(p, grid, st);
+  else launch_nb<NK, 4, BWD>(p, grid, st);
 }
 template <bool BWD>
 hipError_t run(const AttF& p, int B, hipStream_t st) {
@@ -261,9 +253,13 @@ bool al16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
 
 }  // namespace
 
-// Sequences of up to 256 (a row's scores and their gradients are 128 registers), heads in whole 16-byte pieces.
+// Sequences of up to 64 tokens, heads in whole 16-byte pieces.  Beyond 64 the separate contractions and softmax are the faster way
+// whatever the number of heads: a wavefront here walks its blocks of keys one after the other and there are only S / 16 a head, while they
+// spread over many tiles.  Sweeps of four layers, one kernel / separate ones, ms: heads of 16, 1 x 8 of them, 64 tokens 1.76 / 1.89, 128
+// 2.04 / 1.95, 256 2.51 / 2.11; heads of 64, 1 x 2, 32 tokens 1.69 / 1.85, 64 1.90 / 1.90, 100 2.23 / 1.99, 256 3.08 / 2.04; 4 x 8,
+// 32 2.86 / 2.97, 64 3.35 / 3.30, 256 6.76 / 5.96.
 bool attention_f32_applies(int dt, int B, int H, int S, int hd, int64_t ld, int64_t ldc, const void* qkv, const void* ctx) {
-  return dt == DT_F32 && S >= 1 && S <= 256 && hd >= 4 && hd <= 64 && hd % 4 == 0 && ld % 4 == 0 && ldc % 4 == 0 && al16(qkv) && al16(ctx) &&
+  return dt == DT_F32 && S >= 1 && S <= 64 && hd >= 4 && hd <= 64 && hd % 4 == 0 && ld % 4 == 0 && ldc % 4 == 0 && al16(qkv) && al16(ctx) &&
          (int64_t)B * H <= 65535;
 }
 hipError_t attention_fwd_f32(int B, int H, int S, int hd, bool causal, const void* qkv, int64_t ld, void* ctx, int64_t ldc, hipStream_t st) {

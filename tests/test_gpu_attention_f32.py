@@ -34,7 +34,8 @@ def _compare_gradients(wl, seed):
         assert np.linalg.norm((got - want)[ones]) <= TOL * np.linalg.norm(want[ones]) + np.linalg.norm(rounding[ones & moved]), t
 
 
-# sixteens of queries and keys, powers of two of them (32, 64, 128, 256), heads of less than, one, two and four sixteens
+# sixteens of queries and keys, powers of two of them (32, 64; longer sequences take separate kernels), heads of less than, one, two and four
+# sixteens
 @pytest.mark.parametrize("arch,batch,seq,heads,hd", [
     (0, 2, 1, 2, 16), (1, 3, 5, 2, 4), (0, 1, 16, 3, 16), (1, 2, 17, 3, 20), (2, 2, 32, 2, 32), (0, 2, 33, 2, 32), (1, 1, 64, 2, 36), (2, 1, 65, 2, 64),
     (0, 1, 127, 2, 48), (1, 1, 128, 1, 64), (0, 2, 129, 2, 16), (1, 1, 250, 2, 64), (2, 1, 256, 2, 64), (0, 1, 257, 2, 16), (0, 2, 24, 2, 68)])
@@ -79,3 +80,17 @@ def test_column_sums_of_any_number_of_rows(batch, seq):
     wl = dict(arch=1, n_layers=1, d_model=68, n_heads=1, d_ffn=20, vocab=64, max_seq=max(seq, 8), n_classes=2, norm_eps=1e-5, rope_base=10000.0,
               dtype=0, batch=batch, seq=seq, m=1, strategy="top2down", opt=SGD1)
     _compare_gradients(wl, 47)
+
+
+@pytest.mark.parametrize("seq,hd,one_kernel", [(64, 16, True), (65, 16, False), (64, 64, True), (128, 64, False), (256, 32, False), (64, 68, False)])
+def test_one_kernel_up_to_64_tokens(seq, hd, one_kernel):
+    """Longer sequences take the separate contractions and softmax kernels, which are faster there."""
+    import paper_2401_15207_amd as H
+    wl = dict(WORKLOADS["C1"], batch=2, d_model=2 * hd, n_heads=2, d_ffn=40, max_seq=256)
+    gpu = H.HiftModel(model_config(wl), SGD1, 1, 2, seq)
+    gpu.set_group_schedule("bottom2up", 1)
+    gpu.profile_enable(True)
+    gpu.step(*to_dev(*make_batch(dict(wl, seq=seq), 43, 1)), 0)
+    rows = gpu.profile_read_rowwise()
+    launches = [n for name, (n, _ms, _bytes) in rows.items() if "softmax" in name]
+    assert len(launches) == 2 and all((n == 0) == one_kernel for n in launches), rows
