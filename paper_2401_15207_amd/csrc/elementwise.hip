@@ -80,28 +80,31 @@ __global__ void __launch_bounds__(BLK) embed_fwd_k(const int32_t* __restrict__ t
 // their part of the table row once; the workgroups of later occurrences have nothing to do.  (Rows of tokens
 // that do not occur are zeroed by the caller; with `add` the row's previous content is kept and added to.)
 // The positions holding the token are first collected, in order, into a list in LDS (a frequent token of a
-// Zipf-distributed batch occurs hundreds of times), 2048 tokens at a time that are all requested before the first is looked at, then
-// only those rows are read.  What bounds it is the workgroup of the most frequent token, a chain of sums over its rows: EMB_U rows are
+// Zipf-distributed batch occurs hundreds of times), R BLK tokens at a time that are all requested before the first is looked at, then
+// only those rows are read.  What bounds it is the workgroup of the most frequent token, a chain of sums over its rows: U rows are
 // requested together, in pieces of V values a thread where rows are aligned for it.  2048 tokens x 4096 by the bounded Zipf law
-// (exponent 1.1): 414 us with one row in flight, EMB_TIME now.
-constexpr int EMB_R = 8, EMB_U = 16;  // rounds of BLK tokens per list; rows in flight
-template <typename T, int V>
+// (exponent 1.1): 310 us with one row in flight, 39 now.
+// Where tokens hardly repeat, what bounds it is the search, so that wavefronts count: R no larger than the batch needs (256 tokens of width
+// 768: 4.8 us with R = 8, 4.2 with 1), and 8 rows in flight where 16 would take more than 64 registers: values one by one (16384 tokens of
+// width 770: 174 us with 16, 133 with 8), and fp32 in large batches (width 256: 136 and 126).
+template <typename T, int V, int R>
 __global__ void __launch_bounds__(BLK) embed_bwd_tok_k(const int32_t* __restrict__ tokens, int64_t T_, int d, int vocab,
                                                         const T* __restrict__ dx, float* __restrict__ g_tok, bool add) {
-  constexpr int NW = BLK / 64, G = 4 / V;  // pieces of V columns a thread sums
-  __shared__ int list[EMB_R * BLK];
-  __shared__ int wcount[EMB_R][NW];
+  constexpr int NW = BLK / 64, G = 4 / V;                           // pieces of V columns a thread sums
+  constexpr int U = V == 1 || (sizeof(T) == 4 && R == 8) ? 8 : 16;  // rows in flight
+  __shared__ int list[R * BLK];
+  __shared__ int wcount[R][NW];
   const int64_t p = blockIdx.x;
   const int j0 = (int)blockIdx.y * (BLK * 4);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   auto clamp = [vocab](int id) { return id < 0 ? 0 : (id >= vocab ? vocab - 1 : id); };
   const int id = clamp(tokens[p]);
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  auto add_rows = [&](auto U_, int i) __attribute__((always_inline)) {  // rows list[i .. i + U), requested together, added in order
-    constexpr int U = decltype(U_)::value;
-    Vec<T, V> x[U][G];
+  auto add_rows = [&](auto N_, int i) __attribute__((always_inline)) {  // rows list[i .. i + N), requested together, added in order
+    constexpr int N = decltype(N_)::value;
+    Vec<T, V> x[N][G];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < N; ++u) {
       const T* dr = dx + (int64_t)list[i + u] * d;
 #pragma unroll
       for (int q = 0; q < G; ++q) {
@@ -110,27 +113,27 @@ __global__ void __launch_bounds__(BLK) embed_bwd_tok_k(const int32_t* __restrict
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < N; ++u)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[e] += to_f32(x[u][e / V].v[e % V]);
   };
-  for (int64_t c0 = 0; c0 < T_; c0 += EMB_R * BLK) {
-    int tk[EMB_R];
-    unsigned long long m[EMB_R];
+  for (int64_t c0 = 0; c0 < T_; c0 += R * BLK) {
+    int tk[R];
+    unsigned long long m[R];
 #pragma unroll
-    for (int r = 0; r < EMB_R; ++r) {
+    for (int r = 0; r < R; ++r) {
       const int64_t q = c0 + r * BLK + threadIdx.x;
       tk[r] = tokens[q < T_ ? q : T_ - 1];
     }
 #pragma unroll
-    for (int r = 0; r < EMB_R; ++r) {
+    for (int r = 0; r < R; ++r) {
       m[r] = __ballot(c0 + r * BLK + threadIdx.x < T_ && clamp(tk[r]) == id);
       if (lane == 0) wcount[r][wave] = __popcll(m[r]);
     }
     __syncthreads();
     int n = 0;
 #pragma unroll
-    for (int r = 0; r < EMB_R; ++r) {
+    for (int r = 0; r < R; ++r) {
       int before = n;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
@@ -142,7 +145,7 @@ __global__ void __launch_bounds__(BLK) embed_bwd_tok_k(const int32_t* __restrict
     __syncthreads();
     if (n > 0 && list[0] < p) return;  // a workgroup further up has this token
     int i = 0;
-    for (; i + EMB_U <= n; i += EMB_U) add_rows(std::integral_constant<int, EMB_U>{}, i);
+    for (; i + U <= n; i += U) add_rows(std::integral_constant<int, U>{}, i);
     for (; i + 4 <= n; i += 4) add_rows(std::integral_constant<int, 4>{}, i);
     for (; i < n; ++i) add_rows(std::integral_constant<int, 1>{}, i);
     __syncthreads();  // the list is rebuilt in the next batch
@@ -1125,20 +1128,24 @@ hipError_t embed_fwd(int dt, const int32_t* tokens, int64_t T_, int S, int d, in
   LAUNCH_CHECK();
 }
 
+template <typename T>
+static void launch_embed_bwd(const int32_t* tokens, int64_t T_, int S, int d, int V_, const T* dx, float* g_tok, float* g_pos, bool add, hipStream_t st) {
+  const dim3 grid((unsigned)T_, (unsigned)cdiv(d, BLK * 4));
+  auto rounds = [&](auto V) {
+    constexpr int P = decltype(V)::value;
+    if (T_ <= BLK) embed_bwd_tok_k<T, P, 1><<<grid, BLK, 0, st>>>(tokens, T_, d, V_, dx, g_tok, add);
+    else if (T_ <= 4 * BLK) embed_bwd_tok_k<T, P, 4><<<grid, BLK, 0, st>>>(tokens, T_, d, V_, dx, g_tok, add);
+    else embed_bwd_tok_k<T, P, 8><<<grid, BLK, 0, st>>>(tokens, T_, d, V_, dx, g_tok, add);
+  };
+  if (d % 4 == 0 && aligned16(dx)) rounds(std::integral_constant<int, 4>{});  // rows in whole pieces of four
+  else rounds(std::integral_constant<int, 1>{});
+  if (g_pos) embed_bwd_pos_k<T><<<dim3(S), BLK, 0, st>>>((int)(T_ / S), S, d, dx, g_pos);
+}
 hipError_t embed_bwd(int dt, const int32_t* tokens, int64_t T_, int S, int d, int V_, const void* dx,
                      float* g_tok, float* g_pos, bool add, hipStream_t st) {
   if (T_ == 0) return hipSuccess;
-  const dim3 tok_grid((unsigned)T_, (unsigned)cdiv(d, BLK * 4));
-  const bool four = d % 4 == 0 && aligned16(dx);  // rows in whole pieces of four
-  if (dt == DT_F32) {
-    if (four) embed_bwd_tok_k<float, 4><<<tok_grid, BLK, 0, st>>>(tokens, T_, d, V_, (const float*)dx, g_tok, add);
-    else embed_bwd_tok_k<float, 1><<<tok_grid, BLK, 0, st>>>(tokens, T_, d, V_, (const float*)dx, g_tok, add);
-    if (g_pos) embed_bwd_pos_k<float><<<dim3(S), BLK, 0, st>>>((int)(T_ / S), S, d, (const float*)dx, g_pos);
-  } else {
-    if (four) embed_bwd_tok_k<bf16, 4><<<tok_grid, BLK, 0, st>>>(tokens, T_, d, V_, (const bf16*)dx, g_tok, add);
-    else embed_bwd_tok_k<bf16, 1><<<tok_grid, BLK, 0, st>>>(tokens, T_, d, V_, (const bf16*)dx, g_tok, add);
-    if (g_pos) embed_bwd_pos_k<bf16><<<dim3(S), BLK, 0, st>>>((int)(T_ / S), S, d, (const bf16*)dx, g_pos);
-  }
+  if (dt == DT_F32) launch_embed_bwd<float>(tokens, T_, S, d, V_, (const float*)dx, g_tok, g_pos, add, st);
+  else launch_embed_bwd<bf16>(tokens, T_, S, d, V_, (const bf16*)dx, g_tok, g_pos, add, st);
   LAUNCH_CHECK();
 }
 

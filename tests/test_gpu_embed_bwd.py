@@ -1,4 +1,5 @@
-"""Gradient of the token table where the lists of positions are at their edges: a row's positions spread over two batches of tokens,
+"""Gradient of the token table where the lists of positions are at their edges: a row's positions spread over two batches of tokens, batches as long as the
+lists of each length,
 their number around the rows read together, widths with and without whole pieces of four, a last piece of columns partly empty.
 Against the oracle; plain SGD at rate 1 writes the gradient into the weights."""
 import numpy as np
@@ -13,11 +14,12 @@ SGD1 = dict(kind="sgd", lr=1.0, beta1=0, beta2=0, eps=0, weight_decay=0.0, momen
 
 
 @pytest.mark.parametrize("d,heads,batch,seq,tied", [(6, 1, 29, 73, 0), (8, 2, 29, 73, 0), (8, 2, 29, 73, 1), (1032, 3, 2, 24, 0), (1032, 3, 2, 24, 1),
-                                                    (1026, 3, 2, 24, 0)])
+                                                    (1026, 3, 2, 24, 0),
+                                                    (8, 2, 8, 32, 0), (6, 1, 1, 257, 0), (6, 1, 4, 256, 0), (8, 2, 5, 205, 0)])
 def test_rows_of_repeated_tokens(d, heads, batch, seq, tied):
     wl = dict(arch=0, n_layers=1, d_model=d, n_heads=heads, d_ffn=16, vocab=23, max_seq=seq, n_classes=0, norm_eps=1e-5,
               rope_base=10000.0, dtype=0, tie_embeddings=tied, batch=batch, seq=seq, m=1, strategy="bottom2up", opt=SGD1)
-    # token v occurs v times (0, 1, ... 20: on both sides of 4 and 16 rows at a time), token 21 at the very end, 22 everywhere else
+    # token v occurs v times (0, 1, ... 20: on both sides of 4, 8 and 16 rows at a time), token 21 at the very end, 22 everywhere else
     rng = np.random.default_rng(3)
     n = batch * seq
     tok = np.full(n, 22, np.int32)
