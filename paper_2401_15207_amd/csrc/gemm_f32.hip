@@ -271,13 +271,17 @@ hipError_t launch(F32P& p, int nz, hipStream_t st) {
 
 // 64 x 64 tiles where they give every compute unit one (1024 x 1024, k 256: 10.4 us), else 32 x 32 (512 x 1024: 7.9), whose passes are no
 // longer than k needs: elements past its end cost their loads.
+// WIDE, whose loads are bounded one by one, takes 32 x 32 tiles also there (1024 x 1024, k 1024 in rows of 2.2 M values 39 us, 64 x 64: 47; k 256
+// 12.4 and 12.8), but for a single pass of 16 k (5.6 us, 64 x 64: 4.2).
 template <bool AK, bool BKM, typename T, typename OutT, int EPI = EPI_NONE>
 hipError_t pick(F32P& p, int nz, hipStream_t st) {
+  const bool fills = ((p.M + 63) / 64) * ((p.N + 63) / 64) * nz >= 256;
   if (!f32_fits(AK, p.lda, sizeof(T)) || !f32_fits(BKM, p.ldb, sizeof(T))) {
-    if constexpr (EPI == EPI_NONE) return launch<32, 64, 1, AK, BKM, true, T, OutT, EPI>(p, nz, st);
-    return hipErrorInvalidValue;
+    if constexpr (EPI != EPI_NONE) return hipErrorInvalidValue;
+    else if (fills && p.K <= 16) return launch<64, 16, 2, AK, BKM, true, T, OutT, EPI>(p, nz, st);
+    else return launch<32, 64, 1, AK, BKM, true, T, OutT, EPI>(p, nz, st);
   }
-  if (((p.M + 63) / 64) * ((p.N + 63) / 64) * nz >= 256) {
+  if (fills) {
     if (p.K <= 16) return launch<64, 16, 2, AK, BKM, false, T, OutT, EPI>(p, nz, st);
     return launch<64, 32, 2, AK, BKM, false, T, OutT, EPI>(p, nz, st);
   }

@@ -66,10 +66,10 @@ def test_rows_too_far_apart_for_32_bit_offsets():
 
     import paper_2401_15207_amd as H
     rng = np.random.default_rng(5)
-    M, N, K = 35, 3, 71
-    a, b = (rng.standard_normal((r, K)).astype(np.float32) for r in (M, N))
-    want = chain(a, b)
-    for ak, bk, lda, ldb in [(1, 1, K, 8_400_000), (1, 0, K, 2_100_000), (0, 1, 2_100_000, K), (0, 0, M, 2_100_000)]:
+    for M, N, K, ak, bk, lda, ldb in [(35, 3, 71, 1, 1, 71, 8_400_000), (35, 3, 71, 1, 0, 71, 2_100_000), (35, 3, 71, 0, 1, 2_100_000, 71),
+                                      (35, 3, 71, 0, 0, 35, 2_100_000), (1000, 1030, 13, 0, 1, 2_100_000, 13), (1030, 1000, 16, 1, 0, 16, 2_100_000)]:
+        a, b = (rng.standard_normal((r, K)).astype(np.float32) for r in (M, N))
+        want = chain(a, b)
         A = torch.zeros(M if ak else K, lda, device="cuda")
         B = torch.zeros(N if bk else K, ldb, device="cuda")
         A[:, :K if ak else M] = torch.from_numpy(a if ak else a.T.copy()).cuda()
