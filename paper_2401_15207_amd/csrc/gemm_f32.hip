@@ -183,29 +183,7 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
   const OutT* R = p.R ? reinterpret_cast<const OutT*>(p.R) + zb * p.sc1 + zh * p.sc2 : nullptr;
   const T* bias = reinterpret_cast<const T*>(p.bias);
   const int64_t row0 = m0 + wm * WT + (lane & 15), col0 = n0 + wn * WT + (lane >> 4) * 4;
-  if constexpr (EPI != EPI_NONE) {  // no residual, no batch; the library's erff, as the separate kernels take it: the same bits
-    float* C2 = reinterpret_cast<float*>(p.C2);
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int64_t row = row0 + i * 16;
-      if (row >= p.M) continue;
-#pragma unroll
-      for (int j = 0; j < MT; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t col = col0 + j * 16 + e;
-          if (col >= p.N) continue;
-          const float v = acc[i][j][e] + (bias ? to_f32(bias[col]) : 0.f);
-          if constexpr (EPI == EPI_GELU) {
-            if (p.C) C[row * p.ldc + col] = v;
-            C2[row * p.ldc2 + col] = gelu_f(v);
-          } else {
-            C[row * p.ldc + col] = v * gelu_df(C2[row * p.ldc2 + col]);
-          }
-        }
-    }
-    return;
-  }
+  float* C2 = reinterpret_cast<float*>(p.C2);  // of the GELU epilogues: fp32, no residual, no batch; the library's erff, as the separate kernels take it: the same bits
   if (p.vec && m0 + BT <= p.M && n0 + BT <= p.N) {
 #pragma unroll
     for (int j = 0; j < MT; ++j) {
@@ -223,6 +201,20 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
           const Vec<OutT, 4> t = *reinterpret_cast<const Vec<OutT, 4>*>(R + row * p.ldr + col0 + j * 16);
 #pragma unroll
           for (int e = 0; e < 4; ++e) v[e] += to_f32(t.v[e]);
+        }
+        if constexpr (EPI != EPI_NONE) {
+          Vec<float, 4>* const c2 = reinterpret_cast<Vec<float, 4>*>(C2 + row * p.ldc2 + col0 + j * 16);
+          Vec<float, 4> t;
+          if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t.v[e] = gelu_f(v[e]);
+            *c2 = t;
+            if (!p.C) continue;
+          } else {
+            t = *c2;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] *= gelu_df(t.v[e]);
+          }
         }
         Vec<OutT, 4> out;
 #pragma unroll
@@ -244,6 +236,12 @@ __global__ void __launch_bounds__(256) gemm_f32_k(F32P p) {
         if (col >= p.N) continue;
         float v = acc[i][j][e] + (bias ? to_f32(bias[col]) : 0.f);
         if (R) v += to_f32(R[row * p.ldr + col]);
+        if constexpr (EPI == EPI_GELU) {
+          C2[row * p.ldc2 + col] = gelu_f(v);
+          if (!p.C) continue;
+        } else if constexpr (EPI == EPI_GELU_BWD) {
+          v *= gelu_df(C2[row * p.ldc2 + col]);
+        }
         C[row * p.ldc + col] = from_f32<OutT>(v);
       }
     }
@@ -292,9 +290,6 @@ hipError_t pick(F32P& p, int nz, hipStream_t st) {
 
 template <typename T, typename OutT>
 hipError_t pick_layout(const Gemm& g, F32P& p, int nz, hipStream_t st) {
-  const auto fours = [](const void* q, size_t size) { return reinterpret_cast<uintptr_t>(q) % (4 * size) == 0; };
-  p.vec = g.ldc % 4 == 0 && g.sc1 % 4 == 0 && g.sc2 % 4 == 0 && fours(g.C, sizeof(OutT)) && (!g.R || (g.ldr % 4 == 0 && fours(g.R, sizeof(OutT)))) &&
-          (!g.bias || fours(g.bias, sizeof(T)));
   if (g.a_kmajor) return g.b_kmajor ? pick<true, true, T, OutT>(p, nz, st) : pick<true, false, T, OutT>(p, nz, st);
   return g.b_kmajor ? pick<false, true, T, OutT>(p, nz, st) : pick<false, false, T, OutT>(p, nz, st);
 }
@@ -315,6 +310,9 @@ hipError_t gemm_f32(const Gemm& g, hipStream_t st) {
   p.bias = g.bias; p.R = g.R; p.ldr = g.ldr;
   p.nh = g.nh; p.sa1 = g.sa1; p.sa2 = g.sa2; p.sb1 = g.sb1; p.sb2 = g.sb2; p.sc1 = g.sc1; p.sc2 = g.sc2;
   const int nz = g.nb * g.nh;
+  const size_t in = dt_size(g.dtype), out = g.out_f32 || g.dtype == DT_F32 ? 4 : 2;
+  const auto fours = [](const void* q, size_t size, int64_t ld) { return !q || (reinterpret_cast<uintptr_t>(q) % (4 * size) == 0 && ld % 4 == 0); };
+  p.vec = fours(g.C, out, g.ldc) && g.sc1 % 4 == 0 && g.sc2 % 4 == 0 && fours(g.R, out, g.ldr) && fours(g.bias, in, 0) && fours(g.C2, 4, g.ldc2);
   if (g.epi != EPI_NONE) {
     if (!f32_gelu_applies(g)) return hipErrorInvalidValue;
     p.C2 = g.C2; p.ldc2 = g.ldc2;
