@@ -8,8 +8,6 @@
 // wavefront shuffles.  Arithmetic is fp32 whatever the storage type is.
 #include <type_traits>
 
-#include <algorithm>
-
 #include "common.h"
 #include "kernels.h"
 #include "optimizer.h"
@@ -459,28 +457,29 @@ __device__ __forceinline__ void col_chunk(int64_t chunk, int64_t rows, const T* 
   }
   for (; r < r1; ++r) add(r, y[r * ld + j], MODE == 1 ? x[r * ld + j] : T());
 }
-// Up to 4096 rows, one launch: a workgroup takes 64 columns, a wavefront of it a chunk at a time (whose number is uniform, so that the
-// rows' statistics come by scalar loads), and the chunks are added up in LDS.  A sum (MODE 0) of 2048 x 1024 or x 4096 in bf16 takes 6.7
-// to 7.2 us, two launches 8 to 10; 64 x 64 in fp32 2.9, two launches 4.4.  The two sums of MODE 1 up to 1024 rows (1024 x 768: 9.1 us, two
-// launches 9.6; 64 x 64: 3.0 and 5.4), as few workgroups then have twice the loads to wait for: 2048 x 1024 14 us, two launches 9.4.
-constexpr int COL_ONE_CHUNKS = 64, COL_ONE_WAVES = 16;
+// Few rows, one launch: a workgroup takes 64 columns, a wavefront of it a chunk (whose number is uniform, so that the rows' statistics
+// come by scalar loads), and the chunks are added up in LDS.  Beyond that, two launches: there few workgroups would have the loads of several
+// chunks to wait for one after the other.  On the GPU alone (a launch costs the host 3 to 4 us more), one launch / two: a sum (MODE 0) of
+// 1024 columns, 256 rows 2.8 / 5.0 us, 1024 rows 4.0 / 4.4, 2048 rows 6.1 / 4.8, 4096 rows 11 / 5.8; the two sums of MODE 1, 512 rows
+// 4.3 / 6.0, 768 rows 5.8 / 6.2, 960 rows 6.8 / 6.5, 1024 rows 6.5 / 5.4.
+template <int MODE>
+constexpr int COL_ONE_CHUNKS = MODE == 0 ? 16 : 12;
 template <typename T, int MODE>
-__global__ void __launch_bounds__(64 * COL_ONE_WAVES) col_one_k(int64_t rows, int64_t n, const T* __restrict__ y, int64_t ld,
-                                                               const T* __restrict__ x, const float* __restrict__ stats,
-                                                               float* __restrict__ out0, float* __restrict__ out1) {
-  __shared__ float sums[MODE + 1][COL_ONE_CHUNKS][64];
-  const int lane = threadIdx.x & 63, nchunk = (int)((rows + 63) / 64);
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = (int)blockDim.x >> 6;
+__global__ void __launch_bounds__(64 * COL_ONE_CHUNKS<MODE>) col_one_k(int64_t rows, int64_t n, const T* __restrict__ y, int64_t ld,
+                                                                       const T* __restrict__ x, const float* __restrict__ stats,
+                                                                       float* __restrict__ out0, float* __restrict__ out1) {
+  __shared__ float sums[MODE + 1][COL_ONE_CHUNKS<MODE>][64];
+  const int lane = threadIdx.x & 63, nchunk = (int)blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int64_t j = (int64_t)blockIdx.x * 64 + lane;
-  if (j < n)
-    for (int c = wave; c < nchunk; c += waves) {
-      float a, b;
-      col_chunk<T, MODE>(c, rows, y, ld, x, stats, j, a, b);
-      sums[0][c][lane] = a;
-      if (MODE == 1) sums[MODE][c][lane] = b;
-    }
+  if (j < n) {
+    float a, b;
+    col_chunk<T, MODE>(wave, rows, y, ld, x, stats, j, a, b);
+    sums[0][wave][lane] = a;
+    if (MODE == 1) sums[MODE][wave][lane] = b;
+  }
   __syncthreads();
-  for (int o = wave; o <= MODE; o += waves) {
+  for (int o = wave; o <= MODE; o += nchunk) {
     float* out = o ? out1 : out0;
     if (!out || j >= n) continue;
     float t = 0.f;
@@ -517,7 +516,16 @@ __global__ void __launch_bounds__(64) col_final_k(int64_t nchunk, int64_t n, con
 #pragma unroll
     for (int e = 0; e < AT_ONCE; ++e) a += v[e];
   }
-  for (; c < nchunk; ++c) a += src[c * n];
+  if (nchunk - c == 1) {
+    a += src[c * n];
+  } else if (c < nchunk) {  // the rest together as well (one by one, 960 rows took 8.8 us and 1024 took 5.4)
+    float v[AT_ONCE];
+#pragma unroll
+    for (int e = 0; e < AT_ONCE; ++e) v[e] = src[(c + e < nchunk ? c + e : c) * n];
+#pragma unroll
+    for (int e = 0; e < AT_ONCE; ++e)
+      if (c + e < nchunk) a += v[e];
+  }
   (blockIdx.y ? out1 : out0)[j] = a;
 }
 
@@ -1227,8 +1235,8 @@ hipError_t norm_bwd_params(int dt, bool rms, int64_t rows, int d, const void* dy
     if (e == hipSuccess && db) e = fill_zero(db, (size_t)d * 4, st);
     return e;
   }
-  if (nchunk <= COL_ONE_WAVES) {
-    const unsigned blocks = (unsigned)cdiv(d, 64), threads = 64 * (unsigned)std::min<int64_t>(nchunk, COL_ONE_WAVES);
+  if (nchunk <= COL_ONE_CHUNKS<1>) {
+    const unsigned blocks = (unsigned)cdiv(d, 64), threads = 64 * (unsigned)nchunk;
     if (dt == DT_F32) col_one_k<float, 1><<<blocks, threads, 0, st>>>(rows, d, (const float*)dy, d, (const float*)x, stats, dg, db);
     else col_one_k<bf16, 1><<<blocks, threads, 0, st>>>(rows, d, (const bf16*)dy, d, (const bf16*)x, stats, dg, db);
     LAUNCH_CHECK();
@@ -1247,8 +1255,8 @@ hipError_t col_sum(int dt, int64_t rows, int64_t n, const void* y, int64_t ld, f
   if (n == 0) return hipSuccess;
   if (rows == 0) return fill_zero(out, (size_t)n * 4, st);
   const int64_t nchunk = cdiv(rows, 64);
-  if (nchunk <= COL_ONE_CHUNKS) {
-    const unsigned blocks = (unsigned)cdiv(n, 64), threads = 64 * (unsigned)std::min<int64_t>(nchunk, COL_ONE_WAVES);
+  if (nchunk <= COL_ONE_CHUNKS<0>) {
+    const unsigned blocks = (unsigned)cdiv(n, 64), threads = 64 * (unsigned)nchunk;
     if (dt == DT_F32) col_one_k<float, 0><<<blocks, threads, 0, st>>>(rows, n, (const float*)y, ld, nullptr, nullptr, out, nullptr);
     else col_one_k<bf16, 0><<<blocks, threads, 0, st>>>(rows, n, (const bf16*)y, ld, nullptr, nullptr, out, nullptr);
     LAUNCH_CHECK();

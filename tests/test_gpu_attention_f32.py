@@ -74,9 +74,10 @@ def test_gelu_on_the_way_out_changes_no_bit(arch, seq):
     assert np.array_equal(la, lb) and np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("batch,seq", [(1, 1), (1, 63), (1, 64), (1, 65), (4, 257), (16, 256), (17, 241)])
+@pytest.mark.parametrize("batch,seq", [(1, 1), (1, 63), (1, 64), (1, 65), (3, 256), (7, 110), (4, 256), (5, 205), (4, 257), (7, 256), (16, 256), (17, 241)])
 def test_column_sums_of_any_number_of_rows(batch, seq):
-    """Gains and biases: one launch up to 4096 rows, two beyond; chunks of 64 rows, whole and not, 16 of them and one more."""
+    """Gains and biases: one launch up to 1024 rows (two sums at once: 768), two beyond; chunks of 64 rows, whole and not, 12 and 16 of
+    them and one more, several more, 64 and one more."""
     wl = dict(arch=1, n_layers=1, d_model=68, n_heads=1, d_ffn=20, vocab=64, max_seq=max(seq, 8), n_classes=2, norm_eps=1e-5, rope_base=10000.0,
               dtype=0, batch=batch, seq=seq, m=1, strategy="top2down", opt=SGD1)
     _compare_gradients(wl, 47)
