@@ -1,6 +1,6 @@
 """The update that writes the fragment-order copies itself (opt_pack_k): after it, a model computes what a model computes whose copies
 were packed from the same master weights, bit for bit, in the forward pass (loss) and in the backward pass (the update of the lowest
-group, whose gradient crosses every transposed copy)."""
+group, whose gradient crosses every transposed copy); and its weights and state are those of the plain update."""
 import numpy as np
 import pytest
 
@@ -52,3 +52,46 @@ def test_copies_are_those_of_the_new_weights(shape, parked, opt):
     finally:
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("parked", [0, 1])
+@pytest.mark.parametrize("opt", OPTS, ids=["adamw", "adagrad", "sgdm", "sgd"])
+def test_new_weights_and_state_are_those_of_the_plain_update(opt, parked):
+    """Twelve packed matrices in one group, more than one launch takes: new weights and state are, bit for bit, what the plain update
+    makes of the same gradients, and nothing is packed after it.  The gradients: the momentum that SGD leaves after its first step."""
+    import torch
+    import paper_2401_15207_amd as H
+    cfg = dict(arch=2, n_layers=3, d_model=1024, n_heads=8, d_ffn=2816, vocab=3400, max_seq=512, n_classes=0, norm_eps=1e-5, rope_base=10000.0, dtype=1)
+    units, batch, seq, pack = 5, 32, 512, 5  # pack: the profile's category of re-packing
+    g = torch.Generator(device="cuda").manual_seed(9)
+    tok = torch.randint(0, cfg["vocab"], (batch, seq), generator=g, device="cuda", dtype=torch.int32)
+    lab = torch.roll(tok, -1, 1)
+    n_state = {"adamw": 2, "adagrad": 1}.get(opt["kind"], 1 if opt["momentum"] else 0)
+    a = H.HiftModel(cfg, opt, units, batch, seq, state_on_host=parked)
+    try:
+        theta = torch.randn(a.n_params, generator=g, device="cuda") * 0.02
+        state = [torch.zeros_like(theta) for _ in range(n_state)]
+        a.write_params_device(0, units, theta)
+        a.set_group_schedule("bottom2up", units, 0)
+        a.profile_enable(True)
+        assert a.memory()["device_packed"] > 3 * a.n_params  # two copies of nearly everything, two bytes each
+        for t in (1, 2):
+            b = H.HiftModel(cfg, dict(OPTS[2], weight_decay=0.0), units, batch, seq)
+            b.write_params_device(0, units, theta)
+            b.set_group_schedule("bottom2up", units, 0)
+            b.step(tok, lab, 0)
+            grad = torch.from_numpy(b.read_state(0, units, 0)).cuda()
+            b.close()
+            a.step(tok, lab, 0)
+            for _name, shape, kind, _unit, off in a.tensors:
+                n = int(np.prod(shape))
+                parts = [x[off:off + n].clone() for x in (theta, grad, *state)]
+                H.kernel_optimizer(opt, n, kind == 0, t, parts[0], parts[1], *(parts[2:] + [None, None])[:2])
+                for x, part in zip((theta, *state), (parts[0], *parts[2:])):
+                    x[off:off + n] = part
+            assert np.array_equal(a.read_params(), theta.cpu().numpy()), t
+            for j in range(n_state):
+                assert np.array_equal(a.read_state(0, units, j), state[j].cpu().numpy()), (t, j)
+        assert a.profile_read(pack)[0] == 0
+    finally:
+        a.close()
