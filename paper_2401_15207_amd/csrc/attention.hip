@@ -586,11 +586,11 @@ constexpr int KV_QT = 64;  // queries per tile
 template <int HD>
 constexpr int KV_LDS = 2 * (2 * KV_QT * HD * 2 + 2048);  // two buffers of Q | dO | lse (1 KB, 256 bytes used) | D (same)
 
-template <int HD, bool CAUSAL>
+template <bool CAUSAL>
 __device__ __forceinline__ void attn_bwd_keys(unsigned char* lds, const int block, const bf16* __restrict__ qkv, int64_t ld, int S, int H, int BH,
                                               float scale, const float* lse, const float* dsum, const bf16* __restrict__ dctx, int64_t ldc,
                                               bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
-  constexpr int KB = 128;           // keys per workgroup
+  constexpr int HD = 64, KB = 128;  // width of a head, keys per workgroup
   constexpr int QT = KV_QT;
   constexpr int ROWB = HD * 2, PPR = HD / 8, NB = HD / 32, KS = HD / 16;
   constexpr int TQ = QT * ROWB;     // bytes of the Q (or dO) tile
@@ -602,7 +602,6 @@ __device__ __forceinline__ void attn_bwd_keys(unsigned char* lds, const int bloc
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 31, fh = lane >> 5;
   // key blocks early in the sequence see the most queries under the causal mask and go first
-  const int nkb = (S + KB - 1) / KB;
   const int kb = block / BH, bh = block % BH;
   const int b = bh / H, h = bh % H;
   const int64_t d = (int64_t)H * HD;
@@ -612,7 +611,6 @@ __device__ __forceinline__ void attn_bwd_keys(unsigned char* lds, const int bloc
   const int row = j0 + fr;
   const bool row_ok = row < S;
   const float scale_log2e = scale * 1.4426950408889634f;
-  (void)nkb;
 
   bf16x8 kf[KS], vf[KS];  // this lane's key row: fragments of K and V
 #pragma unroll
@@ -807,7 +805,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_kv_k(const bf16* __restrict__
                                                          const float* lse, const float* dsum, const bf16* __restrict__ dctx, int64_t ldc,
                                                          bf16* __restrict__ dqkv, const float2* __restrict__ cos_sin) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[KV_LDS<64>];
-  attn_bwd_keys<64, CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
+  attn_bwd_keys<CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
 }
 
 // The key-major half for heads 128 wide, on eight wavefronts.  One wavefront per 32 keys would need 410 registers, so one a SIMD, which
@@ -925,7 +923,6 @@ __global__ void __launch_bounds__(512) attn_bwd_kv8_k(const bf16* __restrict__ q
     return __builtin_bit_cast(bf16x8, both);
   };
   unsigned char* const mine = lds + 2 * BUF + wave * 4096 + lane * 16;
-  const unsigned char* const theirs = lds + 2 * BUF + (wave ^ 1) * 4096 + lane * 16;
 
   f32x16 vacc[2], kacc[2];
 #pragma unroll
@@ -1040,7 +1037,7 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_one_k(const bf16* __restrict_
   attn_rows<64, CAUSAL, 4, true>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, nullptr, ctx, ldc, dctx, lse, dsum, dqkv, cos_sin);
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   __syncthreads();  // dsum is written, and every wavefront is done with LDS
-  attn_bwd_keys<64, CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
+  attn_bwd_keys<CAUSAL>(lds, (int)blockIdx.x, qkv, ld, S, H, BH, scale, lse, dsum, dctx, ldc, dqkv, cos_sin);
 }
 
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }

@@ -181,7 +181,7 @@ struct OptArgs {
   int kind; double lr, beta1, beta2, eps, wd, momentum;
 };
 // The tensors of one update: n parameters; t the tensor's update number from 1; the fp32 arrays (s1, s2 null where the optimizer
-// keeps none); compute_copy (bf16, or null) receives the rounded new values; grad_fused: see opt_update.  One launch per OPT_TABLE
+// keeps none); compute_copy (bf16, or null) receives the rounded new values; grad_fused: see opt_math (optimizer.h).  One launch per OPT_TABLE
 // tensors.
 struct OptItem {
   int64_t n; bool decay; int64_t t;
