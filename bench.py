@@ -89,10 +89,11 @@ def measured_traffic():
     the kernel source has changed since they were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "gemm_traffic.json")
-    src = os.path.join(ROOT, "paper_2401_15207_amd", "csrc", "gemm.hip")
+    csrc = os.path.join(ROOT, "paper_2401_15207_amd", "csrc")
     try:
         rec = json.load(open(path))
-        if rec.get("gemm_hip_sha256") != hashlib.sha256(open(src, "rb").read()).hexdigest():
+        sources = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("gemm.hip", "packed_layout.h"))
+        if rec.get("sources_sha256") != hashlib.sha256(sources).hexdigest():
             return None
         return rec["hbm_bytes_per_launch"]
     except (OSError, ValueError, KeyError):

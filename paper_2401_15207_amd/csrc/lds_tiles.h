@@ -17,7 +17,8 @@ constexpr int N_LDS_TILES = sizeof(LDS_TILES) / sizeof(LDS_TILES[0]);
 // tile costs besides); a stage takes longer when the round is the only one and the workgroup has its compute unit to itself.
 // The constants are a fit to measured times of all the tiles in the four layouts (83 sizes: 8 to 65536 rows, 8 to 100000
 // columns, k 56 to 11008; 18 batches of 24 to 2048 products): the tile chosen is on average 1.4 % slower than the best and at
-// most 1.23 times.  A ring of four 64 x 64 stages is the better one when it runs alone (231 x 4096, k 11008: 40 us, 47 with
+// most 1.23 times.  It was made with operands in the caches: where the weights come from HBM a stage takes up to 1.5 times as long (231 x 4096,
+// k 11008: 27 us by the fit, 40 measured).  A ring of four 64 x 64 stages is the better one when it runs alone (231 x 4096, k 11008: 40 us, 47 with
 // three), three otherwise (three workgroups per compute unit: 1024 x 2304, k 768: 11.3 us, 12.6 with four).  256 x 256 draws half
 // the operand bytes per product of 128 x 128, but has a compute unit to itself and hides nothing of its start and end: the better
 // one where its rounds are long and nearly full (2048 x 32000, k 4096: 442 us, 128 x 128: 594), not for 2048 x 4096, k 4096 (half
