@@ -54,7 +54,7 @@ class StateSlots {
   // (a caller may step it again), and never are groups whose own update is so recent that their write-back would hold up the copies
   // behind it.  fetch(g, spare, &done) puts g (see put) and queues its copy; a status other than 0 ends the step.
   // A caller that leaves the schedule has what was fetched ahead still in place when it comes back: as long as the last step off
-  // the schedule is less than a round ago, nothing is copied again that a slot holds, and directly after it only the next group is
+  // the schedule is less than a cycle ago, nothing is copied again that a slot holds, and directly after it only the next group is
   // fetched.  (Fetched again, 34 groups of which one is large moved 3.3 times the state they updated where every other step was off the
   // schedule, and 1.4 times with one in ten; 1.15 and 1.02 now, 1.3 and 1.08 with one group to a slot.)
   template <class Fetch>
@@ -140,7 +140,7 @@ class StateSlots {
   std::vector<int> in_[N];
   int64_t fill_[N] = {0, 0, 0}, cap_ = 0;
   int open_ = 0, last_[2] = {-1, -1};
-  int followed_ = 0;  // steps in a row in the schedule's order, counted up to a round
+  int followed_ = 0;  // steps in a row in the schedule's order, counted up to a cycle
 };
 
 }  // namespace hift
