@@ -12,7 +12,8 @@
 // for two or more workgroups in a compute unit's LDS (they hide each other's waits: 2048 x 4096, k 4096 takes 71 us with a ring of two
 // stages of 128 x 128 tiles, 88 us with four stages and one workgroup), and a stage's fragments are all read into registers
 // one stage ahead, under the products of the stage before (231 x 4096, k 11008: 40 us, 50 with fragments read one k-step
-// ahead).  256 x 256 tiles, for products of several full rounds, work differently (see Tile).  An output's sum runs over k in one chain, in ascending order, whatever the tile.
+// ahead).  256 x 256 tiles, for products of several full rounds, work differently (see Tile); long k whose tiles are one round has
+// tiles of its own (LDS_LONG_TILES).  An output's sum runs over k in one chain, in ascending order, whatever the tile.
 // Measured against the kernel before it (operands through registers, turned around on the way, 128 x 128 tiles): 1024 tokens,
 // 768 -> 3072 with input and weight gradients 12 + 50 + 26 us, now 11 + 13 + 13; 231 tokens, 4096 -> 12288: 49 + 185 + 348 us,
 // now 37 + 45 + 63.
@@ -120,13 +121,13 @@ struct Fragments {
   }
 };
 
-// Wavefronts of a tile: 2 x 2, fewer where a tile has fewer than four 32 x 32 blocks; 2 x 4 for the large tile, whose
+// Wavefronts of a tile: 2 x 2, fewer where a tile has fewer than four 32 x 32 blocks; 2 x 4 for 256 x 256 and 4 x 2 for 256 x 128, whose
 // accumulators leave room for the fragments of one k-step ahead instead of a whole stage (two wavefronts a SIMD: 2048 x 32000,
 // k 4096 takes 442 us, with 2 x 2 of them, one a SIMD, 461) and whose outputs pass through LDS in two halves.
 template <int BM, int BN, int RING>
 struct Tile {
   static constexpr bool LARGE = BM * BN > 128 * 128;
-  static constexpr int SWM = BM >= 64 ? 2 : 1, SWN = LARGE ? 4 : (BN >= 64 ? 2 : 1), NW = SWM * SWN;
+  static constexpr int SWN = LARGE ? BN / 64 : (BN >= 64 ? 2 : 1), SWM = LARGE ? 8 / SWN : (BM >= 64 ? 2 : 1), NW = SWM * SWN;
   static constexpr int WM = BM / SWM, WN = BN / SWN;
   static constexpr int OUT_PASSES = LARGE ? 2 : 1;
   static constexpr int RING_BYTES = RING * (BM + BN) * 128, OUT_BYTES = BM / OUT_PASSES * BN * 4;
@@ -366,9 +367,10 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), (Tile<BM, BN, R
 
 inline bool al16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; }
 
-template <int I, bool AK, bool BKM, typename OutT, int EPI>
+template <int I, bool AK, bool BKM, typename OutT, int EPI, bool LONG = false>
 hipError_t launch(LdsP& p, int nz, hipStream_t st) {
-  constexpr int BM = LDS_TILES[I].bm, BN = LDS_TILES[I].bn, RING = LDS_TILES[I].ring;
+  constexpr LdsTile TILE = LONG ? LDS_LONG_TILES[I] : LDS_TILES[I];
+  constexpr int BM = TILE.bm, BN = TILE.bn, RING = TILE.ring;
   constexpr int LDS = Tile<BM, BN, RING>::LDS;
   static_assert(LDS <= 160 * 1024, "LDS of a gfx950 compute unit");
   static bool attr_done = false;  // one flag per instantiation
@@ -386,7 +388,12 @@ hipError_t launch(LdsP& p, int nz, hipStream_t st) {
 
 template <bool AK, bool BKM, typename OutT, int EPI = EPI_NONE>
 hipError_t pick_tile(LdsP& p, int nz, hipStream_t st) {
-  static_assert(N_LDS_TILES == 9, "one case per tile");
+  static_assert(N_LDS_TILES == 9 && N_LDS_LONG_TILES == 2, "one case per tile");
+  switch (p.band == BAND_NONE ? lds_long_tile(p.M, p.N, p.K, nz) : -1) {
+    case 0: return launch<0, AK, BKM, OutT, EPI, true>(p, nz, st);
+    case 1: return launch<1, AK, BKM, OutT, EPI, true>(p, nz, st);
+    default: break;
+  }
   switch (lds_tile(p.M, p.N, p.K, nz)) {
     case 0: return launch<0, AK, BKM, OutT, EPI>(p, nz, st);
     case 1: return launch<1, AK, BKM, OutT, EPI>(p, nz, st);
