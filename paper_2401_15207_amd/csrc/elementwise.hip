@@ -964,7 +964,12 @@ __global__ void __launch_bounds__(BLK) copy_stream_k(u32x4_t* __restrict__ dst, 
 // decay), 1 AdaGrad, 2 SGD with momentum, 3 plain SGD.  Four parameters per thread (16-byte accesses) where a tensor's
 // pieces are aligned for it, else one (20 M parameters of AdamW: 114 us; four to a thread 126, one after the other 134).  A
 // block finds its tensor in the table that came with the launch.
-// Memory bound: 5.8 TB/s on a layer of 202 M parameters.  Launched tensor by tensor, the 16 tensors of an encoder layer took
+// Memory bound: 6.2 TB/s on a layer of 202 M parameters.  Four wavefronts a SIMD (64 KB of AdamW's loads in flight in a compute unit):
+// more of them only make memory change rows more often (202 M parameters 1016 us with eight, 977 with four, 1022 with two; 36 M 162 and 158; of momentum
+// 67 M 210 and 201; up to 20 M the same); plain SGD, which reads two arrays, keeps eight (67 M 121, 125 with four).  A rounded copy of
+// OPT_COPY_PAST_CACHES parameters or more goes past the caches too, like the rest (50 M 238 -> 232 us, 202 M 1045 -> 1008); a smaller one
+// may still be there when it is read or written again (three of 44 M in turn 192 us, 205 past the caches).
+// Launched tensor by tensor, the 16 tensors of an encoder layer took
 // 16 launches of which 12 were gains and biases: 2.8 us each for work of less than one.
 template <int NT>  // 1 for a single tensor (the small table saves 0.2 us of a 3.6 us launch), OPT_TABLE for a group
 struct OptTable {
@@ -982,11 +987,16 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
   stnt<V>(t.master + i, th);
   if (KIND != 3) stnt<V>(t.s1 + i, a);
   if (KIND == 0) stnt<V>(t.s2 + i, b);
-  if (t.cc) stv<bf16, V>(t.cc + i, th);
+  if (t.cc) {
+    if (t.cc_nt) stnt<V>(t.cc + i, th);
+    else stv<bf16, V>(t.cc + i, th);
+  }
 }
 
+constexpr int64_t OPT_COPY_PAST_CACHES = 48000000;  // 96 MB of the 256 MB last-level cache
+constexpr int opt_waves(int kind) { return kind == 3 ? 8 : 4; }
 template <int KIND, int NT>
-__global__ void __launch_bounds__(BLK) opt_k(OptHyper h, OptTable<NT> table) {
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(opt_waves(KIND), opt_waves(KIND)))) opt_k(OptHyper h, OptTable<NT> table) {
   int q = 0;
   if (NT > 1)
     while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].block0) ++q;  // uniform over the block
@@ -1460,6 +1470,7 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
     t = opt_tensor(o, it);
     t.block0 = (uint32_t)blocks;
     t.vec = vec;
+    t.cc_nt = it.n >= OPT_COPY_PAST_CACHES;
     blocks += more;
   }
   if (table.n == 0) return hipSuccess;

@@ -35,6 +35,20 @@ __device__ __forceinline__ void stnt(float* p, const float (&f)[V]) {
   }
 }
 
+// ... and of rounded copies of the new weights that are too large to stay in the last-level cache until the next step reads them
+template <int V>
+__device__ __forceinline__ void stnt(bf16* p, const float (&f)[V]) {
+  typedef bf16 vt __attribute__((ext_vector_type(V)));
+  if constexpr (V == 1) {
+    *p = from_f32<bf16>(f[0]);
+  } else {
+    vt t;
+#pragma unroll
+    for (int e = 0; e < V; ++e) t[e] = from_f32<bf16>(f[e]);
+    __builtin_nontemporal_store(t, reinterpret_cast<vt*>(p));
+  }
+}
+
 struct OptTensor {
   int64_t n;       // parameters
   float* master;
@@ -46,6 +60,7 @@ struct OptTensor {
   uint32_t block0; // first block of the launch that works on it
   int vec;         // opt_k: pieces of four are 16-byte aligned in every array
   int grad_fused;  // AdamW: which product of a moment's sum is fused
+  int cc_nt;       // opt_k: the copy is written past the caches
 };
 struct OptHyper {
   float lr, b1, omb1, b2, omb2, eps, mu;

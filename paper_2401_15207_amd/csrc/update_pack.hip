@@ -4,9 +4,10 @@
 // rounded new values in LDS, and writes from there the tile's part of the forward copy (one 32-row block, 16 k-steps: 16 KB in a row) and
 // of the transposed one (eight blocks, two k-steps each), as pack_b_tile_k does (gemm.hip).  Memory bound: AdamW reads 16 and writes 12
 // bytes of fp32 a parameter, and 2 per copy.  The packers by themselves read the new master weights again for each copy, 8 bytes a
-// parameter more: a layer of 202 M parameters took 1.03 ms in opt_k and 0.45 in the packers, now 1.16 (5.6 TB/s); a sweep of two layers
-// of width 4096 21.26 ms before, 20.83 now.  Loads go out in two batches of four rows a wavefront; both at once would need 128 registers
-// for the data alone.
+// parameter more: a layer of 202 M parameters took 1.03 ms in opt_k and 0.45 in the packers, and takes 1.03 here.  Loads
+// go out in batches of two rows a wavefront, of two wavefronts a SIMD: 64 KB in flight in a compute unit.  More of them only make memory
+// change rows more often, and the copies, which nothing reads in this step, go past the caches (22016 x 4096: 539 us with four rows and
+// wavefronts, 508 with two wavefronts, 495 with two rows as well, 474 with the copies past the caches; one row 530, eight rows 513).
 #include "common.h"
 #include "kernels.h"
 #include "optimizer.h"
@@ -34,9 +35,9 @@ struct OptPackTable {
 };
 
 template <int KIND>
-__global__ void __launch_bounds__(BLK) opt_pack_k(OptHyper h, OptPackTable table) {
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))) opt_pack_k(OptHyper h, OptPackTable table) {
   constexpr int PITCH = TILE_COLS * 2 + 16;  // bytes per tile row in LDS; the pad spreads 16-byte reads of one column over the banks
-  constexpr int NB = 4;                      // rows of a wavefront whose loads are in flight together
+  constexpr int NB = 2;                      // rows of a wavefront whose loads are in flight together
   __shared__ __attribute__((aligned(16))) unsigned char tile[TILE_ROWS * PITCH];
   int q = 0;
   while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].o.block0) ++q;  // uniform over the block
@@ -45,12 +46,12 @@ __global__ void __launch_bounds__(BLK) opt_pack_k(OptHyper h, OptPackTable table
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t row0 = (int64_t)to * TILE_ROWS + wave, col = (int64_t)ti * TILE_COLS + lane * 4;
   const bool col_in = col < t.cols;  // columns come in whole fours
-#pragma unroll
-  for (int half = 0; half < TILE_ROWS / 4 / NB; ++half) {
+#pragma unroll 1
+  for (int batch = 0; batch < TILE_ROWS / 4 / NB; ++batch) {
     float th[NB][4], g[NB][4], a[NB][4], b[NB][4];
 #pragma unroll
     for (int p = 0; p < NB; ++p) {
-      const int64_t row = row0 + (half * NB + p) * 4, i = row * t.cols + col;
+      const int64_t row = row0 + (batch * NB + p) * 4, i = row * t.cols + col;
       if (!(col_in && row < t.rows)) continue;
       ldnt<4>(t.o.master + i, th[p]);
       ldnt<4>(t.o.grad + i, g[p]);
@@ -59,8 +60,8 @@ __global__ void __launch_bounds__(BLK) opt_pack_k(OptHyper h, OptPackTable table
     }
 #pragma unroll
     for (int p = 0; p < NB; ++p) {
-      const int r = wave + (half * NB + p) * 4;
-      const int64_t row = row0 + (half * NB + p) * 4, i = row * t.cols + col;
+      const int r = wave + (batch * NB + p) * 4;
+      const int64_t row = row0 + (batch * NB + p) * 4, i = row * t.cols + col;
       Vec<bf16, 4> w;
 #pragma unroll
       for (int e = 0; e < 4; ++e) w.v[e] = static_cast<bf16>(0.f);  // the copies are zero past the matrix
@@ -71,7 +72,7 @@ __global__ void __launch_bounds__(BLK) opt_pack_k(OptHyper h, OptPackTable table
         if (KIND == 0) stnt<4>(t.o.s2 + i, b[p]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w.v[e] = from_f32<bf16>(th[p][e]);
-        if (t.o.cc) *reinterpret_cast<Vec<bf16, 4>*>(t.o.cc + i) = w;
+        if (t.o.cc) stnt<4>(t.o.cc + i, th[p]);
       }
       *reinterpret_cast<Vec<bf16, 4>*>(tile + r * PITCH + lane * 8) = w;
     }
@@ -86,7 +87,7 @@ __global__ void __launch_bounds__(BLK) opt_pack_k(OptHyper h, OptPackTable table
       if (kk >= k_steps) continue;
       u32x4 v = *reinterpret_cast<const u32x4*>(tile + pi_row(lane & 31) * PITCH + (kkl * 16 + (lane >> 5) * 8) * 2);
       if (t.gain) v = scale8(v, *reinterpret_cast<const u32x4*>(t.gain + kk * 16 + (lane >> 5) * 8));
-      t.fwd[(pk_block_pos(to, t.order, t.rows / 64) * k_steps + kk) * 64 + lane] = v;
+      __builtin_nontemporal_store(v, t.fwd + (pk_block_pos(to, t.order, t.rows / 64) * k_steps + kk) * 64 + lane);
     }
   }
   if (t.bwd) {
@@ -98,7 +99,7 @@ __global__ void __launch_bounds__(BLK) opt_pack_k(OptHyper h, OptPackTable table
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         v[e] = *reinterpret_cast<const bf16*>(tile + (kkl * 16 + (lane >> 5) * 8 + e) * PITCH + (nbl * 32 + pi_row(lane & 31)) * 2);
-      t.bwd[(((int64_t)ti * 8 + nbl) * k_steps + to * 2 + kkl) * 64 + lane] = __builtin_bit_cast(u32x4, v);
+      __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), t.bwd + (((int64_t)ti * 8 + nbl) * k_steps + to * 2 + kkl) * 64 + lane);
     }
   }
 }

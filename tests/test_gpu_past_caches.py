@@ -1,0 +1,54 @@
+"""Outputs too large to stay in the last-level cache are written past it (optimizer's rounded copy, gradient of the logits): the same bits as
+by the launches that do not."""
+import pytest
+
+OPTS = {"adamw": dict(kind="adamw", eps=1e-8, momentum=0.0), "adagrad": dict(kind="adagrad", eps=1e-10, momentum=0.0),
+        "sgdm": dict(kind="sgd", eps=1e-8, momentum=0.9), "sgd": dict(kind="sgd", eps=1e-8, momentum=0.0)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(OPTS))
+@pytest.mark.parametrize("n", [48000000, 48000003])
+def test_large_update_is_the_small_ones(name, n):
+    import torch
+    import paper_2401_15207_amd as H
+    opt = dict(OPTS[name], lr=1e-3, beta1=0.9, beta2=0.999, weight_decay=0.01)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    w, gr, s1 = (torch.randn(n, generator=g, device="cuda") * s for s in (0.02, 1e-3, 1e-4))
+    s1 = s1.square() if name == "adagrad" else s1
+    s2 = torch.rand(n, generator=g, device="cuda") * 1e-8
+    s1, s2 = (None if name == "sgd" else s1), (s2 if name == "adamw" else None)
+    cut = 24000000  # a whole number of 16-byte pieces in every array
+    half = torch.empty(n, device="cuda", dtype=torch.bfloat16)
+    parts = [(t.clone() if t is not None else None) for t in (w, s1, s2)] + [torch.empty_like(half)]
+    H.kernel_optimizer(opt, n, True, 3, w, gr, s1, s2, half)
+    for a, b in ((0, cut), (cut, n)):
+        at = [None if t is None else t[a:b] for t in parts]
+        H.kernel_optimizer(opt, b - a, True, 3, at[0], gr[a:b], at[1], at[2], at[3])
+    torch.cuda.synchronize()
+    for x, y in zip((w, s1, s2, half), parts):
+        assert x is None or torch.equal(x, y)
+    assert torch.equal(half, w.to(torch.bfloat16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,vocab,dtype", [(1600, 32000, "bf16"), (1000, 50272, "bf16"), (1600, 16000, "fp32"), (4200, 12000, "bf16")])
+def test_large_logits_are_the_small_ones(rows, vocab, dtype):
+    """The second half of the rows has no target: the first half's gradient and the loss are those of a call of half the rows."""
+    import torch
+    import paper_2401_15207_amd as H
+    dt, code = (torch.bfloat16, 1) if dtype == "bf16" else (torch.float32, 0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows + vocab)
+    big = (torch.randn(rows, vocab, generator=g, device="cuda") * 2.0).to(dt)
+    labels = torch.randint(0, vocab, (rows,), generator=g, device="cuda", dtype=torch.int32)
+    labels[rows // 2:] = -1
+    small = big[:rows // 2].clone()
+    losses = []
+    for x, n in ((big, rows), (small, rows // 2)):
+        losses.append(torch.empty(1, device="cuda"))
+        H.kernel_cross_entropy(code, n, vocab, x, labels, torch.empty(n + 1, device="cuda"), losses[-1])
+    torch.cuda.synchronize()
+    assert torch.equal(big[:rows // 2], small) and not big[rows // 2:].any()
+    assert torch.equal(*losses)
