@@ -840,7 +840,7 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
 // Same, with the row held in registers (vocab <= BLK * V * NV): every logit is read once and its gradient written
 // once, all loads of a row in flight together; the maximum, the sum of exponentials and the gradient are three
 // passes over registers.  The values stay in their storage type (16 bytes per piece) until they are used.
-template <typename T, int V, int NV, bool COUNT>
+template <typename T, int V, int NV, bool COUNT, bool PAST>
 __global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* __restrict__ logits,
                                                      const int32_t* __restrict__ labels, float* __restrict__ row_loss) {
   __shared__ float red[BLK / 64];
@@ -900,7 +900,12 @@ __global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* 
         if (hit) row_loss[row] = lse - x;
         a[e] = (__builtin_amdgcn_exp2f((x - mx) * LOG2E) * inv - (hit ? 1.f : 0.f)) * inv_n;
       }
-      stv<T, V>(lr + j, a);
+      Vec<T, V> o;
+#pragma unroll
+      for (int e = 0; e < V; ++e) o.v[e] = from_f32<T>(a[e]);
+      const u32x4_t piece = __builtin_bit_cast(u32x4_t, o);
+      if (PAST) __builtin_nontemporal_store(piece, reinterpret_cast<u32x4_t*>(lr + j));
+      else *reinterpret_cast<u32x4_t*>(lr + j) = piece;
     }
   }
 }
@@ -908,8 +913,15 @@ __global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* 
 __global__ void __launch_bounds__(BLK) ce_final_k(int64_t rows, const float* __restrict__ row_loss,
                                                    float* __restrict__ loss_out) {
   __shared__ float red[BLK / 64];
+  constexpr int W = 8;  // losses of a thread on their way together: one after the other, the mean of 2048 took 4.7 us, now 3.2
   float c = 0.f;
-  for (int64_t r = threadIdx.x; r < rows; r += BLK) c += row_loss[r];
+  for (int64_t r0 = threadIdx.x; r0 < rows; r0 += W * BLK) {
+    float v[W];
+#pragma unroll
+    for (int q = 0; q < W; ++q) v[q] = r0 + q * BLK < rows ? row_loss[r0 + q * BLK] : 0.f;
+#pragma unroll
+    for (int q = 0; q < W; ++q) c += v[q];
+  }
   c = block_sum<BLK / 64>(c, red);
   if (threadIdx.x == 0) *loss_out = row_loss[rows] > 0.f ? c / row_loss[rows] : 0.f;  // no row with a target: loss 0
 }
@@ -1374,19 +1386,19 @@ hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_l
   LAUNCH_CHECK();
 }
 
-template <bool COUNT>
+template <bool COUNT, bool PAST>
 static void launch_ce_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss, hipStream_t st) {
   const dim3 grid((unsigned)rows);
 #define OK(v) (V_ % (v) == 0 && aligned16(logits))
   // 16-byte pieces of a row a thread keeps: 16 (rows of up to 32768 bf16 or 16384 fp32 values) or 32
   if (dt == DT_BF16 && OK(8) && V_ <= BLK * 8 * 16) {
-    ce_row_reg_k<bf16, 8, 16, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
+    ce_row_reg_k<bf16, 8, 16, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
   } else if (dt == DT_BF16 && OK(8) && V_ <= BLK * 8 * 32) {
-    ce_row_reg_k<bf16, 8, 32, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
+    ce_row_reg_k<bf16, 8, 32, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
   } else if (dt == DT_F32 && OK(4) && V_ <= BLK * 4 * 16) {
-    ce_row_reg_k<float, 4, 16, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
+    ce_row_reg_k<float, 4, 16, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
   } else if (dt == DT_F32 && OK(4) && V_ <= BLK * 4 * 32) {
-    ce_row_reg_k<float, 4, 32, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
+    ce_row_reg_k<float, 4, 32, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
   } else {
     DISPATCH_TV(dt, OK, (ce_row_k<T, V, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (T*)logits, labels, row_loss)));
   }
@@ -1396,8 +1408,13 @@ static void launch_ce_rows(int dt, int64_t rows, int V_, void* logits, const int
 hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st) {
   if (rows == 0) return hipSuccess;
-  if (cross_entropy_counts_apart(rows)) launch_ce_rows<false>(dt, rows, V_, logits, labels, row_loss, st);
-  else launch_ce_rows<true>(dt, rows, V_, logits, labels, row_loss, st);
+  // A gradient that fills the last-level cache (256 MB) for a good part is written past it: whoever reads it next finds little of it there anyway,
+  // and the writes do not wait for room (2048 x 32000 in bf16, 131 MB, with the mean: 61.0 -> 52.7 us, the step around it as before;
+  // 231 x 32000, 15 MB: the step 0.5 % slower).
+  const bool past_caches = rows * V_ * (dt == DT_BF16 ? 2 : 4) >= (int64_t)96 << 20;
+  const auto launch = cross_entropy_counts_apart(rows) ? (past_caches ? launch_ce_rows<false, true> : launch_ce_rows<false, false>)
+                                                       : (past_caches ? launch_ce_rows<true, true> : launch_ce_rows<true, false>);
+  launch(dt, rows, V_, logits, labels, row_loss, st);
   LAUNCH_CHECK();
 }
 

@@ -19,7 +19,8 @@ def test_large_update_is_the_small_ones(name, n):
     s1 = s1.square() if name == "adagrad" else s1
     s2 = torch.rand(n, generator=g, device="cuda") * 1e-8
     s1, s2 = (None if name == "sgd" else s1), (s2 if name == "adamw" else None)
-    cut = 24000000  # a whole number of 16-byte pieces in every array
+    # which product of AdamW's moments is fused follows from whether the count is a multiple of eight: the same for the parts as for the whole
+    cut = 24000000 if n % 8 == 0 else 24000004
     half = torch.empty(n, device="cuda", dtype=torch.bfloat16)
     parts = [(t.clone() if t is not None else None) for t in (w, s1, s2)] + [torch.empty_like(half)]
     H.kernel_optimizer(opt, n, True, 3, w, gr, s1, s2, half)
