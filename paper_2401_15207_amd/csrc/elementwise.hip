@@ -1408,10 +1408,9 @@ static void launch_ce_rows(int dt, int64_t rows, int V_, void* logits, const int
 hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st) {
   if (rows == 0) return hipSuccess;
-  // A gradient that fills the last-level cache (256 MB) for a good part is written past it: whoever reads it next finds little of it there anyway,
-  // and the writes do not wait for room (2048 x 32000 in bf16, 131 MB, with the mean: 61.0 -> 52.7 us, the step around it as before;
-  // 231 x 32000, 15 MB: the step 0.5 % slower).
-  const bool past_caches = rows * V_ * (dt == DT_BF16 ? 2 : 4) >= (int64_t)96 << 20;
+  // 2048 x 32000 in bf16 (131 MB), with the mean: 61.0 -> 52.7 us past the caches, the step around it as before; 231 x 32000 (15 MB): the
+  // step 0.5 % slower.
+  const bool past_caches = rows * V_ * (dt == DT_BF16 ? 2 : 4) >= PAST_CACHES_BYTES;
   const auto launch = cross_entropy_counts_apart(rows) ? (past_caches ? launch_ce_rows<false, true> : launch_ce_rows<false, false>)
                                                        : (past_caches ? launch_ce_rows<true, true> : launch_ce_rows<true, false>);
   launch(dt, rows, V_, logits, labels, row_loss, st);

@@ -1,5 +1,5 @@
-"""Outputs too large to stay in the last-level cache are written past it (optimizer's rounded copy, gradient of the logits): the same bits as
-by the launches that do not."""
+"""Outputs too large to stay in the last-level cache are written past it (optimizer's rounded copy, gradient of the logits,
+weight gradients): the same bits as by the launches that do not."""
 import pytest
 
 OPTS = {"adamw": dict(kind="adamw", eps=1e-8, momentum=0.0), "adagrad": dict(kind="adagrad", eps=1e-10, momentum=0.0),
@@ -53,3 +53,21 @@ def test_large_logits_are_the_small_ones(rows, vocab, dtype):
     torch.cuda.synchronize()
     assert torch.equal(big[:rows // 2], small) and not big[rows // 2:].any()
     assert torch.equal(*losses)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,cut", [(6144, 4096, 64, 3072), (6152, 4104, 40, 3072), (25176, 1000, 232, 12800), (256, 98400, 24, 128)])
+def test_large_weight_gradient_is_the_small_ones(M, N, K, cut):
+    """fp32 outputs of gemm_tt_k (whole tiles) and gemm_lds_k, in rows of a wider buffer, against two calls of half the rows each."""
+    import torch
+    import paper_2401_15207_amd as H
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    a, b = (torch.randn(K, n, generator=g, device="cuda").to(torch.bfloat16) for n in (M, N))
+    whole, parts = (torch.full((M + 1, N + 8), 7.0, device="cuda") for _ in range(2))
+    H.kernel_gemm(1, 0, 0, 1, M, N, K, a, M, b, N, whole, N + 8)
+    for lo, hi in ((0, cut), (cut, M)):
+        H.kernel_gemm(1, 0, 0, 1, hi - lo, N, K, a[:, lo:], M, b, N, parts[lo:], N + 8)
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
+    assert (whole[M] == 7.0).all() and (whole[:, N:] == 7.0).all() and not (whole[:M, :N] == 7.0).all(1).any()
