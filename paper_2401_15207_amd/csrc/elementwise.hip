@@ -790,11 +790,11 @@ struct CeTargets {
 };
 
 template <typename T, int V, bool COUNT>
-__global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __restrict__ logits,
+__global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, int64_t ld, T* __restrict__ logits,
                                                  const int32_t* __restrict__ labels, float* __restrict__ row_loss) {
   __shared__ float red[BLK / 64];
   const int64_t row = blockIdx.x;
-  T* lr = logits + row * vocab;
+  T* lr = logits + row * ld;
   int lab = labels[row];
   CeTargets<COUNT> targets;
   targets.request(rows, labels, row_loss);
@@ -809,10 +809,18 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
   }
   if (lab >= vocab) lab = vocab - 1;
   const float inv_n = targets.inverse(rows, row_loss, red);
+  const auto piece = [&](int j, float(&a)[V]) __attribute__((always_inline)) {
+    ldv<T, V>(lr + j, a);
+    if (V > 1 && j + V > vocab) {
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+        if (j + e >= vocab) a[e] = -INFINITY;  // past the row's end: no weight, and a gradient of zero
+    }
+  };
   float mx = -INFINITY;
   for (int j = threadIdx.x * V; j < vocab; j += BLK * V) {
     float a[V];
-    ldv<T, V>(lr + j, a);
+    piece(j, a);
 #pragma unroll
     for (int e = 0; e < V; ++e) mx = fmaxf(mx, a[e]);
   }
@@ -820,7 +828,7 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
   float sum = 0.f;
   for (int j = threadIdx.x * V; j < vocab; j += BLK * V) {
     float a[V];
-    ldv<T, V>(lr + j, a);
+    piece(j, a);
 #pragma unroll
     for (int e = 0; e < V; ++e) sum += __builtin_amdgcn_exp2f((a[e] - mx) * 1.4426950408889634f);  // hardware exponential: 1e-7 relative
   }
@@ -830,7 +838,7 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
   __syncthreads();  // the target logit is read before any thread overwrites it
   for (int j = threadIdx.x * V; j < vocab; j += BLK * V) {
     float a[V];
-    ldv<T, V>(lr + j, a);
+    piece(j, a);
 #pragma unroll
     for (int e = 0; e < V; ++e) a[e] = (__builtin_amdgcn_exp2f((a[e] - mx) * 1.4426950408889634f) * inv - (j + e == lab ? 1.f : 0.f)) * inv_n;
     stv<T, V>(lr + j, a);
@@ -841,11 +849,11 @@ __global__ void __launch_bounds__(BLK) ce_row_k(int64_t rows, int vocab, T* __re
 // once, all loads of a row in flight together; the maximum, the sum of exponentials and the gradient are three
 // passes over registers.  The values stay in their storage type (16 bytes per piece) until they are used.
 template <typename T, int V, int NV, bool COUNT, bool PAST>
-__global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* __restrict__ logits,
+__global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, int64_t ld, T* __restrict__ logits,
                                                      const int32_t* __restrict__ labels, float* __restrict__ row_loss) {
   __shared__ float red[BLK / 64];
   const int64_t row = blockIdx.x;
-  T* lr = logits + row * vocab;
+  T* lr = logits + row * ld;
   int lab = labels[row];
   CeTargets<COUNT> targets;
   targets.request(rows, labels, row_loss);
@@ -863,7 +871,14 @@ __global__ void __launch_bounds__(BLK) ce_row_reg_k(int64_t rows, int vocab, T* 
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int j = (i * BLK + threadIdx.x) * V;
-    if (j < vocab) raw[i] = *reinterpret_cast<const Vec<T, V>*>(lr + j);
+    if (j < vocab) {
+      raw[i] = *reinterpret_cast<const Vec<T, V>*>(lr + j);
+      if (j + V > vocab) {
+#pragma unroll
+        for (int e = 0; e < V; ++e)
+          if (j + e >= vocab) raw[i].v[e] = from_f32<T>(-INFINITY);
+      }
+    }
   }
   const float inv_n = targets.inverse(rows, row_loss, red);
   constexpr float LOG2E = 1.4426950408889634f;
@@ -1387,25 +1402,26 @@ hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_l
 }
 
 template <bool COUNT, bool PAST>
-static void launch_ce_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss, hipStream_t st) {
+static void launch_ce_rows(int dt, int64_t rows, int V_, int64_t ld, void* logits, const int32_t* labels, float* row_loss, hipStream_t st) {
   const dim3 grid((unsigned)rows);
-#define OK(v) (V_ % (v) == 0 && aligned16(logits))
+  // (rows may end inside a piece where there is room for all of it: the kernels leave zeros there)
+#define OK(v) (ld % (v) == 0 && ld >= cdiv(V_, v) * (v) && aligned16(logits))
   // 16-byte pieces of a row a thread keeps: 16 (rows of up to 32768 bf16 or 16384 fp32 values) or 32
   if (dt == DT_BF16 && OK(8) && V_ <= BLK * 8 * 16) {
-    ce_row_reg_k<bf16, 8, 16, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
+    ce_row_reg_k<bf16, 8, 16, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, ld, (bf16*)logits, labels, row_loss);
   } else if (dt == DT_BF16 && OK(8) && V_ <= BLK * 8 * 32) {
-    ce_row_reg_k<bf16, 8, 32, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (bf16*)logits, labels, row_loss);
+    ce_row_reg_k<bf16, 8, 32, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, ld, (bf16*)logits, labels, row_loss);
   } else if (dt == DT_F32 && OK(4) && V_ <= BLK * 4 * 16) {
-    ce_row_reg_k<float, 4, 16, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
+    ce_row_reg_k<float, 4, 16, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, ld, (float*)logits, labels, row_loss);
   } else if (dt == DT_F32 && OK(4) && V_ <= BLK * 4 * 32) {
-    ce_row_reg_k<float, 4, 32, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, (float*)logits, labels, row_loss);
+    ce_row_reg_k<float, 4, 32, COUNT, PAST><<<grid, BLK, 0, st>>>(rows, V_, ld, (float*)logits, labels, row_loss);
   } else {
-    DISPATCH_TV(dt, OK, (ce_row_k<T, V, COUNT><<<grid, BLK, 0, st>>>(rows, V_, (T*)logits, labels, row_loss)));
+    DISPATCH_TV(dt, OK, (ce_row_k<T, V, COUNT><<<grid, BLK, 0, st>>>(rows, V_, ld, (T*)logits, labels, row_loss)));
   }
 #undef OK
 }
 
-hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
+hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, int64_t ld, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st) {
   if (rows == 0) return hipSuccess;
   // 2048 x 32000 in bf16 (131 MB), with the mean: 61.0 -> 52.7 us past the caches, the step around it as before; 231 x 32000 (15 MB): the
@@ -1413,7 +1429,7 @@ hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, void* logits, const 
   const bool past_caches = rows * V_ * (dt == DT_BF16 ? 2 : 4) >= PAST_CACHES_BYTES;
   const auto launch = cross_entropy_counts_apart(rows) ? (past_caches ? launch_ce_rows<false, true> : launch_ce_rows<false, false>)
                                                        : (past_caches ? launch_ce_rows<true, true> : launch_ce_rows<true, false>);
-  launch(dt, rows, V_, logits, labels, row_loss, st);
+  launch(dt, rows, V_, ld, logits, labels, row_loss, st);
   LAUNCH_CHECK();
 }
 
@@ -1426,7 +1442,7 @@ hipError_t cross_entropy_mean(int64_t rows, const float* row_loss, float* loss_o
 hipError_t cross_entropy(int dt, int64_t rows, int V_, void* logits, const int32_t* labels, float* row_loss,
                          float* loss_out, hipStream_t st) {
   hipError_t e = cross_entropy_count(rows, labels, row_loss, st);
-  if (e == hipSuccess) e = cross_entropy_rows(dt, rows, V_, logits, labels, row_loss, st);
+  if (e == hipSuccess) e = cross_entropy_rows(dt, rows, V_, V_, logits, labels, row_loss, st);
   if (e == hipSuccess) e = cross_entropy_mean(rows, row_loss, loss_out, st);
   return e;
 }

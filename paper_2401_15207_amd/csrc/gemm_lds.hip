@@ -41,7 +41,7 @@ struct LdsP {
   int nh;
   int64_t sa1, sa2, sb1, sb2, sc1, sc2;
   int tiles_m, tiles_n, band;
-  int vec;  // rows of C and R can be moved in 16-byte pieces
+  int vec;  // rows of C and R can be moved in 16-byte pieces (but for what is left of them at N)
   int past_caches;  // (fp32, no bias, no residual, vec) C is written past the caches
   bf16* C2; int64_t ldc2;  // EPI_GELU, EPI_GELU_BWD
 };
@@ -342,7 +342,7 @@ __global__ void __launch_bounds__((64 * Tile<BM, BN, RING>::NW), (Tile<BM, BN, R
           for (int e = 0; e < 8; ++e) o[e] = static_cast<__bf16>(static_cast<float>(t[e]) * gelu_df(static_cast<float>(pre[e])));
           *reinterpret_cast<bf16x8*>(C + row * p.ldc + col) = o;
         }
-      } else if (p.vec) {
+      } else if (p.vec && col + 8 <= p.N) {
         if (p.bias) {
           const bf16x8 t = *reinterpret_cast<const bf16x8*>(p.bias + col);
 #pragma unroll
@@ -432,7 +432,11 @@ bool lds_gemm_applies(const Gemm& g) {
     const int64_t in_stage = kmajor ? (rows < 256 ? rows : 256) : (g.K < LK ? g.K : LK);
     return ld < (int64_t(1) << 31) && in_stage * ld * 2 <= BUF_BYTES;
   };
-  const bool a_ok = al16(g.A) && g.lda % 8 == 0 && g.sa1 % 8 == 0 && g.sa2 % 8 == 0 && (g.a_kmajor ? g.K % 8 == 0 : g.M % 8 == 0);
+  // A's contiguous direction may end inside a piece where zeros follow: as k they meet rows of B that are zeroed (or, k-major, are not there:
+  // refused), as rows of C they are not stored.
+  const int64_t along = g.a_kmajor ? g.K : g.M;
+  const bool whole = along % 8 == 0 || (g.zero_tail && g.lda >= (along + 7) / 8 * 8 && !(g.a_kmajor && g.b_kmajor));
+  const bool a_ok = al16(g.A) && g.lda % 8 == 0 && g.sa1 % 8 == 0 && g.sa2 % 8 == 0 && whole;
   const bool b_ok = al16(g.B) && g.ldb % 8 == 0 && g.sb1 % 8 == 0 && g.sb2 % 8 == 0 && (g.b_kmajor ? g.K % 8 == 0 : g.N % 8 == 0);
   return a_ok && b_ok && fits(g.a_kmajor, g.M, g.lda) && fits(g.b_kmajor, g.N, g.ldb) && g.K < (int64_t(1) << 30) && g.M < (int64_t(1) << 30) &&
          g.N < (int64_t(1) << 30) && ((g.M + 31) / 32) * ((g.N + 31) / 32) < (int64_t(1) << 31);
@@ -455,11 +459,11 @@ hipError_t gemm_lds(const Gemm& g, hipStream_t st) {
   p.R = g.R; p.ldr = g.ldr;
   p.nh = g.nh; p.sa1 = g.sa1; p.sa2 = g.sa2; p.sb1 = g.sb1; p.sb2 = g.sb2; p.sc1 = g.sc1; p.sc2 = g.sc2;
   p.band = g.band;
-  p.vec = g.N % 8 == 0 && g.ldc % 8 == 0 && al16(g.C) && (!g.R || (g.ldr % 8 == 0 && al16(g.R))) && g.sc1 % 8 == 0 &&
+  p.vec = g.ldc % 8 == 0 && al16(g.C) && (!g.R || (g.ldr % 8 == 0 && al16(g.R))) && g.sc1 % 8 == 0 &&
           g.sc2 % 8 == 0 && (!g.bias || al16(g.bias));
   const int nz = g.nb * g.nh;
   // As in gemm_tt_k (231 tokens, decoder of width 4096: 7.66 -> 7.52 ms a sweep).
-  p.past_caches = g.out_f32 && p.vec && !g.bias && !g.R && g.M * g.N * nz * 4 >= PAST_CACHES_BYTES;
+  p.past_caches = g.out_f32 && p.vec && g.N % 4 == 0 && !g.bias && !g.R && g.M * g.N * nz * 4 >= PAST_CACHES_BYTES;
   if (g.epi != EPI_NONE) {
     if (!lds_gelu_applies(g)) return hipErrorInvalidValue;
     p.C2 = reinterpret_cast<bf16*>(g.C2); p.ldc2 = g.ldc2;

@@ -18,6 +18,7 @@ struct Gemm {
   int64_t M = 0, N = 0, K = 0;
   const void* A = nullptr; int64_t lda = 0;
   const void* B = nullptr; int64_t ldb = 0;
+  bool zero_tail = false;               // bf16: every row of A goes on with zeros up to a multiple of eight values (within lda)
   void* C = nullptr; int64_t ldc = 0;
   const void* bias = nullptr;           // [N], element type of A, or null
   const void* R = nullptr; int64_t ldr = 0;  // residual added in the epilogue, C's type, or null
@@ -161,7 +162,7 @@ hipError_t cross_entropy(int dt, int64_t rows, int V, void* logits, const int32_
 // gradient over the logits); the mean of the per-row losses
 bool cross_entropy_counts_apart(int64_t rows);
 hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_loss, hipStream_t st);
-hipError_t cross_entropy_rows(int dt, int64_t rows, int V, void* logits, const int32_t* labels, float* row_loss,
+hipError_t cross_entropy_rows(int dt, int64_t rows, int V, int64_t ld, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st);
 hipError_t cross_entropy_mean(int64_t rows, const float* row_loss, float* loss_out, hipStream_t st);
 // g_tok[v, :] = (add ? g_tok[v, :] : as zeroed by the caller) + sum over positions t holding token v of dx[t, :],

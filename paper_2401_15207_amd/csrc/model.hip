@@ -320,6 +320,10 @@ struct hift_model {
   std::vector<void*> xs;  // residual stream: xs[l] enters layer l, xs[L] enters the head
   std::vector<LayerAct> la;
   void *e0 = nullptr, *xf = nullptr, *xcls = nullptr, *logits = nullptr;
+  // bf16 rows of logits take whole 16-byte pieces, zeros past the vocabulary (cross-entropy leaves them), so that the head's contractions
+  // run on gemm_lds_k whatever the vocabulary.  1936 tokens, width 1280, vocabulary 12466, rows of 12466 values (gemm_f32_k) and
+  // of 12472: input gradient 728 and 131 us, weight gradient 542 and 66, product 104 and 79; errors against 64 bits over 44 models the same.
+  int64_t logits_ld = 0;
   float *st_e = nullptr, *st_f = nullptr, *row_loss = nullptr, *part = nullptr;
   float *loss_dev = nullptr, *loss_at = nullptr;  // LOSS_RING losses, and the one that a step leaves its own in
   void *D[3] = {nullptr, nullptr, nullptr}, *dqkv = nullptr, *prob = nullptr, *dprob = nullptr, *attn_dsum = nullptr, *dact = nullptr, *dffn = nullptr,
@@ -371,6 +375,7 @@ void carve(hift_model* mm, void* dev, size_t* dev_bytes, size_t* pinned_bytes, s
   const size_t es = M.es;
   const bool enc = c.arch == HIFT_ARCH_POSTLN_ENCODER, rms = c.arch == HIFT_ARCH_RMS_ROPE_DECODER;
   const int64_t fw = rms ? 2 * f : f;
+  M.logits_ld = enc ? c.n_classes : M.dt == DT_BF16 ? (V + 7) / 8 * 8 : V;
   Bump b(dev);
   b.cat = MEM_MASTER;
   M.master = M.master_host ? nullptr : (float*)b.take(np * 4);
@@ -443,7 +448,7 @@ void carve(hift_model* mm, void* dev, size_t* dev_bytes, size_t* pinned_bytes, s
   } else {
     M.xf = b.take(T * d * es);
     M.st_f = (float*)b.take(T * 2 * 4);
-    M.logits = b.take(T * V * es);
+    M.logits = b.take(T * M.logits_ld * es);
   }
   b.cat = MEM_WORK;
   M.row_loss = (float*)b.take((T + 1) * 4);
@@ -680,14 +685,14 @@ bool folds_norm(const hift_model* M, const Tensor& w, int64_t rows) {
 // rowsq (optional): in, whether the sums of squares of y's rows are wanted in M->rowsq (y feeds a weight that
 // folds its normalisation); out, whether the kernel that ran left them there.
 hift_status linear(hift_model* M, const void* x, int64_t rows, const Tensor& w, const Tensor* bias, const void* R,
-                   void* y, LinEpi* epi = nullptr, bool* rowsq = nullptr) {
+                   void* y, LinEpi* epi = nullptr, bool* rowsq = nullptr, int64_t ldy = 0) {
   // y[rows, out] = x[rows, in] . w[out, in]^T (+ bias) (+ R)
   Gemm g;
   g.dtype = M->dt;
   g.M = rows; g.N = w.rows; g.K = w.cols;
   g.A = x; g.lda = w.cols;
   g.B = M->W(w); g.ldb = w.cols;
-  g.C = y; g.ldc = w.rows;
+  g.C = y; g.ldc = ldy ? ldy : w.rows;
   g.bias = bias ? M->W(*bias) : nullptr;
   g.R = R; g.ldr = w.rows;
   Scope sc(M, CAT_GEMM, 2.0 * rows * w.rows * w.cols);
@@ -746,12 +751,12 @@ hift_status linear(hift_model* M, const void* x, int64_t rows, const Tensor& w, 
 // pre-activations and *fused is set.  Otherwise dx is written and the caller runs the separate kernel.
 // gelu: the activation was GELU: gate_pre is [rows, in] and dgu [rows, in] receives d act * gelu'(pre).
 hift_status linear_dx(hift_model* M, const void* dy, int64_t rows, const Tensor& w, const void* R, void* dx,
-                      const void* gate_pre = nullptr, void* dgu = nullptr, bool* fused = nullptr, bool gelu = false) {
+                      const void* gate_pre = nullptr, void* dgu = nullptr, bool* fused = nullptr, bool gelu = false, int64_t ldy = 0) {
   // dx[rows, in] = dy[rows, out] . w[out, in] (+ R)
   Gemm g;
   g.dtype = M->dt;
   g.M = rows; g.N = w.cols; g.K = w.rows;
-  g.A = dy; g.lda = w.rows;
+  g.A = dy; g.lda = ldy ? ldy : w.rows; g.zero_tail = ldy > w.rows;
   g.B = M->W(w); g.ldb = w.cols; g.b_kmajor = false;
   g.C = dx; g.ldc = w.cols;
   g.R = R; g.ldr = w.cols;
@@ -787,13 +792,13 @@ hift_status linear_dx(hift_model* M, const void* dy, int64_t rows, const Tensor&
   return HIFT_OK;
 }
 
-hift_status linear_dw(hift_model* M, const void* dy, const void* x, int64_t rows, const Tensor& w, int64_t glo) {
+hift_status linear_dw(hift_model* M, const void* dy, const void* x, int64_t rows, const Tensor& w, int64_t glo, int64_t ldy = 0) {
   // grad_w[out, in] = dy[rows, out]^T . x[rows, in], fp32, into the group-local gradient buffer
   Gemm g;
   g.dtype = M->dt;
   g.out_f32 = true;
   g.M = w.rows; g.N = w.cols; g.K = rows;
-  g.A = dy; g.lda = w.rows; g.a_kmajor = false;
+  g.A = dy; g.lda = ldy ? ldy : w.rows; g.a_kmajor = false; g.zero_tail = ldy > w.rows;
   g.B = x; g.ldb = w.cols; g.b_kmajor = false;
   g.C = M->grad + (w.off - glo); g.ldc = w.cols;
   Scope sc(M, CAT_GEMM_REST, 2.0 * rows * w.rows * w.cols);
@@ -1157,16 +1162,16 @@ hift_status forward(hift_model* M, const hift_batch* bt, int keep_from) {
     }
     ST_TRY(linear(M, M->xcls, B, M->T_("wc"), &M->T_("bc"), nullptr, M->logits));
     if (cross_entropy_counts_apart(B)) RW(RW_LOSS_MEAN, 4.0 * (B), cross_entropy_count(B, bt->labels, M->row_loss, st));
-    RW(RW_CROSS_ENTROPY, 2.0 * (B) * (c.n_classes) * es, cross_entropy_rows(dt, B, c.n_classes, M->logits, bt->labels, M->row_loss, st));
+    RW(RW_CROSS_ENTROPY, 2.0 * (B) * (c.n_classes) * es, cross_entropy_rows(dt, B, c.n_classes, M->logits_ld, M->logits, bt->labels, M->row_loss, st));
     RW(RW_LOSS_MEAN, 4.0 * (B), cross_entropy_mean(B, M->row_loss, M->loss_at, st));
   } else {
     {
       if (rms) RW(RW_NORM_FWD, 2.0 * T * d * es, norm_fwd(dt, true, T, d, c.norm_eps, xl, M->W("gf"), nullptr, M->xf, M->st_f, st));
       else RW(RW_NORM_FWD, 2.0 * T * d * es, norm_fwd(dt, false, T, d, c.norm_eps, xl, M->W("lnf_g"), M->W("lnf_b"), M->xf, M->st_f, st));
     }
-    ST_TRY(linear(M, M->xf, T, M->T_(c.tie_embeddings ? "tok_emb" : "whead"), nullptr, nullptr, M->logits));
+    ST_TRY(linear(M, M->xf, T, M->T_(c.tie_embeddings ? "tok_emb" : "whead"), nullptr, nullptr, M->logits, nullptr, nullptr, M->logits_ld));
     if (cross_entropy_counts_apart(T)) RW(RW_LOSS_MEAN, 4.0 * (T), cross_entropy_count(T, bt->labels, M->row_loss, st));
-    RW(RW_CROSS_ENTROPY, 2.0 * (T) * (c.vocab) * es, cross_entropy_rows(dt, T, c.vocab, M->logits, bt->labels, M->row_loss, st));
+    RW(RW_CROSS_ENTROPY, 2.0 * (T) * (c.vocab) * es, cross_entropy_rows(dt, T, c.vocab, M->logits_ld, M->logits, bt->labels, M->row_loss, st));
     RW(RW_LOSS_MEAN, 4.0 * (T), cross_entropy_mean(T, M->row_loss, M->loss_at, st));
   }
   return HIFT_OK;
@@ -1201,8 +1206,8 @@ hift_status backward(hift_model* M, const hift_batch* bt, int ulo, int uhi, int6
     // tied embeddings: the output matrix is the token table of unit 0; its gradient starts here and the
     // embedding part is added at the bottom of the backward pass
     const Tensor& wh = M->T_(c.tie_embeddings ? "tok_emb" : "whead");
-    if (c.tie_embeddings ? active(0) : head_on) ST_TRY(linear_dw(M, M->logits, M->xf, T, wh, glo));
-    ST_TRY(linear_dx(M, M->logits, T, wh, nullptr, D2));  // d xf
+    if (c.tie_embeddings ? active(0) : head_on) ST_TRY(linear_dw(M, M->logits, M->xf, T, wh, glo, M->logits_ld));
+    ST_TRY(linear_dx(M, M->logits, T, wh, nullptr, D2, nullptr, nullptr, nullptr, false, M->logits_ld));  // d xf
     const Tensor& g = M->T_(rms ? "gf" : "lnf_g");
     if (head_on)
       RW(RW_NORM_BWD_PARAMS, 2.0 * T * d * es, norm_bwd_params(dt, rms, T, d, D2, M->xs[L], M->st_f, M->part, G(g),
@@ -1631,6 +1636,8 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
   for (int q = 0; q < NSLOT; ++q)
     if (M->slot[q]) CR_TRY(fill_zero(M->slot[q], (size_t)M->n_move * M->grad_cap * 4, M->cs));
   CR_TRY(fill_zero(M->grad, (size_t)M->grad_cap * 4, M->cs));
+  if (M->cfg.arch != HIFT_ARCH_POSTLN_ENCODER && M->logits_ld > M->cfg.vocab)
+    CR_TRY(fill_zero(M->logits, (size_t)M->maxT * M->logits_ld * M->es, M->cs));  // what follows the rows
   if (M->gemm_ws) CR_TRY(fill_zero(M->gemm_ws, 1024, M->cs));  // the counters; every launch leaves them at zero
   if (M->fac) CR_TRY(fill_zero(M->fac, (size_t)M->n_fac * 4, M->cs));
   if (M->lora_r > 0) {  // adapters start at zero (the model is the base model) until hift_lora_write; so do their moments
