@@ -166,9 +166,10 @@ hipError_t cross_entropy_rows(int dt, int64_t rows, int V, int64_t ld, void* log
                               hipStream_t st);
 hipError_t cross_entropy_mean(int64_t rows, const float* row_loss, float* loss_out, hipStream_t st);
 // g_tok[v, :] = (add ? g_tok[v, :] : as zeroed by the caller) + sum over positions t holding token v of dx[t, :],
-// in position order (no atomics: the first position holding a token does its row);  g_pos[s, :] = sum_b dx[b*S+s, :]
+// in position order (no atomics: the first position holding a token does its row);  g_pos[s, :] = sum_b dx[b*S+s, :].
+// stamps (optional, one per token): those of tokens that occur are set to `stamp`.
 hipError_t embed_bwd(int dt, const int32_t* tokens, int64_t T, int S, int d, int V, const void* dx,
-                     float* g_tok, float* g_pos, bool add, hipStream_t st);
+                     float* g_tok, float* g_pos, bool add, hipStream_t st, int32_t* stamps = nullptr, int32_t stamp = 0);
 // rows of x at positions b*S (first token of every sequence) -> y [B, d], and the adjoint
 hipError_t gather_first(int dt, int B, int S, int d, const void* x, void* y, hipStream_t st);
 hipError_t scatter_first(int dt, int B, int S, int d, const void* dy, void* dx, hipStream_t st);
@@ -192,6 +193,8 @@ struct OptItem {
   float* master; const float* grad; float *s1, *s2;
   void* compute_copy;
   bool grad_fused;
+  // (optimizer_update) the gradient's rows of `row` values (a multiple of four) whose entry in `stamps` is not `stamp` are zeros that nobody wrote
+  const int32_t* stamps = nullptr; int32_t stamp = 0, row = 0;
 };
 constexpr int OPT_TABLE = 32;
 hipError_t optimizer_update(const OptArgs& o, const OptItem* items, int n_items, hipStream_t st);

@@ -325,6 +325,8 @@ struct hift_model {
   // of 12472: input gradient 728 and 131 us, weight gradient 542 and 66, product 104 and 79; errors against 64 bits over 44 models the same.
   int64_t logits_ld = 0;
   float *st_e = nullptr, *st_f = nullptr, *row_loss = nullptr, *part = nullptr;
+  int32_t* tok_stamps = nullptr;  // which embeddings backward a token was last seen in, or null: the table's gradient is cleared instead
+  int32_t tok_stamp = 0;
   float *loss_dev = nullptr, *loss_at = nullptr;  // LOSS_RING losses, and the one that a step leaves its own in
   void *D[3] = {nullptr, nullptr, nullptr}, *dqkv = nullptr, *prob = nullptr, *dprob = nullptr, *attn_dsum = nullptr, *dact = nullptr, *dffn = nullptr,
        *dcls = nullptr;
@@ -452,6 +454,8 @@ void carve(hift_model* mm, void* dev, size_t* dev_bytes, size_t* pinned_bytes, s
   }
   b.cat = MEM_WORK;
   M.row_loss = (float*)b.take((T + 1) * 4);
+  // (Adafactor reads the gradient several times, and a tied table's has a part in every row)
+  M.tok_stamps = d % 4 == 0 && !c.tie_embeddings && M.opt.kind != HIFT_ADAFACTOR && c.lora_rank == 0 ? (int32_t*)b.take(V * 4) : nullptr;
   M.loss_dev = M.loss_at = (float*)b.take(LOSS_RING * 4);
   const int64_t wmax = std::max<int64_t>(std::max<int64_t>(3 * d, fw), std::max<int64_t>(d, c.n_classes));
   M.part = (float*)b.take((size_t)2 * ((T + 63) / 64) * wmax * 4);
@@ -1332,14 +1336,16 @@ hift_status backward(hift_model* M, const hift_batch* bt, int ulo, int uhi, int6
     }
     float* gpos = nullptr;
     const bool tied = c.tie_embeddings != 0;  // the table's gradient already holds its part as output matrix
-    int64_t zero_cnt = tied ? 0 : te.count();
+    const bool stamped = M->tok_stamps != nullptr;
+    int64_t zero_cnt = tied || stamped ? 0 : te.count();
     if (!rms) {
       const Tensor& pe = M->T_("pos_emb");
       gpos = G(pe);
       zero_cnt += pe.count();  // pos_emb follows tok_emb in the layout
     }
-    if (zero_cnt) RW(RW_EMBED_BWD, 1.0 * ((size_t)zero_cnt * 4), fill_zero(tied ? gpos : G(te), (size_t)zero_cnt * 4, st));
-    RW(RW_EMBED_BWD, (double)T * d * (es + 4.0), embed_bwd(dt, bt->tokens, T, S, d, c.vocab, dx, G(te), gpos, tied, st));
+    if (zero_cnt) RW(RW_EMBED_BWD, 1.0 * ((size_t)zero_cnt * 4), fill_zero(tied || stamped ? gpos : G(te), (size_t)zero_cnt * 4, st));
+    M->tok_stamp += 1;
+    RW(RW_EMBED_BWD, (double)T * d * (es + 4.0), embed_bwd(dt, bt->tokens, T, S, d, c.vocab, dx, G(te), gpos, tied, st, M->tok_stamps, M->tok_stamp));
   }
   return HIFT_OK;
 }
@@ -1638,6 +1644,7 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
   CR_TRY(fill_zero(M->grad, (size_t)M->grad_cap * 4, M->cs));
   if (M->cfg.arch != HIFT_ARCH_POSTLN_ENCODER && M->logits_ld > M->cfg.vocab)
     CR_TRY(fill_zero(M->logits, (size_t)M->maxT * M->logits_ld * M->es, M->cs));  // what follows the rows
+  if (M->tok_stamps) CR_TRY(fill_zero(M->tok_stamps, ((size_t)M->cfg.vocab * 4 + 15) / 16 * 16, M->cs));
   if (M->gemm_ws) CR_TRY(fill_zero(M->gemm_ws, 1024, M->cs));  // the counters; every launch leaves them at zero
   if (M->fac) CR_TRY(fill_zero(M->fac, (size_t)M->n_fac * 4, M->cs));
   if (M->lora_r > 0) {  // adapters start at zero (the model is the base model) until hift_lora_write; so do their moments
@@ -1963,7 +1970,8 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
       const bool has_copies = M->wpk && (t.pk_fwd >= 0 || t.pk_bwd >= 0);
       void* cc = M->dt == DT_BF16 ? M->W(t) : nullptr;  // null also for a matrix kept only in fragment order
       if (cc) bytes += 2.0 * t.count();
-      const OptItem item{t.count(), t.kind == HIFT_KIND_MATRIX, M->unit_steps[t.unit], master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, grad_fused(t)};
+      OptItem item{t.count(), t.kind == HIFT_KIND_MATRIX, M->unit_steps[t.unit], master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, grad_fused(t)};
+      if (M->tok_stamps && t.name == "tok_emb") { item.stamps = M->tok_stamps; item.stamp = M->tok_stamp; item.row = (int32_t)t.cols; }
       const PackItem pack{t.rows, t.cols, t.pk_fwd >= 0 ? M->wpk + t.pk_fwd : nullptr, t.pk_bwd >= 0 ? M->wpk + t.pk_bwd : nullptr,
                           t.pk_gain >= 0 ? M->W(M->lay.t[t.pk_gain]) : nullptr, t.pk_order};
       if (has_copies && M->opt.kind != HIFT_ADAFACTOR && update_packs(item, pack)) {

@@ -61,6 +61,9 @@ struct OptTensor {
   int vec;         // opt_k: pieces of four are 16-byte aligned in every array
   int grad_fused;  // AdamW: which product of a moment's sum is fused
   int cc_nt;       // opt_k: the copy is written past the caches
+  const int32_t* stamps;  // opt_k: see OptItem
+  int32_t stamp;
+  uint32_t row4;   // pieces of four to a row
 };
 struct OptHyper {
   float lr, b1, omb1, b2, omb2, eps, mu;
@@ -108,6 +111,7 @@ inline OptTensor opt_tensor(const OptArgs& o, const OptItem& it) {
   t.inv_bc2 = (float)(1.0 / (1.0 - pow(o.beta2, (double)it.t)));
   t.first = it.t == 1 ? 1 : 0;
   t.grad_fused = it.grad_fused;
+  t.stamps = it.stamps; t.stamp = it.stamp; t.row4 = (uint32_t)(it.row / 4);
   return t;
 }
 

@@ -1,0 +1,63 @@
+"""The token table's update where most rows have no token in the batch and their gradient is neither cleared nor read: the same as with every row's
+gradient written (a plain update from the moments that the step leaves), over several steps with other tokens each time."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("opt", [dict(kind="adamw", lr=1e-2, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.1, momentum=0.0),
+                                 dict(kind="sgd", lr=1e-1, beta1=0.0, beta2=0.0, eps=0.0, weight_decay=0.1, momentum=0.9),
+                                 dict(kind="sgd", lr=1e-1, beta1=0.0, beta2=0.0, eps=0.0, weight_decay=0.1, momentum=0.0)], ids=["adamw", "sgdm", "sgd"])
+@pytest.mark.parametrize("arch,dtype,d,vocab", [(2, 1, 128, 1001), (0, 0, 64, 999), (0, 1, 128, 515), (1, 0, 36, 333)])
+def test_rows_without_a_token(opt, arch, dtype, d, vocab):
+    import torch
+    import paper_2401_15207_amd as H
+    cfg = dict(arch=arch, n_layers=1, d_model=d, n_heads=2, d_ffn=4 * d, vocab=vocab, max_seq=16, n_classes=3 if arch == 1 else 0, norm_eps=1e-5,
+               rope_base=10000.0, dtype=dtype)
+    m = H.HiftModel(cfg, opt, 1, 2, 16)
+    rng = np.random.default_rng(vocab)
+    name, shape, _kind, unit, off = m.tensors[0]
+    assert name == "tok_emb" and unit == 0 and off == 0
+    size = sum(int(np.prod(s)) for _n, s, _k, u, _o in m.tensors if u == 0)
+    for u in sorted({t[3] for t in m.tensors}):
+        n = sum(int(np.prod(s)) for _n, s, _k, uu, _o in m.tensors if uu == u)
+        w = torch.from_numpy((rng.standard_normal(n) * 0.02).astype(np.float32)).to(torch.bfloat16).float().numpy()
+        m.write_params(u, u + 1, w)
+    m.set_group_schedule("bottom2up", 1, 0)
+    table = vocab * d
+    w, s1, s2 = m.read_params(0, 1)[:table].astype(np.float64), np.zeros(table), np.zeros(table)
+    for t in range(1, 4):
+        tok = torch.from_numpy(rng.integers(0, vocab, (2, 16)).astype(np.int32)).cuda()
+        if arch == 1:
+            lab = torch.tensor([0, 2], dtype=torch.int32, device="cuda")
+        else:
+            lab = torch.full_like(tok, -1)
+            lab[:, :-1] = tok[:, 1:]
+        m.step(tok, lab, 0)
+        rows = np.ones(vocab, dtype=bool)
+        rows[np.unique(tok.cpu().numpy())] = False
+        at = np.repeat(rows, d)
+        new = m.read_params(0, 1)[:table].astype(np.float64)
+        lr, wd = opt["lr"], opt["weight_decay"]
+        # a row without a token: its gradient is zero, so the update is known from what was there before
+        if opt["kind"] == "adamw":
+            s1n, s2n = 0.9 * s1, 0.999 * s2
+            move = lr * (s1n / (1 - 0.9 ** t)) / (np.sqrt(s2n / (1 - 0.999 ** t)) + 1e-8)
+            want, size_of = w * (1 - lr * wd) - move, np.abs(w) + np.abs(move)
+        else:
+            g = wd * w
+            s1n = g if t == 1 else opt["momentum"] * s1 + g
+            want, size_of = w - lr * (s1n if opt["momentum"] else g), np.abs(w) + lr * (np.abs(opt["momentum"] * s1) + np.abs(g))
+        # a dozen roundings in 32 bits (of the rates and of each operation) of the two terms, which may cancel
+        assert (np.abs(new - want)[at] <= 16 * 2.0 ** -24 * size_of[at] + 1e-30).all()
+        assert (new[~at] != want[~at]).mean() > 0.5  # and those of tokens do have one
+        w0, before, w = w, s1, new
+        if opt["kind"] == "adamw" or opt["momentum"]:
+            s1 = m.read_state(0, 1, 0)[:table].astype(np.float64)
+            # sums of two terms that may cancel: four roundings in 32 bits of terms of their size
+            terms = np.abs(opt["momentum"] * before) + np.abs(wd * w0) if opt["kind"] == "sgd" else np.abs(s1n)
+            assert (np.abs(s1 - s1n)[at] <= 4 * 2.0 ** -24 * terms[at] + 1e-30).all()
+        if opt["kind"] == "adamw":
+            s2 = m.read_state(0, 1, 1)[:table].astype(np.float64)
+    assert size >= table
