@@ -1414,6 +1414,7 @@ hipError_t cross_entropy_count(int64_t rows, const int32_t* labels, float* row_l
   LAUNCH_CHECK();
 }
 
+constexpr int64_t CE_PAST_CACHES_BYTES = int64_t(112) << 20;
 template <bool COUNT, bool PAST>
 static void launch_ce_rows(int dt, int64_t rows, int V_, int64_t ld, void* logits, const int32_t* labels, float* row_loss, hipStream_t st) {
   const dim3 grid((unsigned)rows);
@@ -1441,9 +1442,11 @@ static void launch_ce_rows(int dt, int64_t rows, int V_, int64_t ld, void* logit
 hipError_t cross_entropy_rows(int dt, int64_t rows, int V_, int64_t ld, void* logits, const int32_t* labels, float* row_loss,
                               hipStream_t st) {
   if (rows == 0) return hipSuccess;
-  // 2048 x 32000 in bf16 (131 MB), with the mean: 61.0 -> 52.7 us past the caches, the step around it as before; 231 x 32000 (15 MB): the
-  // step 0.5 % slower.
-  const bool past_caches = rows * V_ * (dt == DT_BF16 ? 2 : 4) >= PAST_CACHES_BYTES;
+  // On logits that lie in memory a large gradient leaves faster past the caches (2048 x 32000 in bf16, 131 MB, with the mean: 61 -> 53 us).  On logits that
+  // the head's product has just left in the last-level cache the launch itself gains nothing (56 and 55 us) and a step gains little: whole steps of
+  // ten models with 131 to 820 MB of logits take 0.991 to 1.003 times as long as without.  At 103 MB (1024 x 50257) they take 1.00 to 1.01: the contractions
+  // that come next find a gradient of that size in the cache otherwise.
+  const bool past_caches = rows * ld * (dt == DT_BF16 ? 2 : 4) >= CE_PAST_CACHES_BYTES;
   const auto launch = cross_entropy_counts_apart(rows) ? (past_caches ? launch_ce_rows<false, true> : launch_ce_rows<false, false>)
                                                        : (past_caches ? launch_ce_rows<true, true> : launch_ce_rows<true, false>);
   launch(dt, rows, V_, ld, logits, labels, row_loss, st);
