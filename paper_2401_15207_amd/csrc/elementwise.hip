@@ -997,9 +997,9 @@ __global__ void __launch_bounds__(BLK) copy_stream_k(u32x4_t* __restrict__ dst, 
 // block finds its tensor in the table that came with the launch.
 // Memory bound: 6.2 TB/s on a layer of 202 M parameters.  Four wavefronts a SIMD (64 KB of AdamW's loads in flight in a compute unit):
 // more of them only make memory change rows more often (202 M parameters 1016 us with eight, 977 with four, 1022 with two; 36 M 162 and 158; of momentum
-// 67 M 210 and 201; up to 20 M the same); plain SGD, which reads two arrays, keeps eight (67 M 121, 125 with four).  A rounded copy of
-// OPT_COPY_PAST_CACHES parameters or more goes past the caches too, like the rest (50 M 238 -> 232 us, 202 M 1045 -> 1008); a smaller one
-// may still be there when it is read or written again (three of 44 M in turn 192 us, 205 past the caches).
+// 67 M 210 and 201; up to 20 M the same); plain SGD, which reads two arrays, keeps eight (67 M 121, 125 with four).  A rounded copy that is
+// larger than the last-level cache goes past it too, like the rest (AdamW on 150 M 776 -> 748 us, 202 M 1039 -> 1008; SGD 356 -> 343, 469 -> 448); a smaller one may
+// still be there when it is written or read again, and does worse past it (135 M 713 and 738 us, SGD 280 and 307; 67 M 330 and 345, SGD 133 and 145).
 // Launched tensor by tensor, the 16 tensors of an encoder layer took
 // 16 launches of which 12 were gains and biases: 2.8 us each for work of less than one.
 template <int NT>  // 1 for a single tensor (the small table saves 0.2 us of a 3.6 us launch), OPT_TABLE for a group
@@ -1032,7 +1032,7 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
   }
 }
 
-constexpr int64_t OPT_COPY_PAST_CACHES = 48000000;  // 96 MB of the 256 MB last-level cache
+constexpr int64_t OPT_COPY_PAST_CACHES = 150000000;  // 300 MB; the last-level cache has 256
 constexpr int opt_waves(int kind) { return kind == 3 ? 8 : 4; }
 template <int KIND, int NT>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(opt_waves(KIND), opt_waves(KIND)))) opt_k(OptHyper h, OptTable<NT> table) {
