@@ -996,8 +996,10 @@ __global__ void __launch_bounds__(BLK) copy_stream_k(u32x4_t* __restrict__ dst, 
 // pieces are aligned for it, else one (20 M parameters of AdamW: 114 us; four to a thread 126, one after the other 134).  A
 // block finds its tensor in the table that came with the launch.
 // Memory bound: 6.2 TB/s on a layer of 202 M parameters.  Four wavefronts a SIMD (64 KB of AdamW's loads in flight in a compute unit):
-// more of them only make memory change rows more often (202 M parameters 1016 us with eight, 977 with four, 1022 with two; 36 M 162 and 158; of momentum
-// 67 M 210 and 201; up to 20 M the same); plain SGD, which reads two arrays, keeps eight (67 M 121, 125 with four).  A rounded copy that is
+// more of them only make memory change rows more often (202 M parameters 1016 us with eight, 977 with four, 1022 with two; 36 M 176 and 169; of momentum
+// 67 M 244 and 235).  Plain SGD, which reads two arrays, keeps eight (67 M 121, 125 with four), and so do launches of less than
+// OPT_FOUR_WAVES parameters, much of whose gradients and state is in the caches: in a step AdamW on groups of 6 M 50 us, 55 with
+// four; from memory, momentum on 4 M 17.5 and 18.1; 20 M and more are faster with four (momentum 71.8 and 70.1).  A rounded copy that is
 // larger than the last-level cache goes past it too, like the rest (AdamW on 150 M 776 -> 748 us, 202 M 1039 -> 1008; SGD 356 -> 343, 469 -> 448); a smaller one may
 // still be there when it is written or read again, and does worse past it (135 M 713 and 738 us, SGD 280 and 307; 67 M 330 and 345, SGD 133 and 145).
 // Launched tensor by tensor, the 16 tensors of an encoder layer took
@@ -1033,9 +1035,9 @@ __device__ __forceinline__ void opt_update(const OptHyper& h, const OptTensor& t
 }
 
 constexpr int64_t OPT_COPY_PAST_CACHES = 150000000;  // 300 MB; the last-level cache has 256
-constexpr int opt_waves(int kind) { return kind == 3 ? 8 : 4; }
-template <int KIND, int NT>
-__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(opt_waves(KIND), opt_waves(KIND)))) opt_k(OptHyper h, OptTable<NT> table) {
+constexpr int64_t OPT_FOUR_WAVES = 16000000;
+template <int KIND, int NT, int WAVES>
+__global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) opt_k(OptHyper h, OptTable<NT> table) {
   int q = 0;
   if (NT > 1)
     while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].block0) ++q;  // uniform over the block
@@ -1526,12 +1528,15 @@ static hipError_t launch_update(const OptArgs& o, const OptItem* items, int n_it
     blocks += more;
   }
   if (table.n == 0) return hipSuccess;
+  int64_t n = 0;
+  for (int q = 0; q < table.n; ++q) n += table.t[q].n;
+  const bool four = n >= OPT_FOUR_WAVES;
   const dim3 grid((unsigned)blocks);
   switch (kind) {
-    case 0: opt_k<0, NT><<<grid, BLK, 0, st>>>(h, table); break;
-    case 1: opt_k<1, NT><<<grid, BLK, 0, st>>>(h, table); break;
-    case 2: opt_k<2, NT><<<grid, BLK, 0, st>>>(h, table); break;
-    default: opt_k<3, NT><<<grid, BLK, 0, st>>>(h, table); break;
+    case 0: (four ? opt_k<0, NT, 4> : opt_k<0, NT, 8>)<<<grid, BLK, 0, st>>>(h, table); break;
+    case 1: (four ? opt_k<1, NT, 4> : opt_k<1, NT, 8>)<<<grid, BLK, 0, st>>>(h, table); break;
+    case 2: (four ? opt_k<2, NT, 4> : opt_k<2, NT, 8>)<<<grid, BLK, 0, st>>>(h, table); break;
+    default: opt_k<3, NT, 8><<<grid, BLK, 0, st>>>(h, table); break;
   }
   return hipGetLastError();
 }
