@@ -4,10 +4,12 @@
 // rounded new values in LDS, and writes from there the tile's part of the forward copy (one 32-row block, 16 k-steps: 16 KB in a row) and
 // of the transposed one (eight blocks, two k-steps each), as pack_b_tile_k does (gemm.hip).  Memory bound: AdamW reads 16 and writes 12
 // bytes of fp32 a parameter, and 2 per copy.  The packers by themselves read the new master weights again for each copy, 8 bytes a
-// parameter more: a layer of 202 M parameters took 1.03 ms in opt_k and 0.45 in the packers, and takes 1.03 here.  Loads
-// go out in batches of two rows a wavefront, of two wavefronts a SIMD: 64 KB in flight in a compute unit.  More of them only make memory
-// change rows more often, and the copies, which nothing reads in this step, go past the caches (22016 x 4096: 539 us with four rows and
-// wavefronts, 508 with two wavefronts, 495 with two rows as well, 474 with the copies past the caches; one row 530, eight rows 513).
+// parameter more: a layer of 202 M parameters took 1.03 ms in opt_k and 0.45 in the packers, and takes 1.02 here, in a step.  Loads
+// go out in batches of two rows a wavefront with AdamW, four with the optimizers that read fewer arrays, of two wavefronts a SIMD: 64 KB and less in flight in
+// a compute unit.  More of them only make memory change rows more often (22016 x 4096 alone: 539 us with four rows and wavefronts, 508 with two wavefronts,
+// 495 with two rows as well; one row 530, eight rows 513; momentum at width 4096, updates of a sweep: 2.64 ms with two rows, 2.53 with four).  The copies
+// stay in the caches as far as they fit, where the next step's forward pass finds them.  Past the caches the kernel alone is faster
+// (474 us), but not in a step: updates of a sweep at width 4096 3.53 ms against 3.45, 2048 1.59 and 1.48, 1024 (encoder) 0.66 and 0.64.
 #include "common.h"
 #include "kernels.h"
 #include "optimizer.h"
@@ -37,7 +39,7 @@ struct OptPackTable {
 template <int KIND>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))) opt_pack_k(OptHyper h, OptPackTable table) {
   constexpr int PITCH = TILE_COLS * 2 + 16;  // bytes per tile row in LDS; the pad spreads 16-byte reads of one column over the banks
-  constexpr int NB = 2;                      // rows of a wavefront whose loads are in flight together
+  constexpr int NB = KIND == 0 ? 2 : 4;      // rows of a wavefront whose loads are in flight together
   __shared__ __attribute__((aligned(16))) unsigned char tile[TILE_ROWS * PITCH];
   int q = 0;
   while (q + 1 < table.n && blockIdx.x >= table.t[q + 1].o.block0) ++q;  // uniform over the block
@@ -72,7 +74,7 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (KIND == 0) stnt<4>(t.o.s2 + i, b[p]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w.v[e] = from_f32<bf16>(th[p][e]);
-        if (t.o.cc) stnt<4>(t.o.cc + i, th[p]);
+        if (t.o.cc) *reinterpret_cast<Vec<bf16, 4>*>(t.o.cc + i) = w;
       }
       *reinterpret_cast<Vec<bf16, 4>*>(tile + r * PITCH + lane * 8) = w;
     }
@@ -87,7 +89,7 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))
       if (kk >= k_steps) continue;
       u32x4 v = *reinterpret_cast<const u32x4*>(tile + pi_row(lane & 31) * PITCH + (kkl * 16 + (lane >> 5) * 8) * 2);
       if (t.gain) v = scale8(v, *reinterpret_cast<const u32x4*>(t.gain + kk * 16 + (lane >> 5) * 8));
-      __builtin_nontemporal_store(v, t.fwd + (pk_block_pos(to, t.order, t.rows / 64) * k_steps + kk) * 64 + lane);
+      t.fwd[(pk_block_pos(to, t.order, t.rows / 64) * k_steps + kk) * 64 + lane] = v;
     }
   }
   if (t.bwd) {
@@ -99,7 +101,7 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         v[e] = *reinterpret_cast<const bf16*>(tile + (kkl * 16 + (lane >> 5) * 8 + e) * PITCH + (nbl * 32 + pi_row(lane & 31)) * 2);
-      __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), t.bwd + (((int64_t)ti * 8 + nbl) * k_steps + to * 2 + kkl) * 64 + lane);
+      t.bwd[(((int64_t)ti * 8 + nbl) * k_steps + to * 2 + kkl) * 64 + lane] = __builtin_bit_cast(u32x4, v);
     }
   }
 }
