@@ -1971,7 +1971,10 @@ hift_status hift_step(hift_model* M, const hift_batch* bt, int32_t gid, float* l
       void* cc = M->dt == DT_BF16 ? M->W(t) : nullptr;  // null also for a matrix kept only in fragment order
       if (cc) bytes += 2.0 * t.count();
       OptItem item{t.count(), t.kind == HIFT_KIND_MATRIX, M->unit_steps[t.unit], master_of(t), M->grad + (t.off - plo), state_of(t, 0), state_of(t, 1), cc, grad_fused(t)};
-      if (M->tok_stamps && t.name == "tok_emb") { item.stamps = M->tok_stamps; item.stamp = M->tok_stamp; item.row = (int32_t)t.cols; }
+      if (M->tok_stamps && t.name == "tok_emb") {
+        item.stamps = M->tok_stamps; item.stamp = M->tok_stamp; item.row = (int32_t)t.cols;
+        bytes -= 4.0 * t.cols * std::max<int64_t>(0, t.rows - (int64_t)bt->batch * bt->seq);  // rows without a token: no more tokens than positions
+      }
       const PackItem pack{t.rows, t.cols, t.pk_fwd >= 0 ? M->wpk + t.pk_fwd : nullptr, t.pk_bwd >= 0 ? M->wpk + t.pk_bwd : nullptr,
                           t.pk_gain >= 0 ? M->W(M->lay.t[t.pk_gain]) : nullptr, t.pk_order};
       if (has_copies && M->opt.kind != HIFT_ADAFACTOR && update_packs(item, pack)) {

@@ -61,3 +61,19 @@ def test_rows_without_a_token(opt, arch, dtype, d, vocab):
         if opt["kind"] == "adamw":
             s2 = m.read_state(0, 1, 1)[:table].astype(np.float64)
     assert size >= table
+
+
+@pytest.mark.parametrize("vocab,batch", [(1001, 2), (20, 2)])
+def test_bytes_of_the_update_leave_out_gradients_that_are_not_read(vocab, batch):
+    """The algorithmic bytes that the profile gives for an embeddings step: 28 a parameter of AdamW, without the gradient of the table's rows
+    that no position can name."""
+    import torch
+    import paper_2401_15207_amd as H
+    cfg = dict(arch=0, n_layers=1, d_model=64, n_heads=2, d_ffn=256, vocab=vocab, max_seq=16, n_classes=0, norm_eps=1e-5, rope_base=10000.0, dtype=0)
+    m = H.HiftModel(cfg, dict(kind="adamw", lr=1e-3, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.0), 1, 4, 16)
+    m.write_params(0, 3, np.zeros(sum(int(np.prod(s)) for _n, s, _k, _u, _o in m.tensors), dtype=np.float32))
+    m.set_group_schedule("bottom2up", 1, 0)
+    tok = torch.zeros(batch, 16, dtype=torch.int32, device="cuda")
+    m.profile_enable(True)
+    m.step(tok, tok, 0)
+    assert m.profile_read(3)[2] == 28 * (vocab + 16) * 64 - 4 * 64 * max(0, vocab - 16 * batch)
