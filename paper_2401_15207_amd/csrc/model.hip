@@ -1642,8 +1642,6 @@ hift_status hift_model_create_chunked(const hift_config* cfg, const hift_opt* op
   for (int q = 0; q < NSLOT; ++q)
     if (M->slot[q]) CR_TRY(fill_zero(M->slot[q], (size_t)M->n_move * M->grad_cap * 4, M->cs));
   CR_TRY(fill_zero(M->grad, (size_t)M->grad_cap * 4, M->cs));
-  if (M->cfg.arch != HIFT_ARCH_POSTLN_ENCODER && M->logits_ld > M->cfg.vocab)
-    CR_TRY(fill_zero(M->logits, (size_t)M->maxT * M->logits_ld * M->es, M->cs));  // what follows the rows
   if (M->tok_stamps) CR_TRY(fill_zero(M->tok_stamps, ((size_t)M->cfg.vocab * 4 + 15) / 16 * 16, M->cs));
   if (M->gemm_ws) CR_TRY(fill_zero(M->gemm_ws, 1024, M->cs));  // the counters; every launch leaves them at zero
   if (M->fac) CR_TRY(fill_zero(M->fac, (size_t)M->n_fac * 4, M->cs));
