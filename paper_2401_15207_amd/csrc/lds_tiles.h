@@ -49,7 +49,9 @@ constexpr int N_LDS_LONG_TILES = sizeof(LDS_LONG_TILES) / sizeof(LDS_LONG_TILES[
 
 // Which of them a problem gets, or -1: none.  The constants put the line where it was measured, by the scale of the fit above (their
 // times with weights from HBM are 1.3 times as long): over 115 sizes (64 to 2048 rows, k 1536 to 11008, three layouts) that
-// take one, it is 1.19 times as fast as lds_tile's choice, 1.23 with other work beside it, and at worst 2.5 % slower.  Below k 1536 the start
+// take one, it is 1.19 times as fast as lds_tile's choice, 1.23 with other work beside it, and at worst 3.5 % slower; as 2 to 32 problems in a launch 1.17 to
+// 1.26 (56 sizes, at worst 7 % slower: 32 of 1904 x 128, k 1688); with A transposed and B k-major 1.27 (28 sizes, none slower); with GELU or its
+// derivative the contractions of a model take 0.84 to 1.02 of the time (36 models of width 1536 to 3072, 231 to 1430 tokens).  Below k 1536 the start
 // and the end of a tile, which nothing hides here, are too much of it (720 x 4096, k 1024: 13.2 and 14.5 us).
 inline int lds_long_tile(int64_t M, int64_t N, int64_t K, int64_t nz) {
   if (K < 1536) return -1;

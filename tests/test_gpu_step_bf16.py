@@ -316,7 +316,8 @@ def test_master_on_host_gives_the_same_trajectory(optk):
 
 # arch, batch, seq, width, inner width: every tile of gemm_lds_k is taken by one of them (test_lds_tiles.py)
 GELU_CASES = [(0, 3, 21, 128, 328), (1, 2, 40, 128, 328), (1, 5, 64, 128, 328), (0, 3, 8, 512, 40), (1, 3, 24, 128, 8200), (0, 4, 34, 512, 8200),
-              (1, 8, 29, 64, 8200), (0, 8, 29, 2056, 4104), (1, 4, 34, 2056, 8200), (0, 8, 128, 768, 768), (1, 8, 481, 328, 4040)]
+              (1, 8, 29, 64, 8200), (0, 8, 29, 2056, 4104), (1, 4, 34, 2056, 8200), (0, 8, 128, 768, 768), (1, 8, 481, 328, 4040),
+              (0, 5, 101, 1544, 8200), (1, 9, 145, 1608, 4104), (1, 3, 77, 4104, 8208), (0, 3, 77, 4104, 8208)]
 
 
 @pytest.mark.parametrize("arch,batch,seq,d,f", GELU_CASES)
