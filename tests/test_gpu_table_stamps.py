@@ -8,14 +8,18 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("opt", [dict(kind="adamw", lr=1e-2, beta1=0.9, beta2=0.999, eps=1e-8, weight_decay=0.1, momentum=0.0),
                                  dict(kind="sgd", lr=1e-1, beta1=0.0, beta2=0.0, eps=0.0, weight_decay=0.1, momentum=0.9),
-                                 dict(kind="sgd", lr=1e-1, beta1=0.0, beta2=0.0, eps=0.0, weight_decay=0.1, momentum=0.0)], ids=["adamw", "sgdm", "sgd"])
-@pytest.mark.parametrize("arch,dtype,d,vocab", [(2, 1, 128, 1001), (0, 0, 64, 999), (0, 1, 128, 515), (1, 0, 36, 333)])
-def test_rows_without_a_token(opt, arch, dtype, d, vocab):
+                                 dict(kind="sgd", lr=1e-1, beta1=0.0, beta2=0.0, eps=0.0, weight_decay=0.1, momentum=0.0),
+                                 dict(kind="adagrad", lr=1e-2, beta1=0.0, beta2=0.0, eps=1e-10, weight_decay=0.1, momentum=0.0)],
+                         ids=["adamw", "sgdm", "sgd", "adagrad"])
+@pytest.mark.parametrize("arch,dtype,d,vocab,parked", [(2, 1, 128, 1001, 0), (0, 0, 64, 999, 0), (0, 1, 128, 515, 0), (1, 0, 36, 333, 0),
+                                                       (2, 1, 128, 1001, 1), (1, 0, 36, 333, 1), (0, 1, 128, 515, 2)])
+def test_rows_without_a_token(opt, arch, dtype, d, vocab, parked):
+    """parked: the optimizer's state waits in host memory between steps (1), and the master weights with it (2)."""
     import torch
     import paper_2401_15207_amd as H
     cfg = dict(arch=arch, n_layers=1, d_model=d, n_heads=2, d_ffn=4 * d, vocab=vocab, max_seq=16, n_classes=3 if arch == 1 else 0, norm_eps=1e-5,
                rope_base=10000.0, dtype=dtype)
-    m = H.HiftModel(cfg, opt, 1, 2, 16)
+    m = H.HiftModel(cfg, opt, 1, 2, 16, state_on_host=int(parked > 0), master_on_host=int(parked > 1))
     rng = np.random.default_rng(vocab)
     name, shape, _kind, unit, off = m.tensors[0]
     assert name == "tok_emb" and unit == 0 and off == 0
@@ -45,6 +49,10 @@ def test_rows_without_a_token(opt, arch, dtype, d, vocab):
             s1n, s2n = 0.9 * s1, 0.999 * s2
             move = lr * (s1n / (1 - 0.9 ** t)) / (np.sqrt(s2n / (1 - 0.999 ** t)) + 1e-8)
             want, size_of = w * (1 - lr * wd) - move, np.abs(w) + np.abs(move)
+        elif opt["kind"] == "adagrad":
+            g = wd * w
+            s1n = s1 + g * g
+            want, size_of = w - lr * g / (np.sqrt(s1n) + 1e-10), np.abs(w) + lr
         else:
             g = wd * w
             s1n = g if t == 1 else opt["momentum"] * s1 + g
@@ -53,7 +61,7 @@ def test_rows_without_a_token(opt, arch, dtype, d, vocab):
         assert (np.abs(new - want)[at] <= 16 * 2.0 ** -24 * size_of[at] + 1e-30).all()
         assert (new[~at] != want[~at]).mean() > 0.5  # and those of tokens do have one
         w0, before, w = w, s1, new
-        if opt["kind"] == "adamw" or opt["momentum"]:
+        if opt["kind"] in ("adamw", "adagrad") or opt["momentum"]:
             s1 = m.read_state(0, 1, 0)[:table].astype(np.float64)
             # sums of two terms that may cancel: four roundings in 32 bits of terms of their size
             terms = np.abs(opt["momentum"] * before) + np.abs(wd * w0) if opt["kind"] == "sgd" else np.abs(s1n)
