@@ -254,7 +254,8 @@ hift_status hift_set_lr_schedule(hift_model* mdl, int32_t kind, double base_lr, 
  * takes batches[i mod n_batches], the group the schedule visits next, and, if a schedule was set with
  * hift_set_lr_schedule, the rate of its cycle.  batches: host array of descriptors of device buffers.
  * losses_out: host, n_steps floats, or null (then the call does not wait for the GPU).  They are complete when the call returns, also those of
- * the steps before one that failed. */
+ * the steps before one that was refused, but are not filled in step by step: the call waits for the GPU every 64 steps and at its end, so
+ * an error that the GPU itself reports can come up to 64 steps after its step. */
 hift_status hift_train(hift_model* mdl, const hift_batch* batches, int32_t n_batches, int64_t n_steps,
                        float* losses_out);
 /* Checkpoint: step count, visiting order, per-unit update counts, learning-rate schedule, fp32 master

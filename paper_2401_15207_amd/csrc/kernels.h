@@ -66,8 +66,9 @@ struct Gemm {
 };
 constexpr size_t PACKED_WS_BYTES = 1024 + size_t(256) * 128 * 256 * 4;
 enum { EPI_NONE = 0, EPI_SWIGLU = 1, EPI_ROPE = 2, EPI_SWIGLU_BWD = 3, EPI_GELU = 4, EPI_GELU_BWD = 5 };
-// Outputs of this size and more are written past the caches: they fill the last-level cache (256 MB) for a good part, so whoever reads them next
-// finds little of them there anyway, and the writes do not wait for room.
+// Weight gradients of this size and more are written past the caches: they fill the last-level cache (256 MB) for a good part, so the update finds
+// little of them there anyway, and the writes do not wait for room.  (Other large outputs have lines of their own: CE_PAST_CACHES_BYTES,
+// OPT_COPY_PAST_CACHES.)
 constexpr int64_t PAST_CACHES_BYTES = int64_t(96) << 20;
 enum { BAND_NONE = 0, BAND_SKIP_UPPER = 1, BAND_K_UPTO_ROW = 2, BAND_K_FROM_ROW = 3 };
 hipError_t gemm(const Gemm& g, hipStream_t st);
