@@ -8,8 +8,9 @@
 // go out in batches of two rows a wavefront with AdamW, four with the optimizers that read fewer arrays, of two wavefronts a SIMD: 64 KB and less in flight in
 // a compute unit.  More of them only make memory change rows more often (22016 x 4096 alone: 539 us with four rows and wavefronts, 508 with two wavefronts,
 // 495 with two rows as well; one row 530, eight rows 513; momentum at width 4096, updates of a sweep: 2.64 ms with two rows, 2.53 with four).  The copies
-// stay in the caches as far as they fit, where the next step's forward pass finds them.  Past the caches the kernel alone is faster
-// (474 us), but not in a step: updates of a sweep at width 4096 3.53 ms against 3.45, 2048 1.59 and 1.48, 1024 (encoder) 0.66 and 0.64.
+// of a launch stay in the caches, where the next step's forward pass finds them (updates of a sweep at width 2048 1.59 -> 1.45 ms, of an encoder of width
+// 1024 0.67 -> 0.64), unless they are more than fits there: from COPIES_PAST_CACHES on they go past, as all else here does (22016 x 4096
+// alone 495 -> 474 us; sweeps of two layers of width 4096 20.8 -> 20.6 ms, on 231 tokens 8.56 -> 8.50).
 #include "common.h"
 #include "kernels.h"
 #include "optimizer.h"
@@ -31,12 +32,13 @@ struct OptPackTensor {
   int tiles_inner;    // tiles along a row
 };
 constexpr int OPT_PACK_TABLE = 8;
+constexpr int64_t COPIES_PAST_CACHES = int64_t(300) << 20;  // (of a launch; the last-level cache has 256 MB)
 struct OptPackTable {
   OptPackTensor t[OPT_PACK_TABLE];
   int n;
 };
 
-template <int KIND>
+template <int KIND, bool PAST>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))) opt_pack_k(OptHyper h, OptPackTable table) {
   constexpr int PITCH = TILE_COLS * 2 + 16;  // bytes per tile row in LDS; the pad spreads 16-byte reads of one column over the banks
   constexpr int NB = KIND == 0 ? 2 : 4;      // rows of a wavefront whose loads are in flight together
@@ -74,12 +76,19 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (KIND == 0) stnt<4>(t.o.s2 + i, b[p]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w.v[e] = from_f32<bf16>(th[p][e]);
-        if (t.o.cc) *reinterpret_cast<Vec<bf16, 4>*>(t.o.cc + i) = w;
+        if (t.o.cc) {
+          if (PAST) stnt<4>(t.o.cc + i, th[p]);
+          else *reinterpret_cast<Vec<bf16, 4>*>(t.o.cc + i) = w;
+        }
       }
       *reinterpret_cast<Vec<bf16, 4>*>(tile + r * PITCH + lane * 8) = w;
     }
   }
   __syncthreads();
+  const auto put = [](u32x4* at, u32x4 v) __attribute__((always_inline)) {
+    if (PAST) __builtin_nontemporal_store(v, at);
+    else *at = v;
+  };
   if (t.fwd) {
     const int64_t k_steps = t.cols / 16;
 #pragma unroll
@@ -89,7 +98,7 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))
       if (kk >= k_steps) continue;
       u32x4 v = *reinterpret_cast<const u32x4*>(tile + pi_row(lane & 31) * PITCH + (kkl * 16 + (lane >> 5) * 8) * 2);
       if (t.gain) v = scale8(v, *reinterpret_cast<const u32x4*>(t.gain + kk * 16 + (lane >> 5) * 8));
-      t.fwd[(pk_block_pos(to, t.order, t.rows / 64) * k_steps + kk) * 64 + lane] = v;
+      put(t.fwd + (pk_block_pos(to, t.order, t.rows / 64) * k_steps + kk) * 64 + lane, v);
     }
   }
   if (t.bwd) {
@@ -101,7 +110,7 @@ __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         v[e] = *reinterpret_cast<const bf16*>(tile + (kkl * 16 + (lane >> 5) * 8 + e) * PITCH + (nbl * 32 + pi_row(lane & 31)) * 2);
-      t.bwd[(((int64_t)ti * 8 + nbl) * k_steps + to * 2 + kkl) * 64 + lane] = __builtin_bit_cast(u32x4, v);
+      put(t.bwd + (((int64_t)ti * 8 + nbl) * k_steps + to * 2 + kkl) * 64 + lane, __builtin_bit_cast(u32x4, v));
     }
   }
 }
@@ -127,7 +136,7 @@ hipError_t optimizer_update_packed(const OptArgs& o, const OptItem* items, const
   for (int done = 0; done < n_items;) {
     OptPackTable table;
     table.n = 0;
-    int64_t blocks = 0;
+    int64_t blocks = 0, copied = 0;
     for (; done < n_items && table.n < OPT_PACK_TABLE; ++done) {
       const PackItem& pk = packs[done];
       if (!update_packs(items[done], pk)) return hipErrorInvalidValue;
@@ -141,15 +150,17 @@ hipError_t optimizer_update_packed(const OptArgs& o, const OptItem* items, const
       t.fwd = reinterpret_cast<u32x4*>(pk.fwd); t.bwd = reinterpret_cast<u32x4*>(pk.bwd);
       t.gain = reinterpret_cast<const bf16*>(pk.gain);
       t.order = pk.order;
+      copied += 2 * items[done].n * ((t.fwd != nullptr) + (t.bwd != nullptr) + (t.o.cc != nullptr));
       blocks += more;
       ++table.n;
     }
     const dim3 grid((unsigned)blocks);
+    const bool past = copied >= COPIES_PAST_CACHES;
     switch (opt_kind(o)) {
-      case 0: opt_pack_k<0><<<grid, BLK, 0, st>>>(h, table); break;
-      case 1: opt_pack_k<1><<<grid, BLK, 0, st>>>(h, table); break;
-      case 2: opt_pack_k<2><<<grid, BLK, 0, st>>>(h, table); break;
-      default: opt_pack_k<3><<<grid, BLK, 0, st>>>(h, table); break;
+      case 0: (past ? opt_pack_k<0, true> : opt_pack_k<0, false>)<<<grid, BLK, 0, st>>>(h, table); break;
+      case 1: (past ? opt_pack_k<1, true> : opt_pack_k<1, false>)<<<grid, BLK, 0, st>>>(h, table); break;
+      case 2: (past ? opt_pack_k<2, true> : opt_pack_k<2, false>)<<<grid, BLK, 0, st>>>(h, table); break;
+      default: (past ? opt_pack_k<3, true> : opt_pack_k<3, false>)<<<grid, BLK, 0, st>>>(h, table); break;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
