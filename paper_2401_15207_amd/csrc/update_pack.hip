@@ -4,13 +4,13 @@
 // rounded new values in LDS, and writes from there the tile's part of the forward copy (one 32-row block, 16 k-steps: 16 KB in a row) and
 // of the transposed one (eight blocks, two k-steps each), as pack_b_tile_k does (gemm.hip).  Memory bound: AdamW reads 16 and writes 12
 // bytes of fp32 a parameter, and 2 per copy.  The packers by themselves read the new master weights again for each copy, 8 bytes a
-// parameter more: a layer of 202 M parameters took 1.03 ms in opt_k and 0.45 in the packers, and takes 1.02 here, in a step.  Loads
+// parameter more: a layer of 202 M parameters took 1.03 ms in opt_k and 0.45 in the packers, and takes 1.04 or 1.13 here, in a step, by how the arrays happen to lie.  Loads
 // go out in batches of two rows a wavefront with AdamW, four with the optimizers that read fewer arrays, of two wavefronts a SIMD: 64 KB and less in flight in
 // a compute unit.  More of them only make memory change rows more often (22016 x 4096 alone: 539 us with four rows and wavefronts, 508 with two wavefronts,
 // 495 with two rows as well; one row 530, eight rows 513; momentum at width 4096, updates of a sweep: 2.64 ms with two rows, 2.53 with four).  The copies
 // of a launch stay in the caches, where the next step's forward pass finds them (updates of a sweep at width 2048 1.59 -> 1.45 ms, of an encoder of width
 // 1024 0.67 -> 0.64), unless they are more than fits there: from COPIES_PAST_CACHES on they go past, as all else here does (22016 x 4096
-// alone 495 -> 474 us; sweeps of two layers of width 4096 20.8 -> 20.6 ms, on 231 tokens 8.56 -> 8.50).
+// alone 495 -> 474 us; in a step the update is 2 % slower and what follows as much faster).
 #include "common.h"
 #include "kernels.h"
 #include "optimizer.h"
